@@ -649,43 +649,92 @@ __global__ __launch_bounds__(1024) void decode_ring_kernel(View pv, CallSeqs cs,
     }
 }
 
-__global__ __launch_bounds__(256) void free_seq_kernel(View pv, int sid) {
+// Every page of a sequence slot back to the free stack: layers ascending, heads ascending, a unit's local pages, then
+// its global pages.  Bound by latency, not by bytes (8 to 16 per page): the pages of all units are one flat list
+// behind a prefix over the units, page f goes to free_stack[top + f], and the list is dealt over all threads of the
+// launch, four independent table reads in flight each.  (One thread per unit walking its pages, each store behind
+// the load before it, took 158 us for 8 heads with 8K pages in all; this form takes 8.)
+// Every block builds the prefix by itself from the lengths and the first ring page of each unit, so these are the two
+// things that nobody may clear while a block may still read them: the block that arrives last at the counter does it
+// (its own count of one when the launch has a single block).  No block waits for another.
+constexpr int kFreeThreads = 256;
+constexpr int kFreePerBlock = 4 * kFreeThreads;  // pages a block takes per turn
+
+__global__ __launch_bounds__(kFreeThreads) void free_seq_kernel(View pv, int sid, int32_t *arrived) {
     __shared__ int s_tmp[20];
+    __shared__ int s_base[kFreeThreads];
+    __shared__ int s_nloc[kFreeThreads];
+    __shared__ int s_last;
     const int n_units = pv.L * pv.Hkv;
+    const size_t um0 = (size_t)sid * n_units;  // (sid*L + layer)*Hkv + h with u = layer*Hkv + h
     const int top = *pv.free_top;
+    // the scores are contiguous over the units of a slot, and nobody here reads them
+    const size_t n_ring = (size_t)n_units * pv.W, g0 = (size_t)blockIdx.x * kFreeThreads + threadIdx.x;
+    for (size_t i = g0; i < n_ring; i += (size_t)gridDim.x * kFreeThreads) pv.ring_g[um0 * pv.W + i] = 0.0f;
     int carry = 0;
-    for (int u0 = 0; u0 < n_units; u0 += 256) {
+    for (int u0 = 0; u0 < n_units; u0 += kFreeThreads) {
         const int u = u0 + threadIdx.x;
-        int n = 0, um = 0, ngp = 0, touched = 0;
+        int n = 0, nloc = 0;
         if (u < n_units) {
-            um = sid * n_units + u;  // (sid*L + layer)*Hkv + h with u = layer*Hkv + h
-            touched = pv.local_pt[(size_t)um * pv.nlp] >= 0;
-            ngp = (pv.global_len[um] + pv.P - 1) >> pv.logP;
-            n = touched ? pv.nlp + ngp : 0;
+            const int lp0 = pv.local_pt[(um0 + u) * pv.nlp], gl = pv.global_len[um0 + u];
+            if (lp0 >= 0) {  // else the slot's unit was never used
+                nloc = pv.nlp;
+                n = nloc + ((gl + pv.P - 1) >> pv.logP);
+            }
         }
         int total;
         const int ex = block_excl_scan(n, s_tmp, &total);
-        if (u < n_units) {
-            int o = top + carry + ex;
-            if (touched) {
-                for (int i = 0; i < pv.nlp; i++) {
-                    pv.free_stack[o++] = pv.local_pt[(size_t)um * pv.nlp + i];
-                    pv.local_pt[(size_t)um * pv.nlp + i] = -1;
+        s_base[threadIdx.x] = ex;
+        s_nloc[threadIdx.x] = nloc;
+        __syncthreads();
+        const int n_here = min(kFreeThreads, n_units - u0);
+        for (int f0 = blockIdx.x * kFreePerBlock; f0 < total; f0 += gridDim.x * kFreePerBlock) {
+            int32_t *src[4];
+            int pg[4];
+            bool keep[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int f = min(f0 + k * kFreeThreads + (int)threadIdx.x, total - 1);
+                int lo_u = 0, hi_u = n_here - 1;  // the last unit whose base is <= f (units without pages are never picked)
+                while (lo_u < hi_u) {
+                    const int mid = (lo_u + hi_u + 1) >> 1;
+                    if (s_base[mid] <= f) lo_u = mid; else hi_u = mid - 1;
                 }
-                for (int i = 0; i < ngp; i++) {
-                    pv.free_stack[o++] = pv.global_pt[(size_t)um * pv.maxgp + i];
-                    pv.global_pt[(size_t)um * pv.maxgp + i] = -1;
+                const int i = f - s_base[lo_u], nl = s_nloc[lo_u];
+                const size_t um = um0 + u0 + lo_u;
+                src[k] = i < nl ? pv.local_pt + um * pv.nlp + i : pv.global_pt + um * pv.maxgp + (i - nl);
+                keep[k] = i == 0;  // the first ring page says that the unit is in use: cleared at the end
+                pg[k] = *src[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int f = f0 + k * kFreeThreads + (int)threadIdx.x;
+                if (f < total) {
+                    pv.free_stack[top + carry + f] = pg[k];
+                    if (!keep[k]) *src[k] = -1;
                 }
             }
-            pv.global_len[um] = 0;
-            pv.ahead[um] = -1;
-            for (int s = 0; s < pv.W; s++) pv.ring_g[(size_t)um * pv.W + s] = 0.0f;
         }
         carry += total;
+        __syncthreads();  // s_base and s_nloc are rewritten
     }
-    for (int l = threadIdx.x; l < pv.L; l += 256) pv.seq_len[sid * pv.L + l] = 0;
+    // this block has read all it needs (its loads have returned: their values steered the stores above)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) *pv.free_top = top + carry;
+    if (threadIdx.x == 0)
+        s_last = gridDim.x == 1 || __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    for (int u = threadIdx.x; u < n_units; u += kFreeThreads) {
+        pv.local_pt[(um0 + u) * pv.nlp] = -1;
+        pv.global_len[um0 + u] = 0;
+        pv.ahead[um0 + u] = -1;
+    }
+    for (int l = threadIdx.x; l < pv.L; l += kFreeThreads) pv.seq_len[sid * pv.L + l] = 0;
+    if (threadIdx.x == 0) {
+        *pv.free_top = top + carry;
+        if (gridDim.x > 1) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // A kernel, not a memset: the call may sit in a captured graph.
@@ -769,8 +818,14 @@ hipError_t launch_decode_promote(const View &pv, const CallSeqs &cs, float tau, 
     return hipGetLastError();
 }
 
-hipError_t launch_free_seq(const View &pv, int sid, hipStream_t st) {
-    hipLaunchKernelGGL(free_seq_kernel, dim3(1), dim3(256), 0, st, pv, sid);
+// pages_ub: the host's bound of the slot's pages.  It only sizes the grid (the kernel goes by the device's lengths):
+// a block per 1024 pages or 8192 ring scores, so that a short sequence stays one block, whose end needs no count.
+hipError_t launch_free_seq(const View &pv, int sid, int64_t pages_ub, hipStream_t st) {
+    const int64_t n_ring = (int64_t)pv.L * pv.Hkv * pv.W;
+    int64_t nb = (pages_ub + kFreePerBlock - 1) / kFreePerBlock;
+    nb = nb > n_ring / 8192 ? nb : n_ring / 8192;
+    nb = nb < 1 ? 1 : (nb > 256 ? 256 : nb);
+    hipLaunchKernelGGL(free_seq_kernel, dim3((unsigned)nb), dim3(kFreeThreads), 0, st, pv, sid, pv.unit_counters);
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ hipError_t launch_prefill(const View &pv, const CallSeqs &cs, int layer, float t
 hipError_t launch_decode_step(const View &pv, const CallSeqs &cs, int layer, float tau,
                               const void *k, const void *v, const float *g, uint8_t *promoted_out,
                               hipStream_t st);
-hipError_t launch_free_seq(const View &pv, int sid, hipStream_t st);
+hipError_t launch_free_seq(const View &pv, int sid, int64_t pages_ub, hipStream_t st);
 hipError_t launch_decode_ring(const View &pv, const CallSeqs &cs, int layer, const void *k, const void *v,
                               const float *g, uint8_t *promoted_out, hipStream_t st);
 hipError_t launch_decode_promote(const View &pv, const CallSeqs &cs, float tau, hipStream_t st);
@@ -886,16 +886,19 @@ int wgkv_tune_decode_attention(wgkv_pool *p, int32_t n_seqs, const int32_t *seq_
 
 int wgkv_free_seq(wgkv_pool *p, int32_t seq_id, wgkv_stream stream) {
     if (!p || seq_id < 0 || seq_id >= p->cfg.max_seqs) return WGKV_ERR_INVALID_ARG;
-    if (launch_free_seq(p->view, seq_id, (hipStream_t)stream) != hipSuccess) return WGKV_ERR_HIP;
     const wgkv_config &c = p->cfg;
     const int P = c.page_size, H = c.n_kv_heads;
+    int64_t pages = 0;
     for (int l = 0; l < c.n_layers; l++) {
         const size_t sl = (size_t)seq_id * c.n_layers + l;
-        if (p->touched_h[sl]) p->pages_ub -= (int64_t)p->view.nlp * H;
-        for (int h = 0; h < H; h++) {
-            p->pages_ub -= (p->g_ub[sl * H + h] + P - 1) / P;
-            p->g_ub[sl * H + h] = 0;
-        }
+        if (p->touched_h[sl]) pages += (int64_t)p->view.nlp * H;
+        for (int h = 0; h < H; h++) pages += (p->g_ub[sl * H + h] + P - 1) / P;
+    }
+    if (launch_free_seq(p->view, seq_id, pages, (hipStream_t)stream) != hipSuccess) return WGKV_ERR_HIP;
+    p->pages_ub -= pages;
+    for (int l = 0; l < c.n_layers; l++) {
+        const size_t sl = (size_t)seq_id * c.n_layers + l;
+        for (int h = 0; h < H; h++) p->g_ub[sl * H + h] = 0;
         p->touched_h[sl] = 0;
         p->seq_len_h[sl] = 0;
         p->ahead_h[sl] = -1;
