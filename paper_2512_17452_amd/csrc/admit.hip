@@ -653,7 +653,7 @@ __global__ __launch_bounds__(1024) void decode_ring_kernel(View pv, CallSeqs cs,
 // its global pages.  Bound by latency, not by bytes (8 to 16 per page): the pages of all units are one flat list
 // behind a prefix over the units, page f goes to free_stack[top + f], and the list is dealt over all threads of the
 // launch, four independent table reads in flight each.  (One thread per unit walking its pages, each store behind
-// the load before it, took 158 us for 8 heads with 8K pages in all; this form takes 8.)
+// the load before it, took 158 us for 8 heads with 8K pages in all; this form takes 6.)
 // Every block builds the prefix by itself from the lengths and the first ring page of each unit, so these are the two
 // things that nobody may clear while a block may still read them: the block that arrives last at the counter does it
 // (its own count of one when the launch has a single block).  No block waits for another.

@@ -9,14 +9,24 @@
 // that were neither admitted nor inside the window are gone (Sec. 4.2, "Initial
 // cache population") and are invisible under M_ij anyway.
 //
-// One block owns 64 chunk positions of one (sequence, kv head); its eight waves are
-// (query head of the group) x (row block of 32 positions), so a K/V tile staged in LDS
-// feeds all of them and two waves share each SIMD.
+// One block owns 256 / G chunk positions of one (sequence, kv head) with a group of G query heads;
+// its eight waves are (query head of the group) x (row block of 32 positions), so a K/V tile staged
+// in LDS feeds all of them and two waves share each SIMD.  A tile is 8 KiB of K and of V (16 bytes of
+// each per thread): 32 keys of 128 elements, 64 keys of 64.
 // K and V tiles are staged row-major; the V^T operand is read from the V tile with the
 // transposing LDS load.  Everything is computed transposed, S^T = K Q^T and O^T = V^T P^T with
 // v_mfma_f32_32x32x16_bf16: a lane then owns one query column, so the running max,
 // the denominator and the rescale factor are plain per-lane scalars, and the
 // probabilities leave the first product already in the operand layout of the second.
+//
+// Two forms of the weights P.  For the shape of the paper's models (128 wide, four heads a group) they
+// are rounded to bf16 once, and the denominator sums the rounded ones.  For every other shape they
+// keep 24 bits (PARTS = 3): p = hi + mid + lo, each part the upper half of an fp32 word and hi, mid
+// exact remainders, three products with the same V^T operand; V is bf16, so the products are exact and
+// the sums are fp32 as they are in plain fp32 arithmetic.  The matrix cores have the room: at 64 elements
+// the vector work per score is twice the four extra products.  Measured: a 6001-token prompt of 32 / 8 heads
+// of 64 in chunks of 2048, gate and admission included, 17.3 ms -> 0.55 ms against one wave of plain fp32
+// arithmetic per (query, head), the error against 64 bits 9.3e-7 -> 6.4e-7.
 #include <climits>
 
 #include "wgkv_dev.h"
@@ -27,13 +37,23 @@ typedef __attribute__((ext_vector_type(8))) __bf16 pf_bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 pf_bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
 
-constexpr int kPfD = 128;         // head_dim
-constexpr int kPfQ = 64;          // chunk positions per block (2 row blocks of 32)
-constexpr int kPfKT = 32;         // keys per tile
-constexpr int kPfKStride = 272;   // bytes per key row of the K tile in LDS (256 + 16 pad): rows are read whole
-constexpr int kPfVStride = 320;   // bytes per key row of the V tile (256 + 64 pad): columns are read, four
-                                  // rows and 64 bytes of each at a time per half wave, which this stride
-                                  // spreads over all banks
+// The shape of one instantiation: head_dim D, group size G.
+template <int D_, int G_, int PARTS_>
+struct PfShape {
+    static constexpr int D = D_, G = G_, PARTS = PARTS_;
+    static constexpr int Q = 256 / G;       // chunk positions per block (8 / G row blocks of 32)
+    static constexpr int CPR = D / 8;       // 16-byte chunks per row
+    static constexpr int KT = 512 / CPR;    // keys per tile: a chunk of K and of V per thread
+    static constexpr int NS = KT / 32;      // score tiles of 32 keys
+    static constexpr int KS = D / 16;       // contraction slices of the first product
+    static constexpr int DB = D / 32;       // output blocks of 32 elements
+    static constexpr int KPW = 64 / CPR;    // keys a wave stages
+    static constexpr int KStride = D * 2 + 16;  // bytes per key row of the K tile in LDS: rows are read whole
+    static constexpr int VStride = D * 2 + 64;  // bytes per key row of the V tile: columns are read, four rows and
+                                                // 64 bytes of each at a time per half wave, which this stride
+                                                // (320 or 192 bytes) spreads over all banks
+};
+constexpr int kPfQMin = 32;       // chunk positions per block at the largest group
 
 struct PrefillAttnArgs {
     int nx;                 // blocks per (sequence, kv head) of the launch
@@ -52,13 +72,14 @@ struct PrefillAttnArgs {
 // element i%4 of the 8 bytes addressed by lanes i/4, 4 + i/4, 8 + i/4 and 12 + i/4, so lane s of a
 // group addresses (key s/4 of the four, columns 4*(s%4)..+3 of the group's 16).
 typedef short pf_s16x4_t __attribute__((ext_vector_type(4)));
+template <int STRIDE>
 __device__ __forceinline__ pf_bf16x8_t pf_get_cols(const char *tile, int lane, int db, int r0) {
     const int half = lane >> 5;
-    const char *p = tile + (r0 + 4 * half + ((lane & 15) >> 2)) * kPfVStride +
+    const char *p = tile + (r0 + 4 * half + ((lane & 15) >> 2)) * STRIDE +
                     (db * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
     typedef pf_s16x4_t __attribute__((address_space(3))) *lds_ptr_t;
     const pf_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)p);
-    const pf_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * kPfVStride));
+    const pf_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * STRIDE));
     const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
     const uint4 u4 = make_uint4(l2.x, l2.y, h2.x, h2.y);
     return __builtin_bit_cast(pf_bf16x8_t, u4);
@@ -69,11 +90,58 @@ __device__ __forceinline__ uint32_t pf_pack(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, t);
 }
 
+// The upper halves of two fp32 words as one pair of bf16 (the low word first).
+__device__ __forceinline__ uint32_t pf_top(float lo, float hi) {
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ float pf_rest(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+
+// A pair of bf16 holds no inf and no NaN.
+__device__ __forceinline__ bool pf_finite(uint32_t x) {
+    return (x & 0x7f80u) != 0x7f80u && (x & 0x7f800000u) != 0x7f800000u;
+}
+// Takes the infinities and NaNs out of an operand of V^T and gives them to the columns of o that see their keys (seen:
+// bf16 ones and zeros in the operand layout of P^T): one product of codes counts +inf, -inf and NaN (at most 16 of
+// each: 1, 32 and 1024 apiece), then o gets what the sum would have had.
+__device__ __forceinline__ void pf_take_nonfinite(pf_bf16x8_t &v, const uint32_t (&seen)[4], pf_f32x16_t &o) {
+    uint4 w = __builtin_bit_cast(uint4, v);
+    uint32_t x[4] = {w.x, w.y, w.z, w.w}, code[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        code[i] = 0u;
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            const uint32_t h = (x[i] >> (16 * e)) & 0xffffu;
+            // 1, 32 and 1024 in bf16
+            const uint32_t cd = (h & 0x7f80u) != 0x7f80u ? 0u : h == 0x7f80u ? 0x3f80u : h == 0xff80u ? 0x4200u : 0x4480u;
+            code[i] |= cd << (16 * e);
+            if (cd) x[i] &= ~(0xffffu << (16 * e));
+        }
+    }
+    v = __builtin_bit_cast(pf_bf16x8_t, make_uint4(x[0], x[1], x[2], x[3]));
+    pf_f32x16_t cnt;
+#pragma unroll
+    for (int c = 0; c < 16; c++) cnt[c] = 0.f;
+    cnt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pf_bf16x8_t, make_uint4(code[0], code[1], code[2], code[3])),
+                                                  __builtin_bit_cast(pf_bf16x8_t, make_uint4(seen[0], seen[1], seen[2], seen[3])),
+                                                  cnt, 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < 16; c++)
+        if (cnt[c] > 0.f) {
+            const int n = (int)cnt[c];
+            o[c] += n < 32 ? INFINITY : (n < 1024 && n % 32 == 0) ? -INFINITY : NAN;
+        }
+}
+
+template <int D_, int G_, int PARTS_>
 __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
-    __shared__ __attribute__((aligned(16))) char s_k[2][kPfKT * kPfKStride];
-    __shared__ __attribute__((aligned(16))) char s_v[2][kPfKT * kPfVStride];
-    __shared__ __attribute__((aligned(16))) int s_lo[2][kPfKT];
-    __shared__ __attribute__((aligned(16))) int s_hi[2][kPfKT];
+    using S = PfShape<D_, G_, PARTS_>;
+    constexpr int D = S::D, G = S::G, KT = S::KT, NS = S::NS, KS = S::KS, DB = S::DB;
+    __shared__ __attribute__((aligned(16))) char s_k[2][KT * S::KStride];
+    __shared__ __attribute__((aligned(16))) char s_v[2][KT * S::VStride];
+    __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
+    __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
+    __shared__ int s_bad[2];  // PARTS 3: the masked tile in that buffer if it holds a V that is not finite
 
     // Blocks are handed out in the order of their index and go to the 8 XCDs round-robin: all
     // blocks of the unit with the longest global cache come first, its latest positions (which see
@@ -85,41 +153,41 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
     const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
-    if (qt * kPfQ >= T) return;  // block-uniform
+    if (qt * S::Q >= T) return;  // block-uniform
     const int sid = cs.sid[b];
     const int um = unit_meta(pv, sid, a.layer, h);
-    const int G = 4;
     // eight waves: wave -> (query head of the group, row block of 32 positions); two waves
     // share a SIMD, so one can run its softmax while the other keeps the matrix core busy
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int head = wave & 3, rb = wave >> 2;
+    const int head = wave % G, rb = wave / G;
     const int qn = lane & 31, half = lane >> 5;
     const int gl = pv.global_len[um];
     const int w_eff = min(pv.W, t0);              // ring entries that exist
-    const int i_end = min(T, qt * kPfQ + kPfQ);   // chunk keys this block can see: [0, i_end)
-    const int n_g = (gl + kPfKT - 1) / kPfKT, n_r = (w_eff + kPfKT - 1) / kPfKT;
-    const int n_c = (i_end + kPfKT - 1) / kPfKT;
+    const int i_end = min(T, qt * S::Q + S::Q);   // chunk keys this block can see: [0, i_end)
+    const int n_g = (gl + KT - 1) / KT, n_r = (w_eff + KT - 1) / KT;
+    const int n_c = (i_end + KT - 1) / KT;
     const int n_tiles = n_g + n_r + n_c;
 
-    // ---- Q^T operand: this lane's query, all 8 d-slices of 16 ----
-    pf_bf16x8_t qv[8];
-    const int qi = min(qt * kPfQ + rb * 32 + qn, T - 1);
+    // ---- Q^T operand: this lane's query, all d-slices of 16 ----
+    pf_bf16x8_t qv[KS];
+    const int q_first = qt * S::Q + rb * 32;      // first position of this wave's rows
+    const int qi = min(q_first + qn, T - 1);
     const int qpos = t0 + qi;
     {
-        const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * kPfD * 2;
+        const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * D * 2;
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++)
+        for (int ks = 0; ks < KS; ks++)
             qv[ks] = *reinterpret_cast<const pf_bf16x8_t *>(qp + (ks * 16 + half * 8) * 2);
     }
-    pf_f32x16_t o[4];
+    pf_f32x16_t o[DB];
     float m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int db = 0; db < 4; db++)
+    for (int db = 0; db < DB; db++)
 #pragma unroll
         for (int c = 0; c < 16; c++) o[db][c] = 0.f;
 
     // ---- staging of a key tile: thread -> (key of the tile, 16-byte d chunk), K and V row-major ----
-    const int ld_key = threadIdx.x >> 4, ld_dc = threadIdx.x & 15;
+    const int ld_key = threadIdx.x / S::CPR, ld_dc = threadIdx.x % S::CPR;
     // two sets of staging registers: a tile is requested two iterations before it is multiplied
     // (plain variables passed one by one: a struct of them ends up in scratch memory)
     uint4 k0r, v0r, k1r, v1r;
@@ -138,32 +206,32 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
         int64_t v_delta;
         int lo = INT_MAX, hi = INT_MAX;  // invisible unless shown otherwise
         if (t < n_g) {  // global cache: visible to every query
-            if (((t * kPfKT + kPfKT - 1) >> pv.logP) >= pt_base + 64) {
-                pt_base = (t * kPfKT) >> pv.logP;
+            if (((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
+                pt_base = (t * KT) >> pv.logP;
                 ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
             }
-            const int idx = t * kPfKT + ld_key, idc = min(idx, gl - 1);
+            const int idx = t * KT + ld_key, idc = min(idx, gl - 1);
             const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
-            kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (kPfD * 2);
+            kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
             if (idx < gl) lo = INT_MIN;
             v_delta = pv.v_off;
         } else if (t < n_g + n_r) {  // ring, oldest position first
-            const int idx = (t - n_g) * kPfKT + ld_key, idc = min(idx, w_eff - 1);
+            const int idx = (t - n_g) * KT + ld_key, idc = min(idx, w_eff - 1);
             int slot = slot0 + idc;
             slot = slot >= pv.W ? slot - pv.W : slot;
             const int pos = t0 - w_eff + idc;
             const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
                                      : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
-            kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (kPfD * 2);
+            kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
             if (idx < w_eff) {
                 lo = pos;
                 hi = (pv.ring_g[(size_t)um * pv.W + slot] >= a.tau) ? INT_MAX : pos + pv.W - 1;
             }
             v_delta = pv.v_off;
         } else {  // this chunk
-            const int idx = (t - n_g - n_r) * kPfKT + ld_key, idc = min(idx, T - 1);
+            const int idx = (t - n_g - n_r) * KT + ld_key, idc = min(idx, T - 1);
             const size_t row = (size_t)(base + idc) * pv.Hkv + h;
-            kp = a.k + row * (kPfD * 2);
+            kp = a.k + row * (D * 2);
             if (idx < T) {
                 lo = t0 + idx;
                 hi = (a.g[row] >= a.tau) ? INT_MAX : t0 + idx + pv.W - 1;
@@ -175,36 +243,45 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
         r_lo = lo;
         r_hi = hi;
     };
-    // Full tiles of the global cache, pages of at least 4 tokens: the four keys a wave
-    // stages share a page, so the page base is scalar and a lane only adds a fixed offset.
-    const bool lean_ok = pv.P >= 4;
-    const uint32_t lean_k_off = (uint32_t)(ld_key & (pv.P - 1)) * (kPfD * 2) + ld_dc * 16;
+    // Full tiles of the global cache, pages of at least as many tokens as a wave stages: its keys
+    // share a page, so the page base is scalar and a lane only adds a fixed offset.
+    const bool lean_ok = pv.P >= S::KPW;
+    const uint32_t lean_k_off = (uint32_t)(ld_key & (pv.P - 1)) * (D * 2) + ld_dc * 16;
     auto fetch_lean = [&](int t, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
-        if (((t * kPfKT + kPfKT - 1) >> pv.logP) >= pt_base + 64) {
-            pt_base = (t * kPfKT) >> pv.logP;
+        if (((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
+            pt_base = (t * KT) >> pv.logP;
             ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
         }
-        const int pg = __builtin_amdgcn_readlane(ptreg, ((t * kPfKT + 4 * wave) >> pv.logP) - pt_base);
-        // inside its page the tile begins at row (32 t) mod P (0 unless a page holds several tiles)
-        const char *sb = page_ptr(pv, pg) + (size_t)((t * kPfKT) & (pv.P - 1)) * (kPfD * 2);
+        const int pg = __builtin_amdgcn_readlane(ptreg, ((t * KT + S::KPW * wave) >> pv.logP) - pt_base);
+        // inside its page the tile begins at row (KT t) mod P (0 unless a page holds several tiles)
+        const char *sb = page_ptr(pv, pg) + (size_t)((t * KT) & (pv.P - 1)) * (D * 2);
         r_k = *reinterpret_cast<const uint4 *>(sb + lean_k_off);
         r_v = *reinterpret_cast<const uint4 *>(sb + lean_k_off + pv.v_off);
         r_lo = INT_MIN;
         r_hi = INT_MAX;
     };
     auto stage = [&](int buf, const uint4 &r_k, const uint4 &r_v, int r_lo, int r_hi) __attribute__((always_inline)) {
-        *reinterpret_cast<uint4 *>(&s_k[buf][ld_key * kPfKStride + ld_dc * 16]) = r_k;
-        *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * kPfVStride + ld_dc * 16]) = r_v;
+        *reinterpret_cast<uint4 *>(&s_k[buf][ld_key * S::KStride + ld_dc * 16]) = r_k;
+        *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * S::VStride + ld_dc * 16]) = r_v;
         if (ld_dc == 0) { s_lo[buf][ld_key] = r_lo; s_hi[buf][ld_key] = r_hi; }
     };
+    const int n_plain = gl / KT;  // full tiles of the global cache: no mask
+    // A weight of zero does not keep an inf or NaN of V out of a product, so tiles of which some query sees only a part
+    // are looked through (the three-part shapes; t: the tile that goes to the buffer).
+    auto look = [&](int buf, const uint4 &r_v, int t) __attribute__((always_inline)) {
+        if (S::PARTS > 1 && t >= n_plain && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
+            s_bad[buf] = t;  // all writers of a tile write the same
+    };
+    if (S::PARTS > 1 && threadIdx.x < 2) s_bad[threadIdx.x] = -1;
 
-    const int n_plain = gl / kPfKT;  // full tiles of the global cache: no mask
     auto fetch_any = [&](int t, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
         if (lean_ok && t < n_plain) fetch_lean(t, r_k, r_v, r_lo, r_hi);
         else fetch(t, r_k, r_v, r_lo, r_hi);
     };
     fetch_any(0, k0r, v0r, lo0r, hi0r);
     stage(0, k0r, v0r, lo0r, hi0r);
+    if constexpr (S::PARTS > 1) __syncthreads();  // s_bad is set
+    look(0, v0r, 0);
     if (n_tiles > 1) fetch_any(1, k1r, v1r, lo1r, hi1r);
     __syncthreads();
 
@@ -212,86 +289,135 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     auto body = [&](int t, uint4 &f_k, uint4 &f_v, int &f_lo, int &f_hi, const uint4 &s_kk, const uint4 &s_vv,
                     const int &s_lo_, const int &s_hi_) __attribute__((always_inline)) {
         const int buf = t & 1;
-        // LDS latency is the scarce thing here: the eight K fragments are requested at once,
+        // A block of more than 64 positions has waves whose rows end before a chunk tile begins, and a short
+        // sequence leaves waves without rows: they only stage.  (At 64 positions it is one tile in a block.)
+        const bool act = S::Q <= 64 || (q_first < T && (t - n_g - n_r) * KT <= q_first + 31);  // wave-uniform
+        // LDS latency is the scarce thing here: the K fragments are requested at once,
         // the address arithmetic and global loads of the next tile run while they arrive,
         // and the V fragments are requested before the softmax that hides their latency.
-        pf_bf16x8_t ka[8];
+        pf_bf16x8_t ka[NS][KS];
+        if (act) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++)
-            ka[ks] = *reinterpret_cast<const pf_bf16x8_t *>(&s_k[buf][qn * kPfKStride + (ks * 16 + half * 8) * 2]);
+            for (int n = 0; n < NS; n++)
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++)
+                    ka[n][ks] = *reinterpret_cast<const pf_bf16x8_t *>(
+                        &s_k[buf][(32 * n + qn) * S::KStride + (ks * 16 + half * 8) * 2]);
+        }
         __builtin_amdgcn_sched_barrier(0);
         if (t + 2 < n_tiles) fetch_any(t + 2, f_k, f_v, f_lo, f_hi);  // in flight while this tile and the next are multiplied
         __builtin_amdgcn_sched_barrier(0);
-
-        // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
-        pf_f32x16_t s;
+        if (act) {
+            // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
+            pf_f32x16_t s[NS];
 #pragma unroll
-        for (int c = 0; c < 16; c++) s[c] = 0.f;
+            for (int n = 0; n < NS; n++) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qv[ks], s, 0, 0, 0);
-        // V^T fragments read column-wise from the row-major V tile
-        pf_bf16x8_t va[2][4];
+                for (int c = 0; c < 16; c++) s[n][c] = 0.f;
 #pragma unroll
-        for (int t2 = 0; t2 < 2; t2++)
-#pragma unroll
-            for (int db = 0; db < 4; db++) va[t2][db] = pf_get_cols(s_v[buf], lane, db, 16 * t2);
-        __builtin_amdgcn_sched_barrier(0);
-        // register c = 4j+i of a lane holds key 8j + 4*half + i of the tile
-        const bool plain = t < n_plain;
-        float sc[16];
-        float mt = -INFINITY;
-        if (plain) {
-#pragma unroll
-            for (int c = 0; c < 16; c++) {
-                sc[c] = s[c] * a.scale_log2e;
-                mt = fmaxf(mt, sc[c]);
+                for (int ks = 0; ks < KS; ks++)
+                    s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[n][ks], qv[ks], s[n], 0, 0, 0);
             }
-        } else {
+            // V^T fragments read column-wise from the row-major V tile
+            // (with three parts of P there are no registers for all of them during the softmax: read at their products)
+            pf_bf16x8_t va[2 * NS][DB];
+            auto read_v = [&](int t2) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
-                const int4 hi4 = *reinterpret_cast<const int4 *>(&s_hi[buf][8 * j + 4 * half]);
-                const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi_[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
+                for (int db = 0; db < DB; db++) va[t2][db] = pf_get_cols<S::VStride>(s_v[buf], lane, db, 16 * t2);
+            };
+            if constexpr (S::PARTS == 1) {
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const bool vis = (qpos >= lo_[i]) && (qpos <= hi_[i]);
-                    const float x = vis ? s[4 * j + i] * a.scale_log2e : -INFINITY;
-                    sc[4 * j + i] = x;
-                    mt = fmaxf(mt, x);
+                for (int t2 = 0; t2 < 2 * NS; t2++) read_v(t2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // register c = 4j+i of a lane holds key 8j + 4*half + i of a score tile
+            const bool plain = t < n_plain;
+            float sc[16 * NS];
+            float mt = -INFINITY;
+            if (plain) {
+#pragma unroll
+                for (int c = 0; c < 16 * NS; c++) {
+                    sc[c] = s[c / 16][c % 16] * a.scale_log2e;
+                    mt = fmaxf(mt, sc[c]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4 * NS; j++) {
+                    const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
+                    const int4 hi4 = *reinterpret_cast<const int4 *>(&s_hi[buf][8 * j + 4 * half]);
+                    const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi_[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const bool vis = (qpos >= lo_[i]) && (qpos <= hi_[i]);
+                        const float x = vis ? s[j / 4][4 * (j % 4) + i] * a.scale_log2e : -INFINITY;
+                        sc[4 * j + i] = x;
+                        mt = fmaxf(mt, x);
+                    }
+                }
+            }
+            mt = fmaxf(mt, __shfl_xor(mt, 32));  // the other half of the keys of this query
+            const float mnew = fmaxf(m, mt);
+            const float msafe = mnew == -INFINITY ? 0.f : mnew;
+            const float corr = __builtin_amdgcn_exp2f(m - msafe);
+            uint32_t pb[S::PARTS][8 * NS];
+            float ps = 0.f;
+            const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+            for (int c = 0; c < 8 * NS; c++) {
+                const float p0 = __builtin_amdgcn_exp2f(sc[2 * c] - msafe), p1 = __builtin_amdgcn_exp2f(sc[2 * c + 1] - msafe);
+                if constexpr (S::PARTS == 1) {
+                    pb[0][c] = pf_pack(p0, p1);
+                    // the denominator sums the rounded weights, the ones the second product uses
+                    ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[0][c]), ones, ps, false);
+                } else {
+                    ps += p0 + p1;
+                    const float r0 = pf_rest(p0), r1 = pf_rest(p1);
+                    pb[0][c] = pf_top(p0, p1);
+                    pb[1][c] = pf_top(r0, r1);
+                    pb[2][c] = pf_top(pf_rest(r0), pf_rest(r1));
+                }
+            }
+            l = l * corr + ps;
+            if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
+#pragma unroll
+                for (int db = 0; db < DB; db++)
+#pragma unroll
+                    for (int c = 0; c < 16; c++) o[db][c] *= corr;
+            }
+            m = mnew;
+            // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys, small parts first ----
+            if constexpr (S::PARTS > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t2 = 0; t2 < 2 * NS; t2++) {
+                if constexpr (S::PARTS > 1) {
+                    read_v(t2);
+                    if (s_bad[buf] == t) {  // block-uniform
+                        // the finite values go on to the product; the queries that see the others get them here
+                        uint32_t seen[4];
+#pragma unroll
+                        for (int c = 0; c < 4; c++) {  // pair c of the eight keys of this lane's half
+                            const int key = 16 * t2 + 8 * (c / 2) + 4 * half + 2 * (c % 2);
+                            seen[c] = (qpos >= s_lo[buf][key] && qpos <= s_hi[buf][key] ? 0x3f80u : 0u) |
+                                      (qpos >= s_lo[buf][key + 1] && qpos <= s_hi[buf][key + 1] ? 0x3f800000u : 0u);
+                        }
+#pragma unroll
+                        for (int db = 0; db < DB; db++) pf_take_nonfinite(va[t2][db], seen, o[db]);
+                    }
+                }
+#pragma unroll
+                for (int part = S::PARTS - 1; part >= 0; part--) {
+                    const uint4 p4 = make_uint4(pb[part][4 * t2], pb[part][4 * t2 + 1], pb[part][4 * t2 + 2], pb[part][4 * t2 + 3]);
+                    const pf_bf16x8_t pbv = __builtin_bit_cast(pf_bf16x8_t, p4);
+#pragma unroll
+                    for (int db = 0; db < DB; db++)
+                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t2][db], pbv, o[db], 0, 0, 0);
                 }
             }
         }
-        mt = fmaxf(mt, __shfl_xor(mt, 32));  // the other 16 keys of this query
-        const float mnew = fmaxf(m, mt);
-        const float msafe = mnew == -INFINITY ? 0.f : mnew;
-        const float corr = __builtin_amdgcn_exp2f(m - msafe);
-        uint32_t pb[8];
-        float ps = 0.f;
-        const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-        for (int c = 0; c < 8; c++) {
-            pb[c] = pf_pack(__builtin_amdgcn_exp2f(sc[2 * c] - msafe), __builtin_amdgcn_exp2f(sc[2 * c + 1] - msafe));
-            // the denominator sums the rounded weights, the ones the second product uses
-            ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[c]), ones, ps, false);
+        if (t + 1 < n_tiles) {
+            stage(buf ^ 1, s_kk, s_vv, s_lo_, s_hi_);
+            look(buf ^ 1, s_vv, t + 1);
         }
-        l = l * corr + ps;
-        if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
-#pragma unroll
-            for (int db = 0; db < 4; db++)
-#pragma unroll
-                for (int c = 0; c < 16; c++) o[db][c] *= corr;
-        }
-        m = mnew;
-        // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the 32 keys ----
-#pragma unroll
-        for (int t2 = 0; t2 < 2; t2++) {
-            const uint4 p4 = make_uint4(pb[4 * t2], pb[4 * t2 + 1], pb[4 * t2 + 2], pb[4 * t2 + 3]);
-            const pf_bf16x8_t pbv = __builtin_bit_cast(pf_bf16x8_t, p4);
-#pragma unroll
-            for (int db = 0; db < 4; db++)
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t2][db], pbv, o[db], 0, 0, 0);
-        }
-        if (t + 1 < n_tiles) stage(buf ^ 1, s_kk, s_vv, s_lo_, s_hi_);
         __syncthreads();
     };
     {
@@ -305,13 +431,13 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
 
     // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
     {
-        const int i = qt * kPfQ + rb * 32 + qn;
+        const int i = q_first + qn;
         const float lt = l + __shfl_xor(l, 32);
         if (i < T) {
             const float inv = 1.0f / lt;
-            float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * kPfD;
+            float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * D;
 #pragma unroll
-            for (int db = 0; db < 4; db++)
+            for (int db = 0; db < DB; db++)
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
                     const float4 w4 = make_float4(o[db][4 * j] * inv, o[db][4 * j + 1] * inv,
@@ -341,10 +467,19 @@ size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q) {
     return 256 + sizeof(int32_t) * kMaxCallUnits;  // the order of the units; everything else stays in registers and LDS
 }
 
+template <int D, int G, int PARTS>
+static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t, hipStream_t st) {
+    using S = PfShape<D, G, PARTS>;
+    a.nx = (max_t + S::Q - 1) / S::Q;
+    hipLaunchKernelGGL((attend_prefill_kernel<D, G, PARTS>), dim3(a.nx * pv.Hkv * cs.n), dim3(512), 0, st, pv, cs, a);
+    return hipGetLastError();
+}
+
+// bf16 pools of every head_dim and group size (fp32 pools: launch_attend_prefill_f32)
 hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, const void *q,
                                  const void *k, const void *v, const float *g, float tau,
                                  float scale, float *out, void *ws, hipStream_t st) {
-    if (pv.dtype != WGKV_BF16 || pv.d != kPfD || pv.G != 4) return hipErrorNotSupported;
+    if (pv.dtype != WGKV_BF16) return hipErrorNotSupported;
     PrefillAttnArgs a;
     a.layer = layer;
     a.tau = tau;
@@ -357,13 +492,30 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     int max_t = 0;
     for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
     if (max_t == 0) return hipSuccess;
-    a.nx = (max_t + kPfQ - 1) / kPfQ;
+    // a grid of one block per 32 positions (group of 8) has to stay inside grid.x
+    if ((int64_t)((max_t + kPfQMin - 1) / kPfQMin) * pv.Hkv * cs.n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     a.order = (const int32_t *)ws;
     hipLaunchKernelGGL(prefill_order_kernel, dim3(1), dim3(1024), 0, st, pv, cs, layer, (int32_t *)ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attend_prefill_kernel, dim3(a.nx * pv.Hkv * cs.n), dim3(512), 0, st, pv, cs, a);
-    return hipGetLastError();
+    if (pv.d == 128) {
+        switch (pv.G) {
+            case 1: return launch_shape<128, 1, 3>(pv, cs, a, max_t, st);
+            case 2: return launch_shape<128, 2, 3>(pv, cs, a, max_t, st);
+            case 4: return launch_shape<128, 4, 1>(pv, cs, a, max_t, st);
+            case 8: return launch_shape<128, 8, 3>(pv, cs, a, max_t, st);
+            default: break;
+        }
+    } else if (pv.d == 64) {
+        switch (pv.G) {
+            case 1: return launch_shape<64, 1, 3>(pv, cs, a, max_t, st);
+            case 2: return launch_shape<64, 2, 3>(pv, cs, a, max_t, st);
+            case 4: return launch_shape<64, 4, 3>(pv, cs, a, max_t, st);
+            case 8: return launch_shape<64, 8, 3>(pv, cs, a, max_t, st);
+            default: break;
+        }
+    }
+    return hipErrorNotSupported;
 }
 
 }  // namespace wgkv

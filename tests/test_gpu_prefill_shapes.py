@@ -1,0 +1,95 @@
+"""The prefill form of wgkv_attend for every head shape a pool accepts, at the edges of its tiles: sequences that end
+one short of, on and one past a row block of 32, a key tile and a block's positions, global caches that end inside
+a tile, and values of V that are not finite in a tile of which some queries see only a part."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_17452_amd as wg
+from oracle import attend_definition
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(dt, d, G) for dt in (wg.F32, wg.BF16) for d in (64, 128) for G in (1, 2, 4, 8)]
+IDS = [f"{'f32' if dt == wg.F32 else 'bf16'}-d{d}-G{G}" for dt, d, G in SHAPES]
+
+
+def _tol(dtype, d, G):
+    """max abs error against fp64, V ~ N(0, 1).  The 128-wide group of four rounds its weights to bf16 (2^-9 of a
+    weighted mean of |v - out|).  Every other shape sums fp32 products of fp32 weights: the scores' relative error of
+    about d * 2^-24 moves a weight by scale * |s| * that, and the sums over a few hundred keys add as little."""
+    return 1e-2 if (dtype, d, G) == (wg.BF16, 128, 4) else 2e-5
+
+
+def _feed(dtype, d, G, Hk, chunks, W, P, tau, seed, spoil=None):
+    """chunks: per call the token counts of the sequences.  Yields (sequence, first position, K, V, g so far, q, out)."""
+    tdt = torch.float32 if dtype == wg.F32 else torch.bfloat16
+    dev, B, Hq = torch.device("cuda:0"), len(chunks[0]), G * Hk
+    total = max(sum(c[s] for c in chunks) for s in range(B))
+    max_gp = total // P + 2
+    pool = wg.Pool(wg.Config(1, Hq, Hk, d, dtype, P, W, B, max_gp, B * Hk * (max_gp + -(-W // P)) + 8), B,
+                   max(sum(c) for c in chunks))
+    gen = torch.Generator().manual_seed(seed)
+    hist = [[np.zeros((0, Hk, d), np.float32), np.zeros((0, Hk, d), np.float32), np.zeros((0, Hk), np.float32)] for _ in range(B)]
+    for call, nt in enumerate(chunks):
+        tot = sum(nt)
+        q, k, v = (torch.randn((tot, h, d), generator=gen).to(tdt) for h in (Hq, Hk, Hk))
+        g = torch.rand((tot, Hk), generator=gen)
+        if spoil is not None:
+            spoil(call, v)
+        out = torch.full((tot, Hq, d), float("nan"), device=dev)
+        kd, vd, gd = k.to(dev), v.to(dev), g.to(dev)
+        pool.attend(0, list(range(B)), q.to(dev), out, 1 / math.sqrt(d), n_q=nt, k_chunk=kd, v_chunk=vd, g_chunk=gd, tau=tau)
+        pool.prefill_admit(0, list(range(B)), nt, kd, vd, gd, tau=tau)
+        base = 0
+        for s, n in enumerate(nt):
+            h, t0 = hist[s], len(hist[s][0])
+            for i, x in enumerate((k, v, g)):
+                h[i] = np.concatenate([h[i], x[base:base + n].float().numpy()])
+            if n:
+                yield s, t0, h[0], h[1], h[2], q[base:base + n].float().numpy(), out[base:base + n].cpu().numpy()
+            base += n
+    assert pool.status()[1] == 0
+
+
+@pytest.mark.parametrize("dtype,d,G", SHAPES, ids=IDS)
+@pytest.mark.parametrize("W,P,chunks", [(40, 16, [[1, 31, 32], [33, 63, 64], [65, 1, 127]]),
+                                        (7, 1, [[129, 0, 255], [256, 257, 31]]),
+                                        (100, 64, [[300, 96, 5], [0, 32, 290]])], ids=["short", "page1", "page64"])
+def test_every_shape_at_the_edges(dtype, d, G, W, P, chunks):
+    tau, worst = 0.6, 0.0
+    for s, t0, K, V, g, q, out in _feed(dtype, d, G, 2, chunks, W, P, tau, seed=d + G + W):
+        ref = attend_definition(K, V, g, q, t0 + np.arange(len(q)), W, tau, 1 / math.sqrt(d))
+        assert np.isfinite(out).all(), (s, t0)
+        worst = max(worst, np.abs(out - ref).max())
+    assert worst <= _tol(dtype, d, G), worst
+
+
+@pytest.mark.parametrize("dtype,d,G", [x for x in SHAPES if x != (wg.BF16, 128, 4)],
+                         ids=[i for i in IDS if i != "bf16-d128-G4"])
+def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(dtype, d, G):
+    W, P, tau = 24, 16, 0.6
+    inf = float("inf")
+
+    def spoil(call, v):  # of the first call's 70 tokens, and of the second one's 90
+        for row, col, x in (((10, 3, inf), (40, 5, -inf), (41, d - 1, inf)) if call == 0 else
+                            ((20, 3, -inf), (50, 7, float("nan")), (77, 9, inf), (88, d - 1, -inf))):
+            v[row, 0, col] = x
+
+    for s, t0, K, V, g, q, out in _feed(dtype, d, G, 2, [[70], [90]], W, P, tau, seed=5 * d + G, spoil=spoil):
+        clean = np.where(np.isfinite(V), V, 0.0).astype(np.float32)
+        ref = attend_definition(K, clean, g, q, t0 + np.arange(len(q)), W, tau, 1 / math.sqrt(d))
+        pos = np.arange(len(K))
+        for i in range(len(q)):
+            for h in range(2):
+                see = (pos <= t0 + i) & ((t0 + i - pos < W) | (g[:, h] >= tau))
+                add = np.where(np.isfinite(V[see, h]), 0.0, V[see, h])  # a positive weight times inf or NaN
+                with np.errstate(invalid="ignore"):
+                    ref[i, h * G:(h + 1) * G] += add.sum(0)
+        fin = np.isfinite(ref)
+        np.testing.assert_array_equal(np.isfinite(out), fin)
+        np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
+        np.testing.assert_array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.abs(out[fin] - ref[fin]).max() <= _tol(dtype, d, G)
