@@ -315,7 +315,7 @@ int wgkv_attend(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int32_t *s
                 float *out_dev, void *workspace_dev, size_t workspace_bytes, wgkv_stream stream);
 
 /* Optional tuning of the decode form of wgkv_attend to the machine.  The tiles of a launch are
- * split evenly over its waves except for one correction: blocks go to the 8 XCDs of the GPU in
+ * split evenly over its blocks except for one correction: blocks go to the 8 XCDs of the GPU in
  * turn, and the odd XCD of each pair streams a few per cent slower than the even one, by an amount
  * that differs between machines.  This call runs the decode attention of every layer for the
  * given sequences (arguments as for wgkv_attend, the same queries for every layer; the cache is

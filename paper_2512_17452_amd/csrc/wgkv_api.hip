@@ -41,11 +41,10 @@ hipError_t launch_quest_select(const View &pv, const CallSeqs &cs, int layer, co
 size_t attend_decode_ws_bytes(const View &pv, int n_seqs, int grid);
 hipError_t static_scratch_init();
 void *static_scratch();
-void attend_decode_warm(const View &pv);
 hipError_t launch_attend_decode(const View &pv, int layer, int n_seqs, const int32_t *sids,
                                 const void *q, float scale, float *out, void *ws, int32_t *counters,
-                                int n_cu, int grid_max, int min_tpw, hipStream_t st, hipEvent_t ev0,
-                                hipEvent_t ev1, const int32_t *sel_pages, const int32_t *sel_count,
+                                int n_cu, int grid_max, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
+                                const int32_t *sel_pages, const int32_t *sel_count,
                                 int sel_stride, int skew_permille);
 hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head_dim, int width,
                            const void *k, const void *k_rope, const void *w1, const float *b1,
@@ -80,7 +79,6 @@ namespace {
 
 constexpr int kPrefillBlkHost = 512;    // must match kPrefillBlk in admit.hip
 constexpr int kAttnGridMax = 2048;      // upper bound on the decode-attention grid (blocks of 4 waves)
-constexpr int kAttnMinTilesPerWave = 16;  // below that a share is shorter than the fold of its partial
 constexpr int kAttnDefaultSkewPermille = 50;  // see wgkv_tune_decode_attention
 constexpr int kAttnStaticGridMax = 512;   // grid bound of the entry point that keeps its partials in the static array
 
@@ -256,13 +254,12 @@ int wgkv_init_pool(const wgkv_config *cfg, void *pool_dev, size_t pool_bytes, vo
     p->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
     p->ev0 = p->ev1 = nullptr;
     p->skew_permille = kAttnDefaultSkewPermille;
-    // set-up for wgkv_attend_decode_static: this device's address of the static scratch array and
-    // the launch shape of the pool's attention kernel, so that the call itself asks the runtime nothing
+    // set-up for wgkv_attend_decode_static: this device's address of the static scratch array, so that the call
+    // itself asks the runtime nothing
     if (static_scratch_init() != hipSuccess) {
         delete p;
         return WGKV_ERR_HIP;
     }
-    attend_decode_warm(v);
     if (launch_init(v, (hipStream_t)stream) != hipSuccess) {
         delete p;
         return WGKV_ERR_HIP;
@@ -622,8 +619,7 @@ int wgkv_attend(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int32_t *seq_
             if (n_q_host[b] != 1) return WGKV_ERR_INVALID_ARG;
         if (workspace_bytes < attend_decode_ws_bytes(p->view, n_seqs, kAttnGridMax)) return WGKV_ERR_WORKSPACE;
         return launch_attend_decode(p->view, layer, n_seqs, seq_ids_host, q_dev, scale, out_dev,
-                                    workspace_dev, p->view.unit_counters, p->n_cu, kAttnGridMax,
-                                    kAttnMinTilesPerWave, st, p->ev0, p->ev1, nullptr, nullptr,
+                                    workspace_dev, p->view.unit_counters, p->n_cu, kAttnGridMax, st, p->ev0, p->ev1, nullptr, nullptr,
                                     0, p->skew_permille) == hipSuccess
                    ? WGKV_OK
                    : WGKV_ERR_HIP;
@@ -666,9 +662,8 @@ int wgkv_attend_decode_static(wgkv_pool *p, int32_t layer, int32_t n_seqs, const
     void *ws = static_scratch();
     if (!ws) return WGKV_ERR_HIP;  // no pool was ever initialised on the current device
     return launch_attend_decode(p->view, layer, n_seqs, seq_ids_host, q_dev, scale, out_dev, ws,
-                                p->view.unit_counters, p->n_cu, kAttnStaticGridMax, kAttnMinTilesPerWave,
-                                (hipStream_t)stream, p->ev0, p->ev1, nullptr, nullptr, 0,
-                                p->skew_permille) == hipSuccess
+                                p->view.unit_counters, p->n_cu, kAttnStaticGridMax,
+                                (hipStream_t)stream, p->ev0, p->ev1, nullptr, nullptr, 0, p->skew_permille) == hipSuccess
                ? WGKV_OK
                : WGKV_ERR_HIP;
 }
@@ -749,9 +744,9 @@ int wgkv_attend_selected(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int3
         return WGKV_ERR_INVALID_ARG;
     if (workspace_bytes < attend_decode_ws_bytes(p->view, n_seqs, kAttnGridMax)) return WGKV_ERR_WORKSPACE;
     return launch_attend_decode(p->view, layer, n_seqs, seq_ids_host, q_dev, scale, out_dev, workspace_dev,
-                                p->view.unit_counters, p->n_cu, kAttnGridMax, kAttnMinTilesPerWave,
-                                (hipStream_t)stream, p->ev0, p->ev1, sel_pages_dev, sel_count_dev,
-                                sel_stride, p->skew_permille) == hipSuccess
+                                p->view.unit_counters, p->n_cu, kAttnGridMax,
+                                (hipStream_t)stream, p->ev0, p->ev1, sel_pages_dev, sel_count_dev, sel_stride,
+                                p->skew_permille) == hipSuccess
                ? WGKV_OK
                : WGKV_ERR_HIP;
 }
@@ -853,7 +848,7 @@ int wgkv_tune_decode_attention(wgkv_pool *p, int32_t n_seqs, const int32_t *seq_
             float sum = 0.f;
             for (int l = 0; l < L && ok; l++) {
                 ok = launch_attend_decode(p->view, l, n_seqs, seq_ids_host, q_dev, scale, out_dev, workspace_dev,
-                                          p->view.unit_counters, p->n_cu, kAttnGridMax, kAttnMinTilesPerWave, st, e0,
+                                          p->view.unit_counters, p->n_cu, kAttnGridMax, st, e0,
                                           e1, nullptr, nullptr, 0, kCand[c]) == hipSuccess &&
                      hipEventSynchronize(e1) == hipSuccess;
                 float ms = 0.f;
