@@ -9,6 +9,12 @@
 // that were neither admitted nor inside the window are gone (Sec. 4.2, "Initial
 // cache population") and are invisible under M_ij anyway.
 //
+// What a block reads: the global cache, the ring, and of the chunk the keys that some window of the
+// block reaches, plus those older ones that are admitted.  The latter are picked out by a small kernel
+// in front (one list of admitted chunk positions per unit), so that tiles are full of keys that every
+// query of the block sees, instead of running over the whole chunk with a mask (4096-token chunks at an
+// admission rate of a half, 0-12K tokens before them: 1095 -> 803 us per chunk of two prompts, lists included).
+//
 // One block owns 256 / G chunk positions of one (sequence, kv head) with a group of G query heads;
 // its eight waves are (query head of the group) x (row block of 32 positions), so a K/V tile staged
 // in LDS feeds all of them and two waves share each SIMD.  A tile is 8 KiB of K and of V (16 bytes of
@@ -58,6 +64,8 @@ constexpr int kPfQMin = 32;       // chunk positions per block at the largest gr
 struct PrefillAttnArgs {
     int nx;                 // blocks per (sequence, kv head) of the launch
     const int32_t *order;   // [n_units] (sequence, kv head) units, the one with the longest global cache first
+    const int32_t *pick;    // admitted chunk positions of every unit, ascending (pick_of), or NULL
+    const int32_t *picked;  // how many of them lie below position 32 i, for every i (picked_of)
     int layer;
     float tau;
     float scale_log2e;
@@ -164,9 +172,13 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     const int gl = pv.global_len[um];
     const int w_eff = min(pv.W, t0);              // ring entries that exist
     const int i_end = min(T, qt * S::Q + S::Q);   // chunk keys this block can see: [0, i_end)
+    // tiles: global cache, ring, picked chunk keys below `near`, all chunk keys from there on
+    const int near = a.pick ? max(0, qt * S::Q - pv.W + 1) / KT * KT : 0;  // no window of the block reaches below
+    const int32_t *pick = a.pick ? a.pick + pick_of(pv.Hkv, b, h, base, T) : a.order;
+    const int n_far = near > 0 ? a.picked[picked_of(pv.Hkv, b, h, base, T) + near / 32] : 0;
     const int n_g = (gl + KT - 1) / KT, n_r = (w_eff + KT - 1) / KT;
-    const int n_c = (i_end + KT - 1) / KT;
-    const int n_tiles = n_g + n_r + n_c;
+    const int t_far = n_g + n_r, t_near = t_far + (n_far + KT - 1) / KT;  // first tile of each kind
+    const int n_tiles = t_near + (i_end - near + KT - 1) / KT;
 
     // ---- Q^T operand: this lane's query, all d-slices of 16 ----
     pf_bf16x8_t qv[KS];
@@ -201,7 +213,12 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     const int lpreg = (lp_in_reg && lane < pv.nlp) ? pv.local_pt[(size_t)um * pv.nlp + lane] : 0;
     const int slot0 = t0 > pv.W ? t0 % pv.W : 0;  // ring slot of the oldest position
     const int64_t v_delta_chunk = a.v - a.k;
-    auto fetch = [&](int t, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
+    // position of this thread's key of a picked tile (anything for another tile): asked for an iteration before its
+    // row is
+    auto ask_far = [&](int t) __attribute__((always_inline)) {
+        return pick[max(0, min((t - t_far) * KT + ld_key, n_far - 1))];
+    };
+    auto fetch = [&](int t, int far, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
         const char *kp;
         int64_t v_delta;
         int lo = INT_MAX, hi = INT_MAX;  // invisible unless shown otherwise
@@ -215,7 +232,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
             kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
             if (idx < gl) lo = INT_MIN;
             v_delta = pv.v_off;
-        } else if (t < n_g + n_r) {  // ring, oldest position first
+        } else if (t < t_far) {  // ring, oldest position first
             const int idx = (t - n_g) * KT + ld_key, idc = min(idx, w_eff - 1);
             int slot = slot0 + idc;
             slot = slot >= pv.W ? slot - pv.W : slot;
@@ -228,8 +245,12 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
                 hi = (pv.ring_g[(size_t)um * pv.W + slot] >= a.tau) ? INT_MAX : pos + pv.W - 1;
             }
             v_delta = pv.v_off;
+        } else if (t < t_near) {  // picked keys of this chunk: visible to every query
+            kp = a.k + ((size_t)(base + far) * pv.Hkv + h) * (D * 2);
+            if ((t - t_far) * KT + ld_key < n_far) lo = INT_MIN;
+            v_delta = v_delta_chunk;
         } else {  // this chunk
-            const int idx = (t - n_g - n_r) * KT + ld_key, idc = min(idx, T - 1);
+            const int idx = near + (t - t_near) * KT + ld_key, idc = min(idx, T - 1);
             const size_t row = (size_t)(base + idc) * pv.Hkv + h;
             kp = a.k + row * (D * 2);
             if (idx < T) {
@@ -265,24 +286,28 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
         *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * S::VStride + ld_dc * 16]) = r_v;
         if (ld_dc == 0) { s_lo[buf][ld_key] = r_lo; s_hi[buf][ld_key] = r_hi; }
     };
-    const int n_plain = gl / KT;  // full tiles of the global cache: no mask
+    const int n_plain = gl / KT;  // full tiles of the global cache: no mask; nor do full tiles of picked keys need one
+    const int t_plain = t_far + n_far / KT;
+    auto no_mask = [&](int t) __attribute__((always_inline)) { return t < n_plain || (t >= t_far && t < t_plain); };
     // A weight of zero does not keep an inf or NaN of V out of a product, so tiles of which some query sees only a part
     // are looked through (the three-part shapes; t: the tile that goes to the buffer).
     auto look = [&](int buf, const uint4 &r_v, int t) __attribute__((always_inline)) {
-        if (S::PARTS > 1 && t >= n_plain && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
+        if (S::PARTS > 1 && !no_mask(t) && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
             s_bad[buf] = t;  // all writers of a tile write the same
     };
     if (S::PARTS > 1 && threadIdx.x < 2) s_bad[threadIdx.x] = -1;
 
-    auto fetch_any = [&](int t, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
+    auto fetch_any = [&](int t, int far, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
         if (lean_ok && t < n_plain) fetch_lean(t, r_k, r_v, r_lo, r_hi);
-        else fetch(t, r_k, r_v, r_lo, r_hi);
+        else fetch(t, far, r_k, r_v, r_lo, r_hi);
     };
-    fetch_any(0, k0r, v0r, lo0r, hi0r);
+    const int far0 = ask_far(0), far1 = ask_far(1);
+    int far_next = ask_far(2);
+    fetch_any(0, far0, k0r, v0r, lo0r, hi0r);
     stage(0, k0r, v0r, lo0r, hi0r);
     if constexpr (S::PARTS > 1) __syncthreads();  // s_bad is set
     look(0, v0r, 0);
-    if (n_tiles > 1) fetch_any(1, k1r, v1r, lo1r, hi1r);
+    if (n_tiles > 1) fetch_any(1, far1, k1r, v1r, lo1r, hi1r);
     __syncthreads();
 
     // one iteration: tile t is multiplied, tile t+2 is requested into rf, tile t+1 goes from rs to LDS
@@ -291,7 +316,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
         const int buf = t & 1;
         // A block of more than 64 positions has waves whose rows end before a chunk tile begins, and a short
         // sequence leaves waves without rows: they only stage.  (At 64 positions it is one tile in a block.)
-        const bool act = S::Q <= 64 || (q_first < T && (t - n_g - n_r) * KT <= q_first + 31);  // wave-uniform
+        const bool act = S::Q <= 64 || (q_first < T && near + (t - t_near) * KT <= q_first + 31);  // wave-uniform
         // LDS latency is the scarce thing here: the K fragments are requested at once,
         // the address arithmetic and global loads of the next tile run while they arrive,
         // and the V fragments are requested before the softmax that hides their latency.
@@ -305,7 +330,9 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
                         &s_k[buf][(32 * n + qn) * S::KStride + (ks * 16 + half * 8) * 2]);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (t + 2 < n_tiles) fetch_any(t + 2, f_k, f_v, f_lo, f_hi);  // in flight while this tile and the next are multiplied
+        const int far = far_next;
+        far_next = ask_far(t + 3);
+        if (t + 2 < n_tiles) fetch_any(t + 2, far, f_k, f_v, f_lo, f_hi);  // in flight while this tile and the next are multiplied
         __builtin_amdgcn_sched_barrier(0);
         if (act) {
             // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
@@ -331,7 +358,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
             }
             __builtin_amdgcn_sched_barrier(0);
             // register c = 4j+i of a lane holds key 8j + 4*half + i of a score tile
-            const bool plain = t < n_plain;
+            const bool plain = no_mask(t);
             float sc[16 * NS];
             float mt = -INFINITY;
             if (plain) {
@@ -448,23 +475,56 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     }
 }
 
-// Units of the call by descending length of their global cache (equal lengths: lower unit first).
-__global__ __launch_bounds__(1024) void prefill_order_kernel(View pv, CallSeqs cs, int layer, int32_t *order) {
+// What the attention kernel wants to know about the call first.  Block u < n_units: the admitted positions of unit u's
+// chunk in ascending order, and how many of them lie below every multiple of 32 (a thread takes 8 consecutive positions
+// of every stretch of 2048).  The last block: the units by descending length of their global cache (equal lengths:
+// lower unit first).  Without room for the lists only the last block is launched.
+constexpr int kPickOwn = 8;
+__global__ __launch_bounds__(256) void prefill_look_kernel(View pv, CallSeqs cs, int layer, float tau, const float *g,
+                                                           int32_t *order, int32_t *pick, int32_t *picked) {
     __shared__ int s_len[kMaxCallUnits];
-    const int n_units = cs.n * pv.Hkv, u = threadIdx.x;
-    if (u < n_units) s_len[u] = pv.global_len[unit_meta(pv, cs.sid[u / pv.Hkv], layer, u % pv.Hkv)];
-    __syncthreads();
-    if (u < n_units) {
-        const int mine = s_len[u];
-        int rank = 0;
-        for (int v = 0; v < n_units; v++) rank += (s_len[v] > mine || (s_len[v] == mine && v < u)) ? 1 : 0;
-        order[rank] = u;
+    __shared__ int s_tmp[20];
+    const int n_units = cs.n * pv.Hkv;
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int u = threadIdx.x; u < n_units; u += 256)
+            s_len[u] = pv.global_len[unit_meta(pv, cs.sid[u / pv.Hkv], layer, u % pv.Hkv)];
+        __syncthreads();
+        for (int u = threadIdx.x; u < n_units; u += 256) {
+            const int mine = s_len[u];
+            int rank = 0;
+            for (int v = 0; v < n_units; v++) rank += (s_len[v] > mine || (s_len[v] == mine && v < u)) ? 1 : 0;
+            order[rank] = u;
+        }
+        return;
+    }
+    const int b = (int)blockIdx.x / pv.Hkv, h = (int)blockIdx.x % pv.Hkv;
+    const int T = cs.ntok[b], base = cs.base[b];
+    int32_t *list = pick + pick_of(pv.Hkv, b, h, base, T), *below = picked + picked_of(pv.Hkv, b, h, base, T);
+    const float *gu = g + (size_t)base * pv.Hkv + h;
+    int carry = 0;
+    for (int i0 = 0; i0 <= T; i0 += 256 * kPickOwn) {  // T itself included: the count below T if 32 divides it
+        const int i = i0 + (int)threadIdx.x * kPickOwn;
+        float x[kPickOwn];
+#pragma unroll
+        for (int e = 0; e < kPickOwn; e++) x[e] = T > 0 ? gu[(size_t)min(i + e, T - 1) * pv.Hkv] : 0.f;
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < kPickOwn; e++) n += (i + e < T && x[e] >= tau) ? 1 : 0;
+        int total;
+        int at = carry + block_excl_scan(n, s_tmp, &total);
+        if (i % 32 == 0 && i <= T) below[i / 32] = at;
+#pragma unroll
+        for (int e = 0; e < kPickOwn; e++)
+            if (i + e < T && x[e] >= tau) list[at++] = i + e;
+        carry += total;
     }
 }
 
+// The order of the units, then the lists of picked chunk keys (one entry per token and kv head at most) and their counts.
+constexpr size_t kPfOrderBytes = 256 + sizeof(int32_t) * kMaxCallUnits;
+size_t attend_prefill_ws_min_bytes() { return kPfOrderBytes; }
 size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q) {
-    (void)pv; (void)n_seqs; (void)total_q;
-    return 256 + sizeof(int32_t) * kMaxCallUnits;  // the order of the units; everything else stays in registers and LDS
+    return kPfOrderBytes + sizeof(int32_t) * (size_t)pv.Hkv * (size_t)(total_q + total_q / 32 + n_seqs);
 }
 
 template <int D, int G, int PARTS>
@@ -475,10 +535,31 @@ static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnAr
     return hipGetLastError();
 }
 
+// Lists of picked chunk keys pay as soon as some block of the call has keys behind all its windows, and need room.
+hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, float tau, const float *g, void *ws,
+                               size_t ws_bytes, const int32_t **order, const int32_t **pick, const int32_t **picked,
+                               hipStream_t st) {
+    int64_t total = 0;
+    int max_t = 0;
+    for (int b = 0; b < cs.n; b++) {
+        total += cs.ntok[b];
+        max_t = max(max_t, cs.ntok[b]);
+    }
+    const int n_units = cs.n * pv.Hkv;
+    const bool lists = max_t > pv.W && ws_bytes >= attend_prefill_ws_bytes(pv, cs.n, total);
+    int32_t *o = (int32_t *)ws, *p = lists ? o + kPfOrderBytes / sizeof(int32_t) : nullptr;
+    int32_t *c = lists ? p + (size_t)pv.Hkv * total : nullptr;
+    hipLaunchKernelGGL(prefill_look_kernel, dim3((lists ? n_units : 0) + 1), dim3(256), 0, st, pv, cs, layer, tau, g, o, p, c);
+    *order = o;
+    *pick = p;
+    *picked = c;
+    return hipGetLastError();
+}
+
 // bf16 pools of every head_dim and group size (fp32 pools: launch_attend_prefill_f32)
 hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, const void *q,
                                  const void *k, const void *v, const float *g, float tau,
-                                 float scale, float *out, void *ws, hipStream_t st) {
+                                 float scale, float *out, void *ws, size_t ws_bytes, hipStream_t st) {
     if (pv.dtype != WGKV_BF16) return hipErrorNotSupported;
     PrefillAttnArgs a;
     a.layer = layer;
@@ -494,9 +575,7 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     if (max_t == 0) return hipSuccess;
     // a grid of one block per 32 positions (group of 8) has to stay inside grid.x
     if ((int64_t)((max_t + kPfQMin - 1) / kPfQMin) * pv.Hkv * cs.n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    a.order = (const int32_t *)ws;
-    hipLaunchKernelGGL(prefill_order_kernel, dim3(1), dim3(1024), 0, st, pv, cs, layer, (int32_t *)ws);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &a.order, &a.pick, &a.picked, st);
     if (e != hipSuccess) return e;
     if (pv.d == 128) {
         switch (pv.G) {

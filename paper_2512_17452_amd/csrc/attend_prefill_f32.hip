@@ -3,7 +3,8 @@
 // v_mfma_f32_32x32x2_f32: products and sums are fp32, nothing is rounded to a shorter type.
 //
 // One block = 32 chunk positions of one query head.  Its keys are, in this order, the head's global cache (all
-// visible: admitted and older than every window of the chunk), the ring (oldest position first) and the chunk up to
+// visible: admitted and older than every window of the chunk), the ring (oldest position first), the admitted chunk
+// keys that no window of the block reaches (picked out beforehand, as for bf16 pools) and the rest of the chunk up to
 // the block's last query; a ring or chunk key at position p is visible to the query at position i iff i - p < W or its
 // score >= tau.  The waves of the block take the tiles of 32 keys in turn and are folded once at the end: the
 // matrix instruction is so slow (64 clocks for 4096 multiply-adds) that a tile of 64-element heads occupies a SIMD for
@@ -26,12 +27,17 @@ namespace wgkv {
 
 typedef __attribute__((ext_vector_type(16))) float pw_f32x16_t;
 
+hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, float tau, const float *g, void *ws,
+                               size_t ws_bytes, const int32_t **order, const int32_t **pick, const int32_t **picked,
+                               hipStream_t st);
+
 struct PrefillF32Args {
     int nx;                 // blocks per (sequence, query head) of the launch
     int layer;
     float tau, scale_log2e;
     const char *q, *k, *v;  // chunk tensors, fp32
     const float *g;         // chunk scores
+    const int32_t *pick, *picked;  // admitted chunk positions of every unit and their counts, or NULL
     float *out;
 };
 
@@ -56,8 +62,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
     const int w_eff = min(pv.W, t0);              // ring entries that exist
     const int slot0 = t0 > pv.W ? t0 % pv.W : 0;  // ring slot of the oldest position
     const int i_end = min(T, qt * 32 + 32);       // chunk keys this block can see
-    const int n_g = (gl + 31) / 32, n_r = (w_eff + 31) / 32, n_tiles = n_g + n_r + (i_end + 31) / 32;
-    const int n_plain = gl / 32;                  // full tiles of the global cache: no mask
+    const int near = a.pick ? max(0, qt * 32 - pv.W + 1) / 32 * 32 : 0;  // no window of the block reaches below
+    const int32_t *pick = a.pick + (a.pick ? pick_of(pv.Hkv, b, h, base, T) : 0);
+    const int n_far = near > 0 ? a.picked[picked_of(pv.Hkv, b, h, base, T) + near / 32] : 0;
+    const int n_g = (gl + 31) / 32, n_r = (w_eff + 31) / 32;
+    const int t_far = n_g + n_r, t_near = t_far + (n_far + 31) / 32, n_tiles = t_near + (i_end - near + 31) / 32;
+    const int n_plain = gl / 32;                  // full tiles of the global cache: no mask, nor for full picked ones
+    const int t_plain = t_far + n_far / 32;
     const int qpos = t0 + min(qt * 32 + n, T - 1);
 
     float *s_q = &s_o[0][0];  // [32][OS] until the fold
@@ -69,16 +80,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
     }
     __syncthreads();
     const float *q_half = s_q + n * OS + half * H2;
-    // Lane n looks after key n of a tile.  page_of: the page its row sits in (or -1), one load; locate: the row's
+    // Lane n looks after key n of a tile.  page_of: the page its row sits in (a picked key: its position), one load; locate: the row's
     // address and who sees it.  A key past the end of its region repeats the region's last one, invisibly.
     auto page_of = [&](int t) __attribute__((always_inline)) {
         if (t < n_g) return pv.global_pt[(size_t)um * pv.maxgp + (min(t * 32 + n, gl - 1) >> pv.logP)];
-        if (t < n_g + n_r) {
+        if (t < t_far) {
             int slot = slot0 + min((t - n_g) * 32 + n, w_eff - 1);
             slot = slot >= pv.W ? slot - pv.W : slot;
             return pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
         }
-        return -1;
+        return t < t_near ? pick[min((t - t_far) * 32 + n, n_far - 1)] : -1;
     };
     auto locate = [&](int t, int pg, int buf) __attribute__((always_inline)) {
         const char *kp, *vp;
@@ -88,7 +99,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
             kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * ROWB;
             vp = kp + pv.v_off;
             if (idx < gl) lo = INT_MIN;
-        } else if (t < n_g + n_r) {
+        } else if (t < t_far) {
             const int idx = (t - n_g) * 32 + n, idc = min(idx, w_eff - 1);
             int slot = slot0 + idc;
             slot = slot >= pv.W ? slot - pv.W : slot;
@@ -98,8 +109,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
                 lo = t0 - w_eff + idx;
                 hi = (pv.ring_g[(size_t)um * pv.W + slot] >= a.tau) ? INT_MAX : lo + pv.W - 1;
             }
+        } else if (t < t_near) {
+            const size_t row = (size_t)(base + pg) * pv.Hkv + h;
+            kp = a.k + row * ROWB;
+            vp = a.v + row * ROWB;
+            if ((t - t_far) * 32 + n < n_far) lo = INT_MIN;
         } else {
-            const int idx = (t - n_g - n_r) * 32 + n, idc = min(idx, T - 1);
+            const int idx = near + (t - t_near) * 32 + n, idc = min(idx, T - 1);
             const size_t row = (size_t)(base + idc) * pv.Hkv + h;
             kp = a.k + row * ROWB;
             vp = a.v + row * ROWB;
@@ -130,6 +146,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
     int buf = 0;
     if (wave < n_tiles) load_k(locate(wave, page_of(wave), 0));
     for (int t = wave; t < n_tiles; t += NW, buf ^= 1) {  // wave-uniform; no barrier inside
+        const bool masked = t >= n_plain && (t < t_far || t >= t_plain);
         const int tn = min(t + NW, n_tiles - 1);          // the tile asked for next (the last one again at the end)
         const int pgn = page_of(tn);
         pw_f32x16_t s;
@@ -150,7 +167,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
         uint32_t seen = 0xffffu;  // bit c: the query sees the key of register c
 #pragma unroll
         for (int c = 0; c < 16; c++) sc[c] = s[c] * a.scale_log2e;
-        if (t >= n_plain) {
+        if (masked) {
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[wave][buf][8 * j + 4 * half]);
@@ -196,7 +213,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
 #pragma unroll
                 for (int db = 0; db < DB; db++) vv[i][db] = vp[32 * db];
             }
-            if (t >= n_plain) {
+            if (masked) {
 #pragma unroll
                 for (int i = 0; i < VB; i++)
 #pragma unroll
@@ -273,7 +290,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
 }
 
 hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int layer, const void *q, const void *k,
-                                     const void *v, const float *g, float tau, float scale, float *out, hipStream_t st) {
+                                     const void *v, const float *g, float tau, float scale, float *out, void *ws,
+                                     size_t ws_bytes, hipStream_t st) {
     if (pv.dtype != WGKV_F32) return hipErrorNotSupported;
     PrefillF32Args a;
     a.layer = layer;
@@ -288,6 +306,12 @@ hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int lay
     for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
     if (max_t == 0) return hipSuccess;
     a.nx = (max_t + 31) / 32;
+    a.pick = a.picked = nullptr;
+    if (max_t > pv.W) {
+        const int32_t *order;
+        const hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &order, &a.pick, &a.picked, st);
+        if (e != hipSuccess) return e;
+    }
     const int64_t blocks = (int64_t)a.nx * pv.Hq * cs.n;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // grid.x
     // eight waves of 64-element heads fill the block's 64 KiB of folded outputs, four of 128-element heads do

@@ -65,12 +65,13 @@ hipError_t launch_sparsity_loss(const float *g, int64_t n, int64_t n_total, floa
 hipError_t launch_stream_read(const void *buf, size_t bytes, uint32_t *sink, int n_cu, hipStream_t st,
                               hipEvent_t ev0, hipEvent_t ev1);
 size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q);
+size_t attend_prefill_ws_min_bytes();
 hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, const void *q,
                                  const void *k, const void *v, const float *g, float tau,
-                                 float scale, float *out, void *ws, hipStream_t st);
+                                 float scale, float *out, void *ws, size_t ws_bytes, hipStream_t st);
 hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int layer, const void *q, const void *k,
-                                     const void *v, const float *g, float tau, float scale, float *out,
-                                     hipStream_t st);
+                                     const void *v, const float *g, float tau, float scale, float *out, void *ws,
+                                     size_t ws_bytes, hipStream_t st);
 }  // namespace wgkv
 
 using namespace wgkv;
@@ -639,13 +640,14 @@ int wgkv_attend(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int32_t *seq_
         if (total >= ((int64_t)1 << 31) / p->cfg.n_q_heads) return WGKV_ERR_INVALID_ARG;
     }
     if (total == 0) return WGKV_OK;
-    if (workspace_bytes < attend_prefill_ws_bytes(p->view, n_seqs, total)) return WGKV_ERR_WORKSPACE;
+    if (workspace_bytes < attend_prefill_ws_min_bytes()) return WGKV_ERR_WORKSPACE;  // what is more holds the picked keys
     if (p->ev0 && hipEventRecord(p->ev0, st) != hipSuccess) return WGKV_ERR_HIP;
     const hipError_t e = p->cfg.dtype == WGKV_BF16
                              ? launch_attend_prefill(p->view, cs, layer, q_dev, k_chunk_dev, v_chunk_dev, g_chunk_dev,
-                                                     tau, scale, out_dev, workspace_dev, st)
+                                                     tau, scale, out_dev, workspace_dev, workspace_bytes, st)
                              : launch_attend_prefill_f32(p->view, cs, layer, q_dev, k_chunk_dev, v_chunk_dev,
-                                                         g_chunk_dev, tau, scale, out_dev, st);
+                                                         g_chunk_dev, tau, scale, out_dev, workspace_dev, workspace_bytes,
+                                                         st);
     if (e != hipSuccess) return WGKV_ERR_HIP;
     if (p->ev1 && hipEventRecord(p->ev1, st) != hipSuccess) return WGKV_ERR_HIP;
     return WGKV_OK;

@@ -45,6 +45,12 @@ __device__ __forceinline__ char *page_ptr(const View &pv, int page) {
     return pv.pool + (uint64_t)(uint32_t)page * pv.page_bytes;
 }
 
+// Where a unit's part of the lists of picked chunk keys and of their counts begins; T its chunk length, base its first packed row.
+__device__ __forceinline__ size_t pick_of(int Hkv, int b, int h, int base, int T) { return (size_t)base * Hkv + (size_t)h * T; }
+__device__ __forceinline__ size_t picked_of(int Hkv, int b, int h, int base, int T) {
+    return (size_t)(base / 32 + b) * Hkv + (size_t)h * (T / 32 + 1);  // floors add up to no more than the floor of the sum
+}
+
 // Work items (x, head, z) of a 1-D launch of nx * nh * nz blocks.  Blocks go to the 8 XCDs
 // round-robin by their index, and each XCD has its own L2: when the heads divide evenly, an XCD
 // gets all blocks of its heads and of no others, so the blocks that stream the same K/V (or Q/dO)

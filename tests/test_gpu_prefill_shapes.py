@@ -93,3 +93,34 @@ def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(dtype, 
         np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
         np.testing.assert_array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
         assert np.abs(out[fin] - ref[fin]).max() <= _tol(dtype, d, G)
+
+
+@pytest.mark.parametrize("dtype,d,G,rate", [(wg.BF16, 128, 4, 0.1), (wg.BF16, 64, 1, 0.9), (wg.F32, 64, 8, 0.3), (wg.BF16, 128, 8, 0.0)])
+def test_picked_chunk_keys_and_the_whole_chunk_agree(dtype, d, G, rate):
+    """Chunks longer than the window read their older keys through lists in the workspace; with a workspace that has
+    no room for lists every key of the chunk is read.  Both against the definition; lengths around the list's
+    counting step of 32 positions and its stretch of 2048."""
+    W, P, tau, Hk, lens = 50, 16, 0.5, 2, [2081, 64, 2047, 33]
+    tdt = torch.float32 if dtype == wg.F32 else torch.bfloat16
+    dev, B, Hq, tot = torch.device("cuda:0"), len(lens), G * Hk, sum(lens)
+    max_gp = max(lens) // P + 2
+    pool = wg.Pool(wg.Config(1, Hq, Hk, d, dtype, P, W, B, max_gp, B * Hk * (max_gp + -(-W // P)) + 8), B, tot)
+    gen = torch.Generator().manual_seed(d + G)
+    q, k, v = (torch.randn((tot, h, d), generator=gen).to(tdt) for h in (Hq, Hk, Hk))
+    g = (torch.rand((tot, Hk), generator=gen) < rate).float()
+    outs = []
+    for small in (False, True):
+        if small:
+            pool.workspace = pool.workspace[:4352]
+        out = torch.full((tot, Hq, d), float("nan"), device=dev)
+        pool.attend(0, list(range(B)), q.to(dev), out, 1 / math.sqrt(d), n_q=lens, k_chunk=k.to(dev), v_chunk=v.to(dev),
+                    g_chunk=g.to(dev), tau=tau)
+        outs.append(out.cpu().numpy())
+    base = 0
+    for n in lens:
+        rows = np.unique(np.concatenate([np.arange(max(0, n - 70), n), np.arange(0, n, 13)]))
+        ref = attend_definition(k[base:base + n].float().numpy(), v[base:base + n].float().numpy(), g[base:base + n].numpy(),
+                                q[base:base + n].float().numpy()[rows], rows, W, tau, 1 / math.sqrt(d))
+        for out in outs:
+            assert np.abs(out[base:base + n][rows] - ref).max() <= _tol(dtype, d, G)
+        base += n
