@@ -2,17 +2,19 @@
 // remove from every head its floor(frac * N) lowest-scored entries, pack the survivors
 // to the front in place, give the emptied pages back.
 //
-//  evict_compact_kernel   one block per (sequence, kv head): radix select of the cut in
+//  evict_compact_kernel   several blocks per (sequence, kv head): radix select of the cut in
 //                         the total order of the fp32 bit patterns (equal scores: the
-//                         older entry goes first), then in-place compaction of K/V rows
-//  evict_release_kernel   one block: emptied pages back on the free stack, units in
-//                         (position in the call, kv head) order, a unit's pages in
+//                         older entry goes first), then in-place compaction of the block's
+//                         columns of the K/V rows
+//  evict_release_kernel   one block: new lengths, and the emptied pages back on the free stack,
+//                         units in (position in the call, kv head) order, a unit's pages in
 //                         ascending table index
 #include "wgkv_dev.h"
 
 namespace wgkv {
 
 constexpr int kEvictThreads = 1024;
+constexpr int kEvictKeep = 8;  // tiles of 1024 entries whose keys stay in registers
 
 struct EvictArgs {
     int layer;
@@ -20,30 +22,43 @@ struct EvictArgs {
     const float *scores;   // [n_units][stride]
     long long stride;
     int32_t *n_evicted;    // optional [n_units]
-    int32_t *released;     // workspace [n_units]: pages each unit gives back
+    int slices;            // blocks per unit: 2 or 4
 };
+
+// Entries a unit loses.  A cache longer than the caller's score row (the host's bound was stale) is left alone.
+__device__ __forceinline__ int evict_count(const EvictArgs &a, int N) {
+    return N <= a.stride ? (int)floor((double)a.frac * (double)N) : 0;
+}
 
 __device__ __forceinline__ uint32_t evict_key(float x) {
     const uint32_t u = __float_as_uint(x);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The rows of a head are packed in place, so one block has to walk them in order; but the columns of the rows are
+// independent, so `slices` blocks walk the same head, each with its own 16-byte columns of K or of V, and each finds
+// the cut for itself (18 KB of scores, out of the L2).  A block reads a whole tile of 1024 rows of its columns before it
+// writes any of them: eight requests in flight per thread.  (One block per head with one row in flight per thread,
+// a barrier and a round trip for every 64 rows, took 103 us for 64 heads of 4.4K entries, 270 MB read and written; this
+// form 57, the rate of a plain copy.)
+// Nobody changes a length here, which the other blocks of the head may not have read yet: evict_release_kernel does.
 __global__ __launch_bounds__(kEvictThreads) void evict_compact_kernel(View pv, CallSeqs cs, EvictArgs a) {
     __shared__ unsigned s_hist[256];
     __shared__ unsigned s_sel[4];      // prefix, mask, remaining rank
     __shared__ int s_tmp[20];
     __shared__ int s_src[kEvictThreads], s_dst[kEvictThreads];
-    const int u = blockIdx.x, b = u / pv.Hkv, h = u % pv.Hkv;
+    const int u = (int)blockIdx.x / a.slices, slice = (int)blockIdx.x % a.slices;
+    const int b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int N = pv.global_len[um];
-    // a cache longer than the caller's score row (the host's bound was stale): the head is left alone
-    const int n_e = N <= a.stride ? (int)floor((double)a.frac * (double)N) : 0;
-    if (threadIdx.x == 0) {
-        if (a.n_evicted) a.n_evicted[u] = n_e;
-        if (n_e == 0) a.released[u] = 0;
-    }
+    const int n_e = evict_count(a, N);
+    if (threadIdx.x == 0 && slice == 0 && a.n_evicted) a.n_evicted[u] = n_e;
     if (n_e == 0) return;  // block-uniform
     const float *sc = a.scores + (size_t)u * a.stride;
+    // the first entries' keys stay in registers, one per thread and tile; longer caches read the rest again
+    uint32_t kreg[kEvictKeep];
+#pragma unroll
+    for (int i = 0; i < kEvictKeep; i++) kreg[i] = evict_key(sc[min(i * kEvictThreads + (int)threadIdx.x, N - 1)]);
 
     // ---- the n_e-th smallest key: four passes over one byte each, most significant first ----
     if (threadIdx.x == 0) { s_sel[0] = 0u; s_sel[1] = 0u; s_sel[2] = (unsigned)n_e; }
@@ -51,7 +66,11 @@ __global__ __launch_bounds__(kEvictThreads) void evict_compact_kernel(View pv, C
         if (threadIdx.x < 256) s_hist[threadIdx.x] = 0u;
         __syncthreads();
         const unsigned prefix = s_sel[0], mask = s_sel[1];
-        for (int j = threadIdx.x; j < N; j += kEvictThreads) {
+#pragma unroll
+        for (int i = 0; i < kEvictKeep; i++)
+            if (i * kEvictThreads + (int)threadIdx.x < N && (kreg[i] & mask) == prefix)
+                atomicAdd(&s_hist[(kreg[i] >> (8 * pass)) & 255u], 1u);
+        for (int j = kEvictKeep * kEvictThreads + threadIdx.x; j < N; j += kEvictThreads) {
             const uint32_t key = evict_key(sc[j]);
             if ((key & mask) == prefix) atomicAdd(&s_hist[(key >> (8 * pass)) & 255u], 1u);
         }
@@ -76,16 +95,15 @@ __global__ __launch_bounds__(kEvictThreads) void evict_compact_kernel(View pv, C
 
     // ---- in-place compaction, tiles of 1024 entries in ascending order ----
     // A survivor moves to an index not above its own, and rows are taken in ascending order with all
-    // reads of a group of rows finished before its writes start, so no unread row is overwritten.
-    const int cpr = (int)(pv.row_bytes / 16);        // 16-byte chunks per row
-    const int rows_per_pass = kEvictThreads / cpr;
-    const int my_row = threadIdx.x / cpr, my_chunk = threadIdx.x % cpr;
+    // reads of a tile finished before its writes start, so no unread row is overwritten.
+    const int cps = (int)(pv.row_bytes / 8) / a.slices;      // 16-byte chunks of this block per row (K and V: 2 rows)
+    const int rows_per_turn = kEvictThreads / cps;
+    const int my_row = threadIdx.x / cps, col = slice * cps + threadIdx.x % cps, cpr = (int)(pv.row_bytes / 16);
+    const size_t col_off = col < cpr ? (size_t)col * 16 : pv.v_off + (size_t)(col - cpr) * 16;
     const int32_t *gpt = pv.global_pt + (size_t)um * pv.maxgp;
     int ties_seen = 0, kept = 0;
-    for (int j0 = 0; j0 < N; j0 += kEvictThreads) {
+    auto compact_tile = [&](int j0, uint32_t key) __attribute__((always_inline)) {
         const int j = j0 + threadIdx.x;
-        uint32_t key = 0xffffffffu;
-        if (j < N) key = evict_key(sc[j]);
         const int is_tie = (j < N && key == cut) ? 1 : 0;
         int n_ties;
         const int tie_rank = ties_seen + block_excl_scan(is_tie, s_tmp, &n_ties);
@@ -95,52 +113,70 @@ __global__ __launch_bounds__(kEvictThreads) void evict_compact_kernel(View pv, C
         __syncthreads();  // the previous tile's copy loop is done with s_src / s_dst
         if (stays) { s_src[idx] = j; s_dst[idx] = kept + idx; }
         __syncthreads();
-        for (int r0 = 0; r0 < n_stay; r0 += rows_per_pass) {
-            const int r = r0 + my_row;
-            const bool act = my_row < rows_per_pass && r < n_stay && s_src[r] != s_dst[r];
-            uint4 kv[2];
-            if (act) {
-                const int src = s_src[r];
-                const char *p = page_ptr(pv, gpt[src >> pv.logP]) + (size_t)(src & (pv.P - 1)) * pv.row_bytes + my_chunk * 16;
-                kv[0] = *reinterpret_cast<const uint4 *>(p);
-                kv[1] = *reinterpret_cast<const uint4 *>(p + pv.v_off);
+        // the tile's rows in turns of eight per thread (one turn at 128 bytes a row)
+        for (int r0 = 0; r0 < n_stay; r0 += rows_per_turn * 8) {
+            uint4 x[8];
+            int pg[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) pg[i] = gpt[s_src[min(r0 + i * rows_per_turn + my_row, n_stay - 1)] >> pv.logP];
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const int src = s_src[min(r0 + i * rows_per_turn + my_row, n_stay - 1)];
+                x[i] = *reinterpret_cast<const uint4 *>(page_ptr(pv, pg[i]) + (size_t)(src & (pv.P - 1)) * pv.row_bytes + col_off);
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the rows are in registers before anybody writes
+            // the rows are in registers before anybody writes: naming them here makes the wave wait for them
+#pragma unroll
+            for (int i = 0; i < 8; i++) asm volatile("" : "+v"(x[i].x), "+v"(x[i].y), "+v"(x[i].z), "+v"(x[i].w));
             __syncthreads();
-            if (act) {
-                const int dst = s_dst[r];
-                char *p = page_ptr(pv, gpt[dst >> pv.logP]) + (size_t)(dst & (pv.P - 1)) * pv.row_bytes + my_chunk * 16;
-                *reinterpret_cast<uint4 *>(p) = kv[0];
-                *reinterpret_cast<uint4 *>(p + pv.v_off) = kv[1];
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const int r = r0 + i * rows_per_turn + my_row;
+                if (my_row < rows_per_turn && r < n_stay && s_src[r] != s_dst[r]) {
+                    const int dst = s_dst[r];
+                    *reinterpret_cast<uint4 *>(page_ptr(pv, gpt[dst >> pv.logP]) + (size_t)(dst & (pv.P - 1)) * pv.row_bytes + col_off) = x[i];
+                }
             }
         }
         ties_seen += n_ties;
         kept += n_stay;
-    }
-    if (threadIdx.x == 0) {
-        pv.global_len[um] = kept;  // = N - n_e
-        a.released[u] = ((N + pv.P - 1) >> pv.logP) - ((kept + pv.P - 1) >> pv.logP);
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < kEvictKeep; i++)
+        if (i * kEvictThreads < N) compact_tile(i * kEvictThreads, kreg[i]);  // block-uniform
+    for (int j0 = kEvictKeep * kEvictThreads; j0 < N; j0 += kEvictThreads)
+        compact_tile(j0, evict_key(sc[min(j0 + (int)threadIdx.x, N - 1)]));
 }
 
-// global_len already holds the new lengths; released[u] says how many table entries behind the
-// last one in use each unit gives back.
+// The new lengths, and the table entries behind the last one in use back on the stack: the pages of all units are one
+// flat list behind a prefix over the units (one thread per unit walking its pages took 12 us for 64 heads).
 __global__ __launch_bounds__(kEvictThreads) void evict_release_kernel(View pv, CallSeqs cs, EvictArgs a, int n_units) {
     __shared__ int s_tmp[20];
+    __shared__ int s_base[kMaxCallUnits], s_first[kMaxCallUnits], s_um[kMaxCallUnits];
     const int u = threadIdx.x;
     int n = 0;
-    if (u < n_units) n = a.released[u];
+    if (u < n_units) {
+        const int um = unit_meta(pv, cs.sid[u / pv.Hkv], a.layer, u % pv.Hkv);
+        const int N = pv.global_len[um], kept = N - evict_count(a, N);
+        const int first = (kept + pv.P - 1) >> pv.logP;
+        n = ((N + pv.P - 1) >> pv.logP) - first;
+        pv.global_len[um] = kept;
+        s_first[u] = first;
+        s_um[u] = um;
+    }
     int total;
     const int ex = block_excl_scan(n, s_tmp, &total);
+    if (u < n_units) s_base[u] = ex;
+    __syncthreads();
     const int top = *pv.free_top;
-    if (u < n_units && n > 0) {
-        const int um = unit_meta(pv, cs.sid[u / pv.Hkv], a.layer, u % pv.Hkv);
-        const int first = (pv.global_len[um] + pv.P - 1) >> pv.logP;
-        int32_t *gpt = pv.global_pt + (size_t)um * pv.maxgp;
-        for (int i = 0; i < n; i++) {
-            pv.free_stack[top + ex + i] = gpt[first + i];
-            gpt[first + i] = -1;
+    for (int f = threadIdx.x; f < total; f += kEvictThreads) {
+        int lo_u = 0, hi_u = n_units - 1;  // the last unit whose base is <= f (units that give nothing back are never picked)
+        while (lo_u < hi_u) {
+            const int mid = (lo_u + hi_u + 1) >> 1;
+            if (s_base[mid] <= f) lo_u = mid; else hi_u = mid - 1;
         }
+        int32_t *e = pv.global_pt + (size_t)s_um[lo_u] * pv.maxgp + s_first[lo_u] + (f - s_base[lo_u]);
+        pv.free_stack[top + f] = *e;
+        *e = -1;
     }
     __syncthreads();
     if (threadIdx.x == 0) *pv.free_top = top + total;
@@ -149,17 +185,18 @@ __global__ __launch_bounds__(kEvictThreads) void evict_release_kernel(View pv, C
 size_t evict_ws_bytes(int n_units) { return (size_t)((n_units * 4 + 255) / 256) * 256; }
 
 hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, const float *scores,
-                              int64_t stride, float frac, int32_t *n_evicted, void *ws, hipStream_t st) {
+                              int64_t stride, float frac, int32_t *n_evicted, hipStream_t st) {
     const int n_units = cs.n * pv.Hkv;
-    if (pv.row_bytes % 16 != 0 || pv.row_bytes / 16 > kEvictThreads) return hipErrorNotSupported;
+    if (pv.row_bytes % 128 != 0 || pv.row_bytes / 8 > kEvictThreads) return hipErrorNotSupported;
     EvictArgs a;
     a.layer = layer;
     a.frac = frac;
     a.scores = scores;
     a.stride = stride;
     a.n_evicted = n_evicted;
-    a.released = (int32_t *)ws;
-    hipLaunchKernelGGL(evict_compact_kernel, dim3(n_units), dim3(kEvictThreads), 0, st, pv, cs, a);
+    // 128 bytes a block and row at the least; four blocks per head while that does not exceed a round of blocks by much
+    a.slices = pv.row_bytes >= 256 && n_units <= 256 ? 4 : 2;
+    hipLaunchKernelGGL(evict_compact_kernel, dim3(n_units * a.slices), dim3(kEvictThreads), 0, st, pv, cs, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(evict_release_kernel, dim3(1), dim3(kEvictThreads), 0, st, pv, cs, a, n_units);

@@ -31,7 +31,7 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
                                float scale, int pool_w, float *raw, float *out, int64_t stride, int64_t max_len,
                                void *ws, hipStream_t st);
 hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, const float *scores,
-                              int64_t stride, float frac, int32_t *n_evicted, void *ws, hipStream_t st);
+                              int64_t stride, float frac, int32_t *n_evicted, hipStream_t st);
 size_t quest_landmark_bytes(const View &pv);
 hipError_t launch_quest_update(const View &pv, const CallSeqs &cs, int layer, void *landmarks, int reset,
                                hipStream_t st);
@@ -161,7 +161,7 @@ PrefillWs prefill_ws(const wgkv_config *c, int n_seqs, int64_t total_tokens, int
     const size_t n_units = (size_t)n_seqs * c->n_kv_heads;
     const size_t nblk = (size_t)((max_T + kPrefillBlkHost - 1) / kPrefillBlkHost) + 1;
     w.cnt_off = off; off = align256(off + n_units * nblk * 4);
-    w.plan_off = off; off = align256(off + (1 + n_units) * 4);
+    w.plan_off = off; off = align256(off + (1 + 2 * n_units) * 4);
     w.total = off;
     return w;
 }
@@ -809,7 +809,7 @@ int wgkv_evict_apply(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int32_t 
             if (p->g_ub[sl * H + h] > stride) return WGKV_ERR_INVALID_ARG;
     }
     if (launch_evict_apply(p->view, cs, layer, scores_dev, stride, frac, n_evicted_out_dev,
-                           workspace_dev, (hipStream_t)stream) != hipSuccess)
+                           (hipStream_t)stream) != hipSuccess)
         return WGKV_ERR_HIP;
     // bounds after the call: N - floor(frac N) does not decrease with N, so it maps an upper
     // bound of the length to an upper bound of the new length
