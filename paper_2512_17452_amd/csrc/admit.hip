@@ -1,10 +1,10 @@
 // Admission, paging and promotion kernels for gfx950 (wave64).
 //
 //  init_kernel            free stack + cleared tables                       (Sec. 4.1)
-//  prefill_count_kernel   gate score -> admit mask, per-block admitted counts (Sec. 3.3 last sentence)
-//  prefill_plan_kernel    prefix sums over blocks and units, page hand-out    (Sec. 4.1, 4.2)
-//  prefill_scatter_kernel stable compaction of admitted K/V rows into global pages, then the
-//                         last min(W,T) tokens into the ring                  (Sec. 4.2)
+//  prefill_plan_kernel    gate score -> admit mask, admitted counts (Sec. 3.3 last sentence); in the block that
+//                         is last: prefix sums over blocks and units, what pages everybody gets (Sec. 4.1, 4.2)
+//  prefill_scatter_kernel stable compaction of admitted K/V rows into global pages, the table entries of
+//                         the new ones, then the last min(W,T) tokens into the ring (Sec. 4.2)
 //  decode_step_kernel     lazy promotion of the victim, then overwrite        (Sec. 4.3 (1)-(3))
 //  decode_promote_kernel, decode_promote_move_kernel
 //                         steps (1)-(2) of every layer ahead of the layers' ring writes
@@ -17,9 +17,9 @@
 
 namespace wgkv {
 
-constexpr int kPrefillBlk = 512;   // leaving tokens per block of 256 threads
+constexpr int kPrefillBlk = 512;   // leaving tokens per block of prefill_scatter_kernel (256 threads), and per count
 constexpr int kTok = kPrefillBlk / 256;  // tokens per thread
-constexpr int kPlanThreads = 1024; // the one block of prefill_plan_kernel
+constexpr int kPlanThreads = 1024; // a block of prefill_plan_kernel
 
 struct PrefillArgs {
     int layer;
@@ -30,7 +30,9 @@ struct PrefillArgs {
     const float *g;       // [sumT][Hkv]
     uint8_t *admit_out;   // optional
     int32_t *cnt;         // [n_units][nblk_max] admitted per block -> exclusive offsets
-    int32_t *plan;        // [0]=abort flag, [1+u]=G_old of unit u
+    // [0] = abort flag; [1 + u] = G_old of unit u; [1 + n_units + u] = index in the free stack of unit u's first new
+    // global page (the next ones follow downwards)
+    int32_t *plan;
 };
 
 struct DecodeArgs {
@@ -68,62 +70,89 @@ __device__ __forceinline__ float leaving_score(const View &pv, const PrefillArgs
     return a.g[(size_t)(base + p - t0) * pv.Hkv + h];
 }
 
-__global__ __launch_bounds__(256) void prefill_count_kernel(View pv, CallSeqs cs, PrefillArgs a) {
-    __shared__ int s_w[4];
-    const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
-    const int t0 = cs.t0[b], T = cs.ntok[b], base = cs.base[b];
-    const int um = unit_meta(pv, cs.sid[b], a.layer, h);
-    const int lo = max(0, t0 - pv.W), hi = max(0, t0 + T - pv.W), n_leave = hi - lo;
-    const int i0 = blockIdx.x * kPrefillBlk + threadIdx.x * kTok;
-    if (a.admit_out) {
-#pragma unroll
-        for (int j = 0; j < kTok; j++) {
-            int i = i0 + j;
-            if (i < T) {
-                size_t row = (size_t)(base + i) * pv.Hkv + h;
-                a.admit_out[row] = (uint8_t)(a.g[row] >= a.tau);
-            }
-        }
-    }
-    if (blockIdx.x * kPrefillBlk >= n_leave) return;  // block-uniform
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < kTok; j++) {
-        int i = i0 + j;
-        if (i < n_leave) c += (int)(leaving_score(pv, a, um, h, lo + i, t0, base) >= a.tau);
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    c = wave_incl_scan(c, lane);
-    if (lane == 63) s_w[w] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) a.cnt[(size_t)u * a.nblk_max + blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-}
-
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, CallSeqs cs, PrefillArgs a) {
+// One launch for what used to be two (count: a block per 512 tokens and unit; plan: one block).  Both are latency: 3 MB
+// of scores and a few thousand integers.  A block counts 512 leaving tokens of a sequence for all its heads at once (the
+// scores of a token are contiguous over the heads, so its loads are too; one head's alone are a stride of n_kv_heads apart
+// and every head reads the same lines), and the block that finishes last goes on to the plan.  No block waits.
+// Counts cross compute units inside the launch: they are written and read with device scope, and a block counts itself
+// as finished only after its own stores are complete.
+// Measured: 100K tokens x 8 heads 7.8 + 7.8 us in two launches, 12.9 here; 8 x 18K tokens 8.6 + 18.4 -> 14.0.
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, CallSeqs cs, PrefillArgs a, int32_t *arrived) {
     __shared__ int s_adm[kMaxCallUnits];
     __shared__ int s_gold[kMaxCallUnits];
     __shared__ int s_base[kMaxCallUnits];
     __shared__ int s_dl[kMaxCallUnits];
     __shared__ int s_um[kMaxCallUnits];
     __shared__ int s_tmp[20];
-    __shared__ int s_err, s_over;
-    const int n_units = cs.n * pv.Hkv;
+    __shared__ int s_err, s_over, s_last;
+    const int H = pv.Hkv, n_units = cs.n * H;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     constexpr int NW = kPlanThreads / 64;
-    if (threadIdx.x == 0) { s_err = 0; s_over = 0; }
-    // what phase B needs of the first kPlanThreads units is asked for now: the kernel is a
-    // chain of round trips on cold metadata, and these do not depend on phase A
+    {
+        const int b = blockIdx.y, i0 = blockIdx.x * kPrefillBlk;
+        const int t0 = cs.t0[b], T = cs.ntok[b], base = cs.base[b];
+        const int lo = max(0, t0 - pv.W), hi = max(0, t0 + T - pv.W), n_leave = hi - lo;
+        if (a.admit_out) {
+            const int n = min(kPrefillBlk, T - i0) * H;  // <= 0 past the end
+            const size_t row0 = (size_t)(base + i0) * H;
+            for (int e = threadIdx.x; e < n; e += kPlanThreads) a.admit_out[row0 + e] = (uint8_t)(a.g[row0 + e] >= a.tau);
+        }
+        if (i0 < n_leave) {  // block-uniform
+            for (int h = threadIdx.x; h < H; h += kPlanThreads) s_adm[h] = 0;
+            __syncthreads();
+            // element e = (token i0 + e / H of the leaving ones, head e % H)
+            const int n = min(kPrefillBlk, n_leave - i0) * H;
+            const int um0 = unit_meta(pv, cs.sid[b], a.layer, 0);
+            auto score = [&](int e) __attribute__((always_inline)) {
+                const int p = lo + i0 + e / H;
+                return p < t0 ? pv.ring_g[(size_t)(um0 + e % H) * pv.W + (p % pv.W)] : a.g[(size_t)(base + p - t0) * H + e % H];
+            };
+            if (kPlanThreads % H == 0) {  // a thread meets one head only
+                int c = 0;
+                for (int e = threadIdx.x; e < n; e += 4 * kPlanThreads) {
+                    float x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = score(min(e + k * kPlanThreads, n - 1));
+#pragma unroll
+                    for (int k = 0; k < 4; k++) c += (e + k * kPlanThreads < n && x[k] >= a.tau) ? 1 : 0;
+                }
+                if (64 % H == 0)  // lanes with the same head
+                    for (int o = H; o < 64; o <<= 1) c += __shfl_xor(c, o);
+                if (64 % H != 0 || lane < H) atomicAdd(&s_adm[threadIdx.x % H], c);
+            } else {
+                for (int e = threadIdx.x; e < n; e += kPlanThreads)
+                    if (score(e) >= a.tau) atomicAdd(&s_adm[e % H], 1);
+            }
+            __syncthreads();
+            for (int h = threadIdx.x; h < H; h += kPlanThreads)
+                __hip_atomic_store(&a.cnt[(size_t)(b * H + h) * a.nblk_max + blockIdx.x], s_adm[h], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's counts are complete at device scope
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int n_blocks = (int)(gridDim.x * gridDim.y);
+        s_last = n_blocks == 1 || __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_blocks - 1;
+        s_err = 0;
+        s_over = 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // ---- the plan ----
+    // what phase B needs of the first kPlanThreads units is asked for now: a chain of round trips on cold
+    // metadata, and these do not depend on phase A
     int um0 = 0, gold0 = 0, lp00 = 0;
     if ((int)threadIdx.x < n_units) {
-        um0 = unit_meta(pv, cs.sid[threadIdx.x / pv.Hkv], a.layer, threadIdx.x % pv.Hkv);
+        um0 = unit_meta(pv, cs.sid[threadIdx.x / H], a.layer, threadIdx.x % H);
         gold0 = pv.global_len[um0];
         lp00 = pv.local_pt[(size_t)um0 * pv.nlp];
     }
     const int top = *pv.free_top;
-    __syncthreads();
     // A: one wave per unit turns block counts into exclusive offsets
     for (int u = w; u < n_units; u += NW) {
-        const int b = u / pv.Hkv;
+        const int b = u / H;
         const int t0 = cs.t0[b], T = cs.ntok[b];
         const int n_leave = max(0, t0 + T - pv.W) - max(0, t0 - pv.W);
         const int nblk = (n_leave + kPrefillBlk - 1) / kPrefillBlk;
@@ -131,7 +160,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, Cal
         int run = 0;
         for (int i0 = 0; i0 < nblk; i0 += 64) {
             int i = i0 + lane;
-            int v = i < nblk ? c[i] : 0;
+            int v = i < nblk ? __hip_atomic_load(&c[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
             int inc = wave_incl_scan(v, lane);
             if (i < nblk) c[i] = run + inc - v;
             run += __shfl(inc, 63);
@@ -143,29 +172,22 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, Cal
     }
     __syncthreads();
     // B: page demand of every unit, prefix over units in call order
-    int carry = 0;
-    for (int u0 = 0; u0 < n_units; u0 += kPlanThreads) {
-        const int u = u0 + threadIdx.x;
-        int demand = 0;
-        if (u < n_units) {
-            const int b = u / pv.Hkv, h = u % pv.Hkv;
-            const int um = u0 == 0 ? um0 : unit_meta(pv, cs.sid[b], a.layer, h);
-            const int gold = u0 == 0 ? gold0 : pv.global_len[um];
-            const int lp0 = u0 == 0 ? lp00 : pv.local_pt[(size_t)um * pv.nlp];
-            const int gnew = gold + s_adm[u];
-            const int dl = (cs.ntok[b] > 0 && lp0 < 0) ? pv.nlp : 0;
-            const int pages_new = (gnew + pv.P - 1) >> pv.logP;
-            if (pages_new > pv.maxgp) s_err = WGKV_ERR_PT_OVERFLOW;
-            demand = dl + pages_new - ((gold + pv.P - 1) >> pv.logP);
-            s_gold[u] = gold;
-            s_dl[u] = dl;
-            s_um[u] = um;
-        }
-        int total;
-        int ex = block_excl_scan(demand, s_tmp, &total);
-        if (u < n_units) s_base[u] = carry + ex;
-        carry += total;
+    static_assert(kMaxCallUnits <= kPlanThreads, "one unit per thread");
+    const int u = threadIdx.x;
+    int demand = 0;
+    if (u < n_units) {
+        const int gnew = gold0 + s_adm[u];
+        const int dl = (cs.ntok[u / H] > 0 && lp00 < 0) ? pv.nlp : 0;
+        const int pages_new = (gnew + pv.P - 1) >> pv.logP;
+        if (pages_new > pv.maxgp) s_err = WGKV_ERR_PT_OVERFLOW;
+        demand = dl + pages_new - ((gold0 + pv.P - 1) >> pv.logP);
+        s_gold[u] = gold0;
+        s_dl[u] = dl;
+        s_um[u] = um0;
     }
+    int carry;
+    const int ex = block_excl_scan(demand, s_tmp, &carry);
+    if (u < n_units) s_base[u] = ex;
     __syncthreads();
     if (threadIdx.x == 0) {
         if (s_over) s_err = WGKV_ERR_ADMIT_BOUND;  // reported first: the host's page accounting relied on the bound
@@ -179,38 +201,17 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, Cal
         }
         return;
     }
-    // C: page-table entries.  Page f of the call (in unit order) is free_stack[top-1-f] whatever
-    // unit it goes to, so the hand-out is one flat loop over all threads, four loads in flight per
-    // thread; the owner of f is the last unit whose base is <= f (units without demand share
-    // their base with the next one and are never picked).
-    for (int f0 = 0; f0 < carry; f0 += kPlanThreads * 4) {
-        int pg[4];
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int f = f0 + k * kPlanThreads + (int)threadIdx.x;
-            pg[k] = pv.free_stack[top - 1 - min(f, carry - 1)];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int f = f0 + k * kPlanThreads + (int)threadIdx.x;
-            if (f < carry) {
-                int lo_u = 0, hi_u = n_units - 1;  // invariant: s_base[lo_u] <= f
-                while (lo_u < hi_u) {
-                    const int mid = (lo_u + hi_u + 1) >> 1;
-                    if (s_base[mid] <= f) lo_u = mid; else hi_u = mid - 1;
-                }
-                const int u = lo_u, i = f - s_base[u], dl = s_dl[u], um = s_um[u];
-                if (i < dl) pv.local_pt[(size_t)um * pv.nlp + i] = pg[k];
-                else pv.global_pt[(size_t)um * pv.maxgp + ((s_gold[u] + pv.P - 1) >> pv.logP) + (i - dl)] = pg[k];
-            }
-        }
+    // C: page f of the call (in unit order, a unit's ring pages before its global ones) is free_stack[top-1-f].  The
+    // ring pages go into the tables here; the blocks that write a unit's rows look its global pages up themselves.
+    for (int x = threadIdx.x; x < n_units * pv.nlp; x += kPlanThreads) {
+        const int v = x / pv.nlp, i = x - v * pv.nlp;
+        if (i < s_dl[v]) pv.local_pt[(size_t)s_um[v] * pv.nlp + i] = pv.free_stack[top - 1 - (s_base[v] + i)];
     }
     // D: lengths
-    for (int u = threadIdx.x; u < n_units; u += kPlanThreads) {
-        const int b = u / pv.Hkv, h = u % pv.Hkv;
-        const int um = unit_meta(pv, cs.sid[b], a.layer, h);
-        pv.global_len[um] = s_gold[u] + s_adm[u];
-        a.plan[1 + u] = s_gold[u];
+    if (u < n_units) {
+        pv.global_len[um0] = gold0 + s_adm[u];
+        a.plan[1 + u] = gold0;
+        a.plan[1 + n_units + u] = top - 1 - (ex + s_dl[u]);
     }
     for (int b = threadIdx.x; b < cs.n; b += kPlanThreads) pv.seq_len[cs.sid[b] * pv.L + a.layer] = cs.t0[b] + cs.ntok[b];
     if (threadIdx.x == 0) {
@@ -266,7 +267,8 @@ __global__ __launch_bounds__(256) void prefill_scatter_kernel(View pv, CallSeqs 
         return;
     }
     if (blockIdx.x * kPrefillBlk >= n_leave) return;
-    const int dst0 = a.plan[1 + u] + a.cnt[(size_t)u * a.nblk_max + blockIdx.x];
+    const int gold = a.plan[1 + u], fresh = a.plan[1 + cs.n * pv.Hkv + u];
+    const int dst0 = gold + a.cnt[(size_t)u * a.nblk_max + blockIdx.x];
     const int i0 = blockIdx.x * kPrefillBlk + threadIdx.x * kTok;
     int f[kTok], rpg[kTok], c = 0;
 #pragma unroll
@@ -288,7 +290,14 @@ __global__ __launch_bounds__(256) void prefill_scatter_kernel(View pv, CallSeqs 
         }
     const int pg_first = dst0 >> pv.logP;
     const int n_pg = n_adm > 0 ? ((dst0 + n_adm - 1) >> pv.logP) - pg_first + 1 : 0;  // <= kPrefillBlk
-    for (int i = threadIdx.x; i < n_pg; i += 256) s_gp[i] = pv.global_pt[(size_t)um * pv.maxgp + pg_first + i];
+    const int pg_old = (gold + pv.P - 1) >> pv.logP;  // pages the unit had before this call; the rest come from the stack
+    for (int i = threadIdx.x; i < n_pg; i += 256) {
+        const int pi = pg_first + i;
+        int32_t *entry = pv.global_pt + (size_t)um * pv.maxgp + pi;
+        const int pg = *(pi < pg_old ? entry : pv.free_stack + (fresh - (pi - pg_old)));
+        s_gp[i] = pg;
+        if (pi >= pg_old && (pi << pv.logP) >= dst0) *entry = pg;  // the block that writes a page's first row
+    }
     __syncthreads();
     // copy the admitted rows: lpr lanes of 16 bytes per row, K and V
     const int lpr = pv.row_bytes >> 4;
@@ -770,8 +779,7 @@ hipError_t launch_prefill(const View &pv, const CallSeqs &cs, int layer, float t
     const int n_units = cs.n * pv.Hkv;
     int gx = a.nblk_max;
     if (admit_out) gx = max(gx, (max_T + kPrefillBlk - 1) / kPrefillBlk);
-    hipLaunchKernelGGL(prefill_count_kernel, dim3(gx, n_units), dim3(256), 0, st, pv, cs, a);
-    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, pv, cs, a);
+    hipLaunchKernelGGL(prefill_plan_kernel, dim3(gx, cs.n), dim3(kPlanThreads), 0, st, pv, cs, a, pv.unit_counters);
     // blocks 0 .. nblk_max-1 of a unit: leaving tokens (and the ring slots they vacate); the rest: ring rows
     // that go to slots still empty (max_empty_ring_rows: the most ring rows of a sequence that has any such)
     const int lpr = pv.row_bytes >> 4;
