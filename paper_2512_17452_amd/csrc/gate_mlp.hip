@@ -11,6 +11,9 @@
 // hidden units are per-lane work and the hidden layer never leaves the registers.
 // The normalised features are rounded to bf16 (they are a matrix-core operand), which is
 // what a bf16 model does with its RMSNorm output as well.
+// Bound by the GELU on the vector unit (67 M of them for 16K tokens x 8 heads x width 512) in large
+// calls, by the chain of a wave's products and GELUs in small ones.  Measured: 16K tokens 69 -> 52 us
+// (33 us of which are the vector instructions alone at 2.2 GHz), 1K tokens 23 -> 15.
 #include "wgkv_dev.h"
 
 namespace wgkv {
@@ -22,20 +25,22 @@ typedef __attribute__((ext_vector_type(16))) float gm_f32x16_t;
 constexpr int kGmUnits = 32;   // hidden units per chunk of W1
 constexpr int kGmTokens = 32;  // tokens per wave
 
-// Exact GELU z * Phi(z) with erf from the formula of Abramowitz & Stegun 7.1.26,
-// erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x), x >= 0, whose absolute error is
-// below 1.5e-7 (a fifth of the library routine's instruction count; the GELU is what bounds the
-// kernel).  With q = 1 - erf(|z| / sqrt 2): Phi(z) = 1 - q/2 for z >= 0 and q/2 for z < 0, so no
-// difference of nearly equal numbers is formed on the negative side.
-__device__ __forceinline__ float gm_gelu(float z) {
-    const float x = fabsf(z) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    float p = fmaf(1.061405429f, t, -1.453152027f);
-    p = fmaf(p, t, 1.421413741f);
-    p = fmaf(p, t, -0.284496736f);
-    p = fmaf(p, t, 0.254829592f);
-    const float q = p * t * __builtin_amdgcn_exp2f(x * x * -1.4426950408889634f);
-    return 0.5f * z * (z >= 0.f ? 2.0f - q : q);
+// Twice the exact GELU, 2 z Phi(z) = z + |z| - |z| q(|z|) with q(y) = erfc(y / sqrt 2): no difference of nearly equal
+// numbers on the negative side, and z + |z| carries a NaN or an infinity on.  q = 2^P(y), where log2 erfc(y / sqrt 2)
+// is so smooth that a polynomial of degree six does: weighted by what an error of P does to y q(y), a least-squares fit
+// on [0, 6] reweighted until its largest error was as small as it gets leaves 5e-8 of the GELU.  Beyond 6 the
+// product stays where it is there, 1.2e-8.  Whole function in fp32 against 64 bits, |z| <= 8: 2.8e-7 at most (the
+// rounding of z itself at the far end; 8e-8 for negative z), where the rational erf formula of Abramowitz & Stegun
+// 7.1.26 that stood here before left 4.2e-7 at 26 issue slots; this takes 13 with the one exponential counted as four.
+__device__ __forceinline__ float gm_gelu2(float z) {
+    const float y = fminf(fabsf(z), 6.0f);
+    float p = fmaf(3.309277963e-05f, y, -7.692193612e-04f);
+    p = fmaf(p, y, 8.080715314e-03f);
+    p = fmaf(p, y, -5.341210216e-02f);
+    p = fmaf(p, y, -4.587709606e-01f);
+    p = fmaf(p, y, -1.151201725e+00f);
+    p = fmaf(p, y, 6.938917977e-06f);
+    return fmaf(-y, __builtin_amdgcn_exp2f(p), z + fabsf(z));
 }
 
 __device__ __forceinline__ float gm_bf16_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
@@ -45,79 +50,97 @@ __device__ __forceinline__ uint32_t gm_pack(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, t);
 }
 
+// The normalised features of one token as matrix operands: the 8 features [16 ks + 8 half, +8) of every slice of 16.
 template <int D>
-__global__ __launch_bounds__(256) void gate_mlp_mfma_kernel(const char *k, const char *kr, const char *W1,
-                                                            const float *b1, const char *W2, const float *b2,
-                                                            float eps, float *g_out, long long T, int Hkv,
-                                                            int width) {
-    constexpr int KS = 2 * D / 16;             // contraction slices of 16 features
-    constexpr int kRow = 2 * D * 2 + 16;       // bytes per W1 row in LDS (padded against bank conflicts)
-    constexpr int kRowPieces = 2 * D * 2 / 16;                  // 16-byte pieces per row
-    constexpr int kPieces = kGmUnits * kRowPieces / 256;        // pieces of a chunk per thread
-    static_assert(kPieces == 2 || kPieces == 4, "");
-    __shared__ __attribute__((aligned(16))) char s_w1[2][kGmUnits * kRow];
-    __shared__ __attribute__((aligned(16))) float s_b1[2][kGmUnits];
-    __shared__ __attribute__((aligned(16))) float s_w2[2][kGmUnits];
-
-    const int h = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 31, half = lane >> 5;
-    const long long tok = ((long long)blockIdx.x * 4 + wave) * kGmTokens + n;
-    const long long tok_c = tok < T ? tok : T - 1;  // rows past the end repeat the last token, unwritten
-
-    // ---- features: this lane's token, the 8 features [16 ks + 8 half, +8) of every slice ----
-    gm_bf16x8_t xv[KS];
+__device__ __forceinline__ void gm_features(const char *k, const char *kr, size_t row, int half, float eps,
+                                            gm_bf16x8_t (&xv)[2 * D / 16]) {
+    constexpr int KS = 2 * D / 16;
 #pragma unroll
     for (int part = 0; part < 2; part++) {
-        const char *row = (part == 0 ? k : kr) + ((size_t)tok_c * Hkv + h) * (D * 2);
+        const char *p = (part == 0 ? k : kr) + row * (D * 2);
         uint4 raw[KS / 2];
         float ss = 0.f;
 #pragma unroll
         for (int j = 0; j < KS / 2; j++) {
-            raw[j] = *reinterpret_cast<const uint4 *>(row + (2 * j + half) * 16);
+            raw[j] = *reinterpret_cast<const uint4 *>(p + (2 * j + half) * 16);
             const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                const float a = gm_bf16_to_f32(w[e] & 0xffffu), b = gm_bf16_to_f32(w[e] >> 16);
-                ss = fmaf(a, a, ss);
-                ss = fmaf(b, b, ss);
+                // (not the two-element dot product: its sum is less exact, and more features then land on the other
+                // side of a rounding boundary)
+                const float x = gm_bf16_to_f32(w[e] & 0xffffu), y = __uint_as_float(w[e] & 0xffff0000u);
+                ss = fmaf(x, x, ss);
+                ss = fmaf(y, y, ss);
             }
         }
         ss += __shfl_xor(ss, 32);  // the other half of the row
         const float r = 1.0f / sqrtf(ss / (float)D + eps);
 #pragma unroll
         for (int j = 0; j < KS / 2; j++) {
+            // unpacked again, not kept unpacked: the 64 floats cost the two-column form 46 spilled registers
+            asm volatile("" : "+v"(raw[j].x), "+v"(raw[j].y), "+v"(raw[j].z), "+v"(raw[j].w));
             const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
             uint32_t o[4];
 #pragma unroll
             for (int e = 0; e < 4; e++)
-                o[e] = gm_pack(gm_bf16_to_f32(w[e] & 0xffffu) * r, gm_bf16_to_f32(w[e] >> 16) * r);
+                o[e] = gm_pack(gm_bf16_to_f32(w[e] & 0xffffu) * r, __uint_as_float(w[e] & 0xffff0000u) * r);
             xv[part * (KS / 2) + j] = __builtin_bit_cast(gm_bf16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
         }
     }
+}
+
+// CB: columns of 32 tokens per wave.  US: unit groups of the block, 4 waves each; group us takes chunks us, us + US, ...
+template <int D, int CB, int US>
+__global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *k, const char *kr, const char *W1,
+                                                            const float *b1, const char *W2, const float *b2,
+                                                            float eps, float *g_out, long long T, int Hkv,
+                                                            int width) {
+    constexpr int KS = 2 * D / 16;             // contraction slices of 16 features
+    constexpr int kRow = 2 * D * 2 + 16;       // bytes per W1 row in LDS (padded against bank conflicts)
+    constexpr int kRowPieces = 2 * D * 2 / 16;                  // 16-byte pieces per row
+    constexpr int kPieces = kGmUnits * kRowPieces / 256;        // pieces of a chunk per thread of its group
+    static_assert(kPieces == 2 || kPieces == 4, "");
+    __shared__ __attribute__((aligned(16))) char s_w1[2][US][kGmUnits * kRow];
+    __shared__ __attribute__((aligned(16))) float s_b1[2][US][kGmUnits];
+    __shared__ __attribute__((aligned(16))) float s_w2[2][US][kGmUnits];
+    __shared__ float s_sum[US][4][CB][kGmTokens];
+
+    const int h = blockIdx.y;
+    const int tid = threadIdx.x % 256, us = __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, half = lane >> 5;
+    const long long tok0 = ((long long)blockIdx.x * 4 + wave) * (kGmTokens * CB) + n;  // this lane's first token
+
+    gm_bf16x8_t xv[CB][KS];
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) {
+        const long long tok = tok0 + cb * kGmTokens;  // rows past the end repeat the last token, unwritten
+        gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv[cb]);
+    }
 
     // ---- chunks of 32 hidden units: W1 rows, b1 and W2 through LDS, two buffers ----
-    const int n_chunks = width / kGmUnits;
+    const int n_chunks = width / kGmUnits, n_it = (n_chunks + US - 1) / US;
     uint4 w0, w1, w2, w3;  // this thread's pieces of the chunk on its way to LDS
     w2 = w3 = make_uint4(0u, 0u, 0u, 0u);
     float b1v = 0.f, w2v = 0.f;
-    auto fetch = [&](int c) __attribute__((always_inline)) {
+    auto fetch = [&](int it) __attribute__((always_inline)) {
+        const int c = min(it * US + us, n_chunks - 1);  // a group without a chunk of its own in the last turn drops it
         const char *src = W1 + ((size_t)h * width + (size_t)c * kGmUnits) * (2 * D * 2);  // 32 consecutive rows
-        w0 = *reinterpret_cast<const uint4 *>(src + ((size_t)0 * 256 + threadIdx.x) * 16);
-        w1 = *reinterpret_cast<const uint4 *>(src + ((size_t)1 * 256 + threadIdx.x) * 16);
+        w0 = *reinterpret_cast<const uint4 *>(src + ((size_t)0 * 256 + tid) * 16);
+        w1 = *reinterpret_cast<const uint4 *>(src + ((size_t)1 * 256 + tid) * 16);
         if (kPieces > 2) {
-            w2 = *reinterpret_cast<const uint4 *>(src + ((size_t)2 * 256 + threadIdx.x) * 16);
-            w3 = *reinterpret_cast<const uint4 *>(src + ((size_t)3 * 256 + threadIdx.x) * 16);
+            w2 = *reinterpret_cast<const uint4 *>(src + ((size_t)2 * 256 + tid) * 16);
+            w3 = *reinterpret_cast<const uint4 *>(src + ((size_t)3 * 256 + tid) * 16);
         }
-        if (threadIdx.x < kGmUnits) {
-            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + threadIdx.x;
+        if (tid < kGmUnits) {
+            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + tid;
             b1v = b1[u];
             w2v = gm_bf16_to_f32(*reinterpret_cast<const uint16_t *>(W2 + u * 2));
         }
     };
     auto put = [&](int buf, int p, const uint4 v) __attribute__((always_inline)) {
-        const int piece = p * 256 + threadIdx.x;
-        *reinterpret_cast<uint4 *>(&s_w1[buf][(piece / kRowPieces) * kRow + (piece % kRowPieces) * 16]) = v;
+        const int piece = p * 256 + tid;
+        *reinterpret_cast<uint4 *>(&s_w1[buf][us][(piece / kRowPieces) * kRow + (piece % kRowPieces) * 16]) = v;
     };
     auto stage = [&](int buf) __attribute__((always_inline)) {
         put(buf, 0, w0);
@@ -126,42 +149,134 @@ __global__ __launch_bounds__(256) void gate_mlp_mfma_kernel(const char *k, const
             put(buf, 2, w2);
             put(buf, 3, w3);
         }
-        if (threadIdx.x < kGmUnits) {
-            s_b1[buf][threadIdx.x] = b1v;
-            s_w2[buf][threadIdx.x] = w2v;
+        if (tid < kGmUnits) {
+            s_b1[buf][us][tid] = b1v;
+            s_w2[buf][us][tid] = w2v;
         }
     };
     fetch(0);
     stage(0);
     __syncthreads();
-    float acc_logit = 0.f;
-    for (int c = 0; c < n_chunks; c++) {
-        const int buf = c & 1;
-        if (c + 1 < n_chunks) fetch(c + 1);
-        gm_f32x16_t hcol;
+    float acc_logit[CB];  // twice the logit
 #pragma unroll
-        for (int i = 0; i < 16; i++) hcol[i] = 0.f;
+    for (int cb = 0; cb < CB; cb++) acc_logit[cb] = 0.f;
+    for (int it = 0; it < n_it; it++) {
+        const int buf = it & 1;
+        if (it + 1 < n_it) fetch(it + 1);
+        if (US == 1 || it * US + us < n_chunks) {  // wave-uniform
+        gm_f32x16_t hcol[CB];
+#pragma unroll
+        for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) hcol[cb][i] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
             const gm_bf16x8_t wa =
-                *reinterpret_cast<const gm_bf16x8_t *>(&s_w1[buf][n * kRow + (ks * 16 + half * 8) * 2]);
-            hcol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xv[ks], hcol, 0, 0, 0);
+                *reinterpret_cast<const gm_bf16x8_t *>(&s_w1[buf][us][n * kRow + (ks * 16 + half * 8) * 2]);
+#pragma unroll
+            for (int cb = 0; cb < CB; cb++) hcol[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xv[cb][ks], hcol[cb], 0, 0, 0);
         }
         // register 4j+i of a lane holds hidden unit 8j + 4*half + i of the chunk, for its token
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            const float4 bb = *reinterpret_cast<const float4 *>(&s_b1[buf][8 * j + 4 * half]);
-            const float4 ww = *reinterpret_cast<const float4 *>(&s_w2[buf][8 * j + 4 * half]);
-            acc_logit = fmaf(ww.x, gm_gelu(hcol[4 * j + 0] + bb.x), acc_logit);
-            acc_logit = fmaf(ww.y, gm_gelu(hcol[4 * j + 1] + bb.y), acc_logit);
-            acc_logit = fmaf(ww.z, gm_gelu(hcol[4 * j + 2] + bb.z), acc_logit);
-            acc_logit = fmaf(ww.w, gm_gelu(hcol[4 * j + 3] + bb.w), acc_logit);
+            const float4 bb = *reinterpret_cast<const float4 *>(&s_b1[buf][us][8 * j + 4 * half]);
+            const float4 ww = *reinterpret_cast<const float4 *>(&s_w2[buf][us][8 * j + 4 * half]);
+#pragma unroll
+            for (int cb = 0; cb < CB; cb++) {
+                acc_logit[cb] = fmaf(ww.x, gm_gelu2(hcol[cb][4 * j + 0] + bb.x), acc_logit[cb]);
+                acc_logit[cb] = fmaf(ww.y, gm_gelu2(hcol[cb][4 * j + 1] + bb.y), acc_logit[cb]);
+                acc_logit[cb] = fmaf(ww.z, gm_gelu2(hcol[cb][4 * j + 2] + bb.z), acc_logit[cb]);
+                acc_logit[cb] = fmaf(ww.w, gm_gelu2(hcol[cb][4 * j + 3] + bb.w), acc_logit[cb]);
+            }
         }
-        if (c + 1 < n_chunks) stage(buf ^ 1);
+        }
+        if (it + 1 < n_it) stage(buf ^ 1);
         __syncthreads();
     }
-    acc_logit += __shfl_xor(acc_logit, 32);  // the other 16 units of every chunk
-    if (half == 0 && tok < T) g_out[(size_t)tok * Hkv + h] = 1.0f / (1.0f + __expf(-(acc_logit + b2[h])));
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) acc_logit[cb] += __shfl_xor(acc_logit[cb], 32);  // the other 16 units of every chunk
+    if constexpr (US > 1) {
+        if (half == 0)
+#pragma unroll
+            for (int cb = 0; cb < CB; cb++) s_sum[us][wave][cb][n] = acc_logit[cb];
+        __syncthreads();
+        if (us > 0) return;
+#pragma unroll
+        for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+            for (int g = 1; g < US; g++) acc_logit[cb] += s_sum[g][wave][cb][n];
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) {
+        const long long tok = tok0 + cb * kGmTokens;
+        if (half == 0 && tok < T) g_out[(size_t)tok * Hkv + h] = 1.0f / (1.0f + __expf(-fmaf(0.5f, acc_logit[cb], b2[h])));
+    }
+}
+
+constexpr int kGmSplit = 4;  // waves of the block
+// Few tokens: what a wave has to do one after the other is the time, so a block takes 32 tokens and its four waves
+// a quarter of the hidden units each (eight waves: 15 instead of 13 us, every wave makes the features for itself).  The chunks of W1 go straight into the matrix operand (a lane reads 16 bytes of its
+// unit's row per slice, a line of 128 bytes in four consecutive requests); nothing is shared but the sum at the end.
+template <int D>
+__global__ __launch_bounds__(kGmSplit * 64) void gate_mlp_split_kernel(const char *k, const char *kr, const char *W1,
+                                                             const float *b1, const char *W2, const float *b2,
+                                                             float eps, float *g_out, long long T, int Hkv, int width) {
+    constexpr int KS = 2 * D / 16;
+    __shared__ float s_sum[kGmSplit][kGmTokens];
+    const int h = (int)(blockIdx.x % Hkv);  // blocks go to the XCDs in turn: with eight heads an L2 holds one head's W1
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, half = lane >> 5;
+    const long long tok = (long long)(blockIdx.x / Hkv) * kGmTokens + n;
+    const int n_chunks = width / kGmUnits;
+    gm_bf16x8_t wa[KS], xv[KS];
+    float4 bb[4];
+    uint2 ww[4];
+    auto fetch = [&](int c) __attribute__((always_inline)) {
+        const size_t u = (size_t)h * width + (size_t)min(c, n_chunks - 1) * kGmUnits;
+        const char *src = W1 + (u + n) * (2 * D * 2) + half * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) wa[ks] = *reinterpret_cast<const gm_bf16x8_t *>(src + ks * 32);
+    };
+    auto fetch_b = [&](int c) __attribute__((always_inline)) {
+        const size_t u = (size_t)h * width + (size_t)min(c, n_chunks - 1) * kGmUnits;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            bb[j] = make_float4(b1[u + 8 * j + 4 * half], b1[u + 8 * j + 4 * half + 1], b1[u + 8 * j + 4 * half + 2], b1[u + 8 * j + 4 * half + 3]);
+            const uint16_t *w = reinterpret_cast<const uint16_t *>(W2) + u + 8 * j + 4 * half;
+            ww[j] = make_uint2((uint32_t)w[0] | ((uint32_t)w[1] << 16), (uint32_t)w[2] | ((uint32_t)w[3] << 16));
+        }
+    };
+    fetch(wave);
+    gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv);
+    float acc = 0.f;  // twice the logit
+    for (int c = wave; c < n_chunks; c += kGmSplit) {  // wave-uniform
+        fetch_b(c);
+        gm_f32x16_t h0, h1;  // two chains of products, half as long
+#pragma unroll
+        for (int i = 0; i < 16; i++) { h0[i] = 0.f; h1[i] = 0.f; }
+#pragma unroll
+        for (int ks = 0; ks < KS; ks += 2) {
+            h0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[ks], xv[ks], h0, 0, 0, 0);
+            h1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[ks + 1], xv[ks + 1], h1, 0, 0, 0);
+        }
+        fetch(c + kGmSplit);  // in flight during the GELU
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            acc = fmaf(gm_bf16_to_f32(ww[j].x & 0xffffu), gm_gelu2(h0[4 * j] + h1[4 * j] + bb[j].x), acc);
+            acc = fmaf(gm_bf16_to_f32(ww[j].x >> 16), gm_gelu2(h0[4 * j + 1] + h1[4 * j + 1] + bb[j].y), acc);
+            acc = fmaf(gm_bf16_to_f32(ww[j].y & 0xffffu), gm_gelu2(h0[4 * j + 2] + h1[4 * j + 2] + bb[j].z), acc);
+            acc = fmaf(gm_bf16_to_f32(ww[j].y >> 16), gm_gelu2(h0[4 * j + 3] + h1[4 * j + 3] + bb[j].w), acc);
+        }
+    }
+    acc += __shfl_xor(acc, 32);
+    if (half == 0) s_sum[wave][n] = acc;
+    __syncthreads();
+    if (wave == 0 && half == 0 && tok < T) {
+        float a = 0.f;
+#pragma unroll
+        for (int w = 0; w < kGmSplit; w++) a += s_sum[w][n];
+        g_out[(size_t)tok * Hkv + h] = 1.0f / (1.0f + __expf(-fmaf(0.5f, a, b2[h])));
+    }
 }
 
 // Any other shape or an fp32 model: one block per (token, kv head), one hidden unit per
@@ -200,19 +315,19 @@ __global__ __launch_bounds__(256) void gate_mlp_generic_kernel(const char *k, co
         }
     }
     __syncthreads();
-    float acc = 0.f;
+    float acc = 0.f;  // twice the logit
     for (int u = threadIdx.x; u < width; u += 256) {
         const size_t wrow = ((size_t)h * width + u) * 2 * d;
         float z = b1[(size_t)h * width + u];
         for (int e = 0; e < 2 * d; e++) z = fmaf(ld(W1, wrow + e), s_x[e], z);
-        acc = fmaf(ld(W2, (size_t)h * width + u), gm_gelu(z), acc);
+        acc = fmaf(ld(W2, (size_t)h * width + u), gm_gelu2(z), acc);
     }
     acc = group_sum<64>(acc);
     __syncthreads();
     if (lane == 0) s_red[4 + wave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const float logit = s_red[4] + s_red[5] + s_red[6] + s_red[7] + b2[h];
+        const float logit = 0.5f * (s_red[4] + s_red[5] + s_red[6] + s_red[7]) + b2[h];
         g_out[(size_t)t * Hkv + h] = 1.0f / (1.0f + __expf(-logit));
     }
 }
@@ -223,13 +338,32 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
     if (n_tokens == 0) return hipSuccess;
     const char *kp = (const char *)k, *krp = (const char *)k_rope, *w1p = (const char *)w1, *w2p = (const char *)w2;
     if (dtype == WGKV_BF16 && (head_dim == 128 || head_dim == 64) && width % kGmUnits == 0) {
-        const dim3 grid((unsigned)((n_tokens + 4 * kGmTokens - 1) / (4 * kGmTokens)), n_kv_heads);
-        if (head_dim == 128)
-            hipLaunchKernelGGL(gate_mlp_mfma_kernel<128>, grid, dim3(256), 0, st, kp, krp, w1p, b1, w2p, b2, eps,
-                               g_out, (long long)n_tokens, n_kv_heads, width);
-        else
-            hipLaunchKernelGGL(gate_mlp_mfma_kernel<64>, grid, dim3(256), 0, st, kp, krp, w1p, b1, w2p, b2, eps,
-                               g_out, (long long)n_tokens, n_kv_heads, width);
+        // Which form, by the number of (token, head) pairs: each up to one round of its resident blocks, where its time
+        // is nearly flat.  us at head_dim 128, width 512, for 8K / 32K / 64K / 96K / 128K pairs (the lines lie where
+        // two columns cross; 64-wide heads cross at the same places):
+        //   32 tokens a block, the units split over its waves        15   45    87   129
+        //   128 tokens, two groups of waves with half the units each  20   23    44    65    86
+        //   128 tokens, three blocks per compute unit                 23   26    35    46    63
+        //   256 tokens (a product's W1 operand used twice)            34   37    42    53    56
+        const int64_t cols = n_tokens * n_kv_heads;
+#define WGKV_GM(D_, CB_, US_)                                                                                            \
+    hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_>),                                                            \
+                       dim3((unsigned)((n_tokens + 4 * kGmTokens * CB_ - 1) / (4 * kGmTokens * CB_)), n_kv_heads),       \
+                       dim3(256 * US_), 0, st, kp, krp, w1p, b1, w2p, b2, eps, g_out, (long long)n_tokens, n_kv_heads, width)
+#define WGKV_GM_D(D_)                                                                                                   \
+    if (cols <= 8192)                                                                                              \
+        hipLaunchKernelGGL((gate_mlp_split_kernel<D_>), dim3((unsigned)((n_tokens + kGmTokens - 1) / kGmTokens * n_kv_heads)), \
+                           dim3(kGmSplit * 64), 0, st, kp, krp, w1p, b1, w2p, b2, eps, g_out, (long long)n_tokens, n_kv_heads, width); \
+    else if (cols <= 32768) WGKV_GM(D_, 1, 2);                                                                         \
+    else if (cols <= 98304) WGKV_GM(D_, 1, 1);                                                                        \
+    else WGKV_GM(D_, 2, 1)
+        if (head_dim == 128) {
+            WGKV_GM_D(128);
+        } else {
+            WGKV_GM_D(64);
+        }
+#undef WGKV_GM_D
+#undef WGKV_GM
         return hipGetLastError();
     }
     // grid.x carries the tokens: split very long inputs over several launches
