@@ -4,23 +4,28 @@
 //     B_ij = log(m_ij + eps),   m_ij = max(1(i - j < W_local), g_j),
 // forward with the row log-sum-exp, and the gradients with respect to q, k, v and g.
 //
-//   soft_attn_fwd_kernel       block = 64 query positions x the 4 query heads of a kv head,
-//                              key tiles of 64 staged in LDS; S^T = K Q^T, O^T = V^T P^T
+//   soft_attn_fwd_kernel       block = 32 or 64 query positions x the 4 query heads of a kv head,
+//                              key tiles of 64 in LDS; S^T = K Q^T, O^T = V^T P^T
 //   soft_attn_rowdot_kernel    D_i = dO_i . O_i per (position, query head)
 //   soft_attn_bwd_dq_kernel    same blocking as the forward: S^T and dP^T = V dO^T per key tile,
 //                              dS^T = P^T (dP^T - D), dQ^T += K^T dS^T
-//   soft_attn_bwd_dkv_kernel   block = 128 keys of a kv head; its waves are (32 keys) x (role):
-//                              role 0 recomputes S = Q K^T and P and accumulates dV^T += dO^T P;
-//                              role 1, one tile behind, computes dP = dO V^T, takes P through LDS, forms dS and
-//                              accumulates dK^T += Q^T dS and the sum that becomes dg
+//   soft_attn_bwd_dkv_kernel   a wave owns 32 keys of a kv head and streams (32 queries, head) tiles: S = Q K^T,
+//                              dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS and the sum that becomes dg
 //
 // All products are v_mfma_f32_32x32x16_bf16 with fp32 accumulation; every operand that is
-// reused over the whole loop (the block's own rows) sits in registers, the streamed tiles
-// go through LDS row-major once: products over d read rows of the staged tile, products that
-// contract over positions read its columns with the transposing LDS load (ds_read_b64_tr_b16).
-// A lane of an accumulator tile owns one column, so per-column quantities are plain scalars.
+// reused over the whole loop (the wave's own rows) sits in registers.  The streamed tiles come from memory straight
+// into LDS, once, in an order of their 16-byte pieces that serves products over d (whole rows) and products that contract
+// over positions (columns, with the transposing LDS load) alike; they used to pass through registers into two
+// padded copies.  A lane of an accumulator tile owns one column, so per-column quantities are plain scalars.
+//
+// What bounds them on one 16384-token sequence (8 kv heads, window 256): power.  The chip runs the three kernels at 1.9 /
+// 1.9 / 1.76 GHz of 2.4 with the matrix cores busy 41 / 50 / 48 % of those cycles, no bank conflict, waves waiting for
+// an instruction's result a quarter of their time.  Forward 2.71 -> 2.64 ms, dQ 3.46 -> 3.25, dK/dV 6.32 -> 4.75 (two
+// waves used to share 32 keys, one forming P and dV, one dP and dK, with P in 32 bits through LDS: one and a half
+// times the LDS traffic that the matrix cores hide).
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "wgkv_dev.h"
 
@@ -32,12 +37,8 @@ typedef __attribute__((ext_vector_type(16))) float sa_f32x16_t;
 
 constexpr int kSaD = 128;       // head_dim
 constexpr int kSaG = 4;         // query heads per kv head
-constexpr int kSaQ = 64;        // query positions per block (forward, dQ)
 constexpr int kSaT = 32;        // positions per streamed tile
-constexpr int kSaKB = 128;      // keys per block (dK/dV)
-constexpr int kSaRm = 272;      // bytes per row of a tile in LDS whose rows are read whole (256 + 16 pad)
-constexpr int kSaCm = 320;      // bytes per row of a tile that is only read column-wise (256 + 64 pad): four
-                                // rows and 64 bytes of each per half wave, spread over all banks
+constexpr int kSaTileB = kSaT * kSaD * 2;
 
 struct SoftSeqs {
     int32_t n;
@@ -72,57 +73,123 @@ __device__ __forceinline__ void sa_bias(float gj, float eps, float &b_in, float 
     b_out = __log2f(fmaxf(0.0f, gj) + eps);
 }
 
-// One 16-byte chunk of a row goes to the row-major tile.
-__device__ __forceinline__ void sa_put_rm(char *tile, int row, int dc, uint4 x) {
-    *reinterpret_cast<uint4 *>(tile + row * kSaRm + dc * 16) = x;
-}
-// A operand of a product over d: row qn of a row-major tile, d slice ks.
-__device__ __forceinline__ sa_bf16x8_t sa_get_rm(const char *tile, int qn, int half, int ks) {
-    return *reinterpret_cast<const sa_bf16x8_t *>(tile + qn * kSaRm + (ks * 16 + half * 8) * 2);
-}
-// A operand of a product that contracts over the rows of a row-major tile (rows are positions,
-// columns d): the output row of this lane is d = db*32 + qn, its 8 contraction slots are tile rows
-// r0 + 4*half + {0..3} and r0 + 8 + 4*half + {0..3}, which is where the accumulator layout of the
-// first product leaves this lane's values.  ds_read_b64_tr_b16 transposes inside groups of 16
-// lanes: lane i of a group receives element i%4 of the 8 bytes addressed by lanes i/4, 4 + i/4,
-// 8 + i/4 and 12 + i/4.  So lane s of a group addresses (row s/4 of the four, columns 4*(s%4)..+3 of
-// the group's 16) and ends up with the four rows at its own column.
 typedef short sa_s16x4_t __attribute__((ext_vector_type(4)));
-template <int STRIDE = kSaRm>
-__device__ __forceinline__ sa_bf16x8_t sa_get_cols(const char *tile, int lane, int db, int r0) {
-    const int half = lane >> 5;
-    const char *p = tile + (r0 + 4 * half + ((lane & 15) >> 2)) * STRIDE +
-                    (db * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-    typedef sa_s16x4_t __attribute__((address_space(3))) *lds_ptr_t;
-    const sa_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)p);
-    const sa_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * STRIDE));
+
+// ---- tiles of 32 rows of 256 bytes that come straight from memory into LDS (no registers, no staging stores) ----
+// The rows lie unpadded; 16-byte chunk c of row r sits at chunk c ^ f(r), which the request's lane picks on the memory
+// side.  f takes the row's low two bits to the chunk's high ones and the next two to its low ones: sixteen consecutive
+// rows put one column on sixteen different chunks (reads of whole rows), and four consecutive rows put a 64-byte piece
+// on four different quarters of the banks (reads of columns), so both kinds of read are free of bank conflicts.
+__device__ __forceinline__ int sa_sw_f(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+__device__ __forceinline__ int sa_sw_row(int qn, int half) { return qn * (kSaD * 2) + (half ^ sa_sw_f(qn)) * 16; }
+// row operand of a product over d: row qn of a tile, d slice ks
+__device__ __forceinline__ sa_bf16x8_t sa_sw_get_row(const char *tile, int o_row, int ks) {
+    return *reinterpret_cast<const sa_bf16x8_t *>(tile + (o_row ^ (ks * 32)));
+}
+// Column operand of a product that contracts over the rows of a tile (rows are positions, columns d): the output row of
+// this lane is d = db*32 + qn, its 8 contraction slots are tile rows 16*t2 + 4*half + {0..3} and 16*t2 + 8 + 4*half
+// + {0..3}, which is where the accumulator layout of the first product leaves this lane's values.
+// ds_read_b64_tr_b16 transposes inside groups of 16 lanes: lane i of a group receives element i%4 of the 8 bytes
+// addressed by lanes i/4, 4 + i/4, 8 + i/4 and 12 + i/4.  So lane s of a group addresses (row s/4 of the four, columns
+// 4*(s%4)..+3 of the group's 16) and ends up with the four rows at its own column.
+__device__ __forceinline__ int sa_sw_col(int lane) {
+    const int half = lane >> 5, a = (lane & 15) >> 2;
+    const int c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+    return (4 * half + a) * (kSaD * 2) + ((c ^ half) | (a << 2)) * 16 + 8 * (lane & 1);
+}
+__device__ __forceinline__ sa_bf16x8_t sa_sw_get_cols(const char *tile, int o_col, int db, int t2) {
+    typedef __attribute__((address_space(3))) sa_s16x4_t *lds_ptr_t;
+    const char *p = tile + t2 * 16 * (kSaD * 2);
+    const sa_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + (o_col ^ (db * 64))));
+    const sa_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * (kSaD * 2) + (o_col ^ (db * 64) ^ 32)));
     const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-    const uint4 u4 = make_uint4(l2.x, l2.y, h2.x, h2.y);
-    return __builtin_bit_cast(sa_bf16x8_t, u4);
+    return __builtin_bit_cast(sa_bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
+}
+// 16 (4) bytes per lane from memory at base + off to LDS at dst + 16 (4) * lane; base and dst are wave-uniform.  In
+// assembly, as the compiler would put a wait for every outstanding request in front of the next LDS read; a reader is
+// behind sa_dma_wait_barrier instead.  The request has no result register, and M0 is free for it (LDS
+// instructions do not read it on this machine).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void sa_dma16(const void *base, uint32_t off, const void *dst) {
+    const uint32_t m = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void sa_dma4(const void *base, uint32_t off, const void *dst) {
+    const uint32_t m = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(m), "v"(off), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// all but the N latest requests of this wave have arrived, its LDS reads have returned, and the block has met
+template <int N>
+__device__ __forceinline__ void sa_dma_wait_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// Key tiles of the forward and the dQ kernel: 64 rows of K and of V in two LDS buffers, requested one tile ahead.  The
+// scores g of a tile are requested two tiles ahead into a copy per wave, and a wave turns them into the two biases
+// of a key (both halves of the wave take part) one tile ahead.
+constexpr int kSaT2 = 64;                       // keys per tile
+constexpr int kSaTile2B = kSaT2 * kSaD * 2;
+
+template <int NW>
+struct SoftKeyTiles {
+    __attribute__((aligned(1024))) char t[2][2][kSaTile2B];     // K and V
+    __attribute__((aligned(16))) float b_in[2][NW][kSaT2], b_out[2][NW][kSaT2];
+    __attribute__((aligned(16))) float g[2][NW][kSaT2];
+};
+
+template <int NW>
+__device__ __forceinline__ void sa_fetch_keys(SoftKeyTiles<NW> &l, const SoftArgs &a, int base, int T, int h, int t, int wave, int lane) {
+    asm volatile("" : "+v"(lane));  // the lane's offsets are formed per tile: no registers to keep them
+    {
+        const int last = T - 1 - t * kSaT2;  // >= 0
+        const size_t row = (size_t)(base + t * kSaT2) * a.Hkv + h;
+        const char *kp = a.k + row * (kSaD * 2), *vp = a.v + row * (kSaD * 2);
+        constexpr int kRows = kSaT2 / NW;
+#pragma unroll
+        for (int i = 0; i < kRows / 4; i++) {
+            const int r = wave * kRows + 4 * i + (lane >> 4);
+            const uint32_t o = (uint32_t)(min(r, last) * a.Hkv * (kSaD * 2) + ((lane & 15) ^ sa_sw_f(r)) * 16);
+            sa_dma16(kp, o, &l.t[t & 1][0][(wave * kRows + 4 * i) * (kSaD * 2)]);
+            sa_dma16(vp, o, &l.t[t & 1][1][(wave * kRows + 4 * i) * (kSaD * 2)]);
+        }
+    }
+}
+template <int NW>
+__device__ __forceinline__ void sa_fetch_g(SoftKeyTiles<NW> &l, const SoftArgs &a, int base, int T, int h, int t, int wave, int lane) {
+    const int r0 = min(t * kSaT2, T - 1);  // a tile past the end reads the last row
+    const int off = min(lane, T - 1 - r0) * a.Hkv * 4;
+    sa_dma4(a.g + (size_t)(base + r0) * a.Hkv + h, (uint32_t)off, l.g[t & 1][wave]);
+}
+template <int NW>
+__device__ __forceinline__ void sa_put_bias(SoftKeyTiles<NW> &l, float eps, int t, int wave, int lane) {
+    float b_in, b_out;
+    sa_bias(l.g[t & 1][wave][lane], eps, b_in, b_out);
+    l.b_in[t & 1][wave][lane] = b_in;
+    l.b_out[t & 1][wave][lane] = b_out;
 }
 
 // ---------------------------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------------------------
-constexpr int kSaT2 = 64;   // keys per tile of the forward kernel
-
-__global__ __launch_bounds__(512) void soft_attn_fwd_kernel(SoftSeqs cs, SoftArgs a) {
-    __shared__ __attribute__((aligned(16))) char s_k[2][kSaT2 * kSaRm];
-    __shared__ __attribute__((aligned(16))) char s_v[2][kSaT2 * kSaCm];
-    __shared__ __attribute__((aligned(16))) float s_bin[2][kSaT2];
-    __shared__ __attribute__((aligned(16))) float s_bout[2][kSaT2];
+template <int NRB>
+__global__ __launch_bounds__(256 * NRB, 2) void soft_attn_fwd_kernel(SoftSeqs cs, SoftArgs a) {
+    constexpr int NW = 4 * NRB, kQ = 32 * NRB;
+    __shared__ SoftKeyTiles<NW> l_t;
 
     int bx, h, b;
     xcd_item(a.nx, a.Hkv, cs.n, bx, h, b);
     const int qt = a.nx - 1 - bx;  // longest rows first
     const int T = cs.ntok[b], base = cs.base[b];
-    if (qt * kSaQ >= T) return;  // block-uniform
+    if (qt * kQ >= T) return;  // block-uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int head = wave & 3, rb = wave >> 2;
     const int qn = lane & 31, half = lane >> 5;
-    const int q0 = qt * kSaQ;
-    const int i_end = min(T, q0 + kSaQ);
+    const int q0 = qt * kQ;
+    const int i_end = min(T, q0 + kQ);
     const int n_tiles = (i_end + kSaT2 - 1) / kSaT2;
+    const int n_far = q0 - a.W >= kSaT2 - 1 ? (q0 - a.W + 1) / kSaT2 : 0;  // tiles wholly outside every window of the block
 
     sa_bf16x8_t qv[8];
     const int qi = min(q0 + rb * 32 + qn, T - 1);
@@ -139,85 +206,46 @@ __global__ __launch_bounds__(512) void soft_attn_fwd_kernel(SoftSeqs cs, SoftArg
     for (int db = 0; db < 4; db++)
 #pragma unroll
         for (int c = 0; c < 16; c++) o[db][c] = 0.f;
+    const int o_row = sa_sw_row(qn, half), o_col = sa_sw_col(lane);
 
-    // staging: thread -> (keys ld_key and ld_key + 32 of the tile, 16-byte chunk)
-    const int ld_key = threadIdx.x >> 4, ld_dc = threadIdx.x & 15;
-    const int64_t v_delta = a.v - a.k;
-    uint4 kreg0, kreg1, vreg0, vreg1;
-    float bin0, bout0, bin1, bout1;
-    auto fetch = [&](int t) __attribute__((always_inline)) {
-        const size_t row0 = (size_t)(base + min(t * kSaT2 + ld_key, T - 1)) * a.Hkv + h;
-        const size_t row1 = (size_t)(base + min(t * kSaT2 + 32 + ld_key, T - 1)) * a.Hkv + h;
-        const char *kp0 = a.k + row0 * (kSaD * 2) + ld_dc * 16, *kp1 = a.k + row1 * (kSaD * 2) + ld_dc * 16;
-        kreg0 = *reinterpret_cast<const uint4 *>(kp0);
-        kreg1 = *reinterpret_cast<const uint4 *>(kp1);
-        vreg0 = *reinterpret_cast<const uint4 *>(kp0 + v_delta);
-        vreg1 = *reinterpret_cast<const uint4 *>(kp1 + v_delta);
-        sa_bias(a.g[row0], a.eps, bin0, bout0);
-        sa_bias(a.g[row1], a.eps, bin1, bout1);
-    };
-    auto stage = [&](int buf) __attribute__((always_inline)) {
-        sa_put_rm(s_k[buf], ld_key, ld_dc, kreg0);
-        sa_put_rm(s_k[buf], ld_key + 32, ld_dc, kreg1);
-        *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * kSaCm + ld_dc * 16]) = vreg0;
-        *reinterpret_cast<uint4 *>(&s_v[buf][(ld_key + 32) * kSaCm + ld_dc * 16]) = vreg1;
-        if (ld_dc == 0) {
-            s_bin[buf][ld_key] = bin0; s_bout[buf][ld_key] = bout0;
-            s_bin[buf][ld_key + 32] = bin1; s_bout[buf][ld_key + 32] = bout1;
-        }
-    };
-
-    fetch(0);
-    stage(0);
-    __syncthreads();
-    for (int t = 0; t < n_tiles; t++) {
-        const int buf = t & 1;
+    auto body = [&](int t, auto far_t) __attribute__((always_inline)) {
+        constexpr bool kFar = decltype(far_t)::value;
+        if (t + 1 < n_tiles) sa_fetch_keys(l_t, a, base, T, h, t + 1, wave, lane);
+        sa_fetch_g(l_t, a, base, T, h, t + 2, wave, lane);
+        const char *tk = l_t.t[t & 1][0], *tv = l_t.t[t & 1][1];
         // ---- S^T for the two halves of 32 keys ----
-        sa_f32x16_t s0, s1;
+        sa_f32x16_t s[2];
 #pragma unroll
-        for (int c = 0; c < 16; c++) { s0[c] = 0.f; s1[c] = 0.f; }
-        {
-            sa_bf16x8_t ka[8];
+        for (int hf = 0; hf < 2; hf++) {
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++) ka[ks] = sa_get_rm(s_k[buf], qn, half, ks);
-            __builtin_amdgcn_sched_barrier(0);
-            if (t + 1 < n_tiles) fetch(t + 1);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int c = 0; c < 16; c++) s[hf][c] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qv[ks], s0, 0, 0, 0);
-#pragma unroll
-            for (int ks = 0; ks < 8; ks++) ka[ks] = sa_get_rm(s_k[buf], 32 + qn, half, ks);
-#pragma unroll
-            for (int ks = 0; ks < 8; ks++) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qv[ks], s1, 0, 0, 0);
+            for (int ks = 0; ks < 8; ks++)
+                s[hf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + hf * kSaTileB, o_row, ks), qv[ks], s[hf], 0, 0, 0);
         }
-        // register c = 4j+i of s0 (s1) holds key 8j + 4*half + i (+ 32) of the tile
-        const bool far = t * kSaT2 + kSaT2 - 1 <= q0 - a.W;  // every key outside every window of the block
-        float sc[32];
+        // register c = 4j+i of s[hf] holds key 32*hf + 8j + 4*half + i of the tile
         float mt = -INFINITY;
 #pragma unroll
         for (int hf = 0; hf < 2; hf++)
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const float4 bo4 = *reinterpret_cast<const float4 *>(&s_bout[buf][32 * hf + 8 * j + 4 * half]);
+                const float4 bo4 = *reinterpret_cast<const float4 *>(&l_t.b_out[t & 1][wave][32 * hf + 8 * j + 4 * half]);
                 const float bo[4] = {bo4.x, bo4.y, bo4.z, bo4.w};
-                if (far) {
+                if (kFar) {
 #pragma unroll
                     for (int i = 0; i < 4; i++) {
-                        const float sv = hf ? s1[4 * j + i] : s0[4 * j + i];
-                        sc[16 * hf + 4 * j + i] = fmaf(sv, a.scale_log2e, bo[i]);
-                        mt = fmaxf(mt, sc[16 * hf + 4 * j + i]);
+                        s[hf][4 * j + i] = fmaf(s[hf][4 * j + i], a.scale_log2e, bo[i]);
+                        mt = fmaxf(mt, s[hf][4 * j + i]);
                     }
                 } else {
-                    const float4 bi4 = *reinterpret_cast<const float4 *>(&s_bin[buf][32 * hf + 8 * j + 4 * half]);
+                    const float4 bi4 = *reinterpret_cast<const float4 *>(&l_t.b_in[t & 1][wave][32 * hf + 8 * j + 4 * half]);
                     const float bi[4] = {bi4.x, bi4.y, bi4.z, bi4.w};
 #pragma unroll
                     for (int i = 0; i < 4; i++) {
                         const int jg = t * kSaT2 + 32 * hf + 8 * j + 4 * half + i;
-                        const float sv = hf ? s1[4 * j + i] : s0[4 * j + i];
                         const float bias = (qi - jg < a.W) ? bi[i] : bo[i];
-                        const float x = (jg <= qi) ? fmaf(sv, a.scale_log2e, bias) : -INFINITY;
-                        sc[16 * hf + 4 * j + i] = x;
-                        mt = fmaxf(mt, x);
+                        s[hf][4 * j + i] = (jg <= qi) ? fmaf(s[hf][4 * j + i], a.scale_log2e, bias) : -INFINITY;
+                        mt = fmaxf(mt, s[hf][4 * j + i]);
                     }
                 }
             }
@@ -230,7 +258,8 @@ __global__ __launch_bounds__(512) void soft_attn_fwd_kernel(SoftSeqs cs, SoftArg
         const sa_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
         for (int c = 0; c < 16; c++) {
-            const float p0 = __builtin_amdgcn_exp2f(sc[2 * c] - msafe), p1 = __builtin_amdgcn_exp2f(sc[2 * c + 1] - msafe);
+            const float p0 = __builtin_amdgcn_exp2f(s[c >> 3][(2 * c) & 15] - msafe);
+            const float p1 = __builtin_amdgcn_exp2f(s[c >> 3][(2 * c + 1) & 15] - msafe);
             px += p0 + p1;
             pb[c] = sa_pack(p0, p1);
             ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(sa_bf16x2_t, pb[c]), ones, ps, false);
@@ -251,11 +280,21 @@ __global__ __launch_bounds__(512) void soft_attn_fwd_kernel(SoftSeqs cs, SoftArg
             const sa_bf16x8_t pbv = __builtin_bit_cast(sa_bf16x8_t, p4);
 #pragma unroll
             for (int db = 0; db < 4; db++)
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_get_cols<kSaCm>(s_v[buf], lane, db, 16 * t2), pbv, o[db], 0, 0, 0);
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_cols(tv, o_col, db, t2), pbv, o[db], 0, 0, 0);
         }
-        if (t + 1 < n_tiles) stage(buf ^ 1);
-        __syncthreads();
-    }
+        sa_put_bias(l_t, a.eps, t + 1, wave, lane);
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
+    };
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qv[ks]));  // waited for here, not in the loop
+    sa_fetch_keys(l_t, a, base, T, h, 0, wave, lane);
+    sa_fetch_g(l_t, a, base, T, h, 0, wave, lane);
+    sa_fetch_g(l_t, a, base, T, h, 1, wave, lane);
+    sa_dma_wait_barrier<0>();
+    sa_put_bias(l_t, a.eps, 0, wave, lane);
+    int t = 0;
+    for (; t < n_far; t++) body(t, std::true_type());
+    for (; t < n_tiles; t++) body(t, std::false_type());
     // register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i
     const int i = q0 + rb * 32 + qn;
     const float lt = l + __shfl_xor(l, 32), lxt = lx + __shfl_xor(lx, 32);
@@ -296,24 +335,23 @@ __global__ __launch_bounds__(256) void soft_attn_rowdot_kernel(int64_t n_rows, c
 // ---------------------------------------------------------------------------------------------
 // backward, dQ: columns of every tile are this wave's 32 queries
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void soft_attn_bwd_dq_kernel(SoftSeqs cs, SoftArgs a) {
-    __shared__ __attribute__((aligned(16))) char s_k[2][kSaT * kSaRm];
-    __shared__ __attribute__((aligned(16))) char s_kc[2][kSaT * kSaCm];  // the same tile at the stride of column reads
-    __shared__ __attribute__((aligned(16))) char s_v[2][kSaT * kSaRm];
-    __shared__ __attribute__((aligned(16))) float s_bin[2][kSaT];
-    __shared__ __attribute__((aligned(16))) float s_bout[2][kSaT];
+template <int NRB>
+__global__ __launch_bounds__(256 * NRB, 2) void soft_attn_bwd_dq_kernel(SoftSeqs cs, SoftArgs a) {
+    constexpr int NW = 4 * NRB, kQ = 32 * NRB;
+    __shared__ SoftKeyTiles<NW> l_t;
 
     int bx, h, b;
     xcd_item(a.nx, a.Hkv, cs.n, bx, h, b);
     const int qt = a.nx - 1 - bx;
     const int T = cs.ntok[b], base = cs.base[b];
-    if (qt * kSaQ >= T) return;
+    if (qt * kQ >= T) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int head = wave & 3, rb = wave >> 2;
     const int qn = lane & 31, half = lane >> 5;
-    const int q0 = qt * kSaQ;
-    const int i_end = min(T, q0 + kSaQ);
-    const int n_tiles = (i_end + kSaT - 1) / kSaT;
+    const int q0 = qt * kQ;
+    const int i_end = min(T, q0 + kQ);
+    const int n_tiles = (i_end + kSaT2 - 1) / kSaT2;
+    const int n_far = q0 - a.W >= kSaT2 - 1 ? (q0 - a.W + 1) / kSaT2 : 0;
 
     const int qi = min(q0 + rb * 32 + qn, T - 1);
     const size_t qrow = (size_t)(base + qi) * a.Hq + (size_t)h * kSaG + head;
@@ -326,100 +364,79 @@ __global__ __launch_bounds__(512) void soft_attn_bwd_dq_kernel(SoftSeqs cs, Soft
             dov[ks] = *reinterpret_cast<const sa_bf16x8_t *>(dp + (ks * 16 + half * 8) * 2);
         }
     }
-    const float lse2 = a.lse[qrow] * 1.4426950408889634f;
-    const float Di = a.rowdot[qrow];
+    float lse2 = a.lse[qrow] * 1.4426950408889634f;
+    float Di = a.rowdot[qrow];
     sa_f32x16_t dq[4];
 #pragma unroll
     for (int db = 0; db < 4; db++)
 #pragma unroll
         for (int c = 0; c < 16; c++) dq[db][c] = 0.f;
+    const int o_row = sa_sw_row(qn, half), o_col = sa_sw_col(lane);
 
-    const int ld_key = threadIdx.x >> 4, ld_dc = threadIdx.x & 15;  // thread -> (key of the tile, 16-byte chunk)
-    const int64_t v_delta = a.v - a.k;
-    // two sets of staging registers: a tile is requested two iterations before it is multiplied
-    struct StReg { uint4 kreg, vreg; float bin_reg, bout_reg; };
-    StReg r0, r1;
-    auto fetch = [&](int t, StReg &r) __attribute__((always_inline)) {
-        const size_t row = (size_t)(base + min(t * kSaT + ld_key, T - 1)) * a.Hkv + h;
-        const char *kp = a.k + row * (kSaD * 2) + ld_dc * 16;
-        r.kreg = *reinterpret_cast<const uint4 *>(kp);
-        r.vreg = *reinterpret_cast<const uint4 *>(kp + v_delta);
-        sa_bias(a.g[row], a.eps, r.bin_reg, r.bout_reg);
-    };
-    auto stage = [&](int buf, const StReg &r) __attribute__((always_inline)) {
-        sa_put_rm(s_k[buf], ld_key, ld_dc, r.kreg);
-        *reinterpret_cast<uint4 *>(&s_kc[buf][ld_key * kSaCm + ld_dc * 16]) = r.kreg;
-        sa_put_rm(s_v[buf], ld_key, ld_dc, r.vreg);
-        if (ld_dc == 0) { s_bin[buf][ld_key] = r.bin_reg; s_bout[buf][ld_key] = r.bout_reg; }
-    };
-
-    fetch(0, r0);
-    stage(0, r0);
-    if (n_tiles > 1) fetch(1, r1);
-    __syncthreads();
-    // one iteration: tile t is multiplied, tile t+2 is requested into rf, tile t+1 goes from rs to LDS
-    auto body = [&](int t, StReg &rf, const StReg &rs) __attribute__((always_inline)) {
-        const int buf = t & 1;
-        sa_bf16x8_t ka[8];
+    auto body = [&](int t, auto far_t) __attribute__((always_inline)) {
+        constexpr bool kFar = decltype(far_t)::value;
+        if (t + 1 < n_tiles) sa_fetch_keys(l_t, a, base, T, h, t + 1, wave, lane);
+        sa_fetch_g(l_t, a, base, T, h, t + 2, wave, lane);
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) ka[ks] = sa_get_rm(s_k[buf], qn, half, ks);
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 2 < n_tiles) fetch(t + 2, rf);
-        __builtin_amdgcn_sched_barrier(0);
-        sa_f32x16_t s, dp;
+        for (int hf = 0; hf < 2; hf++) {
+            const char *tk = l_t.t[t & 1][0] + hf * kSaTileB, *tv = l_t.t[t & 1][1] + hf * kSaTileB;
+            sa_f32x16_t s, dp;
 #pragma unroll
-        for (int c = 0; c < 16; c++) { s[c] = 0.f; dp[c] = 0.f; }
+            for (int c = 0; c < 16; c++) { s[c] = 0.f; dp[c] = 0.f; }
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qv[ks], s, 0, 0, 0);
+            for (int ks = 0; ks < 8; ks++)
+                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk, o_row, ks), qv[ks], s, 0, 0, 0);
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) ka[ks] = sa_get_rm(s_v[buf], qn, half, ks);
+            for (int ks = 0; ks < 8; ks++)
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tv, o_row, ks), dov[ks], dp, 0, 0, 0);
+            // dS^T = P^T (dP^T - D_i), rounded to bf16 for the last product
+            uint32_t db_[8];
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], dov[ks], dp, 0, 0, 0);
-        // dS^T = P^T (dP^T - D_i), rounded to bf16 for the last product
-        uint32_t db_[8];
-        const bool far = t * kSaT + kSaT - 1 <= q0 - a.W;  // every key outside every window of the block: no mask, one bias
+            for (int j = 0; j < 4; j++) {
+                const float4 bo4 = *reinterpret_cast<const float4 *>(&l_t.b_out[t & 1][wave][32 * hf + 8 * j + 4 * half]);
+                const float bo[4] = {bo4.x, bo4.y, bo4.z, bo4.w};
+                float ds[4];
+                if (kFar) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const float4 bo4 = *reinterpret_cast<const float4 *>(&s_bout[buf][8 * j + 4 * half]);
-            const float bo[4] = {bo4.x, bo4.y, bo4.z, bo4.w};
-            float ds[4];
-            if (far) {
+                    for (int i = 0; i < 4; i++)
+                        ds[i] = __builtin_amdgcn_exp2f(fmaf(s[4 * j + i], a.scale_log2e, bo[i] - lse2)) * (dp[4 * j + i] - Di);
+                } else {
+                    const float4 bi4 = *reinterpret_cast<const float4 *>(&l_t.b_in[t & 1][wave][32 * hf + 8 * j + 4 * half]);
+                    const float bi[4] = {bi4.x, bi4.y, bi4.z, bi4.w};
 #pragma unroll
-                for (int i = 0; i < 4; i++)
-                    ds[i] = __builtin_amdgcn_exp2f(fmaf(s[4 * j + i], a.scale_log2e, bo[i] - lse2)) * (dp[4 * j + i] - Di);
-            } else {
-                const float4 bi4 = *reinterpret_cast<const float4 *>(&s_bin[buf][8 * j + 4 * half]);
-                const float bi[4] = {bi4.x, bi4.y, bi4.z, bi4.w};
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int jg = t * kSaT + 8 * j + 4 * half + i;
-                    const float bias = (qi - jg < a.W) ? bi[i] : bo[i];
-                    const float x = (jg <= qi) ? fmaf(s[4 * j + i], a.scale_log2e, bias) - lse2 : -INFINITY;
-                    ds[i] = __builtin_amdgcn_exp2f(x) * (dp[4 * j + i] - Di);
+                    for (int i = 0; i < 4; i++) {
+                        const int jg = t * kSaT2 + 32 * hf + 8 * j + 4 * half + i;
+                        const float bias = (qi - jg < a.W) ? bi[i] : bo[i];
+                        const float x = (jg <= qi) ? fmaf(s[4 * j + i], a.scale_log2e, bias) - lse2 : -INFINITY;
+                        ds[i] = __builtin_amdgcn_exp2f(x) * (dp[4 * j + i] - Di);
+                    }
                 }
+                db_[2 * j] = sa_pack(ds[0], ds[1]);
+                db_[2 * j + 1] = sa_pack(ds[2], ds[3]);
             }
-            db_[2 * j] = sa_pack(ds[0], ds[1]);
-            db_[2 * j + 1] = sa_pack(ds[2], ds[3]);
-        }
 #pragma unroll
-        for (int t2 = 0; t2 < 2; t2++) {
-            const uint4 p4 = make_uint4(db_[4 * t2], db_[4 * t2 + 1], db_[4 * t2 + 2], db_[4 * t2 + 3]);
-            const sa_bf16x8_t dsv = __builtin_bit_cast(sa_bf16x8_t, p4);
+            for (int t2 = 0; t2 < 2; t2++) {
+                const uint4 p4 = make_uint4(db_[4 * t2], db_[4 * t2 + 1], db_[4 * t2 + 2], db_[4 * t2 + 3]);
+                const sa_bf16x8_t dsv = __builtin_bit_cast(sa_bf16x8_t, p4);
 #pragma unroll
-            for (int db = 0; db < 4; db++)
-                dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_get_cols<kSaCm>(s_kc[buf], lane, db, 16 * t2), dsv, dq[db], 0, 0, 0);
+                for (int db = 0; db < 4; db++)
+                    dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_cols(tk, o_col, db, t2), dsv, dq[db], 0, 0, 0);
+            }
         }
-        if (t + 1 < n_tiles) stage(buf ^ 1, rs);
-        __syncthreads();
+        sa_put_bias(l_t, a.eps, t + 1, wave, lane);
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
     };
-    {
-        int t = 0;
-        for (; t + 1 < n_tiles; t += 2) {
-            body(t, r0, r1);
-            body(t + 1, r1, r0);
-        }
-        if (t < n_tiles) body(t, r0, r1);
-    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qv[ks]), "+v"(dov[ks]));  // waited for here, not in the loop
+    asm volatile("" : "+v"(lse2), "+v"(Di));
+    sa_fetch_keys(l_t, a, base, T, h, 0, wave, lane);
+    sa_fetch_g(l_t, a, base, T, h, 0, wave, lane);
+    sa_fetch_g(l_t, a, base, T, h, 1, wave, lane);
+    sa_dma_wait_barrier<0>();
+    sa_put_bias(l_t, a.eps, 0, wave, lane);
+    int t = 0;
+    for (; t < n_far; t++) body(t, std::true_type());
+    for (; t < n_tiles; t++) body(t, std::false_type());
     const int i = q0 + rb * 32 + qn;
     if (i < T) {
         float *op = a.dq + qrow * kSaD;
@@ -435,209 +452,251 @@ __global__ __launch_bounds__(512) void soft_attn_bwd_dq_kernel(SoftSeqs cs, Soft
 }
 
 // ---------------------------------------------------------------------------------------------
-// backward, dK / dV / dg: columns of every tile are this wave's 32 keys
+// backward, dK / dV / dg: columns of every tile are this wave's keys
+//
+// A wave owns 32 keys and forms all four products of them: S = Q K^T and dP = dO V^T with its K and V rows in
+// registers as the column operand, dV^T += dO^T P and dK^T += Q^T dS with P and dS straight from the accumulators.
+// Streamed tiles (32 queries of one query head, Q and dO) come through LDS once and are read in both layouts.
+// HS waves of a block share 32 keys and take one query head each (at the end their sums meet in LDS in a fixed
+// order), the other factor of the four waves is keys: HS = 1 reads a streamed tile for 128 keys and runs two blocks
+// per compute unit; HS = 4 makes blocks of a quarter of the length and four times their number.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void soft_attn_bwd_dkv_kernel(SoftSeqs cs, SoftArgs a) {
-    // Role 0 works on tile `it` while role 1 works on tile it-1 (it gets P of that tile from role 0
-    // through LDS, written one iteration earlier): one barrier per iteration, and the two waves of
-    // a SIMD never wait for each other inside one.  What role 0 reads needs two buffers (in use,
-    // being staged), what role 1 reads needs three (in use, waiting, being staged).
-    __shared__ __attribute__((aligned(16))) char s_q[2][kSaT * kSaRm];     // role 0: rows (S = Q K^T)
-    __shared__ __attribute__((aligned(16))) char s_doc[2][kSaT * kSaCm];   // role 0: columns (dV^T += dO^T P)
-    __shared__ __attribute__((aligned(16))) char s_do[3][kSaT * kSaRm];    // role 1: rows (dP = dO V^T)
-    __shared__ __attribute__((aligned(16))) char s_qc[3][kSaT * kSaCm];    // role 1: columns (dK^T += Q^T dS)
-    __shared__ __attribute__((aligned(16))) float s_lse[2][kSaT];
-    __shared__ __attribute__((aligned(16))) float s_dd[3][kSaT];
-    __shared__ float s_p[2][4][16][64];  // P of a (32 keys x 32 queries) tile per key sub-tile, lane-private slots
+template <int HS>
+__global__ __launch_bounds__(256, HS == 1 ? 2 : 1) void soft_attn_bwd_dkv_kernel(SoftSeqs cs, SoftArgs a) {
+    constexpr int kBufs = HS == 4 ? 2 : 3;  // one tile in use, the others arriving
+    constexpr int kReq = 4 * HS + 2;        // requests of a wave per tile
+    constexpr int kTurns = kSaG / HS;       // turns per query tile
+    __shared__ __attribute__((aligned(1024))) char s_t[kBufs][HS][2][kSaTileB];  // Q and dO
+    __shared__ __attribute__((aligned(16))) float s_ld[kBufs][4][128];           // lse and D of the wave's tile
 
     int kbk, h, b;  // early key blocks have the most queries: first
     xcd_item(a.nx, a.Hkv, cs.n, kbk, h, b);
     const int T = cs.ntok[b], base = cs.base[b];
-    const int j0 = kbk * kSaKB;
-    if (j0 >= T) return;
+    const int j0 = kbk * (128 / HS);
+    if (j0 >= T) return;  // block-uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kb = wave & 3, role = wave >> 2;
     const int qn = lane & 31, half = lane >> 5;
-    const int jg = j0 + kb * 32 + qn;        // this lane's key
-    const int jc = min(jg, T - 1);
-    const size_t krow = (size_t)(base + jc) * a.Hkv + h;
+    const int hs = wave % HS;
+    const int jw = j0 + wave / HS * 32;  // first key of this wave
+    const int jg = jw + qn;              // this lane's key
 
-    // the block's own rows: K for role 0, V for role 1, as the N side of a product over d
-    sa_bf16x8_t own[8];
+    sa_bf16x8_t ok[8], ov[8];
+    float gk, b_far, dg_acc = 0.f;
     {
-        const char *p = (role == 0 ? a.k : a.v) + krow * kSaD * 2;
+        const size_t krow = (size_t)(base + min(jg, T - 1)) * a.Hkv + h;
+        const char *kp = a.k + krow * kSaD * 2, *vp = a.v + krow * kSaD * 2;
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) own[ks] = *reinterpret_cast<const sa_bf16x8_t *>(p + (ks * 16 + half * 8) * 2);
+        for (int ks = 0; ks < 8; ks++) {
+            ok[ks] = *reinterpret_cast<const sa_bf16x8_t *>(kp + (ks * 16 + half * 8) * 2);
+            ov[ks] = *reinterpret_cast<const sa_bf16x8_t *>(vp + (ks * 16 + half * 8) * 2);
+        }
+        gk = a.g[krow];
+        b_far = __log2f(fmaxf(0.0f, gk) + a.eps);
     }
-    const float gj = a.g[krow];
-    float b_in, b_out;
-    sa_bias(gj, a.eps, b_in, b_out);
-    const bool follows_in = gj > 1.0f, follows_out = gj > 0.0f;  // where m_ij is g_j rather than the indicator
-    sa_f32x16_t acc[4];  // role 0: dV^T, role 1: dK^T ; rows d, columns keys
+    sa_f32x16_t av[4], ak[4];  // dV^T and dK^T: rows d, columns keys
 #pragma unroll
     for (int db = 0; db < 4; db++)
 #pragma unroll
-        for (int c = 0; c < 16; c++) acc[db][c] = 0.f;
-    float dg_acc = 0.f;
+        for (int c = 0; c < 16; c++) { av[db][c] = 0.f; ak[db][c] = 0.f; }
 
-    // streamed tiles: 32 queries of one query head; iteration it = (query tile, head)
+    // streamed tiles: iteration it = (query tile, HS query heads)
     const int qt_first = j0 / kSaT, n_qt = (T + kSaT - 1) / kSaT;
-    const int n_it = (n_qt - qt_first) * kSaG;
-    const int ld_row = threadIdx.x >> 4, ld_dc = threadIdx.x & 15;  // thread -> (row of the tile, 16-byte chunk)
-    // two sets of staging registers: the loads of a tile are issued two iterations before the
-    // tile is multiplied (one iteration is shorter than the latency of a load under this traffic)
-    struct StReg { uint4 qreg, doreg; float lse_reg, dd_reg; };
-    StReg r0, r1;
-    auto fetch = [&](int it, StReg &r) __attribute__((always_inline)) {
-        const int qt = qt_first + it / kSaG, hd = it % kSaG;
-        const int idx = qt * kSaT + ld_row;
-        const size_t row = (size_t)(base + min(idx, T - 1)) * a.Hq + (size_t)h * kSaG + hd;
-        r.qreg = *reinterpret_cast<const uint4 *>(a.q + row * (kSaD * 2) + ld_dc * 16);
-        r.doreg = *reinterpret_cast<const uint4 *>(a.dout + row * (kSaD * 2) + ld_dc * 16);
-        const bool real = idx < T;  // a row past the end gets weight exp2(-inf) = 0
-        r.lse_reg = real ? a.lse[row] * 1.4426950408889634f : INFINITY;
-        r.dd_reg = real ? a.rowdot[row] : 0.f;
-    };
-    auto stage = [&](int b2, int b3, const StReg &r) __attribute__((always_inline)) {
-        sa_put_rm(s_q[b2], ld_row, ld_dc, r.qreg);
-        sa_put_rm(s_do[b3], ld_row, ld_dc, r.doreg);
-        *reinterpret_cast<uint4 *>(&s_qc[b3][ld_row * kSaCm + ld_dc * 16]) = r.qreg;
-        *reinterpret_cast<uint4 *>(&s_doc[b2][ld_row * kSaCm + ld_dc * 16]) = r.doreg;
-        if (ld_dc == 0) { s_lse[b2][ld_row] = r.lse_reg; s_dd[b3][ld_row] = r.dd_reg; }
+    const int n_it = (n_qt - qt_first) * kTurns;
+    // a wave brings 8 * HS rows of Q and of dO, four rows per request, and its own copy of its tile's lse and D
+    auto fetch = [&](int it_, int buf) __attribute__((always_inline)) {
+        const int it = min(it_, n_it - 1);  // past the end: the last tile again, so that the count of requests stays
+        const int i0 = (qt_first + it / kTurns) * kSaT;
+        const size_t row0 = (size_t)(base + i0) * a.Hq + (size_t)h * kSaG + it % kTurns * HS;  // uniform; lanes add 32 bits
+        const int last = T - 1 - i0;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // the lane's offsets are formed per tile: no registers to keep them
+#pragma unroll
+        for (int i = 0; i < 2 * HS; i++) {
+            const int R = wave * 8 * HS + 4 * i, hd = R / kSaT, r = R % kSaT + (ln >> 4);
+            const uint32_t o = (uint32_t)(min(r, last) * a.Hq * (kSaD * 2) + ((ln & 15) ^ sa_sw_f(r)) * 16);
+            sa_dma16(a.q + (row0 + hd) * (kSaD * 2), o, &s_t[buf][hd][0][R % kSaT * (kSaD * 2)]);
+            sa_dma16(a.dout + (row0 + hd) * (kSaD * 2), o, &s_t[buf][hd][1][R % kSaT * (kSaD * 2)]);
+        }
+        const uint32_t ol = (uint32_t)(min(ln & 31, last) * a.Hq * 4);
+        sa_dma4(a.lse + row0 + hs, ol, s_ld[buf][wave]);
+        sa_dma4(a.rowdot + row0 + hs, ol, s_ld[buf][wave] + 64);
     };
 
-    fetch(0, r0);
-    stage(0, 0, r0);
-    fetch(1, r1);  // n_it >= 4
-    __syncthreads();
-    int b3 = 0;  // it % 3
-    // one iteration: role 0 multiplies tile `it`, role 1 tile it-1; tile it+2 is requested into rf,
-    // tile it+1 goes from rs to LDS
-    auto body = [&](int it, StReg &rf, const StReg &rs) __attribute__((always_inline)) {
-        const int b3p = b3 == 0 ? 2 : b3 - 1, b3n = b3 == 2 ? 0 : b3 + 1;
-        const int mine = role == 0 ? it : it - 1;               // the tile this wave multiplies
-        const bool active = role == 0 ? it < n_it : it >= 1;    // wave-uniform
-        const int i0 = (qt_first + mine / kSaG) * kSaT;         // first query of that tile
-        // first product: rows = queries of the tile, columns = this wave's keys
-        const char *rm = role == 0 ? s_q[it & 1] : s_do[b3p];
-        sa_bf16x8_t fa[8];
-        if (active) {
-#pragma unroll
-            for (int ks = 0; ks < 8; ks++) fa[ks] = sa_get_rm(rm, qn, half, ks);
+    // one tile; far: every query of it follows every key of this wave by at least the window, and none is past the
+    // end, so no pair is masked and every bias is the one outside the window (nearly all tiles of a long sequence)
+    auto body = [&](int it, int buf, auto far_t) __attribute__((always_inline)) {
+        constexpr bool kFar = decltype(far_t)::value;
+        constexpr bool kTight = HS == 1;  // 256 registers: more than four operands in flight would spill
+        const int i0 = (qt_first + it / kTurns) * kSaT;
+        const char *tq = s_t[buf][hs][0], *td = s_t[buf][hs][1];
+        int ln = lane;
+        if (kTight) asm volatile("" : "+v"(ln));  // as above
+        const int qn = ln & 31, half = ln >> 5, o_row = sa_sw_row(qn, half), o_col = sa_sw_col(ln);
+        float b_in = 0.f, b_out = b_far;
+        if (!kFar) {
+            float gg = gk;
+            asm volatile("" : "+v"(gg));
+            sa_bias(gg, a.eps, b_in, b_out);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (it + 2 < n_it) fetch(it + 2, rf);
-        __builtin_amdgcn_sched_barrier(0);
-        if (active) {
-            sa_f32x16_t x;
+        sa_f32x16_t s, dp;
 #pragma unroll
-            for (int c = 0; c < 16; c++) x[c] = 0.f;
+        for (int c = 0; c < 16; c++) { s[c] = 0.f; dp[c] = 0.f; }
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], own[ks], x, 0, 0, 0);
-            // register c = 4j+i of a lane holds query i0 + 8j + 4*half + i
-            uint32_t pk[8];
-            // wave-uniform: every query of the tile follows every key of this wave by at least the window, so no
-            // pair is masked and every bias is the one outside the window (nearly all tiles of a long sequence)
-            const bool interior = i0 - (j0 + kb * 32 + 31) >= a.W;
-            if (role == 0 && interior) {
+        for (int ks = 0; ks < 8; ks++) {
+            const sa_bf16x8_t f = sa_sw_get_row(tq, o_row, ks);
+            if (kTight && (ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, ok[ks], s, 0, 0, 0);
+        }
+        if (kTight) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const float4 l4 = *reinterpret_cast<const float4 *>(&s_lse[it & 1][8 * j + 4 * half]);
-                    const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
+        for (int ks = 0; ks < 8; ks++) {
+            const sa_bf16x8_t f = sa_sw_get_row(td, o_row, ks);
+            if (kTight && (ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, ov[ks], dp, 0, 0, 0);
+        }
+        // register c = 4j+i of a lane holds query i0 + 8j + 4*half + i
+        uint32_t pk[8];
 #pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        x[4 * j + i] = __builtin_amdgcn_exp2f(fmaf(x[4 * j + i], a.scale_log2e, b_out - ls[i]));
-                        s_p[it & 1][kb][4 * j + i][lane] = x[4 * j + i];
-                    }
-                }
+        for (int j = 0; j < 4; j++) {
+            const float4 l4 = *reinterpret_cast<const float4 *>(&s_ld[buf][wave][8 * j + 4 * half]);
+            const float ls[4] = {l4.x * 1.4426950408889634f, l4.y * 1.4426950408889634f, l4.z * 1.4426950408889634f,
+                                 l4.w * 1.4426950408889634f};
 #pragma unroll
-                for (int c = 0; c < 8; c++) pk[c] = sa_pack(x[2 * c], x[2 * c + 1]);
-            } else if (role == 0) {
-                // P = exp2(S * scale + bias - lse); a copy goes to the partner wave through LDS
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const float4 l4 = *reinterpret_cast<const float4 *>(&s_lse[it & 1][8 * j + 4 * half]);
-                    const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const int ig = i0 + 8 * j + 4 * half + i;
-                        const float bias = (ig - jg < a.W) ? b_in : b_out;
-                        const float e = (jg <= ig) ? fmaf(x[4 * j + i], a.scale_log2e, bias) - ls[i] : -INFINITY;
-                        x[4 * j + i] = __builtin_amdgcn_exp2f(e);
-                        s_p[it & 1][kb][4 * j + i][lane] = x[4 * j + i];
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 8; c++) pk[c] = sa_pack(x[2 * c], x[2 * c + 1]);
-            } else if (interior) {
-                float dsum = 0.f;
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const float4 d4 = *reinterpret_cast<const float4 *>(&s_dd[b3p][8 * j + 4 * half]);
-                    const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
-                    float ds[4];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        ds[i] = s_p[mine & 1][kb][4 * j + i][lane] * (x[4 * j + i] - dd[i]);
-                        dsum += ds[i];
-                    }
-                    pk[2 * j] = sa_pack(ds[0], ds[1]);
-                    pk[2 * j + 1] = sa_pack(ds[2], ds[3]);
-                }
-                dg_acc += follows_out ? dsum : 0.f;
-            } else {
-                // dS = P (dP - D_i); the part of it where m_ij follows g_j adds up to dg_j (g_j + eps)
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const float4 d4 = *reinterpret_cast<const float4 *>(&s_dd[b3p][8 * j + 4 * half]);
-                    const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
-                    float ds[4];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const int ig = i0 + 8 * j + 4 * half + i;
-                        ds[i] = s_p[mine & 1][kb][4 * j + i][lane] * (x[4 * j + i] - dd[i]);
-                        const bool follows = (ig - jg < a.W) ? follows_in : follows_out;
-                        dg_acc += follows ? ds[i] : 0.f;
-                    }
-                    pk[2 * j] = sa_pack(ds[0], ds[1]);
-                    pk[2 * j + 1] = sa_pack(ds[2], ds[3]);
+            for (int i = 0; i < 4; i++) {
+                if (kFar) {
+                    s[4 * j + i] = __builtin_amdgcn_exp2f(fmaf(s[4 * j + i], a.scale_log2e, b_out - ls[i]));
+                } else {
+                    const int ig = i0 + 8 * j + 4 * half + i, jl = jw + qn;
+                    const float bias = (ig - jl < a.W) ? b_in : b_out;
+                    const float x = (jl <= ig && ig < T) ? fmaf(s[4 * j + i], a.scale_log2e, bias) - ls[i] : -INFINITY;
+                    s[4 * j + i] = __builtin_amdgcn_exp2f(x);
                 }
             }
-            // second product: rows = d, columns = keys, contraction over the 32 queries (the rows of
-            // the staged tile, read column-wise)
-            const char *tr = role == 0 ? s_doc[it & 1] : s_qc[b3p];
+            pk[2 * j] = sa_pack(s[4 * j], s[4 * j + 1]);
+            pk[2 * j + 1] = sa_pack(s[4 * j + 2], s[4 * j + 3]);
+        }
+        if (kTight) __builtin_amdgcn_sched_barrier(0);
+        // rows = d, columns = keys, contraction over the 32 queries
 #pragma unroll
-            for (int t2 = 0; t2 < 2; t2++) {
-                const uint4 p4 = make_uint4(pk[4 * t2], pk[4 * t2 + 1], pk[4 * t2 + 2], pk[4 * t2 + 3]);
-                const sa_bf16x8_t pv = __builtin_bit_cast(sa_bf16x8_t, p4);
+        for (int t2 = 0; t2 < 2; t2++) {
+            const uint4 p4 = make_uint4(pk[4 * t2], pk[4 * t2 + 1], pk[4 * t2 + 2], pk[4 * t2 + 3]);
 #pragma unroll
-                for (int db = 0; db < 4; db++)
-                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_get_cols<kSaCm>(tr, lane, db, 16 * t2), pv, acc[db], 0, 0, 0);
+            for (int db = 0; db < 4; db++) {
+                const sa_bf16x8_t f = sa_sw_get_cols(td, o_col, db, t2);
+                if (kTight && db == 3) __builtin_amdgcn_sched_barrier(0);
+                av[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, __builtin_bit_cast(sa_bf16x8_t, p4), av[db], 0, 0, 0);
             }
         }
-        if (it + 1 < n_it) stage((it + 1) & 1, b3n, rs);
-        __syncthreads();
-        b3 = b3n;
+        if (kTight) __builtin_amdgcn_sched_barrier(0);
+        // dS = P (dP - D_i); the part of it where m_ij follows g_j adds up to dg_j (g_j + eps)
+        float dsum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const float4 d4 = *reinterpret_cast<const float4 *>(&s_ld[buf][wave][64 + 8 * j + 4 * half]);
+            const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
+            float ds[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                ds[i] = s[4 * j + i] * (dp[4 * j + i] - dd[i]);
+                if (kFar) {
+                    dsum += ds[i];
+                } else {
+                    const int ig = i0 + 8 * j + 4 * half + i, jl = jw + qn;
+                    const bool follows = (ig - jl < a.W) ? gk > 1.0f : gk > 0.0f;
+                    dsum += follows ? ds[i] : 0.f;
+                }
+            }
+            pk[2 * j] = sa_pack(ds[0], ds[1]);
+            pk[2 * j + 1] = sa_pack(ds[2], ds[3]);
+        }
+        dg_acc += dsum;  // of no use where g <= 0, and dropped there at the end
+        if (kTight) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t2 = 0; t2 < 2; t2++) {
+            const uint4 p4 = make_uint4(pk[4 * t2], pk[4 * t2 + 1], pk[4 * t2 + 2], pk[4 * t2 + 3]);
+#pragma unroll
+            for (int db = 0; db < 4; db++) {
+                const sa_bf16x8_t f = sa_sw_get_cols(tq, o_col, db, t2);
+                if (kTight && db == 3) __builtin_amdgcn_sched_barrier(0);
+                ak[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, __builtin_bit_cast(sa_bf16x8_t, p4), ak[db], 0, 0, 0);
+            }
+        }
     };
-    for (int it = 0; it <= n_it; it += 2) {  // n_it is a multiple of 4; one more turn for role 1's last tile
-        body(it, r0, r1);
-        if (it + 1 <= n_it) body(it + 1, r1, r0);
+
+    // the wave's own rows are here before the first request: the compiler's wait for them would otherwise sit in the
+    // loop and wait for the requests too
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(ok[ks]), "+v"(ov[ks]));
+    for (int t = 0; t < kBufs - 1; t++) fetch(t, t);
+    sa_dma_wait_barrier<(kBufs - 2) * kReq>();
+    int buf = 0, it = 0;
+    // runs body(it) while the tile kBufs - 1 turns ahead is requested
+    auto turns = [&](int end, auto &&work) __attribute__((always_inline)) {
+        while (it < end) {
+            fetch(it + kBufs - 1, buf == 0 ? kBufs - 1 : buf - 1);
+            work();
+            sa_dma_wait_barrier<(kBufs - 2) * kReq>();  // tile it + 1 is there, and nobody reads tile it any more
+            buf = buf == kBufs - 1 ? 0 : buf + 1;
+            it++;
+        }
+    };
+    // four stretches of tiles: every query before every key of the wave, some inside a window, far, the ragged end
+    const int it_near = min(n_it, (jw / kSaT - qt_first) * kTurns);
+    const int it_end = min(n_it, max(it_near, (T / kSaT - qt_first) * kTurns));
+    const int it_far = min(it_end, max(it_near, ((jw + 31 + a.W + kSaT - 1) / kSaT - qt_first) * kTurns));
+    turns(it_near, [&]() __attribute__((always_inline)) {});
+    turns(it_far, [&]() __attribute__((always_inline)) { body(it, buf, std::false_type()); });
+    turns(it_end, [&]() __attribute__((always_inline)) { body(it, buf, std::true_type()); });
+    turns(n_it, [&]() __attribute__((always_inline)) { body(it, buf, std::false_type()); });
+    sa_dma_wait_barrier<0>();
+
+    if constexpr (HS > 1) {
+        // the waves that share keys add up, head HS - 1 first, one product's sums at a time
+        float *red = reinterpret_cast<float *>(&s_t[0][0][0][0]);
+        static_assert(kBufs * HS * 2 * kSaTileB >= 4 * 64 * 64 * 4, "the sums of four waves");
+        float *mine = red + wave * 4096, *next = mine + 4096;
+        for (int pass = 0; pass < 2; pass++) {
+            for (int w = HS - 1; w >= 1; w--) {
+                if (hs == w)
+#pragma unroll
+                    for (int db = 0; db < 4; db++)
+#pragma unroll
+                        for (int c = 0; c < 16; c++) mine[(db * 16 + c) * 64 + lane] = pass == 0 ? av[db][c] : ak[db][c];
+                __syncthreads();
+                if (hs == w - 1)
+#pragma unroll
+                    for (int db = 0; db < 4; db++)
+#pragma unroll
+                        for (int c = 0; c < 16; c++) {
+                            if (pass == 0) av[db][c] += next[(db * 16 + c) * 64 + lane];
+                            else ak[db][c] += next[(db * 16 + c) * 64 + lane];
+                        }
+                __syncthreads();
+            }
+        }
+        float *rg = &s_ld[0][0][0];
+        __syncthreads();
+        rg[wave * 64 + lane] = dg_acc;
+        __syncthreads();
+        if (hs != 0) return;
+#pragma unroll
+        for (int w = 1; w < HS; w++) dg_acc += rg[(wave + w) * 64 + lane];
     }
+    const float tot = dg_acc + __shfl_xor(dg_acc, 32);
     if (jg < T) {
-        float *op = (role == 0 ? a.dv : a.dk) + krow * kSaD;
-        const float f = role == 0 ? 1.0f : a.scale;
+        const size_t krow = (size_t)(base + jg) * a.Hkv + h;
+        float *opv = a.dv + krow * kSaD, *opk = a.dk + krow * kSaD;
 #pragma unroll
         for (int db = 0; db < 4; db++)
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const float4 w4 = make_float4(acc[db][4 * j] * f, acc[db][4 * j + 1] * f, acc[db][4 * j + 2] * f,
-                                              acc[db][4 * j + 3] * f);
-                *reinterpret_cast<float4 *>(op + 32 * db + 8 * j + 4 * half) = w4;
+                *reinterpret_cast<float4 *>(opv + 32 * db + 8 * j + 4 * half) =
+                    make_float4(av[db][4 * j], av[db][4 * j + 1], av[db][4 * j + 2], av[db][4 * j + 3]);
+                *reinterpret_cast<float4 *>(opk + 32 * db + 8 * j + 4 * half) =
+                    make_float4(ak[db][4 * j] * a.scale, ak[db][4 * j + 1] * a.scale, ak[db][4 * j + 2] * a.scale,
+                                ak[db][4 * j + 3] * a.scale);
             }
-    }
-    if (role == 1) {
-        const float tot = dg_acc + __shfl_xor(dg_acc, 32);
-        if (half == 0 && jg < T) a.dg[krow] = follows_out ? tot / (gj + a.eps) : 0.f;
+        if (half == 0) a.dg[krow] = gk > 0.0f ? tot / (gk + a.eps) : 0.f;
     }
 }
 
@@ -664,6 +723,12 @@ size_t soft_attn_ws_bytes(int64_t total_tokens, int n_q_heads) {
     return (size_t)((total_tokens * n_q_heads * 4 + 255) / 256) * 256;
 }
 
+// Blocks of 32 positions that share a key tile in the forward and the dQ kernel.  One (four waves, two blocks per compute
+// unit) ends more evenly and meets at its barrier with fewer waves: forward, one / two, in us, 8 kv heads: 1 x 1000
+// tokens 36 / 46, 1 x 3000 107 / 114, 4 x 2000 195 / 214, 7 x 1500 210 / 237.  Two halve the traffic into LDS, which
+// is worth more once the launch runs long: 1 x 12000 1340 / 1317, 1 x 16384 2669 / 2637 (dQ 3354 / 3253).
+static int soft_row_blocks(int max_t) { return max_t >= 8192 ? 2 : 1; }
+
 hipError_t launch_soft_attn_fwd(int n_seqs, const int32_t *n_tokens, int Hq, int Hkv, int d, int W,
                                 const void *q, const void *k, const void *v, const float *g, float scale,
                                 float eps, float *out, float *lse, hipStream_t st) {
@@ -674,12 +739,15 @@ hipError_t launch_soft_attn_fwd(int n_seqs, const int32_t *n_tokens, int Hq, int
     if (!soft_fill(cs, n_seqs, n_tokens, &max_t, &total)) return hipErrorInvalidValue;
     if (max_t == 0) return hipSuccess;
     SoftArgs a = {};
-    a.Hq = Hq; a.Hkv = Hkv; a.W = W;
+    a.Hq = Hq; a.Hkv = Hkv; a.W = min(W, 1 << 24);
     a.scale = scale; a.scale_log2e = scale * 1.4426950408889634f; a.eps = eps;
     a.q = (const char *)q; a.k = (const char *)k; a.v = (const char *)v; a.g = g;
     a.out = out; a.lse = lse;
-    a.nx = (max_t + kSaQ - 1) / kSaQ;
-    hipLaunchKernelGGL(soft_attn_fwd_kernel, dim3(a.nx * Hkv * n_seqs), dim3(512), 0, st, cs, a);
+    a.nx = (max_t + 32 * soft_row_blocks(max_t) - 1) / (32 * soft_row_blocks(max_t));
+    if (soft_row_blocks(max_t) == 2)
+        hipLaunchKernelGGL(soft_attn_fwd_kernel<2>, dim3(a.nx * Hkv * n_seqs), dim3(512), 0, st, cs, a);
+    else
+        hipLaunchKernelGGL(soft_attn_fwd_kernel<1>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
     return hipGetLastError();
 }
 
@@ -694,7 +762,7 @@ hipError_t launch_soft_attn_bwd(int n_seqs, const int32_t *n_tokens, int Hq, int
     if (!soft_fill(cs, n_seqs, n_tokens, &max_t, &total)) return hipErrorInvalidValue;
     if (max_t == 0) return hipSuccess;
     SoftArgs a = {};
-    a.Hq = Hq; a.Hkv = Hkv; a.W = W;
+    a.Hq = Hq; a.Hkv = Hkv; a.W = min(W, 1 << 24);
     a.scale = scale; a.scale_log2e = scale * 1.4426950408889634f; a.eps = eps;
     a.q = (const char *)q; a.k = (const char *)k; a.v = (const char *)v; a.g = g;
     a.out = const_cast<float *>(out); a.lse = const_cast<float *>(lse);
@@ -706,12 +774,29 @@ hipError_t launch_soft_attn_bwd(int n_seqs, const int32_t *n_tokens, int Hq, int
                        a.dout, out, a.rowdot);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.nx = (max_t + kSaQ - 1) / kSaQ;
-    hipLaunchKernelGGL(soft_attn_bwd_dq_kernel, dim3(a.nx * Hkv * n_seqs), dim3(512), 0, st, cs, a);
+    a.nx = (max_t + 32 * soft_row_blocks(max_t) - 1) / (32 * soft_row_blocks(max_t));
+    if (soft_row_blocks(max_t) == 2)
+        hipLaunchKernelGGL(soft_attn_bwd_dq_kernel<2>, dim3(a.nx * Hkv * n_seqs), dim3(512), 0, st, cs, a);
+    else
+        hipLaunchKernelGGL(soft_attn_bwd_dq_kernel<1>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.nx = (max_t + kSaKB - 1) / kSaKB;
-    hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel, dim3(a.nx * Hkv * n_seqs), dim3(512), 0, st, cs, a);
+    // Waves that share keys (HS): the time of a short call is that of its longest block, the one of the first keys, so
+    // blocks of a fraction of the length pay as long as compute units are idle or HS = 1 would run in one go (two
+    // blocks per compute unit); past that the single read of a tile for 128 keys is worth more.  Backward, HS = 1 / 2 / 4,
+    // in us, 8 kv heads: 1 x 1000 tokens 265 / 157 / 133, 1 x 2000 478 / 284 / 261, 1 x 3000 691 / 419 / 476,
+    // 1 x 8000 2306 / 2203 / 2688, 4 x 2000 734 / 722 / 938, 7 x 1500 792 / 825 / 1073, 1 x 12000 4374 / 4831 / 5869.
+    const int64_t n_wide = (int64_t)((max_t + 127) / 128) * Hkv * n_seqs;  // blocks of HS = 1
+    if (n_wide <= 128) {
+        a.nx = (max_t + 31) / 32;
+        hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel<4>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
+    } else if (n_wide <= 512) {
+        a.nx = (max_t + 63) / 64;
+        hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel<2>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
+    } else {
+        a.nx = (max_t + 127) / 128;
+        hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel<1>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
+    }
     return hipGetLastError();
 }
 
