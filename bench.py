@@ -592,7 +592,7 @@ def main_prefill(args, cfg, torch, wg, wl, dev):
                    "admit_us_per_chunk": admit_ms / steps * 1e3, "attend_us_per_chunk": float(durs.mean() * 1e3),
                    "prompt_tokens_per_s": B * Cn * steps / (path_ms * 1e-3)},
         "roofline": {"bound": "mfma", "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": tflops / MFMA_BF16_PEAK_TFLOPS, "traffic": None, "kernel": "attend_prefill_kernel",
+                     "frac": tflops / MFMA_BF16_PEAK_TFLOPS, "traffic": None, "kernel": "attend_prefill_tiles_kernel",
                      "algorithmic_flops": float(np.sum(flops)), "kernel_total_ms": float(durs.sum()),
                      "launches": int(steps)},
         "cpu_baseline": None,

@@ -15,7 +15,8 @@
 // query of the block sees, instead of running over the whole chunk with a mask (4096-token chunks at an
 // admission rate of a half, 0-12K tokens before them: 1095 -> 803 us per chunk of two prompts, lists included).
 //
-// One block owns 256 / G chunk positions of one (sequence, kv head) with a group of G query heads;
+// attend_prefill_kernel (every shape but the one of the paper's models): one block owns 256 / G chunk
+// positions of one (sequence, kv head) with a group of G query heads;
 // its eight waves are (query head of the group) x (row block of 32 positions), so a K/V tile staged
 // in LDS feeds all of them and two waves share each SIMD.  A tile is 8 KiB of K and of V (16 bytes of
 // each per thread): 32 keys of 128 elements, 64 keys of 64.
@@ -25,16 +26,18 @@
 // the denominator and the rescale factor are plain per-lane scalars, and the
 // probabilities leave the first product already in the operand layout of the second.
 //
-// Two forms of the weights P.  For the shape of the paper's models (128 wide, four heads a group) they
-// are rounded to bf16 once, and the denominator sums the rounded ones.  For every other shape they
-// keep 24 bits (PARTS = 3): p = hi + mid + lo, each part the upper half of an fp32 word and hi, mid
+// Two forms of the weights P.  For the shape of the paper's models (128 wide, four heads a group;
+// attend_prefill_tiles_kernel) they are rounded to bf16 once, and the denominator sums the rounded ones.  For
+// every other shape they keep 24 bits: p = hi + mid + lo, each part the upper half of an fp32 word and hi, mid
 // exact remainders, three products with the same V^T operand; V is bf16, so the products are exact and
 // the sums are fp32 as they are in plain fp32 arithmetic.  The matrix cores have the room: at 64 elements
 // the vector work per score is twice the four extra products.  Measured: a 6001-token prompt of 32 / 8 heads
 // of 64 in chunks of 2048, gate and admission included, 17.3 ms -> 0.55 ms against one wave of plain fp32
 // arithmetic per (query, head), the error against 64 bits 9.3e-7 -> 6.4e-7.
 #include <climits>
+#include <type_traits>
 
+#include "lds_tiles.h"
 #include "wgkv_dev.h"
 
 namespace wgkv {
@@ -44,9 +47,9 @@ typedef __attribute__((ext_vector_type(2))) __bf16 pf_bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
 
 // The shape of one instantiation: head_dim D, group size G.
-template <int D_, int G_, int PARTS_>
+template <int D_, int G_>
 struct PfShape {
-    static constexpr int D = D_, G = G_, PARTS = PARTS_;
+    static constexpr int D = D_, G = G_;
     static constexpr int Q = 256 / G;       // chunk positions per block (8 / G row blocks of 32)
     static constexpr int CPR = D / 8;       // 16-byte chunks per row
     static constexpr int KT = 512 / CPR;    // keys per tile: a chunk of K and of V per thread
@@ -141,15 +144,29 @@ __device__ __forceinline__ void pf_take_nonfinite(pf_bf16x8_t &v, const uint32_t
         }
 }
 
-template <int D_, int G_, int PARTS_>
+// Whether every query of the block (chunk positions q_first to q_last) sees every key of tile t: full tiles of the global
+// cache and of the picked keys, and those of the ring and the chunk that lie inside all its windows.
+__device__ __forceinline__ bool pf_no_mask(int t, int KT, int n_g, int n_plain, int t_far, int t_near, int n_far, int near,
+                                           int w_eff, int W, int q_first, int q_last) {
+    if (t < n_g) return t < n_plain;
+    if (t < t_far) {
+        const int i0 = (t - n_g) * KT;  // the oldest ring entry is w_eff positions before the chunk
+        return i0 + KT <= w_eff && q_last + w_eff - i0 < W;
+    }
+    if (t < t_near) return t - t_far < n_far / KT;
+    const int i0 = near + (t - t_near) * KT;
+    return i0 + KT - 1 <= q_first && q_last - i0 < W;
+}
+
+template <int D_, int G_>
 __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
-    using S = PfShape<D_, G_, PARTS_>;
+    using S = PfShape<D_, G_>;
     constexpr int D = S::D, G = S::G, KT = S::KT, NS = S::NS, KS = S::KS, DB = S::DB;
     __shared__ __attribute__((aligned(16))) char s_k[2][KT * S::KStride];
     __shared__ __attribute__((aligned(16))) char s_v[2][KT * S::VStride];
     __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
     __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
-    __shared__ int s_bad[2];  // PARTS 3: the masked tile in that buffer if it holds a V that is not finite
+    __shared__ int s_bad[2];  // the masked tile in that buffer if it holds a V that is not finite
 
     // Blocks are handed out in the order of their index and go to the 8 XCDs round-robin: all
     // blocks of the unit with the longest global cache come first, its latest positions (which see
@@ -286,16 +303,17 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
         *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * S::VStride + ld_dc * 16]) = r_v;
         if (ld_dc == 0) { s_lo[buf][ld_key] = r_lo; s_hi[buf][ld_key] = r_hi; }
     };
-    const int n_plain = gl / KT;  // full tiles of the global cache: no mask; nor do full tiles of picked keys need one
-    const int t_plain = t_far + n_far / KT;
-    auto no_mask = [&](int t) __attribute__((always_inline)) { return t < n_plain || (t >= t_far && t < t_plain); };
+    const int n_plain = gl / KT;  // full tiles of the global cache
+    auto no_mask = [&](int t) __attribute__((always_inline)) {
+        return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, qt * S::Q, qt * S::Q + S::Q - 1);
+    };
     // A weight of zero does not keep an inf or NaN of V out of a product, so tiles of which some query sees only a part
-    // are looked through (the three-part shapes; t: the tile that goes to the buffer).
+    // are looked through (t: the tile that goes to the buffer).
     auto look = [&](int buf, const uint4 &r_v, int t) __attribute__((always_inline)) {
-        if (S::PARTS > 1 && !no_mask(t) && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
+        if (!no_mask(t) && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
             s_bad[buf] = t;  // all writers of a tile write the same
     };
-    if (S::PARTS > 1 && threadIdx.x < 2) s_bad[threadIdx.x] = -1;
+    if (threadIdx.x < 2) s_bad[threadIdx.x] = -1;
 
     auto fetch_any = [&](int t, int far, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
         if (lean_ok && t < n_plain) fetch_lean(t, r_k, r_v, r_lo, r_hi);
@@ -305,7 +323,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     int far_next = ask_far(2);
     fetch_any(0, far0, k0r, v0r, lo0r, hi0r);
     stage(0, k0r, v0r, lo0r, hi0r);
-    if constexpr (S::PARTS > 1) __syncthreads();  // s_bad is set
+    __syncthreads();  // s_bad is set
     look(0, v0r, 0);
     if (n_tiles > 1) fetch_any(1, far1, k1r, v1r, lo1r, hi1r);
     __syncthreads();
@@ -346,16 +364,12 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
                     s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[n][ks], qv[ks], s[n], 0, 0, 0);
             }
             // V^T fragments read column-wise from the row-major V tile
-            // (with three parts of P there are no registers for all of them during the softmax: read at their products)
-            pf_bf16x8_t va[2 * NS][DB];
+            // (there are no registers for all of them during the softmax: read at their products)
+            pf_bf16x8_t va[DB];
             auto read_v = [&](int t2) __attribute__((always_inline)) {
 #pragma unroll
-                for (int db = 0; db < DB; db++) va[t2][db] = pf_get_cols<S::VStride>(s_v[buf], lane, db, 16 * t2);
+                for (int db = 0; db < DB; db++) va[db] = pf_get_cols<S::VStride>(s_v[buf], lane, db, 16 * t2);
             };
-            if constexpr (S::PARTS == 1) {
-#pragma unroll
-                for (int t2 = 0; t2 < 2 * NS; t2++) read_v(t2);
-            }
             __builtin_amdgcn_sched_barrier(0);
             // register c = 4j+i of a lane holds key 8j + 4*half + i of a score tile
             const bool plain = no_mask(t);
@@ -386,23 +400,16 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
             const float mnew = fmaxf(m, mt);
             const float msafe = mnew == -INFINITY ? 0.f : mnew;
             const float corr = __builtin_amdgcn_exp2f(m - msafe);
-            uint32_t pb[S::PARTS][8 * NS];
+            uint32_t pb[3][8 * NS];
             float ps = 0.f;
-            const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
             for (int c = 0; c < 8 * NS; c++) {
                 const float p0 = __builtin_amdgcn_exp2f(sc[2 * c] - msafe), p1 = __builtin_amdgcn_exp2f(sc[2 * c + 1] - msafe);
-                if constexpr (S::PARTS == 1) {
-                    pb[0][c] = pf_pack(p0, p1);
-                    // the denominator sums the rounded weights, the ones the second product uses
-                    ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[0][c]), ones, ps, false);
-                } else {
-                    ps += p0 + p1;
-                    const float r0 = pf_rest(p0), r1 = pf_rest(p1);
-                    pb[0][c] = pf_top(p0, p1);
-                    pb[1][c] = pf_top(r0, r1);
-                    pb[2][c] = pf_top(pf_rest(r0), pf_rest(r1));
-                }
+                ps += p0 + p1;
+                const float r0 = pf_rest(p0), r1 = pf_rest(p1);
+                pb[0][c] = pf_top(p0, p1);
+                pb[1][c] = pf_top(r0, r1);
+                pb[2][c] = pf_top(pf_rest(r0), pf_rest(r1));
             }
             l = l * corr + ps;
             if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
@@ -413,31 +420,29 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
             }
             m = mnew;
             // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys, small parts first ----
-            if constexpr (S::PARTS > 1) __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t2 = 0; t2 < 2 * NS; t2++) {
-                if constexpr (S::PARTS > 1) {
-                    read_v(t2);
-                    if (s_bad[buf] == t) {  // block-uniform
-                        // the finite values go on to the product; the queries that see the others get them here
-                        uint32_t seen[4];
+                read_v(t2);
+                if (s_bad[buf] == t) {  // block-uniform
+                    // the finite values go on to the product; the queries that see the others get them here
+                    uint32_t seen[4];
 #pragma unroll
-                        for (int c = 0; c < 4; c++) {  // pair c of the eight keys of this lane's half
-                            const int key = 16 * t2 + 8 * (c / 2) + 4 * half + 2 * (c % 2);
-                            seen[c] = (qpos >= s_lo[buf][key] && qpos <= s_hi[buf][key] ? 0x3f80u : 0u) |
-                                      (qpos >= s_lo[buf][key + 1] && qpos <= s_hi[buf][key + 1] ? 0x3f800000u : 0u);
-                        }
-#pragma unroll
-                        for (int db = 0; db < DB; db++) pf_take_nonfinite(va[t2][db], seen, o[db]);
+                    for (int c = 0; c < 4; c++) {  // pair c of the eight keys of this lane's half
+                        const int key = 16 * t2 + 8 * (c / 2) + 4 * half + 2 * (c % 2);
+                        seen[c] = (qpos >= s_lo[buf][key] && qpos <= s_hi[buf][key] ? 0x3f80u : 0u) |
+                                  (qpos >= s_lo[buf][key + 1] && qpos <= s_hi[buf][key + 1] ? 0x3f800000u : 0u);
                     }
+#pragma unroll
+                    for (int db = 0; db < DB; db++) pf_take_nonfinite(va[db], seen, o[db]);
                 }
 #pragma unroll
-                for (int part = S::PARTS - 1; part >= 0; part--) {
+                for (int part = 2; part >= 0; part--) {
                     const uint4 p4 = make_uint4(pb[part][4 * t2], pb[part][4 * t2 + 1], pb[part][4 * t2 + 2], pb[part][4 * t2 + 3]);
                     const pf_bf16x8_t pbv = __builtin_bit_cast(pf_bf16x8_t, p4);
 #pragma unroll
                     for (int db = 0; db < DB; db++)
-                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t2][db], pbv, o[db], 0, 0, 0);
+                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], pbv, o[db], 0, 0, 0);
                 }
             }
         }
@@ -472,6 +477,261 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
                     *reinterpret_cast<float4 *>(op + 32 * db + 8 * j + 4 * half) = w4;
                 }
         }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The shape of the paper's models: 128 wide, four heads a group, weights rounded to bf16
+//
+// A block is 32 chunk positions x the four heads of a group, one wave each, two blocks to a compute unit; key tiles are
+// 64 rows of K and of V, requested straight into one of two LDS buffers a tile ahead (no staging registers, one unpadded
+// copy each).  Against blocks of 64 positions with tiles of 32 keys staged through registers, which this shape had:
+// two 16K prompts in 4096-token chunks 797 -> 708 us per launch, eight of 131-1501 tokens 81 -> 71, four 128K prompts,
+// all 32 chunks, 350 -> 312 ms (808 -> 906 TFLOP/s).  Two row blocks of 32 that share a tile: 732 us, 81 us, 316 ms.
+// Bound by power like the training-time kernels: the last chunks run at 950 TFLOP/s at about three quarters of the
+// clock that short launches get.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPfTilesQ = 32;
+__global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
+    constexpr int NW = 4, Q = kPfTilesQ, KT = 64, kRows = KT / NW, G = 4, D = kSaD;
+    __shared__ __attribute__((aligned(1024))) char s_t[2][2][KT * D * 2];  // K and V
+    __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
+    __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
+
+    // order of the blocks: as in attend_prefill_kernel
+    const int unit = a.order[blockIdx.x / a.nx];
+    const int b = unit / pv.Hkv, h = unit % pv.Hkv;
+    const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
+    const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
+    if (qt * Q >= T) return;  // block-uniform
+    const int um = unit_meta(pv, cs.sid[b], a.layer, h);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int head = wave;
+    const int qn = lane & 31, half = lane >> 5;
+    const int gl = pv.global_len[um];
+    const int w_eff = min(pv.W, t0);              // ring entries that exist
+    const int i_end = min(T, qt * Q + Q);         // chunk keys this block can see: [0, i_end)
+    // tiles: global cache, ring, picked chunk keys below `near`, all chunk keys from there on
+    const int near = a.pick ? max(0, qt * Q - pv.W + 1) / KT * KT : 0;  // no window of the block reaches below
+    const int32_t *pick = a.pick ? a.pick + pick_of(pv.Hkv, b, h, base, T) : a.order;
+    const int n_far = near > 0 ? a.picked[picked_of(pv.Hkv, b, h, base, T) + near / 32] : 0;
+    const int n_g = (gl + KT - 1) / KT, n_r = (w_eff + KT - 1) / KT;
+    const int t_far = n_g + n_r, t_near = t_far + (n_far + KT - 1) / KT;  // first tile of each kind
+    const int n_tiles = t_near + (i_end - near + KT - 1) / KT;
+
+    sa_bf16x8_t qv[8];
+    const int q_first = qt * Q;
+    const int qi = min(q_first + qn, T - 1);
+    const int qpos = t0 + qi;
+    {
+        const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * D * 2;
+#pragma unroll
+        for (int ks = 0; ks < 8; ks++) qv[ks] = *reinterpret_cast<const sa_bf16x8_t *>(qp + (ks * 16 + half * 8) * 2);
+    }
+    pf_f32x16_t o[4];
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; db++)
+#pragma unroll
+        for (int c = 0; c < 16; c++) o[db][c] = 0.f;
+
+    // Page ids live in registers, one per lane, so that the address of a key row never waits for a page-table load: 64
+    // consecutive entries of the global table (reloaded every 64 pages) and the whole local table of at most 64 entries.
+    int pt_base = 0;
+    int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
+    const bool lp_in_reg = pv.nlp <= 64;
+    int lpreg = (lp_in_reg && lane < pv.nlp) ? pv.local_pt[(size_t)um * pv.nlp + lane] : 0;
+    const int slot0 = t0 > pv.W ? t0 % pv.W : 0;  // ring slot of the oldest position
+    auto ring_slot = [&](int idx) __attribute__((always_inline)) {
+        const int s = slot0 + min(idx, w_eff - 1);
+        return s >= pv.W ? s - pv.W : s;
+    };
+    // chunk positions of the wave's rows of a picked tile, one per lane (anything for another tile): asked for a tile
+    // before its rows are
+    auto ask_far = [&](int t) __attribute__((always_inline)) {
+        return pick[max(0, min((t - t_far) * KT + wave * kRows + (lane & (kRows - 1)), n_far - 1))];
+    };
+    const bool lean_ok = pv.P >= kRows;  // the wave's rows of a full tile of the global cache share a page
+    const int n_plain = gl / KT;         // full tiles of the global cache
+    auto fetch = [&](int t, int far) __attribute__((always_inline)) {
+        char *lk = &s_t[t & 1][0][wave * kRows * (D * 2)], *lv = &s_t[t & 1][1][wave * kRows * (D * 2)];
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // the lane's offsets are formed per tile: no registers to keep them
+        const int sub = ln >> 4;
+        if (t < n_g && ((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
+            pt_base = (t * KT) >> pv.logP;
+            ptreg = (pt_base + ln < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + ln] : 0;
+        }
+        if (lean_ok && t < n_plain) {
+            const int idx = t * KT + kRows * wave;
+            const int pg = __builtin_amdgcn_readlane(ptreg, (idx >> pv.logP) - pt_base);
+            const char *sb = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (D * 2);
+#pragma unroll
+            for (int i = 0; i < kRows / 4; i++) {
+                const uint32_t off = (uint32_t)((4 * i + sub) * (D * 2) + ((ln & 15) ^ sa_sw_f(wave * kRows + 4 * i + sub)) * 16);
+                sa_dma16(sb, off, lk + i * 1024);
+                sa_dma16(sb + pv.v_off, off, lv + i * 1024);
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < kRows / 4; i++) {
+            const int r = wave * kRows + 4 * i + sub;
+            const char *kp;
+            int64_t v_delta = pv.v_off;
+            if (t < n_g) {  // global cache
+                const int idc = min(t * KT + r, gl - 1);
+                const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
+                kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
+            } else if (t < t_far) {  // ring, oldest position first
+                const int slot = ring_slot((t - n_g) * KT + r);
+                const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
+                                         : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
+                kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
+            } else {  // this chunk
+                const int idc = t < t_near ? __shfl(far, 4 * i + sub) : min(near + (t - t_near) * KT + r, T - 1);
+                kp = a.k + ((size_t)(base + idc) * pv.Hkv + h) * (D * 2);
+                v_delta = a.v - a.k;
+            }
+            kp += ((ln & 15) ^ sa_sw_f(r)) * 16;
+            sa_dma16_at(kp, lk + i * 1024);
+            sa_dma16_at(kp + v_delta, lv + i * 1024);
+        }
+    };
+    auto no_mask = [&](int t) __attribute__((always_inline)) {
+        return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, q_first, q_first + Q - 1);
+    };
+    // Who sees key `lane` of a tile with a mask: positions lo to hi.  A wave of the block in turn asks for its score and,
+    // at the end of the turn, writes the two bounds.
+    auto ask_score = [&](int t) __attribute__((always_inline)) {
+        const int idx = t < t_far ? (t - n_g) * KT + lane : near + (t - t_near) * KT + lane;
+        if (t >= n_g && t < t_far) return pv.ring_g[(size_t)um * pv.W + ring_slot(idx)];
+        if (t >= t_near) return a.g[(size_t)(base + min(idx, T - 1)) * pv.Hkv + h];
+        return 0.f;
+    };
+    auto put_bounds = [&](int t, float g) __attribute__((always_inline)) {
+        int lo = INT_MAX, hi = INT_MAX;  // invisible unless shown otherwise
+        if (t < n_g) {
+            if (t * KT + lane < gl) lo = INT_MIN;
+        } else if (t < t_far) {
+            const int idx = (t - n_g) * KT + lane;
+            if (idx < w_eff) {
+                lo = t0 - w_eff + idx;
+                hi = g >= a.tau ? INT_MAX : lo + pv.W - 1;
+            }
+        } else if (t < t_near) {
+            if ((t - t_far) * KT + lane < n_far) lo = INT_MIN;
+        } else {
+            const int idx = near + (t - t_near) * KT + lane;
+            if (idx < T) {
+                lo = t0 + idx;
+                hi = g >= a.tau ? INT_MAX : lo + pv.W - 1;
+            }
+        }
+        s_lo[t & 1][lane] = lo;
+        s_hi[t & 1][lane] = hi;
+    };
+
+    asm volatile("" : "+v"(ptreg), "+v"(lpreg));  // waited for here, not behind the requests; so is the query
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qv[ks]));
+    const int o_row = sa_sw_row(qn, half), o_col = sa_sw_col(lane);
+    int far_next = ask_far(1);
+    fetch(0, ask_far(0));
+    if (wave == 0) put_bounds(0, ask_score(0));
+    sa_dma_wait_barrier<0>();
+    bool plain_next = no_mask(0);
+    for (int t = 0; t < n_tiles; t++) {
+        const int buf = t & 1;
+        const char *tk = s_t[buf][0], *tv = s_t[buf][1];
+        const int far = far_next;
+        far_next = ask_far(t + 2);
+        const bool plain = plain_next;
+        plain_next = no_mask(t + 1);
+        const bool mine = t + 1 < n_tiles && wave == (t + 1) % NW && !plain_next;
+        float g_next = 0.f;
+        if (mine) g_next = ask_score(t + 1);
+        if (t + 1 < n_tiles) fetch(t + 1, far);
+        // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
+        pf_f32x16_t s[2];
+#pragma unroll
+        for (int n = 0; n < 2; n++) {
+#pragma unroll
+            for (int c = 0; c < 16; c++) s[n][c] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ks++)
+                s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + n * kSaTileB, o_row, ks), qv[ks], s[n], 0, 0, 0);
+        }
+        // register c = 4j+i of s[n] holds key 32*n + 8j + 4*half + i
+        float mt = -INFINITY;
+        if (plain) {
+#pragma unroll
+            for (int c = 0; c < 32; c++) {
+                s[c / 16][c % 16] *= a.scale_log2e;
+                mt = fmaxf(mt, s[c / 16][c % 16]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
+                const int4 hi4 = *reinterpret_cast<const int4 *>(&s_hi[buf][8 * j + 4 * half]);
+                const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi_[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const bool vis = (qpos >= lo_[i]) && (qpos <= hi_[i]);
+                    const float x = vis ? s[j / 4][4 * (j % 4) + i] * a.scale_log2e : -INFINITY;
+                    s[j / 4][4 * (j % 4) + i] = x;
+                    mt = fmaxf(mt, x);
+                }
+            }
+        }
+        mt = fmaxf(mt, __shfl_xor(mt, 32));  // the other half of the keys of this query
+        const float mnew = fmaxf(m, mt);
+        const float msafe = mnew == -INFINITY ? 0.f : mnew;
+        const float corr = __builtin_amdgcn_exp2f(m - msafe);
+        uint32_t pb[16];
+        float ps = 0.f;
+        const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+        for (int c = 0; c < 16; c++) {
+            pb[c] = pf_pack(__builtin_amdgcn_exp2f(s[c / 8][2 * c % 16] - msafe), __builtin_amdgcn_exp2f(s[c / 8][2 * c % 16 + 1] - msafe));
+            // the denominator sums the rounded weights, the ones the second product uses
+            ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[c]), ones, ps, false);
+        }
+        l = l * corr + ps;
+        if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
+#pragma unroll
+            for (int db = 0; db < 4; db++)
+#pragma unroll
+                for (int c = 0; c < 16; c++) o[db][c] *= corr;
+        }
+        m = mnew;
+        // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys ----
+#pragma unroll
+        for (int t2 = 0; t2 < 4; t2++) {
+            const uint4 p4 = make_uint4(pb[4 * t2], pb[4 * t2 + 1], pb[4 * t2 + 2], pb[4 * t2 + 3]);
+#pragma unroll
+            for (int db = 0; db < 4; db++)
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_cols(tv, o_col, db, t2), __builtin_bit_cast(sa_bf16x8_t, p4), o[db], 0, 0, 0);
+        }
+        if (mine) put_bounds(t + 1, g_next);
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
+    }
+
+    // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
+    const int i = q_first + qn;
+    const float lt = l + __shfl_xor(l, 32);
+    if (i < T) {
+        const float inv = 1.0f / lt;
+        float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * D;
+#pragma unroll
+        for (int db = 0; db < 4; db++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const float4 w4 = make_float4(o[db][4 * j] * inv, o[db][4 * j + 1] * inv,
+                                              o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv);
+                *reinterpret_cast<float4 *>(op + 32 * db + 8 * j + 4 * half) = w4;
+            }
     }
 }
 
@@ -527,11 +787,11 @@ size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q) {
     return kPfOrderBytes + sizeof(int32_t) * (size_t)pv.Hkv * (size_t)(total_q + total_q / 32 + n_seqs);
 }
 
-template <int D, int G, int PARTS>
+template <int D, int G>
 static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t, hipStream_t st) {
-    using S = PfShape<D, G, PARTS>;
+    using S = PfShape<D, G>;
     a.nx = (max_t + S::Q - 1) / S::Q;
-    hipLaunchKernelGGL((attend_prefill_kernel<D, G, PARTS>), dim3(a.nx * pv.Hkv * cs.n), dim3(512), 0, st, pv, cs, a);
+    hipLaunchKernelGGL((attend_prefill_kernel<D, G>), dim3(a.nx * pv.Hkv * cs.n), dim3(512), 0, st, pv, cs, a);
     return hipGetLastError();
 }
 
@@ -579,18 +839,21 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     if (e != hipSuccess) return e;
     if (pv.d == 128) {
         switch (pv.G) {
-            case 1: return launch_shape<128, 1, 3>(pv, cs, a, max_t, st);
-            case 2: return launch_shape<128, 2, 3>(pv, cs, a, max_t, st);
-            case 4: return launch_shape<128, 4, 1>(pv, cs, a, max_t, st);
-            case 8: return launch_shape<128, 8, 3>(pv, cs, a, max_t, st);
+            case 1: return launch_shape<128, 1>(pv, cs, a, max_t, st);
+            case 2: return launch_shape<128, 2>(pv, cs, a, max_t, st);
+            case 4:
+                a.nx = (max_t + kPfTilesQ - 1) / kPfTilesQ;
+                hipLaunchKernelGGL(attend_prefill_tiles_kernel, dim3(a.nx * pv.Hkv * cs.n), dim3(256), 0, st, pv, cs, a);
+                return hipGetLastError();
+            case 8: return launch_shape<128, 8>(pv, cs, a, max_t, st);
             default: break;
         }
     } else if (pv.d == 64) {
         switch (pv.G) {
-            case 1: return launch_shape<64, 1, 3>(pv, cs, a, max_t, st);
-            case 2: return launch_shape<64, 2, 3>(pv, cs, a, max_t, st);
-            case 4: return launch_shape<64, 4, 3>(pv, cs, a, max_t, st);
-            case 8: return launch_shape<64, 8, 3>(pv, cs, a, max_t, st);
+            case 1: return launch_shape<64, 1>(pv, cs, a, max_t, st);
+            case 2: return launch_shape<64, 2>(pv, cs, a, max_t, st);
+            case 4: return launch_shape<64, 4>(pv, cs, a, max_t, st);
+            case 8: return launch_shape<64, 8>(pv, cs, a, max_t, st);
             default: break;
         }
     }

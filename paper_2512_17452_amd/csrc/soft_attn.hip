@@ -27,18 +27,15 @@
 #include <climits>
 #include <type_traits>
 
+#include "lds_tiles.h"
 #include "wgkv_dev.h"
 
 namespace wgkv {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 sa_bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 sa_bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float sa_f32x16_t;
 
-constexpr int kSaD = 128;       // head_dim
 constexpr int kSaG = 4;         // query heads per kv head
-constexpr int kSaT = 32;        // positions per streamed tile
-constexpr int kSaTileB = kSaT * kSaD * 2;
 
 struct SoftSeqs {
     int32_t n;
@@ -71,59 +68,6 @@ __device__ __forceinline__ uint32_t sa_pack(float lo, float hi) {
 __device__ __forceinline__ void sa_bias(float gj, float eps, float &b_in, float &b_out) {
     b_in = __log2f(fmaxf(1.0f, gj) + eps);
     b_out = __log2f(fmaxf(0.0f, gj) + eps);
-}
-
-typedef short sa_s16x4_t __attribute__((ext_vector_type(4)));
-
-// ---- tiles of 32 rows of 256 bytes that come straight from memory into LDS (no registers, no staging stores) ----
-// The rows lie unpadded; 16-byte chunk c of row r sits at chunk c ^ f(r), which the request's lane picks on the memory
-// side.  f takes the row's low two bits to the chunk's high ones and the next two to its low ones: sixteen consecutive
-// rows put one column on sixteen different chunks (reads of whole rows), and four consecutive rows put a 64-byte piece
-// on four different quarters of the banks (reads of columns), so both kinds of read are free of bank conflicts.
-__device__ __forceinline__ int sa_sw_f(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-__device__ __forceinline__ int sa_sw_row(int qn, int half) { return qn * (kSaD * 2) + (half ^ sa_sw_f(qn)) * 16; }
-// row operand of a product over d: row qn of a tile, d slice ks
-__device__ __forceinline__ sa_bf16x8_t sa_sw_get_row(const char *tile, int o_row, int ks) {
-    return *reinterpret_cast<const sa_bf16x8_t *>(tile + (o_row ^ (ks * 32)));
-}
-// Column operand of a product that contracts over the rows of a tile (rows are positions, columns d): the output row of
-// this lane is d = db*32 + qn, its 8 contraction slots are tile rows 16*t2 + 4*half + {0..3} and 16*t2 + 8 + 4*half
-// + {0..3}, which is where the accumulator layout of the first product leaves this lane's values.
-// ds_read_b64_tr_b16 transposes inside groups of 16 lanes: lane i of a group receives element i%4 of the 8 bytes
-// addressed by lanes i/4, 4 + i/4, 8 + i/4 and 12 + i/4.  So lane s of a group addresses (row s/4 of the four, columns
-// 4*(s%4)..+3 of the group's 16) and ends up with the four rows at its own column.
-__device__ __forceinline__ int sa_sw_col(int lane) {
-    const int half = lane >> 5, a = (lane & 15) >> 2;
-    const int c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    return (4 * half + a) * (kSaD * 2) + ((c ^ half) | (a << 2)) * 16 + 8 * (lane & 1);
-}
-__device__ __forceinline__ sa_bf16x8_t sa_sw_get_cols(const char *tile, int o_col, int db, int t2) {
-    typedef __attribute__((address_space(3))) sa_s16x4_t *lds_ptr_t;
-    const char *p = tile + t2 * 16 * (kSaD * 2);
-    const sa_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + (o_col ^ (db * 64))));
-    const sa_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * (kSaD * 2) + (o_col ^ (db * 64) ^ 32)));
-    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-    return __builtin_bit_cast(sa_bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
-}
-// 16 (4) bytes per lane from memory at base + off to LDS at dst + 16 (4) * lane; base and dst are wave-uniform.  In
-// assembly, as the compiler would put a wait for every outstanding request in front of the next LDS read; a reader is
-// behind sa_dma_wait_barrier instead.  The request has no result register, and M0 is free for it (LDS
-// instructions do not read it on this machine).
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void sa_dma16(const void *base, uint32_t off, const void *dst) {
-    const uint32_t m = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(off), "s"(base) : "memory", "m0");
-}
-__device__ __forceinline__ void sa_dma4(const void *base, uint32_t off, const void *dst) {
-    const uint32_t m = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(m), "v"(off), "s"(base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-// all but the N latest requests of this wave have arrived, its LDS reads have returned, and the block has met
-template <int N>
-__device__ __forceinline__ void sa_dma_wait_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 // Key tiles of the forward and the dQ kernel: 64 rows of K and of V in two LDS buffers, requested one tile ahead.  The
