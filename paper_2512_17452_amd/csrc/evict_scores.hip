@@ -10,6 +10,7 @@
 //   weight pass : block = (unit, 64 keys), all query rows   -> S_raw of its keys
 //   pool pass   : S from S_raw
 // Every sum runs in a fixed order, so the scores (and what gets evicted) repeat run to run.
+#include "lds_tiles.h"
 #include "wgkv_dev.h"
 
 namespace wgkv {
@@ -177,111 +178,141 @@ __global__ __launch_bounds__(256) void evict_weights_kernel(View pv, CallSeqs cs
 
 // ---------------------------------------------------------------------------------------------
 // Matrix-core versions of the two sweeps for the shape of the paper's models (bf16, head_dim 128,
-// group of 4, n_obs a multiple of 8).  Scores are formed transposed, S^T = K Q^T with
-// v_mfma_f32_32x32x16_bf16: rows = 32 keys of a tile staged in LDS, columns = 32 query rows of a
-// wave, ordered (observation row, head) with the four heads of a row adjacent.  A lane then owns
-// one query row: its maximum, denominator and normalisation are per-lane scalars, the maximum
-// over the group is a maximum over the four lanes of a quad, and the sum over the window is a sum
-// over quads and waves.
-typedef __attribute__((ext_vector_type(8))) __bf16 es_bf16x8_t;
+// group of 4, n_obs a multiple of 8), v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  A wave keeps its columns as
+// operands in registers and all waves of a block read the streamed rows from LDS tiles that are requested a tile ahead.
+// Both are bound by the vector unit (a maximum, a multiply-add, a quarter-rate exponential and a sum per score take 26
+// of its clocks where the products take 16), which wants other waves' products and reads beside it.
 typedef __attribute__((ext_vector_type(16))) float es_f32x16_t;
-constexpr int kEmD = 128, kEmKT = 32, kEmRow = 272;  // bytes per key row in LDS: 256 + 16 of padding
+constexpr int kEmD = 128;
 
-// the eight operand slices of a lane's query row (column `col` of the unit), zeros past the end
-__device__ __forceinline__ void em_load_q(const View &pv, const EvictScoreArgs &a, int b, int h, int col, int n_cols,
-                                          int half, es_bf16x8_t (&qv)[8]) {
-    const int cc = min(col, n_cols - 1), i = cc >> 2, g = cc & 3;
-    const char *qp = a.q + (((size_t)b * a.n_obs + i) * pv.Hq + (size_t)h * 4 + g) * (kEmD * 2);
-#pragma unroll
-    for (int ks = 0; ks < 8; ks++) qv[ks] = *reinterpret_cast<const es_bf16x8_t *>(qp + (ks * 16 + half * 8) * 2);
+// byte offset of query row `col` (observation row col / 4, head col % 4 of the group) of a unit
+__device__ __forceinline__ size_t em_q_off(const View &pv, const EvictScoreArgs &a, int b, int h, int col) {
+    return (((size_t)b * a.n_obs + (col >> 2)) * pv.Hq + (size_t)h * 4 + (col & 3)) * (kEmD * 2);
 }
 
-__global__ __launch_bounds__(512) void evict_stats_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    __shared__ __attribute__((aligned(16))) char s_k[2][kEmKT * kEmRow];
+// Statistics, S^T = K Q^T: rows = 32 keys, columns = 32 query rows of a wave, so a lane owns one query row and its
+// maximum and denominator are per-lane scalars.  Four waves of a block hold 128 query rows, four more hold the
+// same ones and take the other 64 keys of a tile of 128: four waves to a SIMD with two blocks on a compute unit.
+// 64 heads of 4.5K entries, 1024 rows: 132 -> 105 us against 256 rows a block, tiles of 32 keys through registers
+// and a scaled score per product; 8 heads of 2.2K 57 -> 28.
+constexpr int kEmStatRows = 128, kEmStatKeys = 128;
+__global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
+    __shared__ __attribute__((aligned(1024))) char s_k[2][kEmStatKeys * kEmD * 2];
+    __shared__ float s_ml[4][2][64];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int N = pv.global_len[um], n_cols = a.n_obs * 4;
     if (N == 0) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 31, half = lane >> 5;
-    const int col = (blockIdx.x * 8 + wave) * 32 + n;
-    es_bf16x8_t qv[8];
-    em_load_q(pv, a, b, h, col, n_cols, half, qv);
-    // staging: thread -> (key of the tile, 16-byte chunk); page ids in a per-lane register
-    const int ld_key = threadIdx.x >> 4, ld_c = threadIdx.x & 15;
-    int pt_base = 0;
-    int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
-    uint4 kreg;
-    auto fetch = [&](int t) __attribute__((always_inline)) {
-        if (((t * kEmKT + kEmKT - 1) >> pv.logP) >= pt_base + 64) {
-            pt_base = (t * kEmKT) >> pv.logP;
-            ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
-        }
-        const int idx = min(t * kEmKT + ld_key, N - 1);
-        const int pg = __shfl(ptreg, (idx >> pv.logP) - pt_base);
-        kreg = *reinterpret_cast<const uint4 *>(page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (kEmD * 2) + ld_c * 16);
-    };
-    const int n_tiles = (N + kEmKT - 1) / kEmKT;
-    fetch(0);
-    *reinterpret_cast<uint4 *>(&s_k[0][ld_key * kEmRow + ld_c * 16]) = kreg;
-    __syncthreads();
-    float m = -INFINITY, l = 0.f;
-    for (int t = 0; t < n_tiles; t++) {
-        const int buf = t & 1;
-        if (t + 1 < n_tiles) fetch(t + 1);
-        es_f32x16_t s;
-#pragma unroll
-        for (int c = 0; c < 16; c++) s[c] = 0.f;
+    const int n = lane & 31, half = lane >> 5, part = wave >> 2;
+    const int col = blockIdx.x * kEmStatRows + (wave & 3) * 32 + n;
+    sa_bf16x8_t qv[8];
+    // the maximum is taken of the products themselves: a negative scale turns the query's sign instead
+    // (and one of zero stays a hair above it: the initial maximum of -inf times it is -inf, not a NaN)
+    const float c = fmaxf(fabsf(a.scale_log2e), 1e-37f);
+    const uint32_t sign = a.scale_log2e < 0.f ? 0x80008000u : 0u;
+    {
+        const char *qp = a.q + em_q_off(pv, a, b, h, min(col, n_cols - 1));
 #pragma unroll
         for (int ks = 0; ks < 8; ks++) {
-            const es_bf16x8_t ka = *reinterpret_cast<const es_bf16x8_t *>(&s_k[buf][n * kEmRow + (ks * 16 + half * 8) * 2]);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qv[ks], s, 0, 0, 0);
+            uint4 w = *reinterpret_cast<const uint4 *>(qp + (ks * 16 + half * 8) * 2);
+            w.x ^= sign; w.y ^= sign; w.z ^= sign; w.w ^= sign;
+            qv[ks] = __builtin_bit_cast(sa_bf16x8_t, w);
         }
-        // register 4j+i of a lane holds key 8j + 4*half + i of the tile
-        float x[16], mt = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < 16; c++) x[c] = s[c] * a.scale_log2e;
-        if (t == n_tiles - 1) {  // block-uniform: only the last tile can reach past the end of the cache
-            const int k0 = t * kEmKT + 4 * half;
-#pragma unroll
-            for (int c = 0; c < 16; c++) x[c] = (k0 + 8 * (c >> 2) + (c & 3) < N) ? x[c] : -INFINITY;
-        }
-#pragma unroll
-        for (int c = 0; c < 16; c++) mt = fmaxf(mt, x[c]);
-        const float mn = fmaxf(m, mt);
-        const float ms = mn == -INFINITY ? 0.f : mn;  // this half may hold no valid key of the last tile
-        // the hardware exponential: one instruction, a relative error of about an ulp, 0 for -inf
-        float ps = 0.f;
-#pragma unroll
-        for (int c = 0; c < 16; c++) ps += __builtin_amdgcn_exp2f(x[c] - ms);
-        l = l * __builtin_amdgcn_exp2f(m - ms) + ps;
-        m = mn;
-        if (t + 1 < n_tiles) *reinterpret_cast<uint4 *>(&s_k[buf ^ 1][ld_key * kEmRow + ld_c * 16]) = kreg;
-        __syncthreads();
     }
-    // the two halves of the wave hold different keys of the same query row
-    const float m2 = __shfl_xor(m, 32), l2 = __shfl_xor(l, 32);
-    const float M = fmaxf(m, m2);  // finite: N > 0
-    const float Lsum = l * exp2f(m - M) + l2 * exp2f(m2 - M);
+    int pt_base = 0;  // 64 page ids from here on, one per lane
+    int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        // a wave brings 16 rows, four per request; rows past the last key of the cache repeat it or are left as they are
+        const int r0 = t * kEmStatKeys + wave * 16;
+        if (r0 >= N) return;
+        if (((r0 + 15) >> pv.logP) >= pt_base + 64) {
+            pt_base = r0 >> pv.logP;
+            ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int r = 4 * i + (lane >> 4), idx = min(r0 + r, N - 1);
+            const int pg = __shfl(ptreg, (idx >> pv.logP) - pt_base);
+            const char *kp = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (kEmD * 2) + ((lane & 15) ^ sa_sw_f(r)) * 16;
+            sa_dma16_at(kp, &s_k[t & 1][(wave * 16 + 4 * i) * (kEmD * 2)]);
+        }
+    };
+    const int n_tiles = (N + kEmStatKeys - 1) / kEmStatKeys;
+    const int o_row = sa_sw_row(n, half);
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qv[ks]));  // waited for here, not in the loop
+    fetch(0);
+    sa_dma_wait_barrier<0>();
+    float m = -INFINITY, l = 0.f;  // m in units of the products
+    for (int t = 0; t < n_tiles; t++) {
+        if (t + 1 < n_tiles) fetch(t + 1);
+        const char *tk = s_k[t & 1] + part * (64 * kEmD * 2);
+        const int k0 = t * kEmStatKeys + part * 64;
+        if (k0 < N) {  // wave-uniform
+            es_f32x16_t s[2];
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+#pragma unroll
+                for (int i = 0; i < 16; i++) s[j][i] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ks++)
+                    s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + j * kSaTileB, o_row, ks), qv[ks], s[j], 0, 0, 0);
+            }
+            // register i of s[j] holds key 32*j + 8*(i/4) + 4*half + i%4 of the tile
+            if (k0 + 64 > N) {  // only the last tile can reach past the end of the cache
+#pragma unroll
+                for (int i = 0; i < 32; i++)
+                    s[i >> 4][i & 15] = (k0 + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * half + (i & 3) < N) ? s[i >> 4][i & 15] : -INFINITY;
+            }
+            float mt = m;
+#pragma unroll
+            for (int i = 0; i < 32; i++) mt = fmaxf(mt, s[i >> 4][i & 15]);
+            const float ms = mt == -INFINITY ? 0.f : mt;  // this half may hold no valid key of the last tile
+            // the hardware exponential: one instruction, a relative error of about an ulp, 0 for -inf
+            const float off = -ms * c;
+            float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                p0 += __builtin_amdgcn_exp2f(fmaf(s[0][i], c, off));
+                p1 += __builtin_amdgcn_exp2f(fmaf(s[1][i], c, off));
+            }
+            l = l * __builtin_amdgcn_exp2f(fmaf(m, c, off)) + (p0 + p1);
+            m = mt;
+        }
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
+    }
+    // the halves of a wave and the two waves of the same query rows hold different keys
+    auto join = [&](float m2, float l2) __attribute__((always_inline)) {
+        const float M = fmaxf(m, m2), off = M == -INFINITY ? 0.f : -M * c;
+        l = l * exp2f(fmaf(m, c, off)) + l2 * exp2f(fmaf(m2, c, off));
+        m = M;
+    };
+    join(__shfl_xor(m, 32), __shfl_xor(l, 32));
+    if (part == 1) { s_ml[wave & 3][0][lane] = m; s_ml[wave & 3][1][lane] = l; }
+    __syncthreads();
+    if (part == 1) return;
+    join(s_ml[wave][0][lane], s_ml[wave][1][lane]);  // m is finite: N > 0
     // per unit: first n_cols values M + log2(L), what the weight sweep subtracts in the exponent
     // (exp2(x - M) / L = exp2(x - (M + log2 L))), then the n_cols denominators
     if (half == 0 && col < n_cols) {
-        a.stats[(size_t)u * n_cols * 2 + col] = M + log2f(Lsum);
-        a.stats[(size_t)u * n_cols * 2 + n_cols + col] = Lsum;
+        a.stats[(size_t)u * n_cols * 2 + col] = m * c + log2f(l);
+        a.stats[(size_t)u * n_cols * 2 + n_cols + col] = l;
     }
 }
 
-constexpr int kEmKeys = 128;  // keys per block of the weight sweep (4 tiles)
-
-// The weight sweep forms S = Q K^T, the other way round: rows = 32 query rows of a turn, columns = 32 keys.  A lane
+// Weights, S = Q K^T, the other way round: rows = 32 query rows of a streamed tile of 64, columns = 32 keys.  A lane
 // then owns one key, and its 16 registers are four observation rows x the four heads of the group: the maximum
 // over the group is a maximum over four registers of the lane (no cross-lane step per weight), the sum over
-// the window a sum inside the lane, then over the two halves of the wave and over the waves, in a fixed order.
-// A block holds 128 keys as matrix operands in registers for all its turns (4 products per query operand
-// loaded); the four waves take the turns of 32 query rows in turn.  n_cols is a multiple of 32 (n_obs of 8).
-__global__ __launch_bounds__(256, 2) void evict_weights_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    __shared__ __attribute__((aligned(16))) char s_k[kEmKeys * kEmRow];
-    __shared__ float s_acc[4][kEmKeys];
+// the window a sum inside the lane, then over the two halves of the wave, then over the TS waves that share keys,
+// in a fixed order.  64 heads of 4.5K entries, 1024 rows: 125 -> 93 us against 128 keys a wave with its query rows
+// loaded by every wave for itself.  A wave holds 64 keys, a block 256 / TS; n_cols is a multiple of 32 (n_obs of 8).
+template <int TS>
+__global__ __launch_bounds__(256, TS == 4 ? 2 : 4) void evict_weights_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
+    constexpr int kEmKeys = 256 / TS, kEmTurn = TS == 4 ? 128 : 64, kRows = kEmTurn / 4;
+    __shared__ __attribute__((aligned(1024))) char s_q[2][kEmTurn * kEmD * 2];
+    __shared__ __attribute__((aligned(16))) float s_off[2][kEmTurn];
+    __shared__ float s_acc[4][64];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int N = pv.global_len[um], n_cols = a.n_obs * 4;
@@ -290,90 +321,88 @@ __global__ __launch_bounds__(256, 2) void evict_weights_mfma_kernel(View pv, Cal
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
     const float *off_u = a.stats + (size_t)u * n_cols * 2;
-    // the first turn's query rows, on their way while the keys are staged
-    es_bf16x8_t qv[8];
-    em_load_q(pv, a, b, h, wave * 32 + n, n_cols, half, qv);
-    // the block's keys into LDS, zero rows past the end of the cache: eight 16-byte pieces per thread, their page
-    // ids requested together and then the pieces together (keys past the end read the last key: no branch around a load)
+    // a wave brings a quarter of a tile's query rows, four (the heads of an observation row: 1 KiB) per request; rows past the
+    // last one are never multiplied
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // the lane's offsets are formed per tile: no registers to keep them
+#pragma unroll
+        for (int i = 0; i < kRows / 4; i++) {
+            const int r = wave * kRows + 4 * i, rl = r + (ln >> 4);
+            sa_dma16(a.q + em_q_off(pv, a, b, h, min(t * kEmTurn + r, n_cols - 4)),
+                     (uint32_t)((ln >> 4) * (kEmD * 2) + ((ln & 15) ^ sa_sw_f(rl)) * 16), &s_q[t & 1][r * (kEmD * 2)]);
+        }
+        if (wave == (t & 3))
+#pragma unroll
+            for (int i = 0; i < kEmTurn; i += 64)
+                sa_dma4(off_u, (uint32_t)min(t * kEmTurn + i + ln, n_cols - 1) * 4u, &s_off[t & 1][i]);
+    };
+    const int key_w = key0 + wave / TS * 64;
+    sa_bf16x8_t kreg[2][8];
     {
-        static_assert(kEmKeys * 16 == 8 * 256, "eight pieces per thread");
-        int pg[8];
-        uint4 v[8];
+        int pg[2];
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const int key = min(key0 + ((int)threadIdx.x >> 4) + 16 * j, N - 1);
-            pg[j] = pv.global_pt[(size_t)um * pv.maxgp + (key >> pv.logP)];
-        }
+        for (int kt = 0; kt < 2; kt++) pg[kt] = pv.global_pt[(size_t)um * pv.maxgp + (min(key_w + kt * 32 + n, N - 1) >> pv.logP)];
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const int key = min(key0 + ((int)threadIdx.x >> 4) + 16 * j, N - 1);
-            v[j] = *reinterpret_cast<const uint4 *>(page_ptr(pv, pg[j]) + (size_t)(key & (pv.P - 1)) * (kEmD * 2) +
-                                                    (threadIdx.x & 15) * 16);
-        }
+        for (int kt = 0; kt < 2; kt++) {
+            const char *kp = page_ptr(pv, pg[kt]) + (size_t)(min(key_w + kt * 32 + n, N - 1) & (pv.P - 1)) * (kEmD * 2);
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const int kl = ((int)threadIdx.x >> 4) + 16 * j;
-            if (key0 + kl >= N) v[j] = make_uint4(0u, 0u, 0u, 0u);
-            *reinterpret_cast<uint4 *>(&s_k[kl * kEmRow + (threadIdx.x & 15) * 16]) = v[j];
+            for (int ks = 0; ks < 8; ks++) kreg[kt][ks] = *reinterpret_cast<const sa_bf16x8_t *>(kp + (ks * 16 + half * 8) * 2);
         }
     }
-    __syncthreads();
-    es_bf16x8_t kreg[4][8];
 #pragma unroll
-    for (int kt = 0; kt < 4; kt++)
+    for (int kt = 0; kt < 2; kt++)
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++)
-            kreg[kt][ks] = *reinterpret_cast<const es_bf16x8_t *>(&s_k[(kt * 32 + n) * kEmRow + (ks * 16 + half * 8) * 2]);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const int n_turns = n_cols >> 5;
-    for (int qt = wave; qt < n_turns; qt += 4) {  // wave-uniform
-        // the exponent offsets of the turn's rows arrive while its products run
-        float4 off4[4];
+        for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(kreg[kt][ks]));  // waited for here, not in the loop
+    const int o_row = sa_sw_row(n, half);
+    const int n_turns = (n_cols + kEmTurn - 1) / kEmTurn;
+    float acc[2] = {0.f, 0.f};
+    fetch(0);
+    sa_dma_wait_barrier<0>();
+    for (int t = 0; t < n_turns; t++) {
+        if (t + 1 < n_turns) fetch(t + 1);
 #pragma unroll
-        for (int j = 0; j < 4; j++) off4[j] = *reinterpret_cast<const float4 *>(off_u + qt * 32 + 8 * j + 4 * half);
-        // register 4j+i of a product: query row 8j + 4*half + i of the turn = observation row 2j + half, head i
-        auto weigh = [&](const es_f32x16_t &sc, float &sum) __attribute__((always_inline)) {
+        for (int i = 0; i < kEmTurn / 32 / TS; i++) {
+            const int sub = i * TS + wave % TS;
+            if (t * kEmTurn + 32 * sub >= n_cols) break;  // uniform
+            const char *tq = s_q[t & 1] + sub * kSaTileB;
+            es_f32x16_t s[2];
+#pragma unroll
+            for (int c = 0; c < 16; c++) { s[0][c] = 0.f; s[1][c] = 0.f; }
+#pragma unroll
+            for (int ks = 0; ks < 8; ks++) {
+                const sa_bf16x8_t f = sa_sw_get_row(tq, o_row, ks);
+                s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kreg[0][ks], s[0], 0, 0, 0);
+                s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kreg[1][ks], s[1], 0, 0, 0);
+            }
+            // register 4j+i of a product: query row 8j + 4*half + i of the rows = observation row 2j + half, head i
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[4 * j], a.scale_log2e, -off4[j].x));
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[4 * j + 1], a.scale_log2e, -off4[j].y));
-                const float p2 = __builtin_amdgcn_exp2f(fmaf(sc[4 * j + 2], a.scale_log2e, -off4[j].z));
-                const float p3 = __builtin_amdgcn_exp2f(fmaf(sc[4 * j + 3], a.scale_log2e, -off4[j].w));
-                sum += fmaxf(fmaxf(p0, p1), fmaxf(p2, p3));
+                const float4 off = *reinterpret_cast<const float4 *>(&s_off[t & 1][32 * sub + 8 * j + 4 * half]);
+#pragma unroll
+                for (int kt = 0; kt < 2; kt++) {
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kt][4 * j], a.scale_log2e, -off.x));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kt][4 * j + 1], a.scale_log2e, -off.y));
+                    const float p2 = __builtin_amdgcn_exp2f(fmaf(s[kt][4 * j + 2], a.scale_log2e, -off.z));
+                    const float p3 = __builtin_amdgcn_exp2f(fmaf(s[kt][4 * j + 3], a.scale_log2e, -off.w));
+                    acc[kt] += fmaxf(fmaxf(p0, p1), fmaxf(p2, p3));
+                }
             }
-        };
-        es_f32x16_t s0, s1;
-#pragma unroll
-        for (int c = 0; c < 16; c++) { s0[c] = 0.f; s1[c] = 0.f; }
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv[ks], kreg[0][ks], s0, 0, 0, 0);
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv[ks], kreg[1][ks], s1, 0, 0, 0);
-        weigh(s0, acc[0]);
-        es_f32x16_t s2, s3;
-#pragma unroll
-        for (int c = 0; c < 16; c++) { s2[c] = 0.f; s3[c] = 0.f; }
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) s2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv[ks], kreg[2][ks], s2, 0, 0, 0);
-        weigh(s1, acc[1]);
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) s3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv[ks], kreg[3][ks], s3, 0, 0, 0);
-        // the turn's products are issued: the next turn's query rows are requested into the same registers
-        // and arrive while the last weights of this turn are formed
-        if (qt + 4 < n_turns) em_load_q(pv, a, b, h, (qt + 4) * 32 + n, n_cols, half, qv);
-        weigh(s2, acc[2]);
-        weigh(s3, acc[3]);
+        }
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
     }
-    // the two halves of a wave hold different observation rows of the same key; then the waves
+    // the two halves of a wave hold different observation rows of the same key
 #pragma unroll
-    for (int kt = 0; kt < 4; kt++) {
-        const float v = acc[kt] + __shfl_xor(acc[kt], 32);
-        if (half == 0) s_acc[wave][kt * 32 + n] = v;
+    for (int kt = 0; kt < 2; kt++) acc[kt] += __shfl_xor(acc[kt], 32);
+    float v = half ? acc[1] : acc[0];  // of key key_w + lane
+    if constexpr (TS > 1) {
+        s_acc[wave][lane] = v;
+        __syncthreads();
+        if (wave % TS != 0) return;
+#pragma unroll
+        for (int w = 1; w < TS; w++) v += s_acc[wave + w][lane];
     }
-    __syncthreads();
-    if (threadIdx.x < kEmKeys && key0 + threadIdx.x < N && key0 + threadIdx.x < a.stride)  // never past the caller's row
-        a.raw[(size_t)u * a.stride + key0 + threadIdx.x] =
-            ((s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x]) + s_acc[2][threadIdx.x]) + s_acc[3][threadIdx.x];
+    if (key_w + lane < N && key_w + lane < a.stride) a.raw[(size_t)u * a.stride + key_w + lane] = v;  // never past the caller's row
 }
 
 __global__ __launch_bounds__(256) void evict_pool_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
@@ -413,10 +442,18 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
     const dim3 g_keys((unsigned)((max_len + kEsTile - 1) / kEsTile), n_units);
     const dim3 g_pool((unsigned)((max_len + 255) / 256), n_units);
     if (pv.dtype == WGKV_BF16 && pv.d == kEmD && pv.G == 4 && n_obs % 8 == 0) {
-        const dim3 g_stats_m((n_rows + 255) / 256, n_units);
-        const dim3 g_keys_m((unsigned)((max_len + kEmKeys - 1) / kEmKeys), n_units);
+        const dim3 g_stats_m((n_rows + kEmStatRows - 1) / kEmStatRows, n_units);
         hipLaunchKernelGGL(evict_stats_mfma_kernel, g_stats_m, dim3(512), 0, st, pv, cs, a);
-        hipLaunchKernelGGL(evict_weights_mfma_kernel, g_keys_m, dim3(256), 0, st, pv, cs, a);
+        // A wave that walks the whole window alone takes 25 us for 256 observation rows, however few keys there are: waves
+        // share keys as long as compute units are idle.  TS = 1 / 2 / 4, in us, 8 kv heads, 256 rows: 1 sequence of 2250
+        // entries a head 26 / - / 17, 2 of 2250 27 / 24 / 28, 2 of 4500 39 / - / 43, 4 of 3000 40 / - / 56.
+        const int64_t n_blocks = (int64_t)((max_len + 255) / 256) * n_units;  // of TS = 1
+        if (n_blocks <= 96)
+            hipLaunchKernelGGL(evict_weights_mfma_kernel<4>, dim3((unsigned)((max_len + 63) / 64), n_units), dim3(256), 0, st, pv, cs, a);
+        else if (n_blocks <= 256)
+            hipLaunchKernelGGL(evict_weights_mfma_kernel<2>, dim3((unsigned)((max_len + 127) / 128), n_units), dim3(256), 0, st, pv, cs, a);
+        else
+            hipLaunchKernelGGL(evict_weights_mfma_kernel<1>, dim3((unsigned)((max_len + 255) / 256), n_units), dim3(256), 0, st, pv, cs, a);
     } else if (pv.dtype == WGKV_F32) {
         hipLaunchKernelGGL(evict_stats_kernel<WGKV_F32>, g_stats, dim3(256), 0, st, pv, cs, a);
         hipLaunchKernelGGL(evict_weights_kernel<WGKV_F32>, g_keys, dim3(256), 0, st, pv, cs, a);
