@@ -107,9 +107,10 @@ __device__ __forceinline__ uint32_t pf_top(float lo, float hi) {
 }
 __device__ __forceinline__ float pf_rest(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 
-// A pair of bf16 holds no inf and no NaN.
-__device__ __forceinline__ bool pf_finite(uint32_t x) {
-    return (x & 0x7f80u) != 0x7f80u && (x & 0x7f800000u) != 0x7f800000u;
+// Eight bf16 hold an inf or a NaN: an exponent of ones carries into the bit above it.
+__device__ __forceinline__ bool pf_nonfinite(const uint4 &x) {
+    constexpr uint32_t kExp = 0x7f807f80u, kOne = 0x00800080u;
+    return ((((x.x & kExp) + kOne) | ((x.y & kExp) + kOne) | ((x.z & kExp) + kOne) | ((x.w & kExp) + kOne)) & 0x80008000u) != 0u;
 }
 // Takes the infinities and NaNs out of an operand of V^T and gives them to the columns of o that see their keys (seen:
 // bf16 ones and zeros in the operand layout of P^T): one product of codes counts +inf, -inf and NaN (at most 16 of
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     __shared__ __attribute__((aligned(16))) char s_v[2][KT * S::VStride];
     __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
     __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
-    __shared__ int s_bad[2];  // the masked tile in that buffer if it holds a V that is not finite
+    __shared__ int s_bad[2];  // the tile in that buffer if it holds a V that is not finite
 
     // Blocks are handed out in the order of their index and go to the 8 XCDs round-robin: all
     // blocks of the unit with the longest global cache come first, its latest positions (which see
@@ -307,11 +308,10 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     auto no_mask = [&](int t) __attribute__((always_inline)) {
         return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, qt * S::Q, qt * S::Q + S::Q - 1);
     };
-    // A weight of zero does not keep an inf or NaN of V out of a product, so tiles of which some query sees only a part
-    // are looked through (t: the tile that goes to the buffer).
+    // A weight of zero does not keep an inf or NaN of V out of a product, and the middle and low parts of a weight are often zero,
+    // of a visible key too: every tile is looked through (t: the one that goes to the buffer).
     auto look = [&](int buf, const uint4 &r_v, int t) __attribute__((always_inline)) {
-        if (!no_mask(t) && !(pf_finite(r_v.x) && pf_finite(r_v.y) && pf_finite(r_v.z) && pf_finite(r_v.w)))
-            s_bad[buf] = t;  // all writers of a tile write the same
+        if (pf_nonfinite(r_v)) s_bad[buf] = t;  // all writers of a tile write the same
     };
     if (threadIdx.x < 2) s_bad[threadIdx.x] = -1;
 

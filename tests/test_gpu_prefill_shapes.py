@@ -124,3 +124,35 @@ def test_picked_chunk_keys_and_the_whole_chunk_agree(dtype, d, G, rate):
         for out in outs:
             assert np.abs(out[base:base + n][rows] - ref).max() <= _tol(dtype, d, G)
         base += n
+
+
+def _with_nonfinite(K, V, g, q, i0, W, tau, scale, G):
+    """attend_definition where V may hold infinities and NaNs: each reaches exactly the queries that see its key."""
+    ref = attend_definition(K, np.where(np.isfinite(V), V, 0.0).astype(np.float32), g, q, i0 + np.arange(len(q)), W, tau, scale)
+    pos = np.arange(len(K))
+    for i in range(len(q)):
+        for h in range(V.shape[1]):
+            see = (pos <= i0 + i) & ((i0 + i - pos < W) | (g[:, h] >= tau))
+            add = np.where(np.isfinite(V[see, h]), 0.0, V[see, h])  # a positive weight times inf or NaN
+            with np.errstate(invalid="ignore"):
+                ref[i, h * G:(h + 1) * G] += add.sum(0)
+    return ref
+
+
+@pytest.mark.parametrize("dtype,d,G", [x for x in SHAPES if x != (wg.BF16, 128, 4)],
+                         ids=[i for i in IDS if i != "bf16-d128-G4"])
+def test_values_that_are_not_finite_in_tiles_that_every_query_sees(dtype, d, G):
+    """Full tiles of the global cache and of picked chunk keys, ring and chunk tiles inside all windows of a block: there
+    too an infinity gives infinities, not the NaN that a weight's parts of zero would make of it."""
+    W, P, tau, step = 400, 16, 0.6, 5
+
+    def spoil(call, v):  # every fifth row, both kv heads, one of the odd columns in turn (sums of a few of them)
+        for n, row in enumerate(range(2, len(v), step)):
+            v[row, :, (2 * n + 1) % d] = (float("inf"), float("inf"), -float("inf"), float("inf"), float("nan"), -float("inf"), -float("inf"))[n % 7]
+
+    for s, t0, K, V, g, q, out in _feed(dtype, d, G, 2, [[700], [150]], W, P, tau, seed=3 * d + G, spoil=spoil):
+        ref = _with_nonfinite(K, V, g, q, t0, W, tau, 1 / math.sqrt(d), G)
+        fin = np.isfinite(ref)
+        np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
+        np.testing.assert_array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.abs(out[fin] - ref[fin]).max() <= _tol(dtype, d, G)
