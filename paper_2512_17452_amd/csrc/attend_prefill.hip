@@ -492,6 +492,9 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
 // 8192 cubed reaches 1260 on the same card.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPfTilesQ = 32;
+// What stands in V past the last row of a region: a weight of zero does not keep an infinity out of a product, so these
+// rows do not repeat the last one.
+static __device__ const uint4 pf_zero_row[kSaD * 2 / 16] = {};
 __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
     constexpr int NW = 4, Q = kPfTilesQ, KT = 64, kRows = KT / NW, G = 4, D = kSaD;
     __shared__ __attribute__((aligned(1024))) char s_t[2][2][KT * D * 2];  // K and V
@@ -574,29 +577,38 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
             }
             return;
         }
+        // rows of the region from this tile on: the tile's others are past its end
+        const int rows = t < n_g ? gl - t * KT : t < t_far ? w_eff - (t - n_g) * KT : t < t_near ? n_far - (t - t_far) * KT
+                                                                                              : T - near - (t - t_near) * KT;
+        auto pieces = [&](auto last_t) __attribute__((always_inline)) {
+            constexpr bool kLast = decltype(last_t)::value;
 #pragma unroll
-        for (int i = 0; i < kRows / 4; i++) {
-            const int r = wave * kRows + 4 * i + sub;
-            const char *kp;
-            int64_t v_delta = pv.v_off;
-            if (t < n_g) {  // global cache
-                const int idc = min(t * KT + r, gl - 1);
-                const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
-                kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
-            } else if (t < t_far) {  // ring, oldest position first
-                const int slot = ring_slot((t - n_g) * KT + r);
-                const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
-                                         : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
-                kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
-            } else {  // this chunk
-                const int idc = t < t_near ? __shfl(far, 4 * i + sub) : min(near + (t - t_near) * KT + r, T - 1);
-                kp = a.k + ((size_t)(base + idc) * pv.Hkv + h) * (D * 2);
-                v_delta = a.v - a.k;
+            for (int i = 0; i < kRows / 4; i++) {
+                const int r = wave * kRows + 4 * i + sub;
+                const char *kp;
+                int64_t v_delta = pv.v_off;
+                if (t < n_g) {  // global cache
+                    const int idc = min(t * KT + r, gl - 1);
+                    const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
+                    kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
+                } else if (t < t_far) {  // ring, oldest position first
+                    const int slot = ring_slot((t - n_g) * KT + r);
+                    const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
+                                             : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
+                    kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
+                } else {  // this chunk
+                    const int idc = t < t_near ? __shfl(far, 4 * i + sub) : min(near + (t - t_near) * KT + r, T - 1);
+                    kp = a.k + ((size_t)(base + idc) * pv.Hkv + h) * (D * 2);
+                    v_delta = a.v - a.k;
+                }
+                const int at = ((ln & 15) ^ sa_sw_f(r)) * 16;
+                kp += at;
+                sa_dma16_at(kp, lk + i * 1024);
+                sa_dma16_at(kLast && r >= rows ? reinterpret_cast<const char *>(pf_zero_row) + at : kp + v_delta, lv + i * 1024);
             }
-            kp += ((ln & 15) ^ sa_sw_f(r)) * 16;
-            sa_dma16_at(kp, lk + i * 1024);
-            sa_dma16_at(kp + v_delta, lv + i * 1024);
-        }
+        };
+        if (rows >= KT) pieces(std::false_type());
+        else pieces(std::true_type());
     };
     auto no_mask = [&](int t) __attribute__((always_inline)) {
         return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, q_first, q_first + Q - 1);

@@ -156,3 +156,39 @@ def test_values_that_are_not_finite_in_tiles_that_every_query_sees(dtype, d, G):
         np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
         np.testing.assert_array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
         assert np.abs(out[fin] - ref[fin]).max() <= _tol(dtype, d, G)
+
+
+@pytest.mark.parametrize("n_old,W", [(32, 96), (96, 32), (64, 160), (40, 70)])
+def test_rows_past_the_end_of_a_region_hold_no_infinities(n_old, W):
+    """The 128-wide group of four: tiles of 64 keys are filled up with rows that no query sees.  Whatever the last row of
+    the global cache, of the ring and of the picked keys holds in V, a query that sees all rows of its tile gets the
+    sum of what it sees."""
+    d, G, Hk, P, tau = 128, 4, 1, 16, 0.5
+    dev, T = torch.device("cuda:0"), 64 + W + 32
+    pool = wg.Pool(wg.Config(1, G, Hk, d, wg.BF16, P, W, 1, 64, 256), 1, 1024)
+    gen = torch.Generator().manual_seed(n_old + W)
+    K = torch.randn((n_old + W + T, Hk, d), generator=gen).bfloat16()
+    V = torch.randn((n_old + W + T, Hk, d), generator=gen).bfloat16()
+    g = torch.zeros((n_old + W + T, Hk))
+    g[:n_old] = 1.0                 # the global cache
+    g[n_old + W - 1] = 1.0          # the newest ring row
+    t0 = n_old + W
+    g[t0:t0 + 32] = 1.0             # picked keys of the chunk
+    V[n_old - 1, 0, 5] = float("inf")
+    V[t0 - 1, 0, 9] = -float("inf")
+    V[t0 + 31, 0, 77] = float("inf")
+    q = torch.randn((T, G, d), generator=gen).bfloat16()
+    Kd, Vd, gd = K.to(dev), V.to(dev), g.to(dev)
+    pool.prefill_admit(0, [0], [t0], Kd[:t0].contiguous(), Vd[:t0].contiguous(), gd[:t0].contiguous(), tau=tau)
+    out = torch.full((T, G, d), float("nan"), device=dev)
+    pool.attend(0, [0], q.to(dev), out, 1 / math.sqrt(d), n_q=[T], k_chunk=Kd[t0:].contiguous(), v_chunk=Vd[t0:].contiguous(),
+                g_chunk=gd[t0:].contiguous(), tau=tau)
+    ref = _with_nonfinite(K.float().numpy(), V.float().numpy(), g.numpy(), q.float().numpy(), t0, W, tau, 1 / math.sqrt(d), G)
+    out = out.cpu().numpy()
+    # every query sees the global cache and the ring's newest row, those from position 31 on the last of the picked keys,
+    # which are a tile of their own for the last block
+    np.testing.assert_array_equal(out[:, :, [5, 9]], ref[:, :, [5, 9]])
+    np.testing.assert_array_equal(out[31:, :, 77], ref[31:, :, 77])
+    fin = np.isfinite(ref)
+    fin[:31, :, 77] = False
+    assert np.abs(out[fin] - ref[fin]).max() <= _tol(wg.BF16, d, G)
