@@ -27,19 +27,20 @@ constexpr int kGmTokens = 32;  // tokens per wave
 
 // Twice the exact GELU, 2 z Phi(z) = z + |z| - |z| q(|z|) with q(y) = erfc(y / sqrt 2): no difference of nearly equal
 // numbers on the negative side, and z + |z| carries a NaN or an infinity on.  q = 2^P(y), where log2 erfc(y / sqrt 2)
-// is so smooth that a polynomial of degree six does: weighted by what an error of P does to y q(y), a least-squares fit
-// on [0, 6] reweighted until its largest error was as small as it gets leaves 5e-8 of the GELU.  Beyond 6 the
-// product stays where it is there, 1.2e-8.  Whole function in fp32 against 64 bits, |z| <= 8: 2.8e-7 at most (the
-// rounding of z itself at the far end; 8e-8 for negative z), where the rational erf formula of Abramowitz & Stegun
-// 7.1.26 that stood here before left 4.2e-7 at 26 issue slots; this takes 13 with the one exponential counted as four.
+// is so smooth that a polynomial of degree six does: a least-squares fit on [0, 7], weighted by what an error of P does to
+// (y + 0.1) q(y) (the 0.1 holds a small z: without it the constant term is off by 4.8e-6 of one) and reweighted until its
+// largest error was as small as it gets.  Beyond 8 the product stays where it is there, 5e-15.  Whole function in fp32
+// against 64 bits, largest error at |z| < 0.05 / < 2 / < 8: 1.0e-8 (1.7e-6 of z) / 1.5e-7 / 3.1e-7 (the rounding of z
+// itself at the far end), where the rational erf formula of Abramowitz & Stegun 7.1.26 that stood here before left
+// 1.4e-8 / 2.6e-7 / 4.2e-7 at 26 issue slots; this takes 13 with the one exponential counted as four.
 __device__ __forceinline__ float gm_gelu2(float z) {
-    const float y = fminf(fabsf(z), 6.0f);
-    float p = fmaf(3.309277963e-05f, y, -7.692193612e-04f);
-    p = fmaf(p, y, 8.080715314e-03f);
-    p = fmaf(p, y, -5.341210216e-02f);
-    p = fmaf(p, y, -4.587709606e-01f);
-    p = fmaf(p, y, -1.151201725e+00f);
-    p = fmaf(p, y, 6.938917977e-06f);
+    const float y = fminf(fabsf(z), 8.0f);
+    float p = fmaf(3.042223024e-05f, y, -7.449424051e-04f);
+    p = fmaf(p, y, 7.997222006e-03f);
+    p = fmaf(p, y, -5.327548117e-02f);
+    p = fmaf(p, y, -4.588803671e-01f);
+    p = fmaf(p, y, -1.151162603e+00f);
+    p = fmaf(p, y, 2.378846442e-06f);
     return fmaf(-y, __builtin_amdgcn_exp2f(p), z + fabsf(z));
 }
 

@@ -123,3 +123,21 @@ def test_gate_mlp_chunk_of_the_prefill_workload():
     rows = np.unique(np.concatenate([[0, 31, 32, 127, 128, T - 129, T - 1], rng.integers(0, T, 1500)]))
     _, ref = _oracle(k[rows].cpu(), kr[rows].cpu(), w1.cpu(), b1.cpu(), w2.cpu(), b2.cpu(), 1e-6, True)
     assert np.abs(g[rows] - ref).max() <= TOL_BF16
+
+
+@pytest.mark.parametrize("dtype,width", [(torch.bfloat16, 64), (torch.float32, 40)])
+def test_gelu_loses_nothing_of_small_and_of_large_arguments(dtype, width):
+    """W1 = 0 makes the pre-activation the bias b1 itself, and one large W2 per head lifts the GELU of it to the size of a logit."""
+    z = torch.tensor([0.02, -0.02, 0.003, -0.0011, 0.05, -8.5])
+    lift = torch.tensor([128.0, 128.0, 1024.0, 2048.0, 32.0, 2.0 ** 24])  # exact in bf16
+    Hk, d = len(z), 64
+    k = torch.randn((5, Hk, d), generator=torch.Generator().manual_seed(1)).to(dtype).cuda()
+    w1, w2 = torch.zeros((Hk, width, 2 * d), dtype=dtype), torch.zeros((Hk, width), dtype=dtype)
+    b1, b2 = torch.zeros((Hk, width)), torch.zeros((Hk,))
+    b1[:, 7], w2[:, 7] = z, lift.to(dtype)
+    g = wg.gate_mlp_scores(k, k, w1.cuda(), b1.cuda(), w2.cuda(), b2.cuda()).cpu().double()
+    logit = torch.log(g / (1.0 - g))
+    ref = torch.nn.functional.gelu(z.double()) * lift.double()
+    # exponential, sum and quotient leave the score within 4 * 2^-24 of its value (0.8 at most), the logit is 1 / (g (1 - g)) <= 6.4
+    # times that; the GELU's own error is 1.7e-6 of a small z's (a logit of 1.4 at most here)
+    assert (logit - ref).abs().max() <= 6.4 * 0.8 * 4 * 2.0 ** -24 + 1.7e-6 * 1.4, (logit - ref)
