@@ -34,6 +34,7 @@
 // the vector work per score is twice the four extra products.  Measured: a 6001-token prompt of 32 / 8 heads
 // of 64 in chunks of 2048, gate and admission included, 17.3 ms -> 0.55 ms against one wave of plain fp32
 // arithmetic per (query, head), the error against 64 bits 9.3e-7 -> 6.4e-7.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -62,10 +63,10 @@ struct PfShape {
                                                 // 64 bytes of each at a time per half wave, which this stride
                                                 // (320 or 192 bytes) spreads over all banks
 };
-constexpr int kPfQMin = 32;       // chunk positions per block at the largest group
 
 struct PrefillAttnArgs {
     int nx;                 // blocks per (sequence, kv head) of the launch
+    int rank0;              // place in the order of the launch's first unit
     const int32_t *order;   // [n_units] (sequence, kv head) units, the one with the longest global cache first
     const int32_t *pick;    // admitted chunk positions of every unit, ascending (pick_of), or NULL
     const int32_t *picked;  // how many of them lie below position 32 i, for every i (picked_of)
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     // differ several-fold in work: with the long ones at the front the launch does not end on a
     // late-started long one, and every unit is spread evenly over the XCDs (giving each XCD whole
     // heads, for the sake of its L2, leaves the XCDs as unbalanced as the heads are).
-    const int unit = a.order[blockIdx.x / a.nx];
+    const int unit = a.order[a.rank0 + blockIdx.x / a.nx];
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
     const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
 
     // order of the blocks: as in attend_prefill_kernel
-    const int unit = a.order[blockIdx.x / a.nx];
+    const int unit = a.order[a.rank0 + blockIdx.x / a.nx];
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
     const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
@@ -799,12 +800,24 @@ size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q) {
     return kPfOrderBytes + sizeof(int32_t) * (size_t)pv.Hkv * (size_t)(total_q + total_q / 32 + n_seqs);
 }
 
+// Blocks of q positions for every unit of the call.  A launch holds fewer than 2^32 threads: where one long chunk beside many
+// short ones would be over that (every unit has the blocks of the longest), the units go to several launches.
+template <class Kernel>
+static hipError_t launch_units(Kernel kernel, int q, int threads, const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t,
+                               hipStream_t st) {
+    a.nx = (max_t + q - 1) / q;
+    const int n_units = cs.n * pv.Hkv;
+    const int per = (int)std::min<int64_t>(n_units, (((int64_t)1 << 32) - 1) / ((int64_t)a.nx * threads));
+    for (a.rank0 = 0; a.rank0 < n_units; a.rank0 += per) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.nx * std::min(per, n_units - a.rank0)), dim3(threads), 0, st, pv, cs, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 template <int D, int G>
 static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t, hipStream_t st) {
-    using S = PfShape<D, G>;
-    a.nx = (max_t + S::Q - 1) / S::Q;
-    hipLaunchKernelGGL((attend_prefill_kernel<D, G>), dim3(a.nx * pv.Hkv * cs.n), dim3(512), 0, st, pv, cs, a);
-    return hipGetLastError();
+    return launch_units(attend_prefill_kernel<D, G>, PfShape<D, G>::Q, 512, pv, cs, a, max_t, st);
 }
 
 // Lists of picked chunk keys pay as soon as some block of the call has keys behind all its windows, and need room.
@@ -845,18 +858,14 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     int max_t = 0;
     for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
     if (max_t == 0) return hipSuccess;
-    // a grid of one block per 32 positions (group of 8) has to stay inside grid.x
-    if ((int64_t)((max_t + kPfQMin - 1) / kPfQMin) * pv.Hkv * cs.n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    if (max_t >= 1 << 28) return hipErrorInvalidValue;  // the blocks of one unit have to fit a launch
     hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &a.order, &a.pick, &a.picked, st);
     if (e != hipSuccess) return e;
     if (pv.d == 128) {
         switch (pv.G) {
             case 1: return launch_shape<128, 1>(pv, cs, a, max_t, st);
             case 2: return launch_shape<128, 2>(pv, cs, a, max_t, st);
-            case 4:
-                a.nx = (max_t + kPfTilesQ - 1) / kPfTilesQ;
-                hipLaunchKernelGGL(attend_prefill_tiles_kernel, dim3(a.nx * pv.Hkv * cs.n), dim3(256), 0, st, pv, cs, a);
-                return hipGetLastError();
+            case 4: return launch_units(attend_prefill_tiles_kernel, kPfTilesQ, 256, pv, cs, a, max_t, st);
             case 8: return launch_shape<128, 8>(pv, cs, a, max_t, st);
             default: break;
         }

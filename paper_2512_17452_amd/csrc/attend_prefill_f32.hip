@@ -32,7 +32,7 @@ hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, fl
                                hipStream_t st);
 
 struct PrefillF32Args {
-    int nx;                 // blocks per (sequence, query head) of the launch
+    int32_t first[kMaxCallSeqs + 1];  // position tiles of the sequences before sequence b
     int layer;
     float tau, scale_log2e;
     const char *q, *k, *v;  // chunk tensors, fp32
@@ -49,12 +49,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attend_prefill_f32_kernel(View pv,
     __shared__ __attribute__((aligned(16))) int s_lo[NW][2][32], s_hi[NW][2][32];  // first and last position that sees it
     __shared__ float s_m[NW][32], s_l[NW][32];
     __shared__ __attribute__((aligned(16))) float s_o[NW][32 * OS];
-    // all query heads of a position tile next to each other (they share K and V), the latest positions first
-    const int per_seq = a.nx * pv.Hq;
-    const int b = (int)blockIdx.x / per_seq, r = (int)blockIdx.x % per_seq;
-    const int qt = a.nx - 1 - r / pv.Hq, qh = r % pv.Hq, h = qh / pv.G;
+    // all query heads of a position tile next to each other (they share K and V), a sequence's latest positions first
+    const int x = (int)blockIdx.x / pv.Hq, qh = (int)blockIdx.x % pv.Hq, h = qh / pv.G;
+    int b = 0;
+    for (int hi = cs.n - 1; b < hi;) {  // the last sequence whose tiles begin at or before tile x (not one without tokens)
+        const int mid = (b + hi + 1) >> 1;
+        if (a.first[mid] <= x) b = mid; else hi = mid - 1;
+    }
+    const int qt = a.first[b + 1] - 1 - x;
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
-    if (qt * 32 >= T) return;  // block-uniform
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
@@ -303,17 +306,22 @@ hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int lay
     a.g = g;
     a.out = out;
     int max_t = 0;
-    for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
+    a.first[0] = 0;
+    for (int b = 0; b < cs.n; b++) {
+        max_t = max(max_t, cs.ntok[b]);
+        a.first[b + 1] = a.first[b] + (cs.ntok[b] + 31) / 32;
+    }
     if (max_t == 0) return hipSuccess;
-    a.nx = (max_t + 31) / 32;
     a.pick = a.picked = nullptr;
     if (max_t > pv.W) {
         const int32_t *order;
         const hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &order, &a.pick, &a.picked, st);
         if (e != hipSuccess) return e;
     }
-    const int64_t blocks = (int64_t)a.nx * pv.Hq * cs.n;
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // grid.x
+    // Blocks for the tiles that there are: a launch holds fewer than 2^32 threads, and one long chunk beside many short ones
+    // would be over that if every sequence had the blocks of the longest.
+    const int64_t blocks = (int64_t)a.first[cs.n] * pv.Hq;
+    if (blocks * (pv.d == 64 ? 512 : 256) >= ((int64_t)1 << 32)) return hipErrorInvalidValue;
     // eight waves of 64-element heads fill the block's 64 KiB of folded outputs, four of 128-element heads do
     if (pv.d == 64)
         hipLaunchKernelGGL((attend_prefill_f32_kernel<64, 8>), dim3((unsigned)blocks), dim3(512), 0, st, pv, cs, a);

@@ -192,3 +192,30 @@ def test_rows_past_the_end_of_a_region_hold_no_infinities(n_old, W):
     fin = np.isfinite(ref)
     fin[:31, :, 77] = False
     assert np.abs(out[fin] - ref[fin]).max() <= _tol(wg.BF16, d, G)
+
+
+@pytest.mark.parametrize("dtype,Hk,G,long_n,n_short", [(wg.F32, 4, 8, 131072, 63), (wg.BF16, 8, 8, 262144, 126)], ids=["f32", "bf16"])
+def test_one_long_chunk_beside_many_short_ones(dtype, Hk, G, long_n, n_short):
+    """A launch with the longest chunk's blocks for every sequence would be at the limit of 2^32 threads.  The same bits as
+    the long chunk alone and the short ones alone."""
+    d, W, P, tau, Hq = 64, 64, 64, 0.5, G * Hk
+    dt = torch.float32 if dtype == wg.F32 else torch.bfloat16
+    dev, lens = torch.device("cuda:0"), [5] * (n_short - 1) + [long_n, 0, 33]
+    B, tot = len(lens), sum(lens)
+    pool = wg.Pool(wg.Config(1, Hq, Hk, d, dtype, P, W, B, 4, 64), B, tot)
+    gen = torch.Generator(device=dev).manual_seed(1)
+    q, k, v = (torch.randn((tot, h, d), generator=gen, device=dev, dtype=dt) for h in (Hq, Hk, Hk))
+    g = (torch.rand((tot, Hk), generator=gen, device=dev) < 1e-4).float()
+
+    def attend(ids, lo, hi):
+        out = torch.full((hi - lo, Hq, d), float("nan"), device=dev)
+        pool.attend(0, ids, q[lo:hi], out, 1 / math.sqrt(d), n_q=[lens[s] for s in ids], k_chunk=k[lo:hi], v_chunk=v[lo:hi],
+                    g_chunk=g[lo:hi], tau=tau)
+        return out
+
+    whole = attend(list(range(B)), 0, tot)
+    at = sum(lens[:n_short - 1])
+    assert bool(torch.isfinite(whole).all())
+    assert torch.equal(whole[:at], attend(list(range(n_short - 1)), 0, at))
+    assert torch.equal(whole[at:at + long_n], attend([n_short - 1], at, at + long_n))
+    assert torch.equal(whole[at + long_n:], attend([n_short + 1], at + long_n, tot))
