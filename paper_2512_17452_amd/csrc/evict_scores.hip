@@ -441,7 +441,9 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
     const dim3 g_stats((n_rows + kEsTile - 1) / kEsTile, n_units);
     const dim3 g_keys((unsigned)((max_len + kEsTile - 1) / kEsTile), n_units);
     const dim3 g_pool((unsigned)((max_len + 255) / 256), n_units);
-    if (pv.dtype == WGKV_BF16 && pv.d == kEmD && pv.G == 4 && n_obs % 8 == 0) {
+    // (the matrix-core kernels read the queries 16 bytes at a time, part of them straight into LDS; the general ones one by one)
+    const bool q_aligned = ((uintptr_t)q_obs & 15) == 0;
+    if (pv.dtype == WGKV_BF16 && pv.d == kEmD && pv.G == 4 && n_obs % 8 == 0 && q_aligned) {
         const dim3 g_stats_m((n_rows + kEmStatRows - 1) / kEmStatRows, n_units);
         hipLaunchKernelGGL(evict_stats_mfma_kernel, g_stats_m, dim3(512), 0, st, pv, cs, a);
         // A wave that walks the whole window alone takes 25 us for 256 observation rows, however few keys there are: waves

@@ -46,3 +46,23 @@ def test_scores_match_fp64(B, Hk, n_obs, lens, scale):
             np.testing.assert_array_equal(pooled[s * Hk + h, :n], np.lib.stride_tricks.sliding_window_view(pad, 5).max(-1))
             assert not raw[s * Hk + h, n:].any() and not pooled[s * Hk + h, n:].any()
         base += n_tok[s]
+
+
+def test_scores_of_queries_that_are_not_16_byte_aligned():
+    """The matrix-core sweeps read queries 16 bytes at a time: others go to the general kernels, any element's address will do."""
+    B, Hk, n_obs, n, d, W, dev = 2, 2, 16, 150, 128, 16, torch.device("cuda:0")
+    pool = wg.Pool(wg.Config(1, 4 * Hk, Hk, d, wg.BF16, 16, W, B, 16, B * Hk * 18), B, B * (n + W))
+    gen = torch.Generator(device=dev).manual_seed(4)
+    k, v = (torch.randn((B * (n + W), Hk, d), generator=gen, device=dev).bfloat16() for _ in range(2))
+    pool.prefill_admit(0, [0, 1], [n + W] * B, k, v, torch.ones((B * (n + W), Hk), device=dev), tau=0.5)
+    q = torch.randn((B, n_obs, 4 * Hk, d), generator=gen, device=dev).bfloat16()
+    room = torch.zeros(q.numel() + 8, dtype=torch.bfloat16, device=dev)
+    raw, pooled = pool.evict_scores(0, [0, 1], q, 1 / math.sqrt(d), n)
+    for off in (1, 2, 4):
+        q_off = room[off:off + q.numel()].view(q.shape)
+        q_off.copy_(q)
+        assert q_off.data_ptr() % 16 != 0
+        raw2, pooled2 = pool.evict_scores(0, [0, 1], q_off, 1 / math.sqrt(d), n)
+        # both within 1e-5 of the definition (see above)
+        torch.testing.assert_close(raw2, raw, rtol=2e-5, atol=0)
+        torch.testing.assert_close(pooled2, pooled, rtol=2e-5, atol=0)
