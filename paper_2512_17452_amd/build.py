@@ -10,6 +10,7 @@ host-only boundary tests under it, from the repository root:
     ASAN_OPTIONS=detect_leaks=0:protect_shadow_gap=0 UBSAN_OPTIONS=halt_on_error=1 \
     WGKV_LIB=paper_2512_17452_amd/libwgkv_hostsan.so python -m pytest tests/test_boundary_host.py -q
 """
+import glob
 import os
 import subprocess
 import sys
@@ -50,10 +51,14 @@ def build_hostsan() -> str:
     return LIB_HOSTSAN
 
 
+def dependencies() -> list:
+    """Every file that goes into the library: the sources, the headers beside them and the public one."""
+    return [os.path.join(CSRC, s) for s in SOURCES] + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + \
+        [os.path.join(HERE, "..", "include", "wgkv.h")]
+
+
 def build(force: bool = True) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(CSRC, "wgkv_dev.h"),
-                                                        os.path.join(HERE, "..", "include", "wgkv.h")]
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(s) for s in srcs):
+    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(s) for s in dependencies()):
         return LIB
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:

@@ -71,3 +71,43 @@ def test_null_handles_are_rejected(lib):
     assert lib.wgkv_attend_decode_static(None, 0, 1, (C.c_int32 * 1)(0), None, 1.0, None, None) == -1
     assert lib.wgkv_stream_read_probe(None, 1024, None, None, None, None) == -1
     lib.wgkv_destroy(None)
+
+
+def test_every_included_header_makes_the_library_stale(monkeypatch, tmp_path):
+    """build(force=False) compiles again when any file that the sources include is newer than the library."""
+    import os
+    import re
+    from paper_2512_17452_amd import build as lib_build
+    used = set()
+    for src in [os.path.join(lib_build.CSRC, s) for s in lib_build.SOURCES]:
+        todo = [src]
+        while todo:
+            path = todo.pop()
+            for name in re.findall(r'#include "([^"]+)"', open(path).read()):
+                inc = os.path.normpath(os.path.join(os.path.dirname(path), name))
+                if inc not in used:
+                    used.add(inc)
+                    todo.append(inc)
+    assert len(used) >= 3
+    lib = tmp_path / "lib.so"
+    lib.write_bytes(b"")
+    monkeypatch.setattr(lib_build, "LIB", str(lib))
+    asked = []
+
+    class Asked(Exception):
+        pass
+
+    def compile_(src, sanitize_host=False):
+        raise Asked
+
+    monkeypatch.setattr(lib_build, "_compile", compile_)
+    real = os.path.getmtime
+    for newer in sorted(used):
+        stamp = lambda p: real(p) if os.path.normpath(p) == newer else 0.0 if p != str(lib) else 1.0
+        monkeypatch.setattr(lib_build.os.path, "getmtime", stamp)
+        try:
+            lib_build.build(force=False)
+        except Asked:
+            asked.append(newer)
+        monkeypatch.setattr(lib_build.os.path, "getmtime", real)
+    assert asked == sorted(used)
