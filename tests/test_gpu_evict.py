@@ -96,6 +96,24 @@ def test_evict_apply_many_entries_and_units():
     pair.check_attend(0, seqs, q)
 
 
+@pytest.mark.parametrize("dtype,d,Hk,frac", [(wg.BF16, 128, 96, 0.3), (wg.F32, 128, 96, 0.1), (wg.BF16, 64, 90, 0.5)])
+def test_evict_apply_more_than_256_units(dtype, d, Hk, frac):
+    """Two blocks per head instead of four, each with 64 to 256 bytes of a row, several turns to a tile of 1024 entries, and
+    heads of more than one such tile."""
+    rng = np.random.default_rng(Hk + d)
+    P, W, lens = 16, 16, [1300, 170, 90]
+    max_gp = lens[0] // P + 4
+    pair = Pair(1, Hk, Hk, d, dtype, P, W, 3, max_gp, Hk * sum(-(-n // P) + 3 for n in lens), max_call_seqs=3,
+                max_call_tokens=sum(lens))
+    rates = np.where(np.arange(Hk) % 24 == 0, 0.97, 0.1)
+    k, v, g = rand_tokens(rng, sum(lens), Hk, d, pair.tdt, rates=list(rates))
+    pair.prefill(0, [0, 1, 2], lens, k, v, g, 0.5)
+    pair.pool.status()  # the score rows are as long as the heads, not as the host's bound
+    assert max(pair.orc.global_len(0, 0, h) for h in range(Hk)) > 1024
+    pair.evict(0, [2, 0, 1], _scores(rng, pair, 0, [2, 0, 1], "ties"), frac)
+    pair.check_state()
+
+
 def test_evict_apply_rejects_bad_arguments():
     rng = np.random.default_rng(1)
     pair = Pair(1, 4, 2, 64, wg.F32, 4, 8, 2, 64, 400, max_call_seqs=2, max_call_tokens=256)
