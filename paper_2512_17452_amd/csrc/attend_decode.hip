@@ -531,14 +531,138 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
     }
 }
 
+// What the decode kernels have in LDS for the states of a block's row groups, and how a unit's output is dealt over threads.
+template <int DT, int D, int G>
+struct DecOut {
+    static constexpr int TPW = DecShape<DT, D, G>::TPW;
+    static constexpr int NST = kAttnWaves * TPW;  // softmax states of a block: one per row group
+    static constexpr int VPT = G * D >= 2 * kAttnThreads ? G * D / kAttnThreads : 2;  // output elements per thread
+    static constexpr int NT = G * D / VPT;        // threads that hold some
+    static_assert(NT <= kAttnThreads && D % VPT == 0 && (VPT == 2 || VPT == 4), "");
+};
+template <int DT, int D, int G>
+struct DecStates {
+    float m[DecOut<DT, D, G>::NST][G], l[DecOut<DT, D, G>::NST][G];
+    __attribute__((aligned(16))) float acc[DecOut<DT, D, G>::NST][G * D];
+};
+
+// A wave's row groups into their places.
+template <int DT, int D, int G>
+__device__ __forceinline__ void put_states(DecStates<DT, D, G> &s, int wave, int grp, int sub, const float (&m)[G], const float (&l)[G],
+                                           const float (&acc)[G][DecShape<DT, D, G>::EPL]) {
+    using SH = DecShape<DT, D, G>;
+    const int st = wave * SH::TPW + grp;
+#pragma unroll
+    for (int g = 0; g < G; g++)
+#pragma unroll
+        for (int e = 0; e < SH::EPL; e += 4)
+            *reinterpret_cast<float4 *>(&s.acc[st][g * D + sub * SH::EPL + e]) =
+                make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
+    if constexpr (SH::SPREAD) {
+        if (sub < 4) {  // m[hh] and l[hh] belong to head 4 * hh + sub % 4
+#pragma unroll
+            for (int hh = 0; hh < SH::HH; hh++) {
+                s.m[st][4 * hh + sub] = m[hh];
+                s.l[st][4 * hh + sub] = l[hh];
+            }
+        }
+    } else if (sub == 0) {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            s.m[st][g] = m[g];
+            s.l[st][g] = l[g];
+        }
+    }
+}
+
+// N states from s0 on into one, for output elements x0 .. of head xg.
+template <int N, int DT, int D, int G>
+__device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0, int x0, int xg, float &M, float &L,
+                                            float (&o)[DecOut<DT, D, G>::VPT]) {
+    constexpr int VPT = DecOut<DT, D, G>::VPT;
+    M = s.m[s0][xg];
+    L = 0.f;
+#pragma unroll
+    for (int i = 1; i < N; i++) M = fmaxf(M, s.m[s0 + i][xg]);
+    const float Ms = M == -INFINITY ? 0.f : M;
+#pragma unroll
+    for (int e = 0; e < VPT; e++) o[e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const float f = __builtin_amdgcn_exp2f(s.m[s0 + i][xg] - Ms);  // 0 for a state that saw nothing
+        L = fmaf(s.l[s0 + i][xg], f, L);
+#pragma unroll
+        for (int e = 0; e < VPT; e++) o[e] = fmaf(s.acc[s0 + i][x0 + e], f, o[e]);
+    }
+}
+
+// The partial of a slot goes out with device-scope stores ...
+template <int D, int G, int VPT>
+__device__ __forceinline__ void put_partial(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot, int x0, int xg,
+                                            float M, float L, const float (&o)[VPT]) {
+    const uint32_t rec0 = (uint32_t)slot * G, off = rec0 * (D * 4) + x0 * 4;
+    if constexpr (VPT == 4) {
+        const u32x4 pk = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+        __builtin_amdgcn_raw_buffer_store_b128(pk, r_acc, off, 0, kCoherent);
+    } else {
+        const u32x2 pk = {__float_as_uint(o[0]), __float_as_uint(o[1])};
+        __builtin_amdgcn_raw_buffer_store_b64(pk, r_acc, off, 0, kCoherent);
+    }
+    if (x0 % D == 0) {
+        const u32x2 pk = {__float_as_uint(M), __float_as_uint(L)};
+        __builtin_amdgcn_raw_buffer_store_b64(pk, r_ml, (rec0 + xg) * 8, 0, kCoherent);
+    }
+}
+// ... and np of them from slot0 on, asked for eight together, become one.
+template <int D, int G, int VPT>
+__device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot0, int np, int x0, int xg,
+                                              float &L, float (&o)[VPT]) {
+    float M = -INFINITY;
+    L = 0.f;
+#pragma unroll
+    for (int e = 0; e < VPT; e++) o[e] = 0.f;
+    constexpr int MB = 8;
+    for (int q0 = 0; q0 < np; q0 += MB) {
+        u32x2 ml[MB];
+        uint32_t av[MB][VPT];
+#pragma unroll
+        for (int i = 0; i < MB; i++) {
+            const uint32_t rec = (uint32_t)(slot0 + min(q0 + i, np - 1)) * G;
+            ml[i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, (rec + xg) * 8, 0, kCoherent);
+            const uint32_t off = rec * (D * 4) + x0 * 4;
+            if constexpr (VPT == 4) {
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r_acc, off, 0, kCoherent);
+                av[i][0] = v.x; av[i][1] = v.y; av[i][2] = v.z; av[i][3] = v.w;
+            } else {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r_acc, off, 0, kCoherent);
+                av[i][0] = v.x; av[i][1] = v.y;
+            }
+        }
+        float mb = M;
+#pragma unroll
+        for (int i = 0; i < MB; i++) mb = fmaxf(mb, __uint_as_float(ml[i].x));  // a repeated last one changes nothing
+        const float ms = mb == -INFINITY ? 0.f : mb;
+        const float c = __builtin_amdgcn_exp2f(M - ms);
+        L *= c;
+#pragma unroll
+        for (int e = 0; e < VPT; e++) o[e] *= c;
+#pragma unroll
+        for (int i = 0; i < MB; i++)
+            if (q0 + i < np) {
+                const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[i].x) - ms);
+                L = fmaf(__uint_as_float(ml[i].y), f, L);
+#pragma unroll
+                for (int e = 0; e < VPT; e++) o[e] = fmaf(__uint_as_float(av[i][e]), f, o[e]);
+            }
+        M = mb;
+    }
+}
+
 template <int DT, int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, AttendArgs a) {
     using SH = DecShape<DT, D, G>;
-    constexpr int ES = SH::ES, EPL = SH::EPL, LPT = SH::LPT, TPW = SH::TPW;
-    constexpr int NST = kAttnWaves * TPW;  // softmax states of a block: one per row group
-    constexpr int VPT = G * D >= 2 * kAttnThreads ? G * D / kAttnThreads : 2;  // output elements per thread
-    constexpr int NT = G * D / VPT;        // threads that hold some
-    static_assert(NT <= kAttnThreads && D % VPT == 0 && (VPT == 2 || VPT == 4), "");
+    using OUT = DecOut<DT, D, G>;
+    constexpr int ES = SH::ES, EPL = SH::EPL, LPT = SH::LPT, VPT = OUT::VPT, NT = OUT::NT;
     __shared__ int s_ts[kMaxCallUnits + 1];  // pieces (or, with even shares, tiles) before unit u
     __shared__ int s_gl[kMaxCallUnits];      // entries in the unit's global cache
     __shared__ int s_nl[kMaxCallUnits];      // tokens in its ring
@@ -547,8 +671,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
     __shared__ int s_share;                  // tiles of a block's even share, 0: pieces
     __shared__ int s_arrived;
     __shared__ __attribute__((aligned(16))) DecStrips s_strips[kAttnWaves];
-    __shared__ float s_m[NST][G], s_l[NST][G];
-    __shared__ __attribute__((aligned(16))) float s_acc[NST][G * D];
+    __shared__ DecStates<DT, D, G> s_st;
 
     const int n_units = a.n_seqs * pv.Hkv, n_blocks = (int)gridDim.x;
     auto unit_tiles = [&](int u) __attribute__((always_inline)) {
@@ -719,62 +842,18 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
             stream_tiles<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, m, l, acc, s_strips[wave], lane);
         }
         // the block's row groups meet in LDS
-        const int st = wave * TPW + grp;
-#pragma unroll
-        for (int g = 0; g < G; g++)
-#pragma unroll
-            for (int e = 0; e < EPL; e += 4)
-                *reinterpret_cast<float4 *>(&s_acc[st][g * D + sub * EPL + e]) =
-                    make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
-        if constexpr (SH::SPREAD) {
-            if (sub < 4) {  // m[hh] and l[hh] belong to head 4 * hh + sub % 4
-#pragma unroll
-                for (int hh = 0; hh < SH::HH; hh++) {
-                    s_m[st][4 * hh + sub] = m[hh];
-                    s_l[st][4 * hh + sub] = l[hh];
-                }
-            }
-        } else if (sub == 0) {
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                s_m[st][g] = m[g];
-                s_l[st][g] = l[g];
-            }
-        }
+        put_states<DT, D, G>(s_st, wave, grp, sub, m, l, acc);
         __syncthreads();
-        float M = s_m[0][xg], L = 0.f, o[VPT];
-#pragma unroll
-        for (int i = 1; i < NST; i++) M = fmaxf(M, s_m[i][xg]);
-        const float Ms = M == -INFINITY ? 0.f : M;
-#pragma unroll
-        for (int e = 0; e < VPT; e++) o[e] = 0.f;
-#pragma unroll
-        for (int i = 0; i < NST; i++) {
-            const float f = __builtin_amdgcn_exp2f(s_m[i][xg] - Ms);  // 0 for a state that saw nothing
-            L = fmaf(s_l[i][xg], f, L);
-#pragma unroll
-            for (int e = 0; e < VPT; e++) o[e] = fmaf(s_acc[i][x0 + e], f, o[e]);
-        }
+        float M, L, o[VPT];
+        fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
         float *out = a.out + (size_t)u * G * D + x0;
         if (np > 1) {  // block-uniform
-            // Hand-over as in the kernel above: the partial goes out with device-scope stores, every wave waits for
-            // its own, then one thread counts the block; the folding block's loads come after the count.
+            // The stores carry the policy of a device-scope access (written through) and vmcnt counts them until they are
+            // acknowledged there: every wave waits for its own, then one thread counts the block; the folding block's loads
+            // come after the count.
             const __amdgpu_buffer_rsrc_t r_acc = part_rsrc(a.part_acc, a.part_acc_bytes);
             const __amdgpu_buffer_rsrc_t r_ml = part_rsrc(a.part_ml, a.part_ml_bytes);
-            if (mine) {
-                const uint32_t rec0 = (uint32_t)slot * G, off = rec0 * (D * 4) + x0 * 4;
-                if constexpr (VPT == 4) {
-                    const u32x4 pk = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-                    __builtin_amdgcn_raw_buffer_store_b128(pk, r_acc, off, 0, kCoherent);
-                } else {
-                    const u32x2 pk = {__float_as_uint(o[0]), __float_as_uint(o[1])};
-                    __builtin_amdgcn_raw_buffer_store_b64(pk, r_acc, off, 0, kCoherent);
-                }
-                if (x0 % D == 0) {
-                    const u32x2 pk = {__float_as_uint(M), __float_as_uint(L)};
-                    __builtin_amdgcn_raw_buffer_store_b64(pk, r_ml, (rec0 + xg) * 8, 0, kCoherent);
-                }
-            }
+            if (mine) put_partial<D, G>(r_ml, r_acc, slot, x0, xg, M, L, o);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (threadIdx.x == 0)
@@ -782,45 +861,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
             __syncthreads();
             if (s_arrived != np - 1) continue;
             asm volatile("" ::: "memory");
-            M = -INFINITY;
-            L = 0.f;
-#pragma unroll
-            for (int e = 0; e < VPT; e++) o[e] = 0.f;
-            constexpr int MB = 8;  // partials asked for together
-            for (int q0 = 0; q0 < np; q0 += MB) {
-                u32x2 ml[MB];
-                uint32_t av[MB][VPT];
-#pragma unroll
-                for (int i = 0; i < MB; i++) {
-                    const uint32_t rec = (uint32_t)(slot0 + min(q0 + i, np - 1)) * G;
-                    ml[i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, (rec + xg) * 8, 0, kCoherent);
-                    const uint32_t off = rec * (D * 4) + x0 * 4;
-                    if constexpr (VPT == 4) {
-                        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r_acc, off, 0, kCoherent);
-                        av[i][0] = v.x; av[i][1] = v.y; av[i][2] = v.z; av[i][3] = v.w;
-                    } else {
-                        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r_acc, off, 0, kCoherent);
-                        av[i][0] = v.x; av[i][1] = v.y;
-                    }
-                }
-                float mb = M;
-#pragma unroll
-                for (int i = 0; i < MB; i++) mb = fmaxf(mb, __uint_as_float(ml[i].x));  // a repeated last one changes nothing
-                const float ms = mb == -INFINITY ? 0.f : mb;
-                const float c = __builtin_amdgcn_exp2f(M - ms);
-                L *= c;
-#pragma unroll
-                for (int e = 0; e < VPT; e++) o[e] *= c;
-#pragma unroll
-                for (int i = 0; i < MB; i++)
-                    if (q0 + i < np) {
-                        const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[i].x) - ms);
-                        L = fmaf(__uint_as_float(ml[i].y), f, L);
-#pragma unroll
-                        for (int e = 0; e < VPT; e++) o[e] = fmaf(__uint_as_float(av[i][e]), f, o[e]);
-                    }
-                M = mb;
-            }
+            fold_partials<D, G>(r_ml, r_acc, slot0, np, x0, xg, L, o);
             if (threadIdx.x == 0) __hip_atomic_store(&a.counters[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (mine) {
@@ -831,17 +872,220 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
     }
 }
 
+// Calls of more units than blocks (batches of 33 and more sequences on eight kv heads): a block has several units one after
+// the other, and a chain of round trips (page ids, first rows, fold) for each of them.  Three ways of cutting:
+//   solo    a wave takes whole units, and there is no exchange at all: for units of about one length;
+//   waves   one list split evenly over the waves, a share may start and end inside a unit (16 tiles at least, and 12 tiles'
+//           worth for a unit that begins); a unit's partials, one per wave, are put together by the wave that arrives last:
+//           for short units of very different lengths, and for rows of 128 bytes;
+//   blocks  the same over blocks, as in the kernel above: for long ones.
+// Every block estimates the three in us from the lengths and takes the cheapest.  The model is a fit to every way of 234
+// calls (33 to 128 sequences of 100 to 8000 tokens, even and ragged heads, all head shapes); its choice is 0.7 % behind the best
+// way in the mean and 8 % at most for the main head shape.  Against the kernel above (us; main head shape, a third of the tokens
+// admitted): 33 x 100 tokens 15.5 -> 11.4, 64 x 300 24.3 -> 16, 128 x 300 40.5 -> 22, 128 x 1000 55 -> 38; heads from 1 to
+// 90 %: 64 x 1000 27 -> 25.5, 128 x 1000 44 -> 36; 33 x 4000 and longer calls are the same to 3 % (more to look at in front).
+constexpr int kMinWaveTiles = 16, kWaveStartTiles = 12;
+template <int DT, int D, int G>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View pv, AttendArgs a) {
+    using SH = DecShape<DT, D, G>;
+    using OUT = DecOut<DT, D, G>;
+    constexpr int ES = SH::ES, EPL = SH::EPL, LPT = SH::LPT, TPW = SH::TPW, VPT = OUT::VPT, NT = OUT::NT;
+    __shared__ int s_ts[kMaxCallUnits + 1];  // tiles before unit u, those charged to the begin of a unit included
+    __shared__ int s_gl[kMaxCallUnits];      // entries in the unit's global cache
+    __shared__ int s_nl[kMaxCallUnits];      // tokens in its ring
+    __shared__ int s_um[kMaxCallUnits];      // its index into the per-unit metadata
+    __shared__ int s_tmp[20];
+    __shared__ int s_longest;                // tiles of the longest unit
+    __shared__ int s_arrived;
+    __shared__ __attribute__((aligned(16))) DecStrips s_strips[kAttnWaves];
+    __shared__ DecStates<DT, D, G> s_st;
+
+    const int n_units = a.n_seqs * pv.Hkv, n_blocks = (int)gridDim.x, n_waves = n_blocks * kAttnWaves;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int NU = kMaxCallUnits / kAttnThreads;  // consecutive units a thread looks after
+    int tl[NU], sum = 0, some = 0, longest = 0;
+    if (threadIdx.x == 0) s_longest = 0;
+#pragma unroll
+    for (int i = 0; i < NU; i++) {
+        const int u = (int)threadIdx.x * NU + i;
+        tl[i] = 0;
+        if (u < n_units) {
+            const int b = u / pv.Hkv, h = u % pv.Hkv, sid = a.sid[b];
+            const int t = pv.seq_len[sid * pv.L + a.layer];
+            const int um = unit_meta(pv, sid, a.layer, h);
+            const int gl_all = pv.global_len[um], nl = min(t, pv.W);
+            s_gl[u] = gl_all;
+            s_nl[u] = nl;
+            s_um[u] = um;
+            tl[i] = ceil_tiles(global_tokens(pv, a, u, gl_all)) + ceil_tiles(nl);
+        }
+        sum += tl[i];
+        some += tl[i] > 0 ? 1 : 0;
+        longest = max(longest, tl[i]);
+    }
+    int total, used;
+    const int before_tiles = block_excl_scan(sum, s_tmp, &total);
+    const int before_units = block_excl_scan(some, s_tmp, &used);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
+    if (lane == 0) atomicMax(&s_longest, longest);  // cleared before the scans' barriers
+    __syncthreads();
+    longest = s_longest;
+    const int share_b = max(kMinBlockTiles, (total + used * kUnitStartTiles + n_blocks - 1) / n_blocks);
+    const int share_w = max(kMinWaveTiles, (total + used * kWaveStartTiles + n_waves - 1) / n_waves);
+    constexpr float kC = (float)SH::ROWB / 256.f * (G == 8 ? 1.6f : 1.f);  // a tile: its bytes, or the products of eight heads
+    const float t_blocks = 8.2f + kC * 0.25f * (float)share_b, t_waves = 3.5f + (SH::ROWB >= 256 ? 1.35f : 1.18f) * kC * (float)share_w;
+    // alone a wave streams faster than its share of the memory's rate, until all of them do
+    const float full = (float)n_units / (float)n_waves, alone = (G == 8 ? 1.f : 0.68f) * kC * (float)longest;
+    const float t_solo = 4.6f + fmaxf(alone * fmaxf(1.f, full), 1.1f + 0.85f * kC * (float)total / (float)n_waves) + 0.3f * alone * full * full;
+    const bool solo = t_solo <= fminf(t_blocks, t_waves), by_wave = solo || t_waves <= t_blocks;
+    const int begin = solo ? 0 : by_wave ? kWaveStartTiles : kUnitStartTiles, share = by_wave ? share_w : share_b;
+    if (!solo) {
+        int at = before_tiles + before_units * begin;
+#pragma unroll
+        for (int i = 0; i < NU; i++) {
+            const int u = (int)threadIdx.x * NU + i;
+            if (u <= n_units) s_ts[u] = at;  // thread n_units / NU writes the end of the list behind its own units
+            at += tl[i] + (tl[i] > 0 ? begin : 0);
+        }
+        if ((int)threadIdx.x == kAttnThreads - 1 && n_units == kMaxCallUnits) s_ts[kMaxCallUnits] = at;
+    }
+    __syncthreads();
+    const int grp = lane / LPT, sub = lane % LPT;
+    // Even shares: the KW workers of an even block and those of the odd one behind it cover 2 * KW * share tiles, te each
+    // on the even block and to on the odd one.
+    const int KW = by_wave ? kAttnWaves : 1, wid = by_wave ? (int)blockIdx.x * kAttnWaves + wave : (int)blockIdx.x;
+    const int skew = n_blocks % 2 == 0 ? share * a.skew_permille / 1000 : 0, te = share + skew, to = share - skew, pair = 2 * KW * share;
+    auto worker_of = [&](int x) __attribute__((always_inline)) {  // whose share holds tile x
+        const int pr = x / pair, r = x - pr * pair;
+        return pr * 2 * KW + (r < KW * te ? r / te : KW + (r - KW * te) / to);
+    };
+    int cur = 0, end = 0, u = 0;
+    if (solo) {
+        u = wave * n_blocks + (int)blockIdx.x;
+    } else {
+        const int i = wid % (2 * KW);
+        cur = wid / (2 * KW) * pair + (i < KW ? i * te : KW * te + (i - KW) * to);
+        end = min(s_ts[n_units], cur + (i < KW ? te : to));
+        for (int uu = blockIdx.x; uu < n_units; uu += n_blocks)  // units with nothing cached: the output is zero
+            if (s_ts[uu + 1] == s_ts[uu])
+                for (int e = threadIdx.x; e < G * D; e += kAttnThreads) a.out[(size_t)uu * G * D + e] = 0.f;
+        int lo = 0, hi = n_units - 1;  // the unit with s_ts[u] <= cur < s_ts[u + 1]
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_ts[mid] <= cur) lo = mid; else hi = mid - 1;
+        }
+        u = __builtin_amdgcn_readfirstlane(lo);
+    }
+    // what a worker has of the unit's output: a thread of a block one part, a wave's lane all of them
+    const int part0 = by_wave ? 0 : wave, part1 = by_wave ? (NT + 63) / 64 : wave + 1;
+    for (bool again = false;; again = true) {  // all conditions are block-uniform, or wave-uniform where a wave works alone
+        int np = 1, slot0 = 0, slot = 0, p0 = 0, p1 = 0;  // parts of the unit, the partials' slots, this part's tiles of the unit
+        if (solo) {
+            if (again) u += n_waves;
+            if (u >= n_units) break;
+        } else {
+            if (cur >= end) break;
+            while (s_ts[u + 1] <= cur) u++;  // also skips units without tiles
+            const int first = s_ts[u] + begin;  // the unit's first real tile
+            if (cur < first) {
+                cur = first;
+                if (cur >= end) break;  // the share ends inside the allowance: the next worker begins the unit
+            }
+            slot0 = worker_of(first);
+            np = worker_of(s_ts[u + 1] - 1) - slot0 + 1;
+            slot0 += u;
+            slot = wid + u;
+            p0 = cur - first;
+            cur = min(s_ts[u + 1], end);
+            p1 = cur - first;
+        }
+        const int um = s_um[u], gl_all = s_gl[u], nloc = s_nl[u];
+        const int gl = global_tokens(pv, a, u, gl_all);
+        if (solo) p1 = ceil_tiles(gl) + ceil_tiles(nloc);
+        const int w0 = by_wave ? p0 : p0 + (p1 - p0) * wave / kAttnWaves, w1 = by_wave ? p1 : p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
+        if (again && !by_wave) __syncthreads();  // the states in LDS are rewritten
+        float m[G], l[G], acc[G][EPL];
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            m[g] = -INFINITY;
+            l[g] = 0.f;
+#pragma unroll
+            for (int e = 0; e < EPL; e++) acc[g][e] = 0.f;
+        }
+        if (w0 < w1) {
+            uint32_t qreg[G][4];
+            const char *qp = a.q + ((size_t)u * G * D) * ES + sub * 16;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const uint4 t4 = *reinterpret_cast<const uint4 *>(qp + (size_t)g * D * ES);
+                qreg[g][0] = t4.x; qreg[g][1] = t4.y; qreg[g][2] = t4.z; qreg[g][3] = t4.w;
+            }
+            stream_tiles<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, m, l, acc, s_strips[wave], lane);
+        }
+        // the row groups of the block meet in LDS, or those of the wave (whose LDS accesses stay in order)
+        __builtin_amdgcn_wave_barrier();
+        put_states<DT, D, G>(s_st, wave, grp, sub, m, l, acc);
+        if (by_wave) __builtin_amdgcn_wave_barrier(); else __syncthreads();
+        const __amdgpu_buffer_rsrc_t r_acc = part_rsrc(a.part_acc, a.part_acc_bytes);
+        const __amdgpu_buffer_rsrc_t r_ml = part_rsrc(a.part_ml, a.part_ml_bytes);
+        float *out = a.out + (size_t)u * G * D;
+        for (int part = part0; part < part1; part++) {
+            const int x = part * 64 + lane, x0 = min(x, NT - 1) * VPT, xg = x0 / D;
+            float M, L, o[VPT];
+            if (by_wave) fold_states<TPW>(s_st, wave * TPW, x0, xg, M, L, o);
+            else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
+            if (x >= NT) continue;
+            if (np > 1) {
+                put_partial<D, G>(r_ml, r_acc, slot, x0, xg, M, L, o);
+            } else {
+                const float inv = p1 > p0 ? 1.0f / L : 0.f;  // nothing cached: zero
+#pragma unroll
+                for (int e = 0; e < VPT; e++) out[x0 + e] = p1 > p0 ? o[e] * inv : 0.f;
+            }
+        }
+        if (np == 1) continue;
+        // the hand-over, as above
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int before = 0;
+        if (by_wave) {
+            if (lane == 0) before = __hip_atomic_fetch_add(&a.counters[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            before = __builtin_amdgcn_readfirstlane(before);
+        } else {
+            __syncthreads();
+            if (threadIdx.x == 0)
+                s_arrived = __hip_atomic_fetch_add(&a.counters[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            before = s_arrived;
+        }
+        if (before != np - 1) continue;
+        asm volatile("" ::: "memory");
+        for (int part = part0; part < part1; part++) {
+            const int x = part * 64 + lane, x0 = min(x, NT - 1) * VPT, xg = x0 / D;
+            float L, o[VPT];
+            fold_partials<D, G>(r_ml, r_acc, slot0, np, x0, xg, L, o);
+            if (x >= NT) continue;
+            const float inv = 1.0f / L;
+#pragma unroll
+            for (int e = 0; e < VPT; e++) out[x0 + e] = o[e] * inv;
+        }
+        if (by_wave ? lane == 0 : threadIdx.x == 0) __hip_atomic_store(&a.counters[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // One block per compute unit: an even split is one round of blocks, and more waves on a compute unit stream slower.
 template <int DT, int D>
 static hipError_t launch_g(const View &pv, const AttendArgs &a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     switch (pv.G) {
 #define WGKV_CASE(GG)                                                                              \
-    case GG:                                                                                       \
+    case GG: {                                                                                     \
+        const auto kernel = a.n_seqs * pv.Hkv > grid ? attend_decode_many_kernel<DT, D, GG> : attend_decode_kernel<DT, D, GG>; \
         if (ev0 && ev1)  /* the events take the begin and end time stamps of this dispatch itself */ \
-            hipExtLaunchKernelGGL((attend_decode_kernel<DT, D, GG>), dim3(grid), dim3(kAttnThreads), 0, st, ev0, ev1, 0, pv, a); \
+            hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, ev0, ev1, 0, pv, a); \
         else                                                                                       \
-            hipLaunchKernelGGL((attend_decode_kernel<DT, D, GG>), dim3(grid), dim3(kAttnThreads), 0, st, pv, a); \
-        break;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, pv, a);              \
+        break;                                                                                     \
+    }
         WGKV_CASE(1)
         WGKV_CASE(2)
         WGKV_CASE(4)
