@@ -727,14 +727,17 @@ hipError_t launch_soft_attn_bwd(int n_seqs, const int32_t *n_tokens, int Hq, int
     if (e != hipSuccess) return e;
     // Waves that share keys (HS): the time of a short call is that of its longest block, the one of the first keys, so
     // blocks of a fraction of the length pay as long as compute units are idle or HS = 1 would run in one go (two
-    // blocks per compute unit); past that the single read of a tile for 128 keys is worth more.  Backward, HS = 1 / 2 / 4,
-    // in us, 8 kv heads: 1 x 1000 tokens 265 / 157 / 133, 1 x 2000 478 / 284 / 261, 1 x 3000 691 / 419 / 476,
-    // 1 x 8000 2306 / 2203 / 2688, 4 x 2000 734 / 722 / 938, 7 x 1500 792 / 825 / 1073, 1 x 12000 4374 / 4831 / 5869.
+    // blocks per compute unit, 256 of these); past that the single read of a tile for 128 keys is worth more.  Adding up what
+    // four waves have takes some 25 us more than a long block saves below 400 tokens.  Backward, HS = 1 / 2 / 4, in us, 8 kv heads:
+    // 1 x 64 tokens 34 / 29 / 46, 16 x 64 45 / 39 / 57, 32 x 128 111 / 121 / 217, 1 x 300 110 / 71 / 72, 16 x 300 196 / 194 / 304,
+    // 1 x 500 158 / 96 / 89, 4 x 500 184 / 124 / 163, 1 x 1000 267 / 158 / 136, 2 x 1000 290 / 182 / 193, 4 x 1000 329 / 301 / 345,
+    // 8 x 1000 457 / 520 / 667, 1 x 2000 478 / 284 / 261, 1 x 3000 691 / 419 / 476, 1 x 8000 2306 / 2203 / 2688,
+    // 1 x 9000 2759 / 2773 / 3446, 1 x 12000 4374 / 4831 / 5869.
     const int64_t n_wide = (int64_t)((max_t + 127) / 128) * Hkv * n_seqs;  // blocks of HS = 1
-    if (n_wide <= 128) {
+    if (n_wide <= (max_t >= 2000 ? 128 : max_t >= 400 ? 64 : 0)) {
         a.nx = (max_t + 31) / 32;
         hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel<4>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
-    } else if (n_wide <= 512) {
+    } else if (n_wide <= (max_t >= 2000 ? 512 : max_t > 128 ? 384 : 192)) {
         a.nx = (max_t + 63) / 64;
         hipLaunchKernelGGL(soft_attn_bwd_dkv_kernel<2>, dim3(a.nx * Hkv * n_seqs), dim3(256), 0, st, cs, a);
     } else {

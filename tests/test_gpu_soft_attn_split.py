@@ -1,5 +1,5 @@
 """Training-time attention where the dK/dV kernel splits a kv head's work differently: four, two or one waves over the
-same keys by the number of key blocks in the call (at most 128 and at most 512 blocks of 128 keys).  Many short
+same keys by the longest sequence (four only from 400 tokens on) and the number of 128-key blocks in the call.  Many short
 sequences reach each form at sizes that the fp64 oracle checks whole; bars as in test_gpu_soft_attn.py."""
 import math
 
@@ -13,11 +13,21 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("seed,n_seqs,longest,Hk,W", [
-    (21, 16, 128, 8, 20),   # 128 blocks: the last call of four waves per key group
-    (22, 17, 128, 8, 20),   # 136: the first of two
-    (23, 64, 65, 8, 33),    # 512: the last of two
-    (24, 65, 65, 8, 33),    # 520: the first of one
+    (21, 16, 128, 8, 20),   # 128 blocks
+    (22, 17, 128, 8, 20),   # 136
+    (23, 64, 65, 8, 33),    # 512
+    (24, 65, 65, 8, 33),    # 520
     (25, 43, 161, 8, 1),    # 688, two blocks of keys per sequence, ends inside a tile
+    (26, 1, 399, 8, 40),    # 32 blocks, two waves per key group
+    (27, 2, 400, 8, 40),    # 64: four
+    (28, 3, 401, 4, 300),   # 48: four, heads that do not divide over the XCDs
+    (29, 3, 401, 8, 40),    # 96: two
+    (30, 24, 128, 8, 20),   # 192: the last of two at this length
+    (31, 25, 128, 8, 20),   # 200: the first of one
+    (32, 24, 200, 8, 20),   # 384: the last of two
+    (33, 25, 200, 8, 20),   # 400: the first of one
+    (34, 16, 97, 3, 20),    # three heads, sequences dealt over the XCDs
+    (35, 7, 97, 5, 20),     # five heads dealt over them
 ])
 def test_every_split_matches_fp64(seed, n_seqs, longest, Hk, W):
     n_tokens = [longest - (7 * i) % longest for i in range(n_seqs)]
