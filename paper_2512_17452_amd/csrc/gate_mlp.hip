@@ -14,6 +14,8 @@
 // Bound by the GELU on the vector unit (67 M of them for 16K tokens x 8 heads x width 512) in large
 // calls, by the chain of a wave's products and GELUs in small ones.  Measured: 16K tokens 69 -> 52 us
 // (33 us of which are the vector instructions alone at 2.2 GHz), 1K tokens 23 -> 15.
+#include <algorithm>
+
 #include "wgkv_dev.h"
 
 namespace wgkv {
@@ -346,7 +348,11 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         //   128 tokens, two groups of waves with half the units each  20   23    44    65    86
         //   128 tokens, three blocks per compute unit                 23   26    35    46    63
         //   256 tokens (a product's W1 operand used twice)            34   37    42    53    56
-        const int64_t cols = n_tokens * n_kv_heads;
+        // One or two chunks of hidden units leave nothing to split over waves, one chunk nothing to use twice either: those calls
+        // count as of the size that takes the third form.  Width 32, 33 / 4096 / 16384 tokens x 8 heads: 6.3 / 7.5 / 19.3 us, by
+        // their own size 8.5 / 9.6 / 20.5.
+        const int64_t pairs = n_tokens * n_kv_heads;
+        const int64_t cols = width == kGmUnits ? 98304 : width <= 2 * kGmUnits ? std::max<int64_t>(pairs, 98304) : pairs;
 #define WGKV_GM(D_, CB_, US_)                                                                                            \
     hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_>),                                                            \
                        dim3((unsigned)((n_tokens + 4 * kGmTokens * CB_ - 1) / (4 * kGmTokens * CB_)), n_kv_heads),       \

@@ -14,7 +14,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,Hk,d,width", [(1, 1, 64, 32), (33, 3, 128, 96), (1024, 8, 64, 160),     # split, one round full
                                           (1025, 8, 128, 32), (4096, 8, 64, 96),                    # two unit groups
                                           (4097, 8, 128, 32), (12288, 8, 64, 32),                   # one group
-                                          (12289, 8, 128, 64), (12700, 8, 64, 96)])                 # two columns a wave
+                                          (12289, 8, 128, 64), (12700, 8, 64, 96),                  # two columns a wave
+                                          # widths up to 64 are one group (two columns past the last line with 64)
+                                          (1, 8, 128, 64), (12300, 8, 128, 32), (1024, 8, 128, 96), (1025, 8, 128, 96),
+                                          (4097, 8, 64, 96), (12288, 8, 128, 96)])
 def test_every_form_matches_fp64(T, Hk, d, width):
     ins = _inputs(torch.bfloat16, T, Hk, d, width, T + width)
     g = wg.gate_mlp_scores(*[x.cuda() for x in ins], eps=1e-6).cpu().numpy()
