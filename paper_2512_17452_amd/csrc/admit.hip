@@ -20,6 +20,7 @@ namespace wgkv {
 constexpr int kPrefillBlk = 512;   // leaving tokens per block of prefill_scatter_kernel (256 threads), and per count
 constexpr int kTok = kPrefillBlk / 256;  // tokens per thread
 constexpr int kPlanThreads = 1024; // a block of prefill_plan_kernel
+constexpr int kCountHeads = 16;    // kv heads whose tokens such a block counts (a power of two up to 64)
 
 struct PrefillArgs {
     int layer;
@@ -71,9 +72,10 @@ __device__ __forceinline__ float leaving_score(const View &pv, const PrefillArgs
 }
 
 // One launch for what used to be two (count: a block per 512 tokens and unit; plan: one block).  Both are latency: 3 MB
-// of scores and a few thousand integers.  A block counts 512 leaving tokens of a sequence for all its heads at once (the
+// of scores and a few thousand integers.  A block counts 512 leaving tokens of a sequence for up to 16 heads at once (the
 // scores of a token are contiguous over the heads, so its loads are too; one head's alone are a stride of n_kv_heads apart
-// and every head reads the same lines), and the block that finishes last goes on to the plan.  No block waits.
+// and every head reads the same lines; 128 heads in one block take 28 -> 39 us with a call of 512 tokens, spread 26), and the
+// block that finishes last goes on to the plan.  No block waits.
 // Counts cross compute units inside the launch: they are written and read with device scope, and a block counts itself
 // as finished only after its own stores are complete.
 // Measured: 100K tokens x 8 heads 7.8 + 7.8 us in two launches, 12.9 here; 8 x 18K tokens 8.6 + 18.4 -> 14.0.
@@ -92,22 +94,26 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, Cal
         const int b = blockIdx.y, i0 = blockIdx.x * kPrefillBlk;
         const int t0 = cs.t0[b], T = cs.ntok[b], base = cs.base[b];
         const int lo = max(0, t0 - pv.W), hi = max(0, t0 + T - pv.W), n_leave = hi - lo;
+        const int h0 = blockIdx.z * kCountHeads, nh = min(kCountHeads, H - h0);  // the block's heads
         if (a.admit_out) {
-            const int n = min(kPrefillBlk, T - i0) * H;  // <= 0 past the end
-            const size_t row0 = (size_t)(base + i0) * H;
-            for (int e = threadIdx.x; e < n; e += kPlanThreads) a.admit_out[row0 + e] = (uint8_t)(a.g[row0 + e] >= a.tau);
+            const int n = min(kPrefillBlk, T - i0) * nh;  // <= 0 past the end
+            const size_t row0 = (size_t)(base + i0) * H + h0;
+            for (int e = threadIdx.x; e < n; e += kPlanThreads) {
+                const size_t x = row0 + (size_t)(e / nh) * H + e % nh;
+                a.admit_out[x] = (uint8_t)(a.g[x] >= a.tau);
+            }
         }
         if (i0 < n_leave) {  // block-uniform
-            for (int h = threadIdx.x; h < H; h += kPlanThreads) s_adm[h] = 0;
+            for (int h = threadIdx.x; h < nh; h += kPlanThreads) s_adm[h] = 0;
             __syncthreads();
-            // element e = (token i0 + e / H of the leaving ones, head e % H)
-            const int n = min(kPrefillBlk, n_leave - i0) * H;
-            const int um0 = unit_meta(pv, cs.sid[b], a.layer, 0);
+            // element e = (token i0 + e / nh of the leaving ones, head h0 + e % nh)
+            const int n = min(kPrefillBlk, n_leave - i0) * nh;
+            const int um0 = unit_meta(pv, cs.sid[b], a.layer, h0);
             auto score = [&](int e) __attribute__((always_inline)) {
-                const int p = lo + i0 + e / H;
-                return p < t0 ? pv.ring_g[(size_t)(um0 + e % H) * pv.W + (p % pv.W)] : a.g[(size_t)(base + p - t0) * H + e % H];
+                const int p = lo + i0 + e / nh;
+                return p < t0 ? pv.ring_g[(size_t)(um0 + e % nh) * pv.W + (p % pv.W)] : a.g[(size_t)(base + p - t0) * H + h0 + e % nh];
             };
-            if (kPlanThreads % H == 0) {  // a thread meets one head only
+            if (kPlanThreads % nh == 0) {  // a thread meets one head only
                 int c = 0;
                 for (int e = threadIdx.x; e < n; e += 4 * kPlanThreads) {
                     float x[4];
@@ -116,23 +122,22 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(View pv, Cal
 #pragma unroll
                     for (int k = 0; k < 4; k++) c += (e + k * kPlanThreads < n && x[k] >= a.tau) ? 1 : 0;
                 }
-                if (64 % H == 0)  // lanes with the same head
-                    for (int o = H; o < 64; o <<= 1) c += __shfl_xor(c, o);
-                if (64 % H != 0 || lane < H) atomicAdd(&s_adm[threadIdx.x % H], c);
+                for (int o = nh; o < 64; o <<= 1) c += __shfl_xor(c, o);  // lanes with the same head
+                if (lane < nh) atomicAdd(&s_adm[lane], c);
             } else {
                 for (int e = threadIdx.x; e < n; e += kPlanThreads)
-                    if (score(e) >= a.tau) atomicAdd(&s_adm[e % H], 1);
+                    if (score(e) >= a.tau) atomicAdd(&s_adm[e % nh], 1);
             }
             __syncthreads();
-            for (int h = threadIdx.x; h < H; h += kPlanThreads)
-                __hip_atomic_store(&a.cnt[(size_t)(b * H + h) * a.nblk_max + blockIdx.x], s_adm[h], __ATOMIC_RELAXED,
+            for (int h = threadIdx.x; h < nh; h += kPlanThreads)
+                __hip_atomic_store(&a.cnt[(size_t)(b * H + h0 + h) * a.nblk_max + blockIdx.x], s_adm[h], __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's counts are complete at device scope
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int n_blocks = (int)(gridDim.x * gridDim.y);
+        const int n_blocks = (int)(gridDim.x * gridDim.y * gridDim.z);
         s_last = n_blocks == 1 || __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_blocks - 1;
         s_err = 0;
         s_over = 0;
@@ -779,7 +784,7 @@ hipError_t launch_prefill(const View &pv, const CallSeqs &cs, int layer, float t
     const int n_units = cs.n * pv.Hkv;
     int gx = a.nblk_max;
     if (admit_out) gx = max(gx, (max_T + kPrefillBlk - 1) / kPrefillBlk);
-    hipLaunchKernelGGL(prefill_plan_kernel, dim3(gx, cs.n), dim3(kPlanThreads), 0, st, pv, cs, a, pv.unit_counters);
+    hipLaunchKernelGGL(prefill_plan_kernel, dim3(gx, cs.n, (pv.Hkv + kCountHeads - 1) / kCountHeads), dim3(kPlanThreads), 0, st, pv, cs, a, pv.unit_counters);
     // blocks 0 .. nblk_max-1 of a unit: leaving tokens (and the ring slots they vacate); the rest: ring rows
     // that go to slots still empty (max_empty_ring_rows: the most ring rows of a sequence that has any such)
     const int lpr = pv.row_bytes >> 4;
