@@ -22,7 +22,7 @@ struct EvictArgs {
     const float *scores;   // [n_units][stride]
     long long stride;
     int32_t *n_evicted;    // optional [n_units]
-    int slices;            // blocks per unit: 2 or 4
+    int slices;            // blocks per unit: 1, 2 or 4
 };
 
 // Entries a unit loses.  A cache longer than the caller's score row (the host's bound was stale) is left alone.
@@ -115,6 +115,8 @@ __global__ __launch_bounds__(kEvictThreads) void evict_compact_kernel(View pv, C
         __syncthreads();
         // the tile's rows in turns of eight per thread (one turn at 128 bytes a row)
         for (int r0 = 0; r0 < n_stay; r0 += rows_per_turn * 8) {
+            const int last = min(r0 + rows_per_turn * 8, n_stay) - 1;
+            if (s_src[last] == s_dst[last]) continue;  // nothing before it went: the turn's rows stay where they are (block-uniform)
             uint4 x[8];
             int pg[8];
 #pragma unroll
@@ -185,7 +187,7 @@ __global__ __launch_bounds__(kEvictThreads) void evict_release_kernel(View pv, C
 size_t evict_ws_bytes(int n_units) { return (size_t)((n_units * 4 + 255) / 256) * 256; }
 
 hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, const float *scores,
-                              int64_t stride, float frac, int32_t *n_evicted, hipStream_t st) {
+                              int64_t stride, float frac, int32_t *n_evicted, int64_t max_len, hipStream_t st) {
     const int n_units = cs.n * pv.Hkv;
     if (pv.row_bytes % 128 != 0 || pv.row_bytes / 8 > kEvictThreads) return hipErrorNotSupported;
     EvictArgs a;
@@ -194,8 +196,12 @@ hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, con
     a.scores = scores;
     a.stride = stride;
     a.n_evicted = n_evicted;
-    // 128 bytes a block and row at the least; four blocks per head while that does not exceed a round of blocks by much
-    a.slices = pv.row_bytes >= 256 && n_units <= 256 ? 4 : 2;
+    // Blocks per head as long as they are one round (a block of 1024 threads fills a compute unit), then one, as every block
+    // finds the cut for itself, or two where the rows are what takes the time (max_len: the host's bound of the longest head);
+    // 128 bytes a block and row at the least are kept for four.  us for 1 / 2 / 4, 8 heads of 256-byte rows: 8 sequences of 2250
+    // entries 54 / 40 / 36, 16 of 300 20 / 18 / 27 and of 2250 58 / 49 / 63, 32 of 300 23 / 31 / 51, 64 of 300 43 / 58 / 95,
+    // 40 of 1000 64 / 70 / 83, of 4500 287 / 249 / 258.
+    a.slices = n_units <= 64 && pv.row_bytes >= 256 ? 4 : n_units <= 128 || (n_units > 256 && max_len >= 2048) ? 2 : 1;
     hipLaunchKernelGGL(evict_compact_kernel, dim3(n_units * a.slices), dim3(kEvictThreads), 0, st, pv, cs, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -31,7 +31,7 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
                                float scale, int pool_w, float *raw, float *out, int64_t stride, int64_t max_len,
                                void *ws, hipStream_t st);
 hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, const float *scores,
-                              int64_t stride, float frac, int32_t *n_evicted, hipStream_t st);
+                              int64_t stride, float frac, int32_t *n_evicted, int64_t max_len, hipStream_t st);
 size_t quest_landmark_bytes(const View &pv);
 hipError_t launch_quest_update(const View &pv, const CallSeqs &cs, int layer, void *landmarks, int reset,
                                hipStream_t st);
@@ -800,15 +800,18 @@ int wgkv_evict_apply(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int32_t 
     CallSeqs cs;
     memset(&cs, 0, sizeof(cs));
     cs.n = n_seqs;
+    int64_t max_len = 0;
     for (int b = 0; b < n_seqs; b++) {
         const size_t sl = (size_t)seq_ids_host[b] * c.n_layers + layer;
         cs.sid[b] = seq_ids_host[b];
         cs.t0[b] = p->seq_len_h[sl];
         // a score row must cover every entry the head may hold (the host knows an upper bound)
-        for (int h = 0; h < H; h++)
+        for (int h = 0; h < H; h++) {
             if (p->g_ub[sl * H + h] > stride) return WGKV_ERR_INVALID_ARG;
+            max_len = std::max<int64_t>(max_len, p->g_ub[sl * H + h]);
+        }
     }
-    if (launch_evict_apply(p->view, cs, layer, scores_dev, stride, frac, n_evicted_out_dev,
+    if (launch_evict_apply(p->view, cs, layer, scores_dev, stride, frac, n_evicted_out_dev, max_len,
                            (hipStream_t)stream) != hipSuccess)
         return WGKV_ERR_HIP;
     // bounds after the call: N - floor(frac N) does not decrease with N, so it maps an upper

@@ -96,21 +96,28 @@ def test_evict_apply_many_entries_and_units():
     pair.check_attend(0, seqs, q)
 
 
-@pytest.mark.parametrize("dtype,d,Hk,frac", [(wg.BF16, 128, 96, 0.3), (wg.F32, 128, 96, 0.1), (wg.BF16, 64, 90, 0.5)])
-def test_evict_apply_more_than_256_units(dtype, d, Hk, frac):
-    """Two blocks per head instead of four, each with 64 to 256 bytes of a row, several turns to a tile of 1024 entries, and
-    heads of more than one such tile."""
+@pytest.mark.parametrize("dtype,d,Hk,lens,rate,frac", [
+    (wg.BF16, 128, 22, [1300, 170, 90], 0.1, 0.3), (wg.F32, 128, 40, [1300, 170, 90], 0.1, 0.1),     # 66 and 120 units: two blocks a head
+    (wg.BF16, 128, 43, [1300, 170, 90], 0.1, 0.3), (wg.BF16, 64, 90, [1300, 170, 90], 0.1, 0.5),     # 129 and 270: one
+    (wg.F32, 64, 96, [1300, 170, 90], 0.1, 0.9), (wg.F32, 128, 90, [1300, 170, 90], 0.1, 0.2),
+    (wg.BF16, 128, 90, [2200, 170, 90], 0.05, 0.2)])                                                   # 270 units, a long head: two
+def test_evict_apply_of_many_units(dtype, d, Hk, lens, rate, frac):
+    """One or two blocks per head instead of four, each with 64 to 512 bytes of a row pair, several turns to a tile of 1024
+    entries, heads of more than one such tile, and heads whose first entries all stay."""
     rng = np.random.default_rng(Hk + d)
-    P, W, lens = 16, 16, [1300, 170, 90]
+    P, W = 16, 16
     max_gp = lens[0] // P + 4
     pair = Pair(1, Hk, Hk, d, dtype, P, W, 3, max_gp, Hk * sum(-(-n // P) + 3 for n in lens), max_call_seqs=3,
                 max_call_tokens=sum(lens))
-    rates = np.where(np.arange(Hk) % 24 == 0, 0.97, 0.1)
+    rates = np.where(np.arange(Hk) % 24 == 0, 0.97, rate)
     k, v, g = rand_tokens(rng, sum(lens), Hk, d, pair.tdt, rates=list(rates))
     pair.prefill(0, [0, 1, 2], lens, k, v, g, 0.5)
     pair.pool.status()  # the score rows are as long as the heads, not as the host's bound
     assert max(pair.orc.global_len(0, 0, h) for h in range(Hk)) > 1024
-    pair.evict(0, [2, 0, 1], _scores(rng, pair, 0, [2, 0, 1], "ties"), frac)
+    sc = _scores(rng, pair, 0, [2, 0, 1], "ties")
+    late = _scores(rng, pair, 0, [2, 0, 1], "uniform")
+    late[1::2, :1100] += 1.0  # every other head: only entries past the first tile go, as far as there are any
+    pair.evict(0, [2, 0, 1], sc if frac > 0.25 else late, frac)
     pair.check_state()
 
 
