@@ -67,6 +67,7 @@ struct PfShape {
 struct PrefillAttnArgs {
     int nx;                 // blocks per (sequence, kv head) of the launch
     int rank0;              // place in the order of the launch's first unit
+    int ordered;            // else the units in their own order, and `order` is only somewhere to read from
     const int32_t *order;   // [n_units] (sequence, kv head) units, the one with the longest global cache first
     const int32_t *pick;    // admitted chunk positions of every unit, ascending (pick_of), or NULL
     const int32_t *picked;  // how many of them lie below position 32 i, for every i (picked_of)
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
     // differ several-fold in work: with the long ones at the front the launch does not end on a
     // late-started long one, and every unit is spread evenly over the XCDs (giving each XCD whole
     // heads, for the sake of its L2, leaves the XCDs as unbalanced as the heads are).
-    const int unit = a.order[a.rank0 + blockIdx.x / a.nx];
+    const int rank = a.rank0 + (int)(blockIdx.x / a.nx), unit = a.ordered ? a.order[rank] : rank;
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
     const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
@@ -503,7 +504,7 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
 
     // order of the blocks: as in attend_prefill_kernel
-    const int unit = a.order[a.rank0 + blockIdx.x / a.nx];
+    const int rank = a.rank0 + (int)(blockIdx.x / a.nx), unit = a.ordered ? a.order[rank] : rank;
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
     const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
@@ -820,9 +821,10 @@ static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnAr
     return launch_units(attend_prefill_kernel<D, G>, PfShape<D, G>::Q, 512, pv, cs, a, max_t, st);
 }
 
-// Lists of picked chunk keys pay as soon as some block of the call has keys behind all its windows, and need room.
+// Lists of picked chunk keys pay as soon as some block of the call has keys behind all its windows, and need room; without them
+// and without a need of the order there is nothing to look at.
 hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, float tau, const float *g, void *ws,
-                               size_t ws_bytes, const int32_t **order, const int32_t **pick, const int32_t **picked,
+                               size_t ws_bytes, bool need_order, const int32_t **order, const int32_t **pick, const int32_t **picked,
                                hipStream_t st) {
     int64_t total = 0;
     int max_t = 0;
@@ -834,7 +836,8 @@ hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, fl
     const bool lists = max_t > pv.W && ws_bytes >= attend_prefill_ws_bytes(pv, cs.n, total);
     int32_t *o = (int32_t *)ws, *p = lists ? o + kPfOrderBytes / sizeof(int32_t) : nullptr;
     int32_t *c = lists ? p + (size_t)pv.Hkv * total : nullptr;
-    hipLaunchKernelGGL(prefill_look_kernel, dim3((lists ? n_units : 0) + 1), dim3(256), 0, st, pv, cs, layer, tau, g, o, p, c);
+    if (lists || need_order)
+        hipLaunchKernelGGL(prefill_look_kernel, dim3((lists ? n_units : 0) + 1), dim3(256), 0, st, pv, cs, layer, tau, g, o, p, c);
     *order = o;
     *pick = p;
     *picked = c;
@@ -844,7 +847,7 @@ hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, fl
 // bf16 pools of every head_dim and group size (fp32 pools: launch_attend_prefill_f32)
 hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, const void *q,
                                  const void *k, const void *v, const float *g, float tau,
-                                 float scale, float *out, void *ws, size_t ws_bytes, hipStream_t st) {
+                                 float scale, float *out, void *ws, size_t ws_bytes, int n_cu, hipStream_t st) {
     if (pv.dtype != WGKV_BF16) return hipErrorNotSupported;
     PrefillAttnArgs a;
     a.layer = layer;
@@ -859,7 +862,12 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
     if (max_t == 0) return hipSuccess;
     if (max_t >= 1 << 28) return hipErrorInvalidValue;  // the blocks of one unit have to fit a launch
-    hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &a.order, &a.pick, &a.picked, st);
+    // The order is for launches of more than one round of blocks (a block per compute unit, two of the tiles kernel): below, its
+    // own launch is all it adds.  us with / without: 33 tokens of 16 / 8 heads of 128 12.5 / 9.8, 16 x 100 of 32 / 8 24.2 / 19.4.
+    const bool tiles = pv.d == 128 && pv.G == 4;
+    const int per_block = tiles ? kPfTilesQ : 256 / pv.G;
+    a.ordered = (int64_t)((max_t + per_block - 1) / per_block) * pv.Hkv * cs.n > (int64_t)n_cu * (tiles ? 2 : 1);
+    hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, a.ordered, &a.order, &a.pick, &a.picked, st);
     if (e != hipSuccess) return e;
     if (pv.d == 128) {
         switch (pv.G) {

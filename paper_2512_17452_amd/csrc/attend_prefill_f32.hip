@@ -28,7 +28,7 @@ namespace wgkv {
 typedef __attribute__((ext_vector_type(16))) float pw_f32x16_t;
 
 hipError_t launch_prefill_look(const View &pv, const CallSeqs &cs, int layer, float tau, const float *g, void *ws,
-                               size_t ws_bytes, const int32_t **order, const int32_t **pick, const int32_t **picked,
+                               size_t ws_bytes, bool need_order, const int32_t **order, const int32_t **pick, const int32_t **picked,
                                hipStream_t st);
 
 struct PrefillF32Args {
@@ -315,7 +315,7 @@ hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int lay
     a.pick = a.picked = nullptr;
     if (max_t > pv.W) {
         const int32_t *order;
-        const hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, &order, &a.pick, &a.picked, st);
+        const hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, false, &order, &a.pick, &a.picked, st);
         if (e != hipSuccess) return e;
     }
     // Blocks for the tiles that there are: a launch holds fewer than 2^32 threads, and one long chunk beside many short ones

@@ -68,7 +68,7 @@ size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q);
 size_t attend_prefill_ws_min_bytes();
 hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, const void *q,
                                  const void *k, const void *v, const float *g, float tau,
-                                 float scale, float *out, void *ws, size_t ws_bytes, hipStream_t st);
+                                 float scale, float *out, void *ws, size_t ws_bytes, int n_cu, hipStream_t st);
 hipError_t launch_attend_prefill_f32(const View &pv, const CallSeqs &cs, int layer, const void *q, const void *k,
                                      const void *v, const float *g, float tau, float scale, float *out, void *ws,
                                      size_t ws_bytes, hipStream_t st);
@@ -644,7 +644,7 @@ int wgkv_attend(wgkv_pool *p, int32_t layer, int32_t n_seqs, const int32_t *seq_
     if (p->ev0 && hipEventRecord(p->ev0, st) != hipSuccess) return WGKV_ERR_HIP;
     const hipError_t e = p->cfg.dtype == WGKV_BF16
                              ? launch_attend_prefill(p->view, cs, layer, q_dev, k_chunk_dev, v_chunk_dev, g_chunk_dev,
-                                                     tau, scale, out_dev, workspace_dev, workspace_bytes, st)
+                                                     tau, scale, out_dev, workspace_dev, workspace_bytes, p->n_cu, st)
                              : launch_attend_prefill_f32(p->view, cs, layer, q_dev, k_chunk_dev, v_chunk_dev,
                                                          g_chunk_dev, tau, scale, out_dev, workspace_dev, workspace_bytes,
                                                          st);

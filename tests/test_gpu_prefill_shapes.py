@@ -219,3 +219,18 @@ def test_one_long_chunk_beside_many_short_ones(dtype, Hk, G, long_n, n_short):
     assert torch.equal(whole[:at], attend(list(range(n_short - 1)), 0, at))
     assert torch.equal(whole[at:at + long_n], attend([n_short - 1], at, at + long_n))
     assert torch.equal(whole[at + long_n:], attend([n_short + 1], at + long_n, tot))
+
+
+@pytest.mark.parametrize("d,G,B,T", [(128, 4, 16, 128), (128, 4, 16, 129), (64, 4, 8, 256), (64, 4, 8, 257)])
+def test_one_round_of_blocks_and_one_more(d, G, B, T):
+    """Launches of one round of blocks take the units as they come, larger ones by the length of their global caches."""
+    W, P, tau, worst = 300, 16, 0.6, 0.0
+    first = [(37 * s) % 400 + 1 for s in range(B)]
+    for s, t0, K, V, g, q, out in _feed(wg.BF16, d, G, 8, [first, [T] * B], W, P, tau, seed=T):
+        if t0 == 0 and len(q) > 40:
+            continue  # the second call is what this is about
+        rows = np.arange(0, len(q), 9)
+        ref = attend_definition(K, V, g, q[rows], t0 + rows, W, tau, 1 / math.sqrt(d))
+        assert np.isfinite(out).all(), (s, t0)
+        worst = max(worst, np.abs(out[rows] - ref).max())
+    assert worst <= _tol(wg.BF16, d, G), worst
