@@ -95,7 +95,8 @@ typedef struct {
  *   err_flag   int32                 sticky: 0 ok, else first WGKV_ERR_* seen on device
  *   ahead      int32 [S][L][H]       (t << 1) | promoted once wgkv_decode_promote has handled the
  *                                    step that feeds token t of this head, else -1
- *   unit_counters int32 [WGKV_MAX_CALL_UNITS]  scratch of wgkv_attend, zero between calls
+ *   unit_counters int32 [WGKV_MAX_CALL_UNITS]  arrival counters of wgkv_attend's decode form, the admission calls and
+ *                                    wgkv_free_seq, zero between calls
  * Pool: element [page][0=K,1=V][slot 0..P-1][head_dim]. */
 typedef struct {
     size_t seq_len, global_len, local_pt, global_pt, ring_g, free_stack, free_top, err_flag;
@@ -315,7 +316,8 @@ int wgkv_attend(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int32_t *s
                 float *out_dev, void *workspace_dev, size_t workspace_bytes, wgkv_stream stream);
 
 /* Optional tuning of the decode form of wgkv_attend to the machine.  The tiles of a launch are
- * split evenly over its blocks except for one correction: blocks go to the 8 XCDs of the GPU in
+ * split evenly over its blocks (or, where that is cheaper, its waves; calls of several (sequence, kv
+ * head) units per block may also give whole units to waves) except for one correction: blocks go to the 8 XCDs of the GPU in
  * turn, and the odd XCD of each pair streams a few per cent slower than the even one, by an amount
  * that differs between machines.  This call runs the decode attention of every layer for the
  * given sequences (arguments as for wgkv_attend, the same queries for every layer; the cache is
@@ -416,7 +418,10 @@ int wgkv_attend_selected(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const i
  *   scores_raw_out_dev, scores_out_dev : two distinct float buffers [n_seqs * n_kv_heads][stride];
  *               entries [0, N) of each row are written, the rest is left alone; stride must
  *               cover the host's upper bound of every head's length (see wgkv_status)
- * fp32 arithmetic; sums run in a fixed order, so the result repeats run to run.  The
+ * fp32 arithmetic; sums run in a fixed order, so the result repeats run to run (the order over the
+ * observation rows follows the call's size: the number of heads and the host's bound of their lengths).
+ * q_obs_dev may have any alignment; from 16 bytes on bf16 / head_dim 128 / group 4 with n_obs a multiple
+ * of 8 runs on the matrix cores.  The
  * workspace from wgkv_query_sizes covers n_obs <= 256 (n_units * n_obs * group * 8 bytes
  * are needed); n_obs <= 4096, pool_w <= 255, the group size must divide 64.
  * Errors: INVALID_ARG, WORKSPACE, HIP. */
@@ -440,6 +445,7 @@ int wgkv_evict_scores(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int3
  *                in a graph since the last wgkv_status) is left as it is, and
  *                wgkv_evict_scores writes no score past the end of a row
  *   n_evicted_out_dev : optional int32 [n_seqs * n_kv_heads]
+ *   workspace_dev : at least 4 bytes per (sequence, kv head), rounded up to 256; reserved, nothing is kept there
  * Errors: INVALID_ARG, WORKSPACE, HIP. */
 int wgkv_evict_apply(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int32_t *seq_ids_host,
                      const float *scores_dev, int64_t stride, float frac,

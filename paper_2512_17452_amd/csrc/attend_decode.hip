@@ -6,8 +6,9 @@
 // Sec. 2.1 equation; head-to-batch folding of App. A).  The cached tokens of all
 // units are cut into 16-token tiles, and the tiles are split over the blocks of the launch,
 // one block per compute unit (the split-then-reduce balancing of App. E "Decode phase",
-// without a second launch and without any block waiting for another).  Two ways of
-// cutting, and every block works out by itself which one has the shorter longest block:
+// without a second launch and without any block waiting for another).  For calls of at most
+// one unit per block there are two ways of cutting (attend_decode_kernel), and every block works
+// out by itself which one has the shorter longest block:
 //   pieces  every unit in equal pieces of at least 24 tiles, one piece per block: what a
 //           small call wants, whose time is the chain in front of and behind its loops
 //           (launch, lengths, page ids, first rows, publish, count, fold), and a unit of
@@ -18,6 +19,8 @@
 // The four waves of a block take a quarter each of what the block has of a unit and meet
 // in LDS; a unit that several blocks share is put together from one partial (m, l, acc)
 // per block, by all threads of the block that arrives last, in a fixed order.
+// Calls of more units than blocks go to attend_decode_many_kernel, which can also give whole units or
+// even shares to single waves; its three ways stand above it.
 // Measured against shares and partials per wave, which need 16 tiles a wave to be worth
 // their fold (us per launch, one layer): 180 tokens x 2 heads fp32 13.4 -> 7.4; batch 8 at
 // 1K 19.5 -> 11.7; batch 1 at 32K (26 MB) 27.3 -> 17.8; batch 2 at 60K 41.5 -> 26.9; batch 4
@@ -61,10 +64,10 @@ struct AttendArgs {
     float scale_log2e;        // scale * log2(e)
     const char *q;            // [n_seqs][Hq][d]
     float *out;               // [n_seqs][Hq][d]
-    float *part_ml;           // [(waves + n_units)][G][2]
-    float *part_acc;          // [(waves + n_units)][G][d]
+    float *part_ml;           // [(waves of the launch + n_units)][G][2]: a worker's partial of unit u is in slot worker + u
+    float *part_acc;          // [(waves of the launch + n_units)][G][d]
     uint32_t part_ml_bytes, part_acc_bytes;
-    int32_t *counters;        // [n_units] zero between calls: waves (blocks) done per unit
+    int32_t *counters;        // [n_units] zero between calls: workers (blocks, or waves in calls of many units) done per unit
     // optional page selection: only these pages of each head's global cache are read
     const int32_t *sel_pages; // [n_units][sel_stride] ascending indices into the head's global table, or NULL
     const int32_t *sel_count; // [n_units]
@@ -881,7 +884,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
 //   blocks  the same over blocks, as in the kernel above: for long ones.
 // Every block estimates the three in us from the lengths and takes the cheapest.  The model is a fit to every way of 234
 // calls (33 to 128 sequences of 100 to 8000 tokens, even and ragged heads, all head shapes); its choice is 0.7 % behind the best
-// way in the mean and 8 % at most for the main head shape.  Against the kernel above (us; main head shape, a third of the tokens
+// way in the mean and 8 % at most for the main head shape.  The fit was taken with 256 blocks.  Against the kernel above (us; main head shape, a third of the tokens
 // admitted): 33 x 100 tokens 15.5 -> 11.4, 64 x 300 24.3 -> 16, 128 x 300 40.5 -> 22, 128 x 1000 55 -> 38; heads from 1 to
 // 90 %: 64 x 1000 27 -> 25.5, 128 x 1000 44 -> 36; 33 x 4000 and longer calls are the same to 3 % (more to look at in front).
 constexpr int kMinWaveTiles = 16, kWaveStartTiles = 12;
@@ -1096,7 +1099,8 @@ static hipError_t launch_g(const View &pv, const AttendArgs &a, int grid, hipStr
     return hipGetLastError();
 }
 
-// workspace bytes for a decode attend launched with at most grid_max blocks
+// workspace bytes for a decode attend launched with at most grid_max blocks: a partial per wave (calls of many units) and one
+// more per unit, as the slots of two workers on one unit are a unit's number apart
 size_t attend_decode_ws_bytes(const View &pv, int n_seqs, int grid_max) {
     const size_t n_units = (size_t)n_seqs * pv.Hkv, slots = (size_t)grid_max * kAttnWaves + n_units;
     size_t b = slots * pv.G * 2 * sizeof(float);

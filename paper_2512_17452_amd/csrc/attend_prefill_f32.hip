@@ -10,7 +10,7 @@
 // matrix instruction is so slow (64 clocks for 4096 multiply-adds) that a tile of 64-element heads occupies a SIMD for
 // 4096 clocks, so a short call needs its keys spread over the SIMDs, and sharing a tile between waves would gain
 // nothing: the 16 KiB of a tile's rows per 4096 clocks and wave come out of the L2.  Measured on 512 tokens of 8 / 2
-// heads of 64: 73 us with one wave of plain arithmetic per (query, head), 20 us here.
+// heads of 64, window 64 / 1024, lists included: 67 / 112 us with one wave of plain arithmetic per (query, head), 15 / 19 here.
 //
 // The block's queries sit in LDS (in the space that the fold uses at the end): the accumulators of 128 elements, a key
 // row's half and the weights leave no registers for them.

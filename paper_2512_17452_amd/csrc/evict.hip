@@ -184,6 +184,8 @@ __global__ __launch_bounds__(kEvictThreads) void evict_release_kernel(View pv, C
     if (threadIdx.x == 0) *pv.free_top = top + total;
 }
 
+// What the removal asks of the caller's workspace.  Its kernels keep nothing there (the release works out by itself what every
+// unit gives back); the bound is part of the entry point and stays, so that what was refused is refused.
 size_t evict_ws_bytes(int n_units) { return (size_t)((n_units * 4 + 255) / 256) * 256; }
 
 hipError_t launch_evict_apply(const View &pv, const CallSeqs &cs, int layer, const float *scores,

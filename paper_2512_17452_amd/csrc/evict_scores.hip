@@ -181,7 +181,9 @@ __global__ __launch_bounds__(256) void evict_weights_kernel(View pv, CallSeqs cs
 // group of 4, n_obs a multiple of 8), v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  A wave keeps its columns as
 // operands in registers and all waves of a block read the streamed rows from LDS tiles that are requested a tile ahead.
 // Both are bound by the vector unit (a maximum, a multiply-add, a quarter-rate exponential and a sum per score take 26
-// of its clocks where the products take 16), which wants other waves' products and reads beside it.
+// of its clocks where the products take 16), which wants other waves' products and reads beside it.  For the weights
+// that is not a bound of the method: the largest of a group's four weights is the exponential of the largest exponent, so one
+// exponential would do where four are taken.
 typedef __attribute__((ext_vector_type(16))) float es_f32x16_t;
 constexpr int kEmD = 128;
 

@@ -348,6 +348,8 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         //   128 tokens, two groups of waves with half the units each  20   23    44    65    86
         //   128 tokens, three blocks per compute unit                 23   26    35    46    63
         //   256 tokens (a product's W1 operand used twice)            34   37    42    53    56
+        // The rounds are those of 256 compute units, and other widths than 512 (and 32, below) were not timed for the lines:
+        // a pair's work grows with the width in every form alike, what a form leaves idle does not depend on it.
         // One or two chunks of hidden units leave nothing to split over waves, one chunk nothing to use twice either: those calls
         // count as of the size that takes the third form.  Width 32, 33 / 4096 / 16384 tokens x 8 heads: 6.3 / 7.5 / 19.3 us, by
         // their own size 8.5 / 9.6 / 20.5.
