@@ -451,6 +451,9 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
         // A wave that walks the whole window alone takes 25 us for 256 observation rows, however few keys there are: waves
         // share keys as long as compute units are idle.  TS = 1 / 2 / 4, in us, 8 kv heads, 256 rows: 1 sequence of 2250
         // entries a head 26 / - / 17, 2 of 2250 27 / 24 / 28, 2 of 4500 39 / - / 43, 4 of 3000 40 / - / 56.
+        // The lines are those of 256 rows and 256 compute units.  Calls of 1 to 1024 rows were timed against one key a lane and 128
+        // keys a block throughout, the form before: slower only for some 50 entries in each of many heads (40 sequences, 64 rows
+        // 24 -> 32 us), where most of a block of 256 keys is empty.
         const int64_t n_blocks = (int64_t)((max_len + 255) / 256) * n_units;  // of TS = 1
         if (n_blocks <= 96)
             hipLaunchKernelGGL(evict_weights_mfma_kernel<4>, dim3((unsigned)((max_len + 63) / 64), n_units), dim3(256), 0, st, pv, cs, a);

@@ -670,7 +670,7 @@ size_t soft_attn_ws_bytes(int64_t total_tokens, int n_q_heads) {
 // Blocks of 32 positions that share a key tile in the forward and the dQ kernel.  One (four waves, two blocks per compute
 // unit) ends more evenly and meets at its barrier with fewer waves: forward, one / two, in us, 8 kv heads: 1 x 1000
 // tokens 36 / 46, 1 x 3000 107 / 114, 4 x 2000 195 / 214, 7 x 1500 210 / 237.  Two halve the traffic into LDS, which
-// is worth more once the launch runs long: 1 x 12000 1340 / 1317, 1 x 16384 2669 / 2637 (dQ 3354 / 3253).
+// is worth more once the launch runs long: 1 x 12000 1340 / 1317, 1 x 16384 2669 / 2637 (dQ 3354 / 3253).  (256 compute units.)
 static int soft_row_blocks(int max_t) { return max_t >= 8192 ? 2 : 1; }
 
 hipError_t launch_soft_attn_fwd(int n_seqs, const int32_t *n_tokens, int Hq, int Hkv, int d, int W,

@@ -75,8 +75,6 @@ def test_null_handles_are_rejected(lib):
 
 def test_every_included_header_makes_the_library_stale(monkeypatch, tmp_path):
     """build(force=False) compiles again when any file that the sources include is newer than the library."""
-    import os
-    import re
     from paper_2512_17452_amd import build as lib_build
     used = set()
     for src in [os.path.join(lib_build.CSRC, s) for s in lib_build.SOURCES]:
