@@ -616,48 +616,59 @@ __device__ __forceinline__ void put_partial(__amdgpu_buffer_rsrc_t r_ml, __amdgp
         __builtin_amdgcn_raw_buffer_store_b64(pk, r_ml, (rec0 + xg) * 8, 0, kCoherent);
     }
 }
-// ... and np of them from slot0 on, asked for eight together, become one.
-template <int D, int G, int VPT>
-__device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot0, int np, int x0, int xg,
-                                              float &L, float (&o)[VPT]) {
-    float M = -INFINITY;
-    L = 0.f;
+// ... and np of them from slot0 on, asked for eight together, become one; a thread has NP parts of the output, 64 threads
+// apart, whose loads go out together too.
+template <int D, int G, int NP, int VPT>
+__device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot0, int np, const int (&x0)[NP],
+                                              float (&L)[NP], float (&o)[NP][VPT]) {
+    float M[NP];
 #pragma unroll
-    for (int e = 0; e < VPT; e++) o[e] = 0.f;
+    for (int k = 0; k < NP; k++) {
+        M[k] = -INFINITY;
+        L[k] = 0.f;
+#pragma unroll
+        for (int e = 0; e < VPT; e++) o[k][e] = 0.f;
+    }
     constexpr int MB = 8;
     for (int q0 = 0; q0 < np; q0 += MB) {
-        u32x2 ml[MB];
-        uint32_t av[MB][VPT];
+        u32x2 ml[NP][MB];
+        uint32_t av[NP][MB][VPT];
 #pragma unroll
         for (int i = 0; i < MB; i++) {
             const uint32_t rec = (uint32_t)(slot0 + min(q0 + i, np - 1)) * G;
-            ml[i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, (rec + xg) * 8, 0, kCoherent);
-            const uint32_t off = rec * (D * 4) + x0 * 4;
-            if constexpr (VPT == 4) {
-                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r_acc, off, 0, kCoherent);
-                av[i][0] = v.x; av[i][1] = v.y; av[i][2] = v.z; av[i][3] = v.w;
-            } else {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r_acc, off, 0, kCoherent);
-                av[i][0] = v.x; av[i][1] = v.y;
+#pragma unroll
+            for (int k = 0; k < NP; k++) {
+                ml[k][i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, (rec + x0[k] / D) * 8, 0, kCoherent);
+                const uint32_t off = rec * (D * 4) + x0[k] * 4;
+                if constexpr (VPT == 4) {
+                    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r_acc, off, 0, kCoherent);
+                    av[k][i][0] = v.x; av[k][i][1] = v.y; av[k][i][2] = v.z; av[k][i][3] = v.w;
+                } else {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r_acc, off, 0, kCoherent);
+                    av[k][i][0] = v.x; av[k][i][1] = v.y;
+                }
             }
         }
-        float mb = M;
 #pragma unroll
-        for (int i = 0; i < MB; i++) mb = fmaxf(mb, __uint_as_float(ml[i].x));  // a repeated last one changes nothing
-        const float ms = mb == -INFINITY ? 0.f : mb;
-        const float c = __builtin_amdgcn_exp2f(M - ms);
-        L *= c;
+        for (int k = 0; k < NP; k++) {
+            float mb = M[k];
 #pragma unroll
-        for (int e = 0; e < VPT; e++) o[e] *= c;
+            for (int i = 0; i < MB; i++) mb = fmaxf(mb, __uint_as_float(ml[k][i].x));  // a repeated last one changes nothing
+            const float ms = mb == -INFINITY ? 0.f : mb;
+            const float c = __builtin_amdgcn_exp2f(M[k] - ms);
+            L[k] *= c;
 #pragma unroll
-        for (int i = 0; i < MB; i++)
-            if (q0 + i < np) {
-                const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[i].x) - ms);
-                L = fmaf(__uint_as_float(ml[i].y), f, L);
+            for (int e = 0; e < VPT; e++) o[k][e] *= c;
 #pragma unroll
-                for (int e = 0; e < VPT; e++) o[e] = fmaf(__uint_as_float(av[i][e]), f, o[e]);
-            }
-        M = mb;
+            for (int i = 0; i < MB; i++)
+                if (q0 + i < np) {
+                    const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[k][i].x) - ms);
+                    L[k] = fmaf(__uint_as_float(ml[k][i].y), f, L[k]);
+#pragma unroll
+                    for (int e = 0; e < VPT; e++) o[k][e] = fmaf(__uint_as_float(av[k][i][e]), f, o[k][e]);
+                }
+            M[k] = mb;
+        }
     }
 }
 
@@ -864,7 +875,12 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
             __syncthreads();
             if (s_arrived != np - 1) continue;
             asm volatile("" ::: "memory");
-            fold_partials<D, G>(r_ml, r_acc, slot0, np, x0, xg, L, o);
+            const int xs[1] = {x0};
+            float Ls[1], os[1][VPT];
+            fold_partials<D, G>(r_ml, r_acc, slot0, np, xs, Ls, os);
+            L = Ls[0];
+#pragma unroll
+            for (int e = 0; e < VPT; e++) o[e] = os[0][e];
             if (threadIdx.x == 0) __hip_atomic_store(&a.counters[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (mine) {
@@ -1063,15 +1079,22 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
         }
         if (before != np - 1) continue;
         asm volatile("" ::: "memory");
-        for (int part = part0; part < part1; part++) {
-            const int x = part * 64 + lane, x0 = min(x, NT - 1) * VPT, xg = x0 / D;
-            float L, o[VPT];
-            fold_partials<D, G>(r_ml, r_acc, slot0, np, x0, xg, L, o);
-            if (x >= NT) continue;
-            const float inv = 1.0f / L;
+        auto fold = [&](auto parts) __attribute__((always_inline)) {
+            constexpr int NP = decltype(parts)::value;
+            int x0[NP];
+            float L[NP], o[NP][VPT];
 #pragma unroll
-            for (int e = 0; e < VPT; e++) out[x0 + e] = o[e] * inv;
-        }
+            for (int k = 0; k < NP; k++) x0[k] = min((part0 + k) * 64 + lane, NT - 1) * VPT;
+            fold_partials<D, G>(r_ml, r_acc, slot0, np, x0, L, o);
+#pragma unroll
+            for (int k = 0; k < NP; k++) {
+                if ((part0 + k) * 64 + lane >= NT) continue;
+                const float inv = 1.0f / L[k];
+#pragma unroll
+                for (int e = 0; e < VPT; e++) out[x0[k] + e] = o[k][e] * inv;
+            }
+        };
+        if (by_wave) fold(std::integral_constant<int, (NT + 63) / 64>{}); else fold(std::integral_constant<int, 1>{});
         if (by_wave ? lane == 0 : threadIdx.x == 0) __hip_atomic_store(&a.counters[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
