@@ -900,9 +900,10 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
 //   blocks  the same over blocks, as in the kernel above: for long ones.
 // Every block estimates the three in us from the lengths and takes the cheapest.  The model is a fit to every way of 234
 // calls (33 to 128 sequences of 100 to 8000 tokens, even and ragged heads, all head shapes); its choice is 0.7 % behind the best
-// way in the mean and 8 % at most for the main head shape.  The fit was taken with 256 blocks.  Against the kernel above (us; main head shape, a third of the tokens
-// admitted): 33 x 100 tokens 15.5 -> 11.4, 64 x 300 24.3 -> 16, 128 x 300 40.5 -> 22, 128 x 1000 55 -> 38; heads from 1 to
-// 90 %: 64 x 1000 27 -> 25.5, 128 x 1000 44 -> 36; 33 x 4000 and longer calls are the same to 3 % (more to look at in front).
+// way in the mean and 8 % at most for the main head shape.  The fit was taken with 256 blocks, before the front of the kernel lost 1 us
+// and the fold of a wave's partials some more.  Against the kernel above (us; main head shape, a third of the tokens admitted): 33 x 100
+// tokens 15.2 -> 10.3, 64 x 300 24.3 -> 13.7, 128 x 300 40.7 -> 18.1, 128 x 1000 55 -> 33.7, 33 x 4000 35.7 -> 35.2; heads from 1 to 90 %:
+// 64 x 1000 27.2 -> 22.9, 128 x 1000 44.3 -> 34.4, 33 x 4000 27.8 -> 28.7.
 constexpr int kMinWaveTiles = 16, kWaveStartTiles = 12;
 template <int DT, int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View pv, AttendArgs a) {
@@ -913,8 +914,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
     __shared__ int s_gl[kMaxCallUnits];      // entries in the unit's global cache
     __shared__ int s_nl[kMaxCallUnits];      // tokens in its ring
     __shared__ int s_um[kMaxCallUnits];      // its index into the per-unit metadata
-    __shared__ int s_tmp[20];
-    __shared__ int s_longest;                // tiles of the longest unit
+    __shared__ int s_wave[3][kAttnWaves];    // a wave's tiles, units with any, and tiles of its longest unit
     __shared__ int s_arrived;
     __shared__ __attribute__((aligned(16))) DecStrips s_strips[kAttnWaves];
     __shared__ DecStates<DT, D, G> s_st;
@@ -922,34 +922,56 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
     const int n_units = a.n_seqs * pv.Hkv, n_blocks = (int)gridDim.x, n_waves = n_blocks * kAttnWaves;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int NU = kMaxCallUnits / kAttnThreads;  // consecutive units a thread looks after
-    int tl[NU], sum = 0, some = 0, longest = 0;
-    if (threadIdx.x == 0) s_longest = 0;
+    int tl[NU], um[NU], len[NU], gl_all[NU], sum = 0, some = 0, longest = 0;
+    // What stands in front of the first row is paid by every call: all of a thread's lengths are asked for together, the last unit's
+    // again past the end (a branch around each would wait for every one in turn), three sums share one barrier, and what is cut by a
+    // few comparisons is not divided.  33 x 100 tokens 11.1 -> 10.2 us, 33 x 1000 22.8 -> 21.5, 64 x 1000 24.2 -> 22.7.
+    {
+        int u = min((int)threadIdx.x * NU, n_units - 1), b = u / pv.Hkv, h = u - b * pv.Hkv;
+#pragma unroll
+        for (int i = 0; i < NU; i++) {
+            const int sid = a.sid[b];
+            um[i] = unit_meta(pv, sid, a.layer, h);
+            len[i] = pv.seq_len[sid * pv.L + a.layer];
+            gl_all[i] = pv.global_len[um[i]];
+            if (++u < n_units && ++h == pv.Hkv) {
+                h = 0;
+                b++;
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < NU; i++) {
-        const int u = (int)threadIdx.x * NU + i;
+        const int u = (int)threadIdx.x * NU + i, nl = min(len[i], pv.W);
         tl[i] = 0;
         if (u < n_units) {
-            const int b = u / pv.Hkv, h = u % pv.Hkv, sid = a.sid[b];
-            const int t = pv.seq_len[sid * pv.L + a.layer];
-            const int um = unit_meta(pv, sid, a.layer, h);
-            const int gl_all = pv.global_len[um], nl = min(t, pv.W);
-            s_gl[u] = gl_all;
+            s_gl[u] = gl_all[i];
             s_nl[u] = nl;
-            s_um[u] = um;
-            tl[i] = ceil_tiles(global_tokens(pv, a, u, gl_all)) + ceil_tiles(nl);
+            s_um[u] = um[i];
+            tl[i] = ceil_tiles(global_tokens(pv, a, u, gl_all[i])) + ceil_tiles(nl);
         }
         sum += tl[i];
         some += tl[i] > 0 ? 1 : 0;
         longest = max(longest, tl[i]);
     }
-    int total, used;
-    const int before_tiles = block_excl_scan(sum, s_tmp, &total);
-    const int before_units = block_excl_scan(some, s_tmp, &used);
+    const int inc_tiles = wave_incl_scan(sum, lane), inc_units = wave_incl_scan(some, lane);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
-    if (lane == 0) atomicMax(&s_longest, longest);  // cleared before the scans' barriers
+    if (lane == 63) {
+        s_wave[0][wave] = inc_tiles;
+        s_wave[1][wave] = inc_units;
+        s_wave[2][wave] = longest;
+    }
     __syncthreads();
-    longest = s_longest;
+    int total = 0, used = 0, before_tiles = inc_tiles - sum, before_units = inc_units - some;
+#pragma unroll
+    for (int w = 0; w < kAttnWaves; w++) {
+        before_tiles += w < wave ? s_wave[0][w] : 0;
+        before_units += w < wave ? s_wave[1][w] : 0;
+        total += s_wave[0][w];
+        used += s_wave[1][w];
+        longest = max(longest, s_wave[2][w]);
+    }
     const int share_b = max(kMinBlockTiles, (total + used * kUnitStartTiles + n_blocks - 1) / n_blocks);
     const int share_w = max(kMinWaveTiles, (total + used * kWaveStartTiles + n_waves - 1) / n_waves);
     constexpr float kC = (float)SH::ROWB / 256.f * (G == 8 ? 1.6f : 1.f);  // a tile: its bytes, or the products of eight heads
@@ -973,18 +995,19 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
     const int grp = lane / LPT, sub = lane % LPT;
     // Even shares: the KW workers of an even block and those of the odd one behind it cover 2 * KW * share tiles, te each
     // on the even block and to on the odd one.
-    const int KW = by_wave ? kAttnWaves : 1, wid = by_wave ? (int)blockIdx.x * kAttnWaves + wave : (int)blockIdx.x;
+    const int KW = by_wave ? kAttnWaves : 1, log2KW = by_wave ? 2 : 0, wid = by_wave ? (int)blockIdx.x * kAttnWaves + wave : (int)blockIdx.x;
+    static_assert(kAttnWaves == 4, "a pair of blocks is cut by comparisons");
     const int skew = n_blocks % 2 == 0 ? share * a.skew_permille / 1000 : 0, te = share + skew, to = share - skew, pair = 2 * KW * share;
     auto worker_of = [&](int x) __attribute__((always_inline)) {  // whose share holds tile x
-        const int pr = x / pair, r = x - pr * pair;
-        return pr * 2 * KW + (r < KW * te ? r / te : KW + (r - KW * te) / to);
+        const int pr = x / pair, r = x - pr * pair, rest = r - KW * te, in = rest < 0 ? r : rest, n = rest < 0 ? te : to;
+        return pr * 2 * KW + (rest < 0 ? 0 : KW) + (in >= n) + (in >= 2 * n) + (in >= 3 * n);
     };
     int cur = 0, end = 0, u = 0;
     if (solo) {
         u = wave * n_blocks + (int)blockIdx.x;
     } else {
-        const int i = wid % (2 * KW);
-        cur = wid / (2 * KW) * pair + (i < KW ? i * te : KW * te + (i - KW) * to);
+        const int i = wid & (2 * KW - 1);
+        cur = (wid >> (log2KW + 1)) * pair + (i < KW ? i * te : KW * te + (i - KW) * to);
         end = min(s_ts[n_units], cur + (i < KW ? te : to));
         for (int uu = blockIdx.x; uu < n_units; uu += n_blocks)  // units with nothing cached: the output is zero
             if (s_ts[uu + 1] == s_ts[uu])
