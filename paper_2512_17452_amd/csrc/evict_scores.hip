@@ -453,7 +453,8 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
         // entries a head 26 / - / 17, 2 of 2250 27 / 24 / 28, 2 of 4500 39 / - / 43, 4 of 3000 40 / - / 56.
         // The lines are those of 256 rows and 256 compute units.  Calls of 1 to 1024 rows were timed against one key a lane and 128
         // keys a block throughout, the form before: slower only for some 50 entries in each of many heads (40 sequences, 64 rows
-        // 24 -> 32 us), where most of a block of 256 keys is empty.
+        // 24 -> 32 us).  Sharing keys there (TS = 4 up to 64 entries, 2 up to 128) gives 29 with 64 rows, 35 instead of 40 with 16
+        // sequences and 256 rows, and costs up to a fifth with 8 rows (100 sequences 23 -> 28): left.
         const int64_t n_blocks = (int64_t)((max_len + 255) / 256) * n_units;  // of TS = 1
         if (n_blocks <= 96)
             hipLaunchKernelGGL(evict_weights_mfma_kernel<4>, dim3((unsigned)((max_len + 63) / 64), n_units), dim3(256), 0, st, pv, cs, a);
