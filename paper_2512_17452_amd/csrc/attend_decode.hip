@@ -9,7 +9,7 @@
 // without a second launch and without any block waiting for another).  For calls of at most
 // one unit per block there are two ways of cutting (attend_decode_kernel), and every block works
 // out by itself which one has the shorter longest block:
-//   pieces  every unit in equal pieces of at least 24 tiles, one piece per block: what a
+//   pieces  every unit in equal pieces of 8 to 24 tiles at least, one piece per block: what a
 //           small call wants, whose time is the chain in front of and behind its loops
 //           (launch, lengths, page ids, first rows, publish, count, fold), and a unit of
 //           one piece has no exchange through memory at all;
@@ -21,18 +21,16 @@
 // per block, by all threads of the block that arrives last, in a fixed order.
 // Calls of more units than blocks go to attend_decode_many_kernel, which can also give whole units or
 // even shares to single waves; its three ways stand above it.
-// Measured against shares and partials per wave, which need 16 tiles a wave to be worth
-// their fold (us per launch, one layer): 180 tokens x 2 heads fp32 13.4 -> 7.4; batch 8 at
-// 1K 19.5 -> 11.7; batch 1 at 32K (26 MB) 27.3 -> 17.8; batch 2 at 60K 41.5 -> 26.9; batch 4
-// 47.6 -> 39.6; batch 8 at 64K-128K (481 MB) 91 -> 85; 256 ragged heads (890 MB) 158 -> 156.
 //
-// Data path: each lane loads 16 bytes of a K row and of a V row straight into
-// registers; 64 lanes x 16 B = 1 KiB per load instruction, fully coalesced.  A wave
-// keeps several tiles in flight in separate register sets that are refilled in
-// place as soon as they have been consumed, so that few waves per SIMD are enough
-// to cover the HBM latency and no wave depends on the issue priority of another.
-// A group of lanes (16 for a 256-byte row) owns one token per row, so a wave holds several
-// independent online-softmax streams that are only combined when its part of a unit ends.
+// Data path of bf16 pools: rows go straight into LDS, 32 KiB ahead of their use in every wave, and both products run on
+// the matrix cores (stream_pairs).  Of fp32 pools: registers and the vector unit (stream_tiles).  Either way few waves per SIMD
+// cover the HBM latency and no wave depends on the issue priority of another.
+// What bounds a call: a long one the memory's rate; a short one chains of round trips and of instructions.  A wave issues one
+// instruction in four clocks at best, and the first time through, out of a cold instruction cache, 64 bytes of code take
+// about 70 ns, so what runs once is kept small.  Measured, us per launch, registers and dot products on the vector unit
+// throughout / now (rows of memory in both): batch 1 at 32K 15.8 / 13.9; at 8K 12.9 / 10.4; at 2K 12.1 / 10.1; batch 8 at 1K 12.1 /
+// 10.9; batch 2 at 60K 25.1 / 23.3; batch 8 at 100K (442 MB) 77 / 76.5; 32 x 4000 tokens 31.5 / 30.2; 64-wide heads, 2 x 30K 15.7 / 13.5;
+// groups of eight 21.6 / 18.9; of one, batch 1 at 32K 14.4 / 12.8; fp32 128-wide, 2 x 30K 18.0 / 16.5; fp32 2 heads of 20K 13.1 / 10.8.
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -54,9 +52,12 @@ constexpr int kUnitStartTiles = 24;
 // shares an odd block gets a number of thousandths fewer tiles, the even block before it as many
 // more (AttendArgs::skew_permille; 50 unless the pool was tuned on its machine, see
 // wgkv_tune_decode_attention).
-// A smaller piece is over sooner than its partial is published and folded: 8 / 16 / 24 tiles at least give 8.4 /
-// 7.1 / 7.1 us on 180 tokens x 2 heads and 20 / 18.5 / 17.3 on batch 1 at 32K (10.2 / 11.2 / 11.4 on batch 8 at 1K).
-constexpr int kMinBlockTiles = 24;
+// Smaller pieces mean fewer tiles per wave and more partials to publish, count and fold.  Where the blocks do not ask for more than
+// the memory gives, pieces are as small as 8 tiles (of at least 4 / 8 / 12 / 24 tiles, us: batch 1 at 8K 11.7 / 10.6 / 11.0 / 12.9, batch 1
+// at 2K 9.4 / 9.9 / 10.1 / 11.9, fp32 2 heads of 20K 12.5 / 11.2 / 11.9 / 13.1); where 140 blocks already do, smaller ones only cost
+// (batch 1 at 32K, 8 / 16 / 24 tiles: 17.5 / 16.1 / 15.1; 100 and 200 instead of 140 blocks: 14.1 / 15.3 against 14.5 there, but 11.5 /
+// 11.2 against 10.9 on batch 8 at 1K).  Units of up to 16 tiles stay whole: 180 tokens x 2 heads 8.4 / 7.1 us with pieces of 8 / 16.
+constexpr int kMinBlockTiles = 24, kMinPieceTiles = 8, kWholeTiles = 16, kStreamBlocks = 140;
 struct AttendArgs {
     int layer;
     int n_seqs;
@@ -92,19 +93,6 @@ template <int DT> struct Elem;
 template <> struct Elem<WGKV_F32> { static constexpr int es = 4; };
 template <> struct Elem<WGKV_BF16> { static constexpr int es = 2; };
 
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a),
-                                           __builtin_bit_cast(bf16x2_t, b), c, false);
-}
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {  // round to nearest even
-    bf16x2_t t = {(__bf16)lo, (__bf16)hi};
-    return __builtin_bit_cast(uint32_t, t);
-}
-__device__ __forceinline__ float bf16_lo(uint32_t x) { return __uint_as_float(x << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
-
 // Partials cross compute units (and their L2 slices) inside one launch: they are
 // written and read with device-coherent accesses, so no cache-wide flush is needed.
 // Buffer accesses carry the same cache policy as a device-scope atomic access (sc1) at up to
@@ -126,37 +114,343 @@ struct DecShape {
     static constexpr int TPW = 64 / LPT;     // token rows per wave load
     static constexpr int RPT = kTile / TPW;  // wave loads per tile (K and V each)
     static constexpr int ROWB = D * ES;      // bytes of a K or V row
+    static constexpr bool BF = DT == WGKV_BF16;
     static_assert(LPT == 8 || LPT == 16 || LPT == 32, "row must be 128, 256 or 512 bytes");
-    // Groups of four or eight query heads: four heads' scores of a tile are as many as a row group has lanes
+    // fp32: groups of four or eight query heads: four heads' scores of a tile are as many as a row group has lanes
     // (16 / TPW rows x 4 = LPT), so they are spread one per lane, and max, exp and sum run once instead of LPT
     // times.  m[hh] and l[hh] then belong to head 4 * hh + sub % 4; the other entries are unused.
-    static constexpr bool SPREAD = G % 4 == 0;
+    static constexpr bool SPREAD = !BF && G % 4 == 0;
     static constexpr int HH = SPREAD ? G / 4 : 1;
-    // The shape of the paper's two models takes its weights rounded to bf16 and multiplies pairs of them.
-    static constexpr bool PAIRS = DT == WGKV_BF16 && D == 128 && G == 4;
-    // Register sets = tiles in flight per wave.  With one wave per SIMD the loads of a wave's own next tiles are all
+    // bf16: weights enter their product in parts of 8 bits: two for the shape of the paper's two models (error against 64 bits 2.3e-6; rounded
+    // to one part 1.5e-3, and 9.4e-4 where each of 16 streams a wave has its largest weight exact), three for the others
+    static constexpr int PARTS = D == 128 && G == 4 ? 2 : 3;
+    // fp32: register sets = tiles in flight per wave.  With one wave per SIMD the loads of a wave's own next tiles are all
     // there is to cover the latency; 512-byte rows take 64 registers a tile, and with eight heads to a group four sets
-    // leave too few registers.  With this and the scores spread (us per launch, 16 sequences of 40K-60K tokens / 2 of
-    // 30K; one set, four or more blocks per compute unit, scores on every lane before): 64-wide heads 68 -> 58 /
-    // 27 -> 16, groups of eight 184 -> 138 / 53 -> 23 (four sets: 141 / 25), of two 110 -> 101 / 27 -> 19, of one
-    // 116 -> 100 / 26 -> 17, fp32 128-wide 127 -> 113 / 42 -> 20.
+    // leave too few registers.
     static constexpr int S = RPT <= 4 && G <= 4 ? 4 : 2;
+    // bf16: pairs of tiles that a wave has in LDS, 32 KiB
+    static constexpr int NP = 512 / ROWB;
+    static constexpr int EP = D / 16;        // output elements per lane, head and pair
+    static constexpr int NSW = BF ? 1 : TPW; // softmax states of a wave: one, or one per row group
 };
 
-// LDS strips of a wave through which the weights of a tile go back to the row layout.
-struct DecStrips {
-    float p[2][64];         // fp32 weights of a tile, four heads in each half
-    uint32_t pk[4][2][4];   // bf16 weight pairs of a tile: [row group][row pair][head]
-};
-
-// Tiles [cur, u_end) of a unit into the wave's running softmax (m, l, acc): the unit's tiles are those of its global
-// cache followed by those of its ring.
+// What a wave works with in LDS.  fp32: strips through which the weights of a tile go back to the row layout; bf16: its tiles.
 template <int DT, int D, int G>
+struct DecWaveLds {
+    float p[2][64];         // fp32 weights of a tile, four heads in each half
+};
+template <int D, int G>
+struct DecWaveLds<WGKV_BF16, D, G> {
+    __attribute__((aligned(1024))) char t[DecShape<WGKV_BF16, D, G>::NP][2][2][kTile * D * 2];  // [pair][K, V][tile of the pair]
+};
+
+// A wave's running softmax.  fp32: per row group.
+template <int DT, int D, int G>
+struct DecSoftmax {
+    float m[G], l[G], acc[G][DecShape<DT, D, G>::EPL];
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            m[g] = -INFINITY;
+            l[g] = 0.f;
+#pragma unroll
+            for (int e = 0; e < DecShape<DT, D, G>::EPL; e++) acc[g][e] = 0.f;
+        }
+    }
+};
+// bf16: m is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
+// element 16 * c + lane % 16.
+typedef float dec_f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
+typedef unsigned dec_u32x4_t __attribute__((ext_vector_type(4)));
+template <int D, int G>
+struct DecSoftmax<WGKV_BF16, D, G> {
+    static constexpr int EP = DecShape<WGKV_BF16, D, G>::EP;
+    float m;
+    dec_f32x4_t l, acc[EP];
+    __device__ __forceinline__ void init() {
+        m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            l[i] = 0.f;
+#pragma unroll
+            for (int c = 0; c < EP; c++) acc[c][i] = 0.f;
+        }
+    }
+};
+
+// 16 bytes per lane from memory to LDS at dst + 16 * lane, with the non-temporal hint: rows are read once.  In assembly, as the
+// compiler would put a wait for every outstanding request in front of the next LDS read; readers wait by count.  No result
+// register, and M0 is free for it.  The instruction's offset counts on both sides.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ uint32_t dec_lds(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p; }
+__device__ __forceinline__ void dec_dma(const void *base, uint32_t off, const void *dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dec_lds(dst)), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void dec_dma_at(const void *lane_ptr, const void *dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(dec_lds(dst)), "v"(lane_ptr) : "memory", "m0");
+}
+// a tile of N * 1024 bytes, each request with its own lane offsets
+__device__ __forceinline__ void dec_dma_tile(const void *base, const uint32_t (&off)[4], const void *dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5 nt\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024 nt\n\t"
+                 "global_load_lds_dwordx4 %3, %5 offset:2048 nt\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072 nt"
+                 ::"s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void dec_dma_tile(const void *base, const uint32_t (&off)[2], const void *dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024 nt"
+                 ::"s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+template <int N>
+__device__ __forceinline__ void dec_wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ uint32_t dec_pack_bf16(float lo, float hi) {  // round to nearest even
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    const bf16x2_t t = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, t);
+}
+
+// bf16: tiles [cur, u_end) of a unit into the wave's running softmax, on the matrix cores; the unit's tiles are those of its global
+// cache followed by those of its ring.
+// Two tiles (32 keys) at a time.  Rows come from memory straight into LDS (no registers, no copies of the loop's code per register
+// set: the instructions of a launch's first pass come out of a cold cache too), 32 KiB ahead of their use; the K half of a pair is
+// asked for again as soon as its operands are read, then the V half.
+// S = K Q^T with the G heads repeated over the 16 columns: a lane ends up with the scores of one head and keys 4 * (lane / 16) + {0..3}
+// of both tiles, which is the row operand of P V as it stands; the second operand is read transposed.  Sums over keys, those of the denominator too,
+// are the matrix core's.  About 0.65 us a pair where a tile took 0.65 us with dot products and reductions on the vector unit.
+// The maximum is brought up to date when a score exceeds it by 8 (weights of up to 256), so it costs no exchange between lanes in
+// the rule; sums are fp32 either way.
+template <int D, int G, bool SMALL_PAGES>
+__device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int cur, int u_end,
+                                             dec_u32x4_t (&q)[D / 32], float c_exp, DecSoftmax<WGKV_BF16, D, G> &st,
+                                             DecWaveLds<WGKV_BF16, D, G> &lds, int lane) {
+    using SH = DecShape<WGKV_BF16, D, G>;
+    constexpr int ROWB = SH::ROWB, LPT = SH::LPT, NI = SH::RPT, NP = SH::NP, EP = SH::EP, KS = D / 32, TILEB = kTile * ROWB;
+    constexpr int H = 2 * NI, PI = 2 * H;  // requests of half a pair (K or V) and of a pair
+    static_assert(NI * 1024 == TILEB, "");
+    const int n_gt = ceil_tiles(gl);
+    bool first = true;
+    while (cur < u_end) {
+        // one piece: at most 64 tiles [k0, k0+n) of one region (global or local) of unit u
+        const bool is_glob = cur < n_gt;
+        const int k0 = is_glob ? cur : cur - n_gt;
+        const int region_tiles = is_glob ? n_gt : ceil_tiles(nloc);
+        const int count = is_glob ? gl : nloc;
+        const int n = min(min(region_tiles - k0, 64), u_end - cur);
+        const int32_t *pt = is_glob ? pv.global_pt + (size_t)um * pv.maxgp : pv.local_pt + (size_t)um * pv.nlp;
+        // page id of the vp-th page of the region as this call reads it (with a selection: the vp-th selected page; an
+        // index outside the table is clamped, never followed)
+        const int32_t *sel = (is_glob && a.sel_pages) ? a.sel_pages + (size_t)u * a.sel_stride : nullptr;
+        const int last_page = max(((gl_all + pv.P - 1) >> pv.logP) - 1, 0);
+        auto page_at = [&](int vp) __attribute__((always_inline)) { return pt[sel ? min(max(sel[vp], 0), last_page) : vp]; };
+        // A tile inside one page (P >= 16) has one address for the whole wave: lane i keeps that of tile k0 + i.  Smaller
+        // pages are looked up per row, each behind a wait for all requests before it.
+        const int k_lane = (k0 + min(lane, n - 1)) * kTile;
+        int page = 0;
+        if (!SMALL_PAGES) page = page_at(k_lane >> pv.logP);
+        // (what follows from the lane alone is worked out while the page ids come: not hoisted in front of the request for them)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int col = ln & 15, grp = ln >> 4;
+        // Request i of a tile brings rows i * (64 / LPT) .., 16-byte piece x of row r at place x ^ f(r) of its row: K rows r % LPT, so
+        // that one column of sixteen rows is on different banks; V rows by their low two bits, so that 32 bytes of four
+        // consecutive rows are.
+        const int r0 = ln / LPT, x0 = ln % LPT;
+        auto v_sw = [](int r) __attribute__((always_inline)) { return D == 128 ? (r & 3) << 2 : r & 2; };
+        uint32_t off_k[NI], off_v[NI];
+#pragma unroll
+        for (int i = 0; i < NI; i++) {
+            off_k[i] = (uint32_t)(r0 * ROWB + (x0 ^ ((i * (64 / LPT) + r0) % LPT)) * 16);
+            off_v[i] = (uint32_t)(r0 * ROWB + (x0 ^ v_sw(r0)) * 16);
+        }
+        const int o_k = col * ROWB + ((grp ^ (col % LPT)) * 16);  // ^ 64 * ks
+        // ds_read_b64_tr_b16 transposes inside groups of 16 lanes: lane i of a group receives element i % 4 of the 8 bytes addressed by
+        // lanes i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4: lane s addresses (row s / 4 of the group's four, columns 4 * (s % 4)..+3 of
+        // 16) and ends up with the four rows at its own column
+        const int vr = 4 * grp + (col >> 2), o_v = vr * ROWB + (((col & 3) >> 1) ^ v_sw(vr)) * 16 + (col & 1) * 8;  // ^ 32 * c
+        // the page ids and the query are waited for here: a wait that the compiler puts in later would be for the rows too
+        asm volatile("" : "+v"(page));
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(q[ks]));
+        if (first && a.scale_log2e < 0.f) {  // a maximum of the products themselves: a negative scale turns the query's sign instead
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) {
+                q[ks].x ^= 0x80008000u; q[ks].y ^= 0x80008000u; q[ks].z ^= 0x80008000u; q[ks].w ^= 0x80008000u;
+            }
+        }
+        first = false;
+        const uint64_t at = (uint64_t)page_ptr(pv, page) + (uint64_t)(k_lane & (pv.P - 1)) * ROWB;
+        const uint32_t at_lo = (uint32_t)at, at_hi = (uint32_t)(at >> 32);
+        const int pairs = (n + 1) / 2;
+        auto valid_of = [&](int p) __attribute__((always_inline)) { return min(count - (k0 + 2 * p) * kTile, (n - 2 * p) * kTile); };  // keys of a pair that count
+        // Half a pair into its place.  Rows past the last token of the piece read a valid row again (the last one of their tile,
+        // or the first of a tile that is missing) and count for nothing: nothing that is not a cached row of this head is
+        // ever read (a recycled page keeps whatever its last owner left in it, which need not be finite).
+        auto request = [&](int p, bool v_half) __attribute__((always_inline)) {
+            char *dst = lds.t[p % NP][v_half ? 1 : 0][0];
+            auto base_of = [&](int j) __attribute__((always_inline)) {
+                const uint64_t at = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(at_hi, j) << 32) | (uint32_t)__builtin_amdgcn_readlane(at_lo, j);
+                return (const char *)(at + (v_half ? pv.v_off : 0u));
+            };
+            if (!SMALL_PAGES && valid_of(p) >= 2 * kTile) {
+                if (v_half) {
+                    dec_dma_tile(base_of(2 * p), off_v, dst);
+                    dec_dma_tile(base_of(2 * p + 1), off_v, dst + TILEB);
+                } else {
+                    dec_dma_tile(base_of(2 * p), off_k, dst);
+                    dec_dma_tile(base_of(2 * p + 1), off_k, dst + TILEB);
+                }
+                return;
+            }
+#pragma unroll 1
+            for (int t = 0; t < 2; t++) {
+                const bool is = 2 * p + t < n;
+                const int j = 2 * p + (is ? t : 0), k = k0 + j;
+                const int last_row = is ? min(count - 1 - k * kTile, kTile - 1) : 0;
+#pragma unroll
+                for (int i = 0; i < NI; i++) {
+                    const int r = i * (64 / LPT) + r0, row = min(r, last_row);
+                    const uint32_t x = (v_half ? off_v[i] : off_k[i]) - (uint32_t)(r0 * ROWB);
+                    if (SMALL_PAGES) {
+                        const int tok = k * kTile + row;
+                        dec_dma_at(page_ptr(pv, page_at(tok >> pv.logP)) + (size_t)(tok & (pv.P - 1)) * ROWB + (v_half ? pv.v_off : 0u) + x, dst + t * TILEB + i * 1024);
+                    } else {
+                        dec_dma(base_of(j), (uint32_t)(row * ROWB) + x, dst + t * TILEB + i * 1024);
+                    }
+                }
+            }
+        };
+#pragma unroll 1
+        for (int p = 0; p < min(NP, pairs); p++) {
+            request(p, false);
+            request(p, true);
+        }
+        for (int p = 0; p < pairs; p++) {
+            const int left = pairs - p;  // with this one; min(left, NP) of them are asked for
+            if (left >= NP) dec_wait_vm<NP * PI - H>();
+            else if (NP > 2 && left == 3) dec_wait_vm<3 * PI - H>();
+            else if (NP > 2 && left == 2) dec_wait_vm<2 * PI - H>();
+            else dec_wait_vm<PI - H>();
+            const char *tk = lds.t[p % NP][0][0], *tv = lds.t[p % NP][1][0];
+            dec_bf16x8_t kf[2][KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+                for (int t = 0; t < 2; t++) kf[t][ks] = *reinterpret_cast<const dec_bf16x8_t *>(tk + t * TILEB + (o_k ^ (64 * ks)));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            const bool more = left > NP;
+            if (more) request(p + NP, false);
+            dec_f32x4_t s[2];
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) s[t][i] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], __builtin_bit_cast(dec_bf16x8_t, q[ks]), s[t], 0, 0, 0);
+            }
+            const int valid = valid_of(p);  // all 32, but in the last pair of a piece
+            if (valid < 2 * kTile) {
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int i = 0; i < 4; i++) s[t][i] = t * kTile + 4 * grp + i < valid ? s[t][i] : -INFINITY;
+            }
+            float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) * c_exp;
+            if (__builtin_amdgcn_ballot_w64(mt > st.m + 8.f) != 0) {  // rare once the maxima settle
+                const LanePair x = swap16(mt, mt);
+                const float mnew = fmaxf(st.m, max_xor32(fmaxf(x.a, x.b)));
+                const float corr = __builtin_amdgcn_exp2f(st.m - (mnew == -INFINITY ? 0.f : mnew));
+                st.m = mnew;
+                float ch[G];
+#pragma unroll
+                for (int g = 0; g < G; g++) ch[g] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(corr), g));
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const float f = G == 8 ? ((grp & 1) ? ch[(4 + i) % G] : ch[i % G]) : ch[i % G];
+                    st.l[i] *= f;
+#pragma unroll
+                    for (int c = 0; c < EP; c++) st.acc[c][i] *= f;
+                }
+            }
+            const float off = st.m == -INFINITY ? 0.f : -st.m;
+            float w[2][4];
+#pragma unroll
+            for (int t = 0; t < 2; t++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) w[t][i] = __builtin_amdgcn_exp2f(fmaf(s[t][i], c_exp, off));
+            dec_bf16x8_t pw[SH::PARTS];
+#pragma unroll
+            for (int part = 0; part < SH::PARTS; part++) {
+                uint32_t wd[4];
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2) {
+                        uint32_t pk = dec_pack_bf16(w[t][i], w[t][i + 1]);
+                        asm("" : "+v"(pk));  // (or the two are rounded once more, one by one)
+                        wd[2 * t + i / 2] = pk;
+                        if (part + 1 < SH::PARTS) {  // what is left over, exactly
+                            w[t][i] -= __uint_as_float(pk << 16);
+                            w[t][i + 1] -= __uint_as_float(pk & 0xffff0000u);
+                        }
+                    }
+                pw[part] = __builtin_bit_cast(dec_bf16x8_t, make_uint4(wd[0], wd[1], wd[2], wd[3]));
+            }
+            if (more) dec_wait_vm<NP * PI - H>();
+            else if (NP > 2 && left == 4) dec_wait_vm<3 * PI>();
+            else if (NP > 2 && left == 3) dec_wait_vm<2 * PI>();
+            else if (left == 2) dec_wait_vm<PI>();
+            else dec_wait_vm<0>();
+            typedef short dec_s16x4_t __attribute__((ext_vector_type(4)));
+            typedef __attribute__((address_space(3))) dec_s16x4_t *lds_ptr_t;
+            uint2 vw[2][EP];  // rows 4 * grp + {0..3} of both tiles at column 16 * c + col
+#pragma unroll
+            for (int c = 0; c < EP; c++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    vw[t][c] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(tv + t * TILEB + (o_v ^ (32 * c)))));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (more) request(p + NP, true);
+            if (valid < 2 * kTile) {  // a weight of zero times what is not finite
+#pragma unroll
+                for (int t = 0; t < 2; t++) {
+                    const int nv = valid - t * kTile - 4 * grp;
+                    const uint32_t m0 = nv >= 2 ? 0xffffffffu : nv == 1 ? 0xffffu : 0u, m1 = nv >= 4 ? 0xffffffffu : nv == 3 ? 0xffffu : 0u;
+#pragma unroll
+                    for (int c = 0; c < EP; c++) {
+                        vw[t][c].x &= m0;
+                        vw[t][c].y &= m1;
+                    }
+                }
+            }
+            constexpr uint32_t kOnes = 0x3f803f80u;
+            const dec_bf16x8_t ones = __builtin_bit_cast(dec_bf16x8_t, make_uint4(kOnes, kOnes, kOnes, kOnes));
+#pragma unroll
+            for (int part = 0; part < SH::PARTS; part++) {
+                st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pw[part], ones, st.l, 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < EP; c++) {
+                    const dec_bf16x8_t vf = __builtin_bit_cast(dec_bf16x8_t, make_uint4(vw[0][c].x, vw[0][c].y, vw[1][c].x, vw[1][c].y));
+                    st.acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pw[part], vf, st.acc[c], 0, 0, 0);
+                }
+            }
+        }
+        cur += n;
+    }
+}
+
+// fp32: the same on the vector unit.  Each lane loads 16 bytes of a K row and of a V row straight into registers, 1 KiB per
+// instruction; a wave keeps S tiles in flight in register sets that are refilled in place as soon as they have been consumed.
+// A group of lanes (LPT of them) owns one token per row, so a wave holds several independent softmax streams.
+template <int D, int G>
 __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl,
                                              int nloc, int cur, int u_end,
-                                             const uint32_t (&qreg)[G][4], float (&m)[G], float (&l)[G],
-                                             float (&acc)[G][DecShape<DT, D, G>::EPL], DecStrips &strips, int lane) {
-    using SH = DecShape<DT, D, G>;
+                                             const uint32_t (&qreg)[G][4], float scale_log2e, DecSoftmax<WGKV_F32, D, G> &st,
+                                             DecWaveLds<WGKV_F32, D, G> &strips, int lane) {
+    using SH = DecShape<WGKV_F32, D, G>;
+    auto &m = st.m;
+    auto &l = st.l;
+    auto &acc = st.acc;
     constexpr int EPL = SH::EPL, LPT = SH::LPT, TPW = SH::TPW, RPT = SH::RPT, ROWB = SH::ROWB, S = SH::S;
     constexpr bool SPREAD = SH::SPREAD;
     constexpr int HH = SH::HH;
@@ -222,7 +516,6 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
             const char *rowp[RPT];
             if constexpr (REFILL) tile_rows(j + S, rowp);
             if constexpr (SPREAD) {
-                uint32_t pb = 0;
 #pragma unroll
                 for (int hh = 0; hh < HH; hh++) {
                     // ---- LPT partial dot products for four heads: x[r*4+g]; a K row register is
@@ -234,13 +527,8 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 #pragma unroll
                         for (int g = 0; g < 4; g++) {
                             float d = 0.f;
-                            if (DT == WGKV_BF16) {
 #pragma unroll
-                                for (int e = 0; e < 4; e++) d = dot2_bf16(kw[e], qreg[4 * hh + g][e], d);
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[4 * hh + g][e]), d);
-                            }
+                            for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[4 * hh + g][e]), d);
                             x[r * 4 + g] = d;
                         }
                         __builtin_amdgcn_sched_barrier(0);
@@ -291,7 +579,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
                         sc = (sub & 1) ? hi_ : lo_;
                     }
                     const int tok_l = k * kTile + (sub >> 2) * TPW + grp;
-                    sc = tok_l < count ? sc * a.scale_log2e : -INFINITY;
+                    sc = tok_l < count ? sc * scale_log2e : -INFINITY;
                     // ---- online softmax on one (row, head) per lane; the lanes of the row group with
                     //      the same sub%4 hold the rows of the same head ----
                     auto over_rows = [&](float v, auto op) __attribute__((always_inline)) {
@@ -311,13 +599,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
                     const float mnew = fmaxf(m[hh], mt);
                     const float msafe = mnew == -INFINITY ? 0.f : mnew;
                     const float corr = __builtin_amdgcn_exp2f(m[hh] - msafe);
-                    float pl = __builtin_amdgcn_exp2f(sc - msafe);
-                    if constexpr (SH::PAIRS) {
-                        // the weights enter the weighted sum as bf16 pairs (rows 2i, 2i+1);
-                        // the denominator sums the same rounded values
-                        pb = pack_bf16(pl, dpp_f<kDppShl4>(pl));
-                        pl = bf16_lo(pb);
-                    }
+                    const float pl = __builtin_amdgcn_exp2f(sc - msafe);
                     l[hh] = l[hh] * corr + over_rows(pl, [](float p, float q) { return p + q; });
                     if (__builtin_amdgcn_ballot_w64(mnew > m[hh]) != 0) {  // rare once the maxima settle
                         const float c0 = dpp_f<0x00>(corr), c1 = dpp_f<0x55>(corr);
@@ -328,66 +610,27 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
                         }
                     }
                     m[hh] = mnew;
-                    if constexpr (!SH::PAIRS) strips.p[hh][lane] = pl;
+                    strips.p[hh][lane] = pl;
                 }
                 // ---- weights back to the row layout through the wave's LDS strip ----
-                if constexpr (SH::PAIRS) {
-                    if ((sub & 4) == 0) strips.pk[grp][sub >> 3][sub & 3] = pb;
-                    __builtin_amdgcn_wave_barrier();
-                    const uint4 pk0 = *reinterpret_cast<const uint4 *>(&strips.pk[grp][0][0]);
-                    const uint4 pk1 = *reinterpret_cast<const uint4 *>(&strips.pk[grp][1][0]);
-                    const uint32_t pk[2][4] = {{pk0.x, pk0.y, pk0.z, pk0.w}, {pk1.x, pk1.y, pk1.z, pk1.w}};
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int i = 0; i < 2; i++) {
-                        const uint32_t va[4] = {vb[ST][2 * i].x, vb[ST][2 * i].y, vb[ST][2 * i].z, vb[ST][2 * i].w};
-                        const uint32_t vc[4] = {vb[ST][2 * i + 1].x, vb[ST][2 * i + 1].y, vb[ST][2 * i + 1].z,
-                                                vb[ST][2 * i + 1].w};
+                for (int r = 0; r < RPT; r++) {
+                    float pg[G];
 #pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const uint32_t lo2 = __builtin_amdgcn_perm(vc[e], va[e], 0x05040100u);
-                            const uint32_t hi2 = __builtin_amdgcn_perm(vc[e], va[e], 0x07060302u);
-#pragma unroll
-                            for (int g = 0; g < 4; g++) {
-                                acc[g][2 * e] = dot2_bf16(lo2, pk[i][g], acc[g][2 * e]);
-                                acc[g][2 * e + 1] = dot2_bf16(hi2, pk[i][g], acc[g][2 * e + 1]);
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (REFILL) {
-                            vb[ST][2 * i] = load_once16(rowp[2 * i] + pv.v_off);
-                            vb[ST][2 * i + 1] = load_once16(rowp[2 * i + 1] + pv.v_off);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int hh = 0; hh < HH; hh++) {
+                        const float4 pr = *reinterpret_cast<const float4 *>(&strips.p[hh][grp * LPT + r * 4]);
+                        pg[4 * hh] = pr.x; pg[4 * hh + 1] = pr.y; pg[4 * hh + 2] = pr.z; pg[4 * hh + 3] = pr.w;
                     }
-                } else {
-                    __builtin_amdgcn_wave_barrier();
+                    const uint32_t vw[4] = {vb[ST][r].x, vb[ST][r].y, vb[ST][r].z, vb[ST][r].w};
 #pragma unroll
-                    for (int r = 0; r < RPT; r++) {
-                        float pg[G];
+                    for (int e = 0; e < 4; e++) {
 #pragma unroll
-                        for (int hh = 0; hh < HH; hh++) {
-                            const float4 pr = *reinterpret_cast<const float4 *>(&strips.p[hh][grp * LPT + r * 4]);
-                            pg[4 * hh] = pr.x; pg[4 * hh + 1] = pr.y; pg[4 * hh + 2] = pr.z; pg[4 * hh + 3] = pr.w;
-                        }
-                        const uint32_t vw[4] = {vb[ST][r].x, vb[ST][r].y, vb[ST][r].z, vb[ST][r].w};
-#pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            if constexpr (DT == WGKV_BF16) {
-                                const float vlo = bf16_lo(vw[e]), vhi = bf16_hi(vw[e]);
-#pragma unroll
-                                for (int g = 0; g < G; g++) {
-                                    acc[g][2 * e] = fmaf(pg[g], vlo, acc[g][2 * e]);
-                                    acc[g][2 * e + 1] = fmaf(pg[g], vhi, acc[g][2 * e + 1]);
-                                }
-                            } else {
-#pragma unroll
-                                for (int g = 0; g < G; g++) acc[g][e] = fmaf(pg[g], __uint_as_float(vw[e]), acc[g][e]);
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (REFILL) vb[ST][r] = load_once16(rowp[r] + pv.v_off);
-                        __builtin_amdgcn_sched_barrier(0);
+                        for (int g = 0; g < G; g++) acc[g][e] = fmaf(pg[g], __uint_as_float(vw[e]), acc[g][e]);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (REFILL) vb[ST][r] = load_once16(rowp[r] + pv.v_off);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 __builtin_amdgcn_wave_barrier();
             } else {
@@ -400,15 +643,10 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 #pragma unroll
                     for (int g = 0; g < G; g++) {
                         float d = 0.f;
-                        if (DT == WGKV_BF16) {
 #pragma unroll
-                            for (int e = 0; e < 4; e++) d = dot2_bf16(kw[e], qreg[g][e], d);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[g][e]), d);
-                        }
+                        for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[g][e]), d);
                         d = group_sum<LPT>(d);
-                        s[r][g] = tok < count ? d * a.scale_log2e : -INFINITY;
+                        s[r][g] = tok < count ? d * scale_log2e : -INFINITY;
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the K registers are free from here on
@@ -441,22 +679,10 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 #pragma unroll
                 for (int r = 0; r < RPT; r++) {
                     const uint32_t vw[4] = {vb[ST][r].x, vb[ST][r].y, vb[ST][r].z, vb[ST][r].w};
-                    if (DT == WGKV_BF16) {
 #pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const float vlo = bf16_lo(vw[e]), vhi = bf16_hi(vw[e]);
+                    for (int e = 0; e < 4; e++)
 #pragma unroll
-                            for (int g = 0; g < G; g++) {
-                                acc[g][2 * e] = fmaf(p[r][g], vlo, acc[g][2 * e]);
-                                acc[g][2 * e + 1] = fmaf(p[r][g], vhi, acc[g][2 * e + 1]);
-                            }
-                        }
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-#pragma unroll
-                            for (int g = 0; g < G; g++) acc[g][e] = fmaf(p[r][g], __uint_as_float(vw[e]), acc[g][e]);
-                    }
+                        for (int g = 0; g < G; g++) acc[g][e] = fmaf(p[r][g], __uint_as_float(vw[e]), acc[g][e]);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the V registers are free from here on
                 if constexpr (REFILL) {
@@ -534,51 +760,109 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
     }
 }
 
-// What the decode kernels have in LDS for the states of a block's row groups, and how a unit's output is dealt over threads.
+// A wave's part of a unit: its query, and tiles [w0, w1) into a fresh softmax.
+template <int DT, int D, int G, bool SMALL>
+__device__ __forceinline__ void run_part(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int w0, int w1,
+                                         DecSoftmax<DT, D, G> &st, DecWaveLds<DT, D, G> &lds, int lane) {
+    using SH = DecShape<DT, D, G>;
+    st.init();
+    if (w0 >= w1) return;
+    // wave-uniform, which the compiler does not always see: the requests' bases are scalar operands
+    u = __builtin_amdgcn_readfirstlane(u);
+    um = __builtin_amdgcn_readfirstlane(um);
+    gl_all = __builtin_amdgcn_readfirstlane(gl_all);
+    gl = __builtin_amdgcn_readfirstlane(gl);
+    nloc = __builtin_amdgcn_readfirstlane(nloc);
+    w0 = __builtin_amdgcn_readfirstlane(w0);
+    w1 = __builtin_amdgcn_readfirstlane(w1);
+    const char *qu = a.q + (size_t)u * G * D * SH::ES;
+    if constexpr (DT == WGKV_BF16) {
+        dec_u32x4_t q[D / 32];
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ks++)
+            q[ks] = *reinterpret_cast<const dec_u32x4_t *>(qu + ((lane & 15) % G) * (D * 2) + (4 * ks + (lane >> 4)) * 16);
+        // (a scale of zero stays a hair above it: -inf times it stays -inf)
+        stream_pairs<D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, q, fmaxf(fabsf(a.scale_log2e), 1e-37f), st, lds, lane);
+    } else {
+        uint32_t qreg[G][4];
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const uint4 t4 = *reinterpret_cast<const uint4 *>(qu + lane % SH::LPT * 16 + (size_t)g * D * SH::ES);
+            qreg[g][0] = t4.x; qreg[g][1] = t4.y; qreg[g][2] = t4.z; qreg[g][3] = t4.w;
+        }
+        stream_tiles<D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, a.scale_log2e, st, lds, lane);
+    }
+}
+
+// What the decode kernels have in LDS for the states of a block, and how a unit's output is dealt over threads.
 template <int DT, int D, int G>
 struct DecOut {
-    static constexpr int TPW = DecShape<DT, D, G>::TPW;
-    static constexpr int NST = kAttnWaves * TPW;  // softmax states of a block: one per row group
+    static constexpr int NSW = DecShape<DT, D, G>::NSW;
+    static constexpr int NST = kAttnWaves * NSW;  // softmax states of a block
+    static constexpr int PAR = 4 * kAttnThreads / (G * D);  // partials that a block reads side by side, 16 bytes a thread
     static constexpr int VPT = G * D >= 2 * kAttnThreads ? G * D / kAttnThreads : 2;  // output elements per thread
     static constexpr int NT = G * D / VPT;        // threads that hold some
     static_assert(NT <= kAttnThreads && D % VPT == 0 && (VPT == 2 || VPT == 4), "");
 };
 template <int DT, int D, int G>
 struct DecStates {
-    float m[DecOut<DT, D, G>::NST][G], l[DecOut<DT, D, G>::NST][G];
-    __attribute__((aligned(16))) float acc[DecOut<DT, D, G>::NST][G * D];
+    static constexpr int N = DecOut<DT, D, G>::NST > DecOut<DT, D, G>::PAR ? DecOut<DT, D, G>::NST : DecOut<DT, D, G>::PAR;
+    float m[N][G], l[N][G];
+    __attribute__((aligned(16))) float acc[N][G * D];
 };
 
-// A wave's row groups into their places.
+// A wave's states into their places.
 template <int DT, int D, int G>
-__device__ __forceinline__ void put_states(DecStates<DT, D, G> &s, int wave, int grp, int sub, const float (&m)[G], const float (&l)[G],
-                                           const float (&acc)[G][DecShape<DT, D, G>::EPL]) {
+__device__ __forceinline__ void put_states(DecStates<DT, D, G> &s, int wave, int lane, const DecSoftmax<DT, D, G> &w) {
     using SH = DecShape<DT, D, G>;
-    const int st = wave * SH::TPW + grp;
+    if constexpr (DT == WGKV_BF16) {
+        const int grp = lane >> 4, col = lane & 15;
+        if (grp < (G + 3) / 4) {  // the other lanes hold the same
 #pragma unroll
-    for (int g = 0; g < G; g++)
+            for (int i = 0; i < 4; i++)
+                if (4 * grp + i < G) {
 #pragma unroll
-        for (int e = 0; e < SH::EPL; e += 4)
-            *reinterpret_cast<float4 *>(&s.acc[st][g * D + sub * SH::EPL + e]) =
-                make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
-    if constexpr (SH::SPREAD) {
-        if (sub < 4) {  // m[hh] and l[hh] belong to head 4 * hh + sub % 4
-#pragma unroll
-            for (int hh = 0; hh < SH::HH; hh++) {
-                s.m[st][4 * hh + sub] = m[hh];
-                s.l[st][4 * hh + sub] = l[hh];
-            }
+                    for (int c = 0; c < SH::EP; c += 4)
+                        *reinterpret_cast<float4 *>(&s.acc[wave][(4 * grp + i) * D + col * SH::EP + c]) =
+                            make_float4(w.acc[c][i], w.acc[c + 1][i], w.acc[c + 2][i], w.acc[c + 3][i]);
+                    if (col == 0) s.l[wave][4 * grp + i] = w.l[i];
+                }
+            if (lane < G) s.m[wave][lane] = w.m;
         }
-    } else if (sub == 0) {
+    } else {
+        const int grp = lane / SH::LPT, sub = lane % SH::LPT, st = wave * SH::TPW + grp;
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            s.m[st][g] = m[g];
-            s.l[st][g] = l[g];
+        for (int g = 0; g < G; g++)
+#pragma unroll
+            for (int e = 0; e < SH::EPL; e += 4)
+                *reinterpret_cast<float4 *>(&s.acc[st][g * D + sub * SH::EPL + e]) =
+                    make_float4(w.acc[g][e], w.acc[g][e + 1], w.acc[g][e + 2], w.acc[g][e + 3]);
+        if constexpr (SH::SPREAD) {
+            if (sub < 4) {  // m[hh] and l[hh] belong to head 4 * hh + sub % 4
+#pragma unroll
+                for (int hh = 0; hh < SH::HH; hh++) {
+                    s.m[st][4 * hh + sub] = w.m[hh];
+                    s.l[st][4 * hh + sub] = w.l[hh];
+                }
+            }
+        } else if (sub == 0) {
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                s.m[st][g] = w.m[g];
+                s.l[st][g] = w.l[g];
+            }
         }
     }
 }
 
-// N states from s0 on into one, for output elements x0 .. of head xg.
+// Place x of a state's accumulators is output element ...
+template <int DT, int D>
+__device__ __forceinline__ int out_of(int x) {
+    constexpr int EP = D / 16;
+    return DT == WGKV_BF16 ? x / D * D + x % EP * 16 + x % D / EP : x;
+}
+
+// N states from s0 on into one, for places x0 .. of head xg.
 template <int N, int DT, int D, int G>
 __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0, int x0, int xg, float &M, float &L,
                                             float (&o)[DecOut<DT, D, G>::VPT]) {
@@ -599,6 +883,9 @@ __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0
     }
 }
 
+// The maximum of a partial is kept so that what a buffer load returns past the buffer's end, zero, stands for "nothing seen".
+constexpr uint32_t kNoM = 0xff800000u;  // -inf
+__device__ __forceinline__ float partial_m(uint32_t x) { return __uint_as_float(x ^ kNoM); }
 // The partial of a slot goes out with device-scope stores ...
 template <int D, int G, int VPT>
 __device__ __forceinline__ void put_partial(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot, int x0, int xg,
@@ -612,11 +899,11 @@ __device__ __forceinline__ void put_partial(__amdgpu_buffer_rsrc_t r_ml, __amdgp
         __builtin_amdgcn_raw_buffer_store_b64(pk, r_acc, off, 0, kCoherent);
     }
     if (x0 % D == 0) {
-        const u32x2 pk = {__float_as_uint(M), __float_as_uint(L)};
+        const u32x2 pk = {__float_as_uint(M) ^ kNoM, __float_as_uint(L)};
         __builtin_amdgcn_raw_buffer_store_b64(pk, r_ml, (rec0 + xg) * 8, 0, kCoherent);
     }
 }
-// ... and np of them from slot0 on, asked for eight together, become one; a thread has NP parts of the output, 64 threads
+// ... and np of them from slot0 on, asked for eight together (four where a thread has more than two parts), become one; a thread has NP parts of the output, 64 threads
 // apart, whose loads go out together too.
 template <int D, int G, int NP, int VPT>
 __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amdgpu_buffer_rsrc_t r_acc, int slot0, int np, const int (&x0)[NP],
@@ -629,7 +916,7 @@ __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amd
 #pragma unroll
         for (int e = 0; e < VPT; e++) o[k][e] = 0.f;
     }
-    constexpr int MB = 8;
+    constexpr int MB = NP > 2 ? 4 : 8;
     for (int q0 = 0; q0 < np; q0 += MB) {
         u32x2 ml[NP][MB];
         uint32_t av[NP][MB][VPT];
@@ -653,7 +940,7 @@ __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amd
         for (int k = 0; k < NP; k++) {
             float mb = M[k];
 #pragma unroll
-            for (int i = 0; i < MB; i++) mb = fmaxf(mb, __uint_as_float(ml[k][i].x));  // a repeated last one changes nothing
+            for (int i = 0; i < MB; i++) mb = fmaxf(mb, partial_m(ml[k][i].x));  // a repeated last one changes nothing
             const float ms = mb == -INFINITY ? 0.f : mb;
             const float c = __builtin_amdgcn_exp2f(M[k] - ms);
             L[k] *= c;
@@ -662,7 +949,7 @@ __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amd
 #pragma unroll
             for (int i = 0; i < MB; i++)
                 if (q0 + i < np) {
-                    const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[k][i].x) - ms);
+                    const float f = __builtin_amdgcn_exp2f(partial_m(ml[k][i].x) - ms);
                     L[k] = fmaf(__uint_as_float(ml[k][i].y), f, L[k]);
 #pragma unroll
                     for (int e = 0; e < VPT; e++) o[k][e] = fmaf(__uint_as_float(av[k][i][e]), f, o[k][e]);
@@ -672,109 +959,234 @@ __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amd
     }
 }
 
+// The same by all threads of a block: a partial is read by G * D / 4 of them, 16 bytes each, so several partials are read side by
+// side and up to 16 one behind the other in one round trip; the sums of those side by side meet in LDS.
 template <int DT, int D, int G>
-__global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, AttendArgs a) {
-    using SH = DecShape<DT, D, G>;
+__device__ __forceinline__ void fold_partials_block(const AttendArgs &a, int slot0, int np, DecStates<DT, D, G> &s, int tid,
+                                                    int x0, int xg, float &L, float (&o)[DecOut<DT, D, G>::VPT]) {
+    constexpr int TP = G * D / 4, PAR = DecOut<DT, D, G>::PAR;
+    static_assert(TP * PAR == kAttnThreads, "");
+    // (a buffer that ends behind the last partial: an access past it moves no bytes)
+    const uint32_t slots = (uint32_t)__builtin_amdgcn_readfirstlane(slot0 + np);
+    const __amdgpu_buffer_rsrc_t r_acc = part_rsrc(a.part_acc, slots * (G * D * 4));
+    const __amdgpu_buffer_rsrc_t r_ml = part_rsrc(a.part_ml, slots * (G * 8));
+    const int pi = tid / TP, x = (tid % TP) * 4, g = x / D;
+    float M = -INFINITY, l = 0.f, v[4] = {0.f, 0.f, 0.f, 0.f};
+    auto batch = [&](auto mb_tag, int q0) __attribute__((always_inline)) {
+        constexpr int MB = decltype(mb_tag)::value;
+        u32x2 ml[MB];
+        u32x4 av[MB];
+#pragma unroll
+        for (int i = 0; i < MB; i++) {
+            const uint32_t rec = (uint32_t)(slot0 + q0 + i * PAR) * G;
+            ml[i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, (rec + g) * 8, 0, kCoherent);
+            av[i] = __builtin_amdgcn_raw_buffer_load_b128(r_acc, rec * (D * 4) + x * 4, 0, kCoherent);
+        }
+        float mb = M;
+#pragma unroll
+        for (int i = 0; i < MB; i++) mb = fmaxf(mb, partial_m(ml[i].x));
+        const float ms = mb == -INFINITY ? 0.f : mb, c = __builtin_amdgcn_exp2f(M - ms);
+        l *= c;
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[e] *= c;
+#pragma unroll
+        for (int i = 0; i < MB; i++) {
+            const float f = __builtin_amdgcn_exp2f(partial_m(ml[i].x) - ms);
+            l = fmaf(__uint_as_float(ml[i].y), f, l);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] = fmaf(__uint_as_float(av[i][e]), f, v[e]);
+        }
+        M = mb;
+    };
+    for (int q0 = 0; q0 < np; q0 += 16 * PAR) {
+        // (code that runs once comes out of a cold instruction cache: about 70 ns for 64 bytes, so no more of it than it takes)
+        if (np - q0 > 12 * PAR) batch(std::integral_constant<int, 16>{}, q0 + pi);
+        else if (np - q0 > 8 * PAR) batch(std::integral_constant<int, 12>{}, q0 + pi);
+        else batch(std::integral_constant<int, 8>{}, q0 + pi);
+    }
+    if constexpr (PAR == 1) {
+        static_assert(PAR > 1 || DecOut<DT, D, G>::VPT == 4, "");
+        L = l;
+#pragma unroll
+        for (int e = 0; e < DecOut<DT, D, G>::VPT; e++) o[e] = v[e];
+    } else {
+        *reinterpret_cast<float4 *>(&s.acc[pi][x]) = make_float4(v[0], v[1], v[2], v[3]);
+        if (x % D == 0) {
+            s.m[pi][g] = M;
+            s.l[pi][g] = l;
+        }
+        __syncthreads();
+        float m;
+        fold_states<PAR>(s, 0, x0, xg, m, L, o);
+    }
+}
+
+constexpr int kMaxUnits = 512;  // and no more than there are blocks
+template <int DT, int D, int G>
+struct DecBlocksLds {
+    DecWaveLds<DT, D, G> wave[kAttnWaves];
+    DecStates<DT, D, G> states;
+    int ts[kMaxUnits + 1];  // pieces (or, with even shares, tiles) before unit u
+    int gl[kMaxUnits];      // entries in the unit's global cache
+    int gt[kMaxUnits];      // those of them that are read
+    int nl[kMaxUnits];      // tokens in its ring
+    int um[kMaxUnits];      // its index into the per-unit metadata
+    int tmp[3 * kAttnWaves];
+    int arrived;
+};
+template <int DT, int D, int G, bool SMALL, bool FEW>  // FEW: at most 64 units
+__device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &a) {
     using OUT = DecOut<DT, D, G>;
-    constexpr int ES = SH::ES, EPL = SH::EPL, LPT = SH::LPT, VPT = OUT::VPT, NT = OUT::NT;
-    __shared__ int s_ts[kMaxCallUnits + 1];  // pieces (or, with even shares, tiles) before unit u
-    __shared__ int s_gl[kMaxCallUnits];      // entries in the unit's global cache
-    __shared__ int s_nl[kMaxCallUnits];      // tokens in its ring
-    __shared__ int s_um[kMaxCallUnits];      // its index into the per-unit metadata
-    __shared__ int s_tmp[20];
-    __shared__ int s_share;                  // tiles of a block's even share, 0: pieces
-    __shared__ int s_arrived;
-    __shared__ __attribute__((aligned(16))) DecStrips s_strips[kAttnWaves];
-    __shared__ DecStates<DT, D, G> s_st;
+    constexpr int VPT = OUT::VPT, NT = OUT::NT;
+    extern __shared__ __attribute__((aligned(1024))) char s_mem[];
+    auto &lds = *reinterpret_cast<DecBlocksLds<DT, D, G> *>(s_mem);
+    auto &s_wave_lds = lds.wave;
+    auto &s_st = lds.states;
+    auto &s_ts = lds.ts;
+    auto &s_gl = lds.gl;
+    auto &s_gt = lds.gt;
+    auto &s_nl = lds.nl;
+    auto &s_um = lds.um;
+    auto &s_tmp = lds.tmp;
+    auto &s_arrived = lds.arrived;
 
     const int n_units = a.n_seqs * pv.Hkv, n_blocks = (int)gridDim.x;
-    auto unit_tiles = [&](int u) __attribute__((always_inline)) {
-        const int b = u / pv.Hkv, h = u % pv.Hkv, sid = a.sid[b];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // What stands in front of the first row is a chain of round trips and of instructions that a block's one wave per SIMD issues
+    // one after the other, and every call pays it: all that is known early is asked for together, what every block needs is found
+    // by every wave for itself (no barrier) and, for up to 64 units, kept in a register of the unit's lane (no LDS), and
+    // quotients of small numbers come from a reciprocal.
+    asm volatile("" ::"s"(a.out), "s"(a.part_acc_bytes), "s"(a.sel_stride), "s"(pv.v_off), "s"(pv.ahead));  // the arguments' lines
+    auto unit_of = [&](int u, int &um, int &gl, int &gt, int &nl) __attribute__((always_inline)) {
+        const int b = (int)(((float)u + 0.5f) * __builtin_amdgcn_rcpf((float)pv.Hkv)), h = u - b * pv.Hkv;  // exact: u < 1024
+        const int sid = a.sid[b];
+        um = unit_meta(pv, sid, a.layer, h);
         const int t = pv.seq_len[sid * pv.L + a.layer];
-        const int um = unit_meta(pv, sid, a.layer, h);
-        const int gl_all = pv.global_len[um], nl = min(t, pv.W);
-        s_gl[u] = gl_all;
-        s_nl[u] = nl;
-        s_um[u] = um;
-        return ceil_tiles(global_tokens(pv, a, u, gl_all)) + ceil_tiles(nl);
+        gl = pv.global_len[um];
+        gt = global_tokens(pv, a, u, gl);
+        nl = min(t, pv.W);
     };
     // pieces of a unit of `tiles` tiles at about `most` tiles a piece; every unit has one at least (a unit with nothing
     // cached writes its zeros).  Any number is correct: a quotient that rounds the other way moves a boundary.
     auto pieces_of = [](int tiles, int most) __attribute__((always_inline)) {
-        return max(1, (int)((float)(tiles + most - 1) * __builtin_amdgcn_rcpf((float)most)));
+        return tiles <= kWholeTiles ? 1 : max(1, (int)((float)(tiles + most - 1) * __builtin_amdgcn_rcpf((float)most)));
+    };
+    auto least_piece = [&](int total) __attribute__((always_inline)) {
+        return min(max(total / kStreamBlocks, kMinPieceTiles), kMinBlockTiles);
     };
     auto even_share = [&](int total, int used) __attribute__((always_inline)) {
         return max(kMinBlockTiles, (total + used * kUnitStartTiles + n_blocks - 1) / n_blocks);
     };
-    if (n_units <= 64) {  // one wave: scans inside the wave, one barrier
-        if (threadIdx.x < 64) {
-            const int u = threadIdx.x;
-            const int tiles = u < n_units ? unit_tiles(u) : 0;
-            const int total = __builtin_amdgcn_readlane(wave_incl_scan(tiles, u), 63);
-            const int used = __builtin_popcountll(__builtin_amdgcn_ballot_w64(tiles > 0));
-            const int share = even_share(total, used);
-            // the smallest piece with which all pieces fit the grid, between what an even split would need and what
-            // always fits
-            int lo = max(kMinBlockTiles, total / n_blocks), hi = max(lo, total / max(1, n_blocks - n_units) + 1);
-            for (int i = 0; i < 5 && hi - lo > 1; i++) {
-                const int mid = (lo + hi) >> 1;
-                const int np = u < n_units ? pieces_of(tiles, mid) : 0;
-                if (__builtin_amdgcn_readlane(wave_incl_scan(np, u), 63) <= n_blocks) hi = mid; else lo = mid;
-            }
-            // (the rounding of the quotients decides whether they do fit: counted, not assumed)
-            const int fit = __builtin_amdgcn_readlane(wave_incl_scan(u < n_units ? pieces_of(tiles, hi) : 0, u), 63);
-            const bool pieces = fit <= n_blocks && hi <= share;
-            const int mine = u < n_units ? (pieces ? pieces_of(tiles, hi) : tiles + (tiles > 0 ? kUnitStartTiles : 0)) : 0;
-            const int inc = wave_incl_scan(mine, u);
-            if (u < n_units) s_ts[u] = inc - mine;
-            if (u == 63) {
-                s_ts[n_units] = inc;
-                s_share = pieces ? 0 : share;
-            }
+    const int mine_at = FEW ? wave * (kMaxUnits / kAttnWaves) : 0;  // a wave's own part of the lists, or the block's
+    int listed, share = 0, u = 0;  // share: tiles of a block's even share, 0: pieces
+    if constexpr (FEW) {
+        int l_um, l_gl, l_gt, l_nl;  // of unit `lane`
+        unit_of(min(lane, n_units - 1), l_um, l_gl, l_gt, l_nl);
+        const bool is = lane < n_units;
+        const int tiles = is ? ceil_tiles(l_gt) + ceil_tiles(l_nl) : 0;
+        const int total = __builtin_amdgcn_readlane(wave_incl_scan(tiles, lane), 63);
+        const int used = __builtin_popcountll(__builtin_amdgcn_ballot_w64(tiles > 0));
+        // the smallest piece with which all pieces fit the grid, between what an even split would need and what
+        // always fits; a few units leave nothing to look for between the two
+        const float per = (float)total;
+        int lo = max(least_piece(total), (int)(per * __builtin_amdgcn_rcpf((float)n_blocks)));
+        int hi = max(lo, (int)(per * __builtin_amdgcn_rcpf((float)max(1, n_blocks - n_units))) + 1);
+        for (int i = 0; i < 5 && (hi - lo) * 16 > hi; i++) {
+            const int mid = (lo + hi) >> 1;
+            const int np = is ? pieces_of(tiles, mid) : 0;
+            if (__builtin_amdgcn_readlane(wave_incl_scan(np, lane), 63) <= n_blocks) hi = mid; else lo = mid;
         }
+        // (the rounding of the quotients decides whether they do fit: counted, not assumed)
+        int mine = is ? pieces_of(tiles, hi) : 0;
+        int l_te = wave_incl_scan(mine, lane);
+        if (__builtin_amdgcn_readlane(l_te, 63) > n_blocks ||
+            hi > max(kMinBlockTiles, (int)((float)(total + used * kUnitStartTiles) * __builtin_amdgcn_rcpf((float)n_blocks)) + 1)) {
+            share = even_share(total, used);
+            mine = tiles + (tiles > 0 ? kUnitStartTiles : 0);
+            l_te = wave_incl_scan(mine, lane);
+        }
+        listed = __builtin_amdgcn_readlane(l_te, 63);
+        if (is) {
+            s_ts[mine_at + lane] = l_te - mine;
+            s_ts[mine_at + lane + 1] = l_te;
+            s_um[mine_at + lane] = l_um;
+            s_gl[mine_at + lane] = l_gl;
+            s_gt[mine_at + lane] = l_gt;
+            s_nl[mine_at + lane] = l_nl;
+        }
+        __builtin_amdgcn_wave_barrier();
     } else {
-        constexpr int NU = kMaxCallUnits / kAttnThreads;
-        int total = 0, used = 0, tl[NU];
+        constexpr int NU = kMaxUnits / kAttnThreads;  // consecutive units a thread looks after, asked for together
+        int um[NU], gl[NU], gt[NU], nl[NU], tl[NU], sum = 0, some = 0;
+#pragma unroll
+        for (int i = 0; i < NU; i++) unit_of(min((int)threadIdx.x * NU + i, n_units - 1), um[i], gl[i], gt[i], nl[i]);
 #pragma unroll
         for (int i = 0; i < NU; i++) {
-            const int u = i * kAttnThreads + threadIdx.x;
+            const int v = (int)threadIdx.x * NU + i;
             tl[i] = 0;
-            if (i * kAttnThreads < n_units) {  // block-uniform
-                if (u < n_units) tl[i] = unit_tiles(u);
-                int sum;
-                block_excl_scan(tl[i], s_tmp, &sum);
-                total += sum;
-                block_excl_scan(tl[i] > 0 ? 1 : 0, s_tmp, &sum);
-                used += sum;
+            if (v < n_units) {
+                s_um[v] = um[i];
+                s_gl[v] = gl[i];
+                s_gt[v] = gt[i];
+                s_nl[v] = nl[i];
+                tl[i] = ceil_tiles(gt[i]) + ceil_tiles(nl[i]);
+            }
+            sum += tl[i];
+            some += tl[i] > 0 ? 1 : 0;
+        }
+        const int inc_tiles = wave_incl_scan(sum, lane), inc_units = wave_incl_scan(some, lane);
+        if (lane == 63) {
+            s_tmp[wave] = inc_tiles;
+            s_tmp[kAttnWaves + wave] = inc_units;
+        }
+        __syncthreads();
+        int total = 0, used = 0, at = inc_tiles - sum + (inc_units - some) * kUnitStartTiles;  // at: what stands before the thread's units
+#pragma unroll
+        for (int w = 0; w < kAttnWaves; w++) {
+            total += s_tmp[w];
+            used += s_tmp[kAttnWaves + w];
+            at += w < wave ? s_tmp[w] + s_tmp[kAttnWaves + w] * kUnitStartTiles : 0;
+        }
+        const int even = even_share(total, used);
+        const int most = max(least_piece(total), total / max(1, n_blocks - n_units) + 1);
+        const bool pieces = most <= even;  // T / most + n_units pieces at most: they fit
+        int mine[NU];
+#pragma unroll
+        for (int i = 0; i < NU; i++) mine[i] = tl[i] + (tl[i] > 0 ? kUnitStartTiles : 0);
+        listed = total + used * kUnitStartTiles;
+        if (pieces) {  // block-uniform
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < NU; i++) {
+                const int v = (int)threadIdx.x * NU + i;
+                mine[i] = v < n_units ? (tl[i] <= kWholeTiles ? 1 : (tl[i] + most - 1) / most) : 0;
+                n += mine[i];
+            }
+            const int inc = wave_incl_scan(n, lane);
+            if (lane == 63) s_tmp[2 * kAttnWaves + wave] = inc;
+            __syncthreads();
+            listed = 0;
+            at = inc - n;
+#pragma unroll
+            for (int w = 0; w < kAttnWaves; w++) {
+                listed += s_tmp[2 * kAttnWaves + w];
+                at += w < wave ? s_tmp[2 * kAttnWaves + w] : 0;
             }
         }
-        const int share = even_share(total, used);
-        const int most = max(kMinBlockTiles, total / max(1, n_blocks - n_units) + 1);
-        const bool pieces = n_units <= n_blocks && most <= share;  // T / most + n_units pieces at most: they fit
-        int carry = 0;
 #pragma unroll
         for (int i = 0; i < NU; i++) {
-            const int u = i * kAttnThreads + threadIdx.x;
-            if (i * kAttnThreads < n_units) {
-                const int mine = u < n_units ? (pieces ? max(1, (tl[i] + most - 1) / most) : tl[i] + (tl[i] > 0 ? kUnitStartTiles : 0)) : 0;
-                int sum;
-                const int ex = block_excl_scan(mine, s_tmp, &sum);
-                if (u < n_units) s_ts[u] = carry + ex;
-                carry += sum;
-            }
+            const int v = (int)threadIdx.x * NU + i;
+            if (v < n_units) s_ts[v] = at;
+            at += mine[i];
         }
-        if (threadIdx.x == 0) {
-            s_ts[n_units] = carry;
-            s_share = pieces ? 0 : share;
-        }
+        if (threadIdx.x == 0) s_ts[n_units] = listed;
+        share = __builtin_amdgcn_readfirstlane(pieces ? 0 : even);
+        listed = __builtin_amdgcn_readfirstlane(listed);
+        __syncthreads();
     }
-    __syncthreads();
-    const int listed = s_ts[n_units], share = s_share;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int grp = lane / LPT, sub = lane % LPT;
-    // this thread's part of a unit's output
-    const int x0 = min((int)threadIdx.x, NT - 1) * VPT, xg = x0 / D;
-    const bool mine = (int)threadIdx.x < NT;
+    auto of_unit = [&](const int *list, int u) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(list[mine_at + u]); };
+    auto begin_of = [&](int u) __attribute__((always_inline)) { return of_unit(s_ts, u); };
+    auto end_of = [&](int u) __attribute__((always_inline)) { return of_unit(s_ts, u + 1); };
     // even shares: a pair of blocks (even, odd) covers 2 * share tiles, te of them the even block and to the odd one
     const int skew = n_blocks % 2 == 0 ? share * a.skew_permille / 1000 : 0;
     const int te = share + skew, to = share - skew;
@@ -787,20 +1199,19 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
         cur = (int)(blockIdx.x / 2) * 2 * share + ((blockIdx.x & 1) ? te : 0);
         end = min(listed, cur + ((blockIdx.x & 1) ? to : te));
         for (int uu = blockIdx.x; uu < n_units; uu += n_blocks)  // units with nothing cached: the output is zero
-            if (s_ts[uu + 1] == s_ts[uu] && mine)
-                for (int e = 0; e < VPT; e++) a.out[(size_t)uu * G * D + x0 + e] = 0.f;
+            if (begin_of(uu) == end_of(uu))
+                for (int e = threadIdx.x; e < G * D; e += kAttnThreads) a.out[(size_t)uu * G * D + e] = 0.f;
     }
     // the unit u with s_ts[u] <= first < s_ts[u+1]
-    int u = 0;
     {
         const int first = share > 0 ? cur : (int)blockIdx.x;
-        if (n_units <= 64) {  // one comparison per lane; true for lane 0
-            u = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_units && s_ts[lane] <= first)) - 1;
+        if constexpr (FEW) {  // one comparison per lane; true for lane 0
+            u = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_units && s_ts[mine_at + lane] <= first)) - 1;
         } else {
             int lo = 0, hi = n_units - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (s_ts[mid] <= first) lo = mid; else hi = mid - 1;
+                if (begin_of(mid) <= first) lo = mid; else hi = mid - 1;
             }
             u = lo;
         }
@@ -809,58 +1220,49 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
         int np, slot0, slot, p0, p1;  // parts of the unit, the partials' slots, this part's tiles of the unit
         if (share == 0) {
             if (again || (int)blockIdx.x >= listed) break;
-            slot0 = s_ts[u];
+            slot0 = begin_of(u);
             slot = blockIdx.x;
-            np = s_ts[u + 1] - slot0;
+            np = end_of(u) - slot0;
         } else {
             if (cur >= end) break;
-            while (s_ts[u + 1] <= cur) u++;  // also skips units without tiles
-            const int first = s_ts[u] + kUnitStartTiles;  // the unit's first real tile
+            while (end_of(u) <= cur) u++;  // also skips units without tiles
+            const int first = begin_of(u) + kUnitStartTiles;  // the unit's first real tile
             if (cur < first) {
                 cur = first;
                 if (cur >= end) break;  // the share ends inside the allowance: the next block begins the unit
             }
             slot0 = block_of(first);
-            np = block_of(s_ts[u + 1] - 1) - slot0 + 1;
+            np = block_of(end_of(u) - 1) - slot0 + 1;
             slot0 += u;
             slot = (int)blockIdx.x + u;
             p0 = cur - first;
-            cur = min(s_ts[u + 1], end);
+            cur = min(end_of(u), end);
             p1 = cur - first;
         }
-        const int um = s_um[u], gl_all = s_gl[u], nloc = s_nl[u];
-        const int gl = global_tokens(pv, a, u, gl_all);
+        const int um = of_unit(s_um, u), gl_all = of_unit(s_gl, u), gl = of_unit(s_gt, u), nloc = of_unit(s_nl, u);
         const int tiles = ceil_tiles(gl) + ceil_tiles(nloc);
-        if (share == 0) {
-            p0 = (int)((int64_t)tiles * (slot - slot0) / np);
-            p1 = (int)((int64_t)tiles * (slot - slot0 + 1) / np);
+        if (share == 0) {  // ascending in the part, and the same for all blocks of the unit
+            const float each = (float)tiles * __builtin_amdgcn_rcpf((float)np);
+            auto cut = [&](int i) __attribute__((always_inline)) {
+                return i == np ? tiles : min(__builtin_amdgcn_readfirstlane((int)((float)i * each)), tiles);
+            };
+            p0 = cut(slot - slot0);
+            p1 = cut(slot - slot0 + 1);
         }
         const int w0 = p0 + (p1 - p0) * wave / kAttnWaves, w1 = p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
         if (again) __syncthreads();  // the states in LDS are rewritten
-        float m[G], l[G], acc[G][EPL];
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            m[g] = -INFINITY;
-            l[g] = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; e++) acc[g][e] = 0.f;
-        }
-        if (w0 < w1) {
-            uint32_t qreg[G][4];
-            const char *qp = a.q + ((size_t)u * G * D) * ES + sub * 16;
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                const uint4 t4 = *reinterpret_cast<const uint4 *>(qp + (size_t)g * D * ES);
-                qreg[g][0] = t4.x; qreg[g][1] = t4.y; qreg[g][2] = t4.z; qreg[g][3] = t4.w;
-            }
-            stream_tiles<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, m, l, acc, s_strips[wave], lane);
-        }
-        // the block's row groups meet in LDS
-        put_states<DT, D, G>(s_st, wave, grp, sub, m, l, acc);
+        DecSoftmax<DT, D, G> st;
+        run_part<DT, D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
+        // the waves of the block meet in LDS
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // (what follows from it is worked out here and not in front of the first row)
+        const int x0 = min(tid, NT - 1) * VPT, xg = x0 / D;  // this thread's part of the unit's output
+        const bool mine = tid < NT;
+        put_states<DT, D, G>(s_st, wave, tid & 63, st);
         __syncthreads();
         float M, L, o[VPT];
         fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
-        float *out = a.out + (size_t)u * G * D + x0;
+        float *out = a.out + (size_t)u * G * D;
         if (np > 1) {  // block-uniform
             // The stores carry the policy of a device-scope access (written through) and vmcnt counts them until they are
             // acknowledged there: every wave waits for its own, then one thread counts the block; the folding block's loads
@@ -873,20 +1275,24 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
             if (threadIdx.x == 0)
                 s_arrived = __hip_atomic_fetch_add(&a.counters[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-            if (s_arrived != np - 1) continue;
+            if (__builtin_amdgcn_readfirstlane(s_arrived) != np - 1) continue;
             asm volatile("" ::: "memory");
-            const int xs[1] = {x0};
-            float Ls[1], os[1][VPT];
-            fold_partials<D, G>(r_ml, r_acc, slot0, np, xs, Ls, os);
-            L = Ls[0];
+            if (np <= 8) {
+                const int xs[1] = {x0};
+                float Ls[1], os[1][VPT];
+                fold_partials<D, G>(r_ml, r_acc, slot0, np, xs, Ls, os);
+                L = Ls[0];
 #pragma unroll
-            for (int e = 0; e < VPT; e++) o[e] = os[0][e];
+                for (int e = 0; e < VPT; e++) o[e] = os[0][e];
+            } else {
+                fold_partials_block<DT, D, G>(a, slot0, np, s_st, tid, x0, xg, L, o);
+            }
             if (threadIdx.x == 0) __hip_atomic_store(&a.counters[u], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (mine) {
             const float inv = tiles > 0 ? 1.0f / L : 0.f;
 #pragma unroll
-            for (int e = 0; e < VPT; e++) out[e] = tiles > 0 ? o[e] * inv : 0.f;
+            for (int e = 0; e < VPT; e++) out[out_of<DT, D>(x0 + e)] = tiles > 0 ? o[e] * inv : 0.f;
         }
     }
 }
@@ -906,18 +1312,29 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_kernel(View pv, At
 // 64 x 1000 27.2 -> 22.9, 128 x 1000 44.3 -> 34.4, 33 x 4000 27.8 -> 28.7.
 constexpr int kMinWaveTiles = 16, kWaveStartTiles = 12;
 template <int DT, int D, int G>
-__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View pv, AttendArgs a) {
+struct DecManyLds {
+    DecWaveLds<DT, D, G> wave[kAttnWaves];
+    DecStates<DT, D, G> states;
+    int ts[kMaxCallUnits + 1];  // tiles before unit u, those charged to the begin of a unit included
+    int gl[kMaxCallUnits];      // entries in the unit's global cache
+    int nl[kMaxCallUnits];      // tokens in its ring
+    int totals[3][kAttnWaves];  // a wave's tiles, units with any, and tiles of its longest unit
+    int arrived;
+};
+template <int DT, int D, int G, bool SMALL>
+__device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a) {
     using SH = DecShape<DT, D, G>;
     using OUT = DecOut<DT, D, G>;
-    constexpr int ES = SH::ES, EPL = SH::EPL, LPT = SH::LPT, TPW = SH::TPW, VPT = OUT::VPT, NT = OUT::NT;
-    __shared__ int s_ts[kMaxCallUnits + 1];  // tiles before unit u, those charged to the begin of a unit included
-    __shared__ int s_gl[kMaxCallUnits];      // entries in the unit's global cache
-    __shared__ int s_nl[kMaxCallUnits];      // tokens in its ring
-    __shared__ int s_um[kMaxCallUnits];      // its index into the per-unit metadata
-    __shared__ int s_wave[3][kAttnWaves];    // a wave's tiles, units with any, and tiles of its longest unit
-    __shared__ int s_arrived;
-    __shared__ __attribute__((aligned(16))) DecStrips s_strips[kAttnWaves];
-    __shared__ DecStates<DT, D, G> s_st;
+    constexpr int VPT = OUT::VPT, NT = OUT::NT;
+    extern __shared__ __attribute__((aligned(1024))) char s_mem[];
+    auto &lds = *reinterpret_cast<DecManyLds<DT, D, G> *>(s_mem);
+    auto &s_wave_lds = lds.wave;
+    auto &s_st = lds.states;
+    auto &s_ts = lds.ts;
+    auto &s_gl = lds.gl;
+    auto &s_nl = lds.nl;
+    auto &s_wave = lds.totals;
+    auto &s_arrived = lds.arrived;
 
     const int n_units = a.n_seqs * pv.Hkv, n_blocks = (int)gridDim.x, n_waves = n_blocks * kAttnWaves;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -947,7 +1364,6 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
         if (u < n_units) {
             s_gl[u] = gl_all[i];
             s_nl[u] = nl;
-            s_um[u] = um[i];
             tl[i] = ceil_tiles(global_tokens(pv, a, u, gl_all[i])) + ceil_tiles(nl);
         }
         sum += tl[i];
@@ -992,7 +1408,6 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
         if ((int)threadIdx.x == kAttnThreads - 1 && n_units == kMaxCallUnits) s_ts[kMaxCallUnits] = at;
     }
     __syncthreads();
-    const int grp = lane / LPT, sub = lane % LPT;
     // Even shares: the KW workers of an even block and those of the odd one behind it cover 2 * KW * share tiles, te each
     // on the even block and to on the odd one.
     const int KW = by_wave ? kAttnWaves : 1, log2KW = by_wave ? 2 : 0, wid = by_wave ? (int)blockIdx.x * kAttnWaves + wave : (int)blockIdx.x;
@@ -1042,32 +1457,16 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
             cur = min(s_ts[u + 1], end);
             p1 = cur - first;
         }
-        const int um = s_um[u], gl_all = s_gl[u], nloc = s_nl[u];
+        const int b = u / pv.Hkv, um = unit_meta(pv, a.sid[b], a.layer, u - b * pv.Hkv), gl_all = s_gl[u], nloc = s_nl[u];
         const int gl = global_tokens(pv, a, u, gl_all);
         if (solo) p1 = ceil_tiles(gl) + ceil_tiles(nloc);
         const int w0 = by_wave ? p0 : p0 + (p1 - p0) * wave / kAttnWaves, w1 = by_wave ? p1 : p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
         if (again && !by_wave) __syncthreads();  // the states in LDS are rewritten
-        float m[G], l[G], acc[G][EPL];
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            m[g] = -INFINITY;
-            l[g] = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; e++) acc[g][e] = 0.f;
-        }
-        if (w0 < w1) {
-            uint32_t qreg[G][4];
-            const char *qp = a.q + ((size_t)u * G * D) * ES + sub * 16;
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                const uint4 t4 = *reinterpret_cast<const uint4 *>(qp + (size_t)g * D * ES);
-                qreg[g][0] = t4.x; qreg[g][1] = t4.y; qreg[g][2] = t4.z; qreg[g][3] = t4.w;
-            }
-            stream_tiles<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, m, l, acc, s_strips[wave], lane);
-        }
+        DecSoftmax<DT, D, G> st;
+        run_part<DT, D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
         // the row groups of the block meet in LDS, or those of the wave (whose LDS accesses stay in order)
         __builtin_amdgcn_wave_barrier();
-        put_states<DT, D, G>(s_st, wave, grp, sub, m, l, acc);
+        put_states<DT, D, G>(s_st, wave, lane, st);
         if (by_wave) __builtin_amdgcn_wave_barrier(); else __syncthreads();
         const __amdgpu_buffer_rsrc_t r_acc = part_rsrc(a.part_acc, a.part_acc_bytes);
         const __amdgpu_buffer_rsrc_t r_ml = part_rsrc(a.part_ml, a.part_ml_bytes);
@@ -1075,7 +1474,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
         for (int part = part0; part < part1; part++) {
             const int x = part * 64 + lane, x0 = min(x, NT - 1) * VPT, xg = x0 / D;
             float M, L, o[VPT];
-            if (by_wave) fold_states<TPW>(s_st, wave * TPW, x0, xg, M, L, o);
+            if (by_wave) fold_states<OUT::NSW>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
             else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
             if (x >= NT) continue;
             if (np > 1) {
@@ -1083,7 +1482,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
             } else {
                 const float inv = p1 > p0 ? 1.0f / L : 0.f;  // nothing cached: zero
 #pragma unroll
-                for (int e = 0; e < VPT; e++) out[x0 + e] = p1 > p0 ? o[e] * inv : 0.f;
+                for (int e = 0; e < VPT; e++) out[out_of<DT, D>(x0 + e)] = p1 > p0 ? o[e] * inv : 0.f;
             }
         }
         if (np == 1) continue;
@@ -1114,7 +1513,7 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
                 if ((part0 + k) * 64 + lane >= NT) continue;
                 const float inv = 1.0f / L[k];
 #pragma unroll
-                for (int e = 0; e < VPT; e++) out[x0[k] + e] = o[k][e] * inv;
+                for (int e = 0; e < VPT; e++) out[out_of<DT, D>(x0[k] + e)] = o[k][e] * inv;
             }
         };
         if (by_wave) fold(std::integral_constant<int, (NT + 63) / 64>{}); else fold(std::integral_constant<int, 1>{});
@@ -1122,19 +1521,46 @@ __global__ __launch_bounds__(kAttnThreads) void attend_decode_many_kernel(View p
     }
 }
 
+// The kernels.  bf16 keeps to 256 registers (bounds of two waves per SIMD, though its LDS leaves room for one: that is why it is
+// allocated at the launch), where the compiler puts a product's accumulators into vector registers and not into the other half of
+// the file, from which it copies them all back in every turn; fp32 needs more.
+template <int D, int G, bool SMALL, bool FEW>
+__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_kernel(View pv, AttendArgs a) {
+    decode_blocks<WGKV_BF16, D, G, SMALL, FEW>(pv, a);
+}
+template <int D, int G, bool SMALL>
+__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_many_kernel(View pv, AttendArgs a) {
+    decode_many<WGKV_BF16, D, G, SMALL>(pv, a);
+}
+template <int D, int G, bool FEW>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_f32_kernel(View pv, AttendArgs a) { decode_blocks<WGKV_F32, D, G, false, FEW>(pv, a); }
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_f32_kernel(View pv, AttendArgs a) { decode_many<WGKV_F32, D, G, false>(pv, a); }
+
 // One block per compute unit: an even split is one round of blocks, and more waves on a compute unit stream slower.
+template <int DT, int D, int G>
+static void launch_one(const View &pv, const AttendArgs &a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    const int n_units = a.n_seqs * pv.Hkv;
+    const bool many = n_units > min(grid, kMaxUnits), few = n_units <= 64;
+    void (*kernel)(View, AttendArgs);
+    if constexpr (DT == WGKV_F32)
+        kernel = many ? attend_decode_many_f32_kernel<D, G> : few ? attend_decode_f32_kernel<D, G, true> : attend_decode_f32_kernel<D, G, false>;
+    else if (pv.logP < 4)  // a page lookup per row
+        kernel = many ? attend_decode_many_kernel<D, G, true> : few ? attend_decode_kernel<D, G, true, true> : attend_decode_kernel<D, G, true, false>;
+    else
+        kernel = many ? attend_decode_many_kernel<D, G, false> : few ? attend_decode_kernel<D, G, false, true> : attend_decode_kernel<D, G, false, false>;
+    const unsigned lds = many ? sizeof(DecManyLds<DT, D, G>) : sizeof(DecBlocksLds<DT, D, G>);
+    static_assert(sizeof(DecManyLds<DT, D, G>) <= 160 * 1024 && sizeof(DecBlocksLds<DT, D, G>) <= 160 * 1024, "");
+    if (ev0 && ev1)  // the events take the begin and end time stamps of this dispatch itself
+        hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), lds, st, ev0, ev1, 0, pv, a);
+    else
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), lds, st, pv, a);
+}
 template <int DT, int D>
 static hipError_t launch_g(const View &pv, const AttendArgs &a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     switch (pv.G) {
-#define WGKV_CASE(GG)                                                                              \
-    case GG: {                                                                                     \
-        const auto kernel = a.n_seqs * pv.Hkv > grid ? attend_decode_many_kernel<DT, D, GG> : attend_decode_kernel<DT, D, GG>; \
-        if (ev0 && ev1)  /* the events take the begin and end time stamps of this dispatch itself */ \
-            hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, ev0, ev1, 0, pv, a); \
-        else                                                                                       \
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, pv, a);              \
-        break;                                                                                     \
-    }
+#define WGKV_CASE(GG)                                                                                          \
+    case GG: launch_one<DT, D, GG>(pv, a, grid, st, ev0, ev1); break;
         WGKV_CASE(1)
         WGKV_CASE(2)
         WGKV_CASE(4)
