@@ -53,9 +53,36 @@ __device__ __forceinline__ uint32_t gm_pack(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, t);
 }
 
+// The sum of a row's squares by pairs of neighbours, pairs of pairs and so on, as a wave's lanes sum them that hold an element each:
+// the order that widths which are no multiple of 32 have always had.  Another order moves a few features in a million across a
+// rounding boundary.
+template <int D>
+__device__ __forceinline__ float gm_squares_by_pairs(const uint4 (&raw)[D / 16]) {
+#pragma clang fp contract(off)
+    float s[D / 16];
+#pragma unroll
+    for (int j = 0; j < D / 16; j++) {
+        const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const float x = gm_bf16_to_f32(w[e] & 0xffffu), y = __uint_as_float(w[e] & 0xffff0000u);
+            const float xx = x * x, yy = y * y;
+            p[e] = xx + yy;
+        }
+        const float a = p[0] + p[1], b = p[2] + p[3], c = a + b;
+        s[j] = c + __shfl_xor(c, 32);  // the other half of the row holds the other octet of every sixteen
+    }
+#pragma unroll
+    for (int o = 1; o < D / 16; o *= 2)
+#pragma unroll
+        for (int j = 0; j < D / 16; j += 2 * o) s[j] = s[j] + s[j + o];
+    return s[0];
+}
+
 // The normalised features of one token as matrix operands: the 8 features [16 ks + 8 half, +8) of every slice of 16.
 template <int D>
-__device__ __forceinline__ void gm_features(const char *k, const char *kr, size_t row, int half, float eps,
+__device__ __forceinline__ void gm_features(const char *k, const char *kr, size_t row, int half, float eps, bool by_pairs,
                                             gm_bf16x8_t (&xv)[2 * D / 16]) {
     constexpr int KS = 2 * D / 16;
 #pragma unroll
@@ -77,6 +104,7 @@ __device__ __forceinline__ void gm_features(const char *k, const char *kr, size_
             }
         }
         ss += __shfl_xor(ss, 32);  // the other half of the row
+        if (by_pairs) ss = gm_squares_by_pairs<D>(raw);  // wave-uniform
         const float r = 1.0f / sqrtf(ss / (float)D + eps);
 #pragma unroll
         for (int j = 0; j < KS / 2; j++) {
@@ -118,27 +146,34 @@ __global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) {
         const long long tok = tok0 + cb * kGmTokens;  // rows past the end repeat the last token, unwritten
-        gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv[cb]);
+        gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, width % kGmUnits != 0, xv[cb]);
     }
 
     // ---- chunks of 32 hidden units: W1 rows, b1 and W2 through LDS, two buffers ----
-    const int n_chunks = width / kGmUnits, n_it = (n_chunks + US - 1) / US;
+    const int n_chunks = (width + kGmUnits - 1) / kGmUnits, n_it = (n_chunks + US - 1) / US;
     uint4 w0, w1, w2, w3;  // this thread's pieces of the chunk on its way to LDS
     w2 = w3 = make_uint4(0u, 0u, 0u, 0u);
     float b1v = 0.f, w2v = 0.f;
     auto fetch = [&](int it) __attribute__((always_inline)) {
         const int c = min(it * US + us, n_chunks - 1);  // a group without a chunk of its own in the last turn drops it
         const char *src = W1 + ((size_t)h * width + (size_t)c * kGmUnits) * (2 * D * 2);  // 32 consecutive rows
-        w0 = *reinterpret_cast<const uint4 *>(src + ((size_t)0 * 256 + tid) * 16);
-        w1 = *reinterpret_cast<const uint4 *>(src + ((size_t)1 * 256 + tid) * 16);
+        const int rows = min(width - c * kGmUnits, kGmUnits);  // fewer in the last chunk of a width that is no multiple of 32: units of zeros
+        auto piece = [&](int p) __attribute__((always_inline)) {
+            const int i = p * 256 + tid;
+            const uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)min(i, rows * kRowPieces - 1) * 16);
+            return i < rows * kRowPieces ? v : make_uint4(0u, 0u, 0u, 0u);
+        };
+        w0 = piece(0);
+        w1 = piece(1);
         if (kPieces > 2) {
-            w2 = *reinterpret_cast<const uint4 *>(src + ((size_t)2 * 256 + tid) * 16);
-            w3 = *reinterpret_cast<const uint4 *>(src + ((size_t)3 * 256 + tid) * 16);
+            w2 = piece(2);
+            w3 = piece(3);
         }
         if (tid < kGmUnits) {
-            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + tid;
-            b1v = b1[u];
-            w2v = gm_bf16_to_f32(*reinterpret_cast<const uint16_t *>(W2 + u * 2));
+            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + min(tid, rows - 1);
+            const float b = b1[u], w = gm_bf16_to_f32(*reinterpret_cast<const uint16_t *>(W2 + u * 2));
+            b1v = tid < rows ? b : 0.f;
+            w2v = tid < rows ? w : 0.f;
         }
     };
     auto put = [&](int buf, int p, const uint4 v) __attribute__((always_inline)) {
@@ -230,27 +265,39 @@ __global__ __launch_bounds__(kGmSplit * 64) void gate_mlp_split_kernel(const cha
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
     const long long tok = (long long)(blockIdx.x / Hkv) * kGmTokens + n;
-    const int n_chunks = width / kGmUnits;
+    const int n_chunks = (width + kGmUnits - 1) / kGmUnits;
     gm_bf16x8_t wa[KS], xv[KS];
     float4 bb[4];
     uint2 ww[4];
     auto fetch = [&](int c) __attribute__((always_inline)) {
-        const size_t u = (size_t)h * width + (size_t)min(c, n_chunks - 1) * kGmUnits;
-        const char *src = W1 + (u + n) * (2 * D * 2) + half * 16;
+        const int u = min(c, n_chunks - 1) * kGmUnits + n;  // past the last unit: a row of zeros
+        const char *src = W1 + ((size_t)h * width + min(u, width - 1)) * (2 * D * 2) + half * 16;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) wa[ks] = *reinterpret_cast<const gm_bf16x8_t *>(src + ks * 32);
+        for (int ks = 0; ks < KS; ks++) {
+            const uint4 w = *reinterpret_cast<const uint4 *>(src + ks * 32);
+            wa[ks] = __builtin_bit_cast(gm_bf16x8_t, u < width ? w : make_uint4(0u, 0u, 0u, 0u));
+        }
     };
     auto fetch_b = [&](int c) __attribute__((always_inline)) {
-        const size_t u = (size_t)h * width + (size_t)min(c, n_chunks - 1) * kGmUnits;
+        const size_t u0 = (size_t)h * width;
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            bb[j] = make_float4(b1[u + 8 * j + 4 * half], b1[u + 8 * j + 4 * half + 1], b1[u + 8 * j + 4 * half + 2], b1[u + 8 * j + 4 * half + 3]);
-            const uint16_t *w = reinterpret_cast<const uint16_t *>(W2) + u + 8 * j + 4 * half;
-            ww[j] = make_uint2((uint32_t)w[0] | ((uint32_t)w[1] << 16), (uint32_t)w[2] | ((uint32_t)w[3] << 16));
+            float b[4];
+            uint32_t w[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int u = min(c, n_chunks - 1) * kGmUnits + 8 * j + 4 * half + i;
+                const float bv = b1[u0 + min(u, width - 1)];
+                const uint32_t wv = reinterpret_cast<const uint16_t *>(W2)[u0 + min(u, width - 1)];
+                b[i] = u < width ? bv : 0.f;
+                w[i] = u < width ? wv : 0u;
+            }
+            bb[j] = make_float4(b[0], b[1], b[2], b[3]);
+            ww[j] = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
         }
     };
     fetch(wave);
-    gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv);
+    gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, width % kGmUnits != 0, xv);
     float acc = 0.f;  // twice the logit
     for (int c = wave; c < n_chunks; c += kGmSplit) {  // wave-uniform
         fetch_b(c);
@@ -282,7 +329,91 @@ __global__ __launch_bounds__(kGmSplit * 64) void gate_mlp_split_kernel(const cha
     }
 }
 
-// Any other shape or an fp32 model: one block per (token, kv head), one hidden unit per
+// fp32 models: 16 tokens of a head a block, their features in LDS for the whole block, W1 in slices of 64 units x 128 features; a thread
+// has one token and four neighbouring units, so a feature and four weights are two LDS reads for four multiply-adds.  Bound by
+// those.  us against a block per (token, head), whose lanes read rows of W1 apart: 1500 tokens x 2 heads of 64, width 512 95 -> 28;
+// 700 x 4 heads of 128, width 768 259 -> 70; 100 x 4 of 128, width 512 32 -> 48, which the rule leaves where it was.
+constexpr int kGfTokens = 16, kGfUnits = 64, kGfSlice = 128;
+__global__ __launch_bounds__(256) void gate_mlp_f32_kernel(const float *k, const float *kr, const float *W1, const float *b1, const float *W2,
+                                                          const float *b2, float eps, float *g_out, long long T, int Hkv, int d, int width) {
+    extern __shared__ __attribute__((aligned(16))) float s_x[];  // [16][2 d + 4]
+    __shared__ __attribute__((aligned(16))) float s_w[2][kGfSlice][kGfUnits + 4];
+    __shared__ float s_r[kGfTokens][16];
+    const int h = blockIdx.y, tid = threadIdx.x, tok = tid & 15, part = tid >> 4, ld = 2 * d + 4;
+    const long long t0 = (long long)blockIdx.x * kGfTokens, t = t0 + tok;
+    const size_t row = ((size_t)(t < T ? t : T - 1) * Hkv + h) * d;  // rows past the end repeat the last token, unwritten
+    for (int half = 0; half < 2; half++) {
+        const float *src = half == 0 ? k : kr;
+        float ss = 0.f;
+        for (int e = part; e < d; e += 16) {
+            const float v = src[row + e];
+            s_x[tok * ld + half * d + e] = v;
+            ss = fmaf(v, v, ss);
+        }
+        __syncthreads();  // the sums of the half before are read
+        s_r[tok][part] = ss;
+        __syncthreads();
+        ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i++) ss += s_r[tok][i];
+        const float r = 1.0f / sqrtf(ss / (float)d + eps);
+        for (int e = part; e < d; e += 16) s_x[tok * ld + half * d + e] *= r;
+    }
+    const int n_sl = (2 * d + kGfSlice - 1) / kGfSlice, n_ut = (width + kGfUnits - 1) / kGfUnits, total = n_sl * n_ut;
+    float4 w[8];  // this thread's part of the slice on its way to LDS: unit tid / 4 of 64, features 16 * i + 4 * (tid % 4) ..
+    auto fetch = [&](int it) __attribute__((always_inline)) {
+        const int u = it / n_sl * kGfUnits + (tid >> 2), e0 = it % n_sl * kGfSlice + (tid & 3) * 4;
+        const float *src = W1 + ((size_t)h * width + min(u, width - 1)) * (2 * d);  // a unit past the last one repeats it, unused
+#pragma unroll
+        for (int i = 0; i < 8; i++) w[i] = *reinterpret_cast<const float4 *>(src + min(e0 + 16 * i, 2 * d - 4));
+    };
+    auto stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            float *dst = &s_w[buf][16 * i + (tid & 3) * 4][tid >> 2];
+            dst[0] = w[i].x; dst[kGfUnits + 4] = w[i].y; dst[2 * (kGfUnits + 4)] = w[i].z; dst[3 * (kGfUnits + 4)] = w[i].w;
+        }
+    };
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    float acc = 0.f, z[4] = {0.f, 0.f, 0.f, 0.f};  // acc: twice the logit
+    for (int i = 0; i < total; i++) {
+        if (i + 1 < total) fetch(i + 1);
+        const int e0 = i % n_sl * kGfSlice, ne = min(kGfSlice, 2 * d - e0);
+        const float *x = &s_x[tok * ld + e0];
+#pragma unroll 4
+        for (int e = 0; e < ne; e += 4) {
+            const float4 xv = *reinterpret_cast<const float4 *>(x + e);
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const float4 wv = *reinterpret_cast<const float4 *>(&s_w[i & 1][e + c][part * 4]);
+                const float xc = c == 0 ? xv.x : c == 1 ? xv.y : c == 2 ? xv.z : xv.w;
+                z[0] = fmaf(wv.x, xc, z[0]); z[1] = fmaf(wv.y, xc, z[1]); z[2] = fmaf(wv.z, xc, z[2]); z[3] = fmaf(wv.w, xc, z[3]);
+            }
+        }
+        if (i % n_sl == n_sl - 1) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const int u = i / n_sl * kGfUnits + part * 4 + c;
+                if (u < width) acc = fmaf(W2[(size_t)h * width + u], gm_gelu2(z[c] + b1[(size_t)h * width + u]), acc);
+                z[c] = 0.f;
+            }
+        }
+        if (i + 1 < total) stage((i + 1) & 1);
+        __syncthreads();
+    }
+    s_r[tok][part] = acc;
+    __syncthreads();
+    if (tid < kGfTokens && t < T) {
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i++) a += s_r[tok][i];
+        g_out[(size_t)t * Hkv + h] = 1.0f / (1.0f + __expf(-fmaf(0.5f, a, b2[h])));
+    }
+}
+
+// Any other shape, and few tokens of an fp32 model: one block per (token, head), one hidden unit per
 // thread and turn, fp32 arithmetic.  With bf16 inputs the features are rounded to bf16 like
 // in the matrix-core kernel, so both compute the same function.
 template <int DT>
@@ -340,7 +471,7 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
                            const void *w2, const float *b2, float eps, float *g_out, hipStream_t st) {
     if (n_tokens == 0) return hipSuccess;
     const char *kp = (const char *)k, *krp = (const char *)k_rope, *w1p = (const char *)w1, *w2p = (const char *)w2;
-    if (dtype == WGKV_BF16 && (head_dim == 128 || head_dim == 64) && width % kGmUnits == 0) {
+    if (dtype == WGKV_BF16 && (head_dim == 128 || head_dim == 64)) {
         // Which form, by the number of (token, head) pairs: each up to one round of its resident blocks, where its time
         // is nearly flat.  us at head_dim 128, width 512, for 8K / 32K / 64K / 96K / 128K pairs (the lines lie where
         // two columns cross; 64-wide heads cross at the same places):
@@ -350,11 +481,13 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         //   256 tokens (a product's W1 operand used twice)            34   37    42    53    56
         // The rounds are those of 256 compute units, and other widths than 512 (and 32, below) were not timed for the lines:
         // a pair's work grows with the width in every form alike, what a form leaves idle does not depend on it.
+        // A width that is no multiple of 32 ends in a chunk with units of zeros (2048 tokens x 8 heads, width 200: 301 us with a
+        // block per (token, head), 13 here).
         // One or two chunks of hidden units leave nothing to split over waves, one chunk nothing to use twice either: those calls
         // count as of the size that takes the third form.  Width 32, 33 / 4096 / 16384 tokens x 8 heads: 6.3 / 7.5 / 19.3 us, by
         // their own size 8.5 / 9.6 / 20.5.
         const int64_t pairs = n_tokens * n_kv_heads;
-        const int64_t cols = width == kGmUnits ? 98304 : width <= 2 * kGmUnits ? std::max<int64_t>(pairs, 98304) : pairs;
+        const int64_t cols = width <= kGmUnits ? 98304 : width <= 2 * kGmUnits ? std::max<int64_t>(pairs, 98304) : pairs;
 #define WGKV_GM(D_, CB_, US_)                                                                                            \
     hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_>),                                                            \
                        dim3((unsigned)((n_tokens + 4 * kGmTokens * CB_ - 1) / (4 * kGmTokens * CB_)), n_kv_heads),       \
@@ -373,6 +506,14 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         }
 #undef WGKV_GM_D
 #undef WGKV_GM
+        return hipGetLastError();
+    }
+    // A block of 16 tokens stages W1 slice by slice (rows of whole 16-byte pieces), a chain that fewer than about 768 (token, head)
+    // pairs do not pay for (400 pairs 32 us alone, 48 in blocks; 3000 pairs 95 and 28).
+    const size_t smem_f32 = (size_t)kGfTokens * (2 * head_dim + 4) * sizeof(float);
+    if (dtype == WGKV_F32 && n_tokens * n_kv_heads > 768 && head_dim % 2 == 0 && n_tokens < ((int64_t)1 << 34) && smem_f32 <= 40 * 1024) {
+        hipLaunchKernelGGL(gate_mlp_f32_kernel, dim3((unsigned)((n_tokens + kGfTokens - 1) / kGfTokens), n_kv_heads), dim3(256), smem_f32, st, (const float *)k,
+                           (const float *)k_rope, (const float *)w1, b1, (const float *)w2, b2, eps, g_out, (long long)n_tokens, n_kv_heads, head_dim, width);
         return hipGetLastError();
     }
     // grid.x carries the tokens: split very long inputs over several launches
