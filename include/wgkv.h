@@ -387,7 +387,8 @@ int wgkv_quest_update(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int3
  *                       steps replayed in a graph since the last wgkv_status), pages from
  *                       score_stride on are neither scored nor selected
  *   sel_pages_out_dev int32 [n_seqs * n_kv_heads][budget_pages]: ascending indices into the
- *                       head's global page table; sel_count_out_dev int32 [n_seqs * n_kv_heads]
+ *                       head's global page table, -1 past the head's count;
+ *   sel_count_out_dev   int32 [n_seqs * n_kv_heads]
  * fp32 arithmetic.  Errors: INVALID_ARG, HIP. */
 int wgkv_quest_select(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const int32_t *seq_ids_host,
                       const void *q_dev, void *landmarks_dev, size_t landmark_bytes, int32_t budget_pages,

@@ -343,8 +343,9 @@ class Pool:
             scores = torch.zeros((n_units, score_stride), dtype=torch.float32, device=self.device)
         assert scores.is_cuda and scores.is_contiguous() and scores.dtype == torch.float32
         assert scores.numel() == n_units * score_stride
-        sel = torch.full((n_units, budget_pages), -1, dtype=torch.int32, device=self.device)
-        cnt = torch.zeros((n_units,), dtype=torch.int32, device=self.device)
+        # the call writes every element: -1 past a head's count
+        sel = torch.empty((n_units, budget_pages), dtype=torch.int32, device=self.device)
+        cnt = torch.empty((n_units,), dtype=torch.int32, device=self.device)
         _check(self.L.wgkv_quest_select(self.h, layer, len(seq_ids), _ids(seq_ids), _ptr(q), _ptr(landmarks),
                                         landmarks.numel(), budget_pages, _ptr(scores), score_stride, _ptr(sel),
                                         _ptr(cnt), _stream()), "wgkv_quest_select")
