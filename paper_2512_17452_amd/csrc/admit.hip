@@ -13,6 +13,8 @@
 //
 // Page hand-out never races: demands are prefix-summed in (sequence position in
 // the call, kv head) order and unit u takes free_stack[top-1-base_u-i].
+#include <algorithm>
+
 #include "wgkv_dev.h"
 
 namespace wgkv {
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(1024) void decode_step_kernel(View pv, CallSeqs cs,
     if (threadIdx.x == 0) s_err = 0;
     __syncthreads();
     const int top = *pv.free_top;
-    const int u = threadIdx.x;  // n_units <= 1024 = blockDim.x
+    const int u = threadIdx.x;  // n_units <= blockDim.x: a thread per 16 bytes of a row up to 1024, and no more units than that
     int demand = 0, dl = 0, promote = 0, gold = 0, um = 0, slot = 0, lpage = -1, gpage = -1, ahead_mask = -1;
     if (u < n_units) {
         // the token count comes from device memory, not from the launch arguments, so that a
@@ -496,7 +498,7 @@ __global__ __launch_bounds__(1024) void decode_step_kernel(View pv, CallSeqs cs,
             *reinterpret_cast<uint4 *>(dp) = kk;
             *reinterpret_cast<uint4 *>(dp + pv.v_off) = vv;
         }
-        if (c != (int)threadIdx.x) {  // beyond the first 1024 chunks: not in registers yet
+        if (c != (int)threadIdx.x) {  // beyond a thread's first chunk: not in registers yet
             const size_t row = (size_t)uu * pv.row_bytes + sub * 16;
             kn = *reinterpret_cast<const uint4 *>(a.k + row);
             vn = *reinterpret_cast<const uint4 *>(a.v + row);
@@ -794,6 +796,15 @@ hipError_t launch_prefill(const View &pv, const CallSeqs &cs, int layer, float t
     return hipGetLastError();
 }
 
+// Threads of the one block of a decode step: one per 16 bytes of the new rows (so one per unit and sequence too), as far as a block
+// goes.  A block of 16 waves that have nothing to do starts, meets at its barriers and ends later than one wave: us, 1024 threads
+// always / as many as there is work: 2 heads of 64 fp32 4.05 / 3.46; the ring write alone of 8 heads of 128 is level.
+static unsigned step_threads(const View &pv, const CallSeqs &cs) {
+    const int64_t units = (int64_t)cs.n * pv.Hkv, lpr = pv.row_bytes >> 4;
+    const int64_t n = std::max(units * std::max<int64_t>(lpr, 1), (int64_t)cs.n);
+    return (unsigned)std::min<int64_t>(1024, (n + 63) / 64 * 64);
+}
+
 hipError_t launch_decode_step(const View &pv, const CallSeqs &cs, int layer, float tau,
                               const void *k, const void *v, const float *g, uint8_t *promoted_out,
                               hipStream_t st) {
@@ -804,7 +815,7 @@ hipError_t launch_decode_step(const View &pv, const CallSeqs &cs, int layer, flo
     a.v = (const char *)v;
     a.g = g;
     a.promoted_out = promoted_out;
-    hipLaunchKernelGGL(decode_step_kernel, dim3(1), dim3(1024), 0, st, pv, cs, a);
+    hipLaunchKernelGGL(decode_step_kernel, dim3(1), dim3(step_threads(pv, cs)), 0, st, pv, cs, a);
     return hipGetLastError();
 }
 
@@ -819,7 +830,7 @@ hipError_t launch_decode_ring(const View &pv, const CallSeqs &cs, int layer, con
     a.v = (const char *)v;
     a.g = g;
     a.promoted_out = promoted_out;
-    hipLaunchKernelGGL(decode_ring_kernel, dim3(1), dim3(1024), 0, st, pv, cs, a);
+    hipLaunchKernelGGL(decode_ring_kernel, dim3(1), dim3(step_threads(pv, cs)), 0, st, pv, cs, a);
     return hipGetLastError();
 }
 
