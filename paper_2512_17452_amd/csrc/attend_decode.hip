@@ -182,24 +182,31 @@ struct DecSoftmax<WGKV_BF16, D, G> {
 // 16 bytes per lane from memory to LDS at dst + 16 * lane, with the non-temporal hint: rows are read once.  In assembly, as the
 // compiler would put a wait for every outstanding request in front of the next LDS read; readers wait by count.  No result
 // register, and M0 is free for it.  The instruction's offset counts on both sides.
+// The base comes out of a lane (v_readlane), and a vector-memory instruction may not read a scalar register within five wait states of the
+// vector unit's writing it; the compiler, which sees to that elsewhere, does not look into an assembly block.  So the base is copied by the
+// scalar unit, whose reads of such a register the hardware holds back, and whose writes need no wait.  The copy is also
+// the wait state that a request needs behind M0.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ uint32_t dec_lds(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p; }
 __device__ __forceinline__ void dec_dma(const void *base, uint32_t off, const void *dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dec_lds(dst)), "v"(off), "s"(base) : "memory", "m0");
+    const void *b;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 nt" : "=&s"(b) : "s"(dec_lds(dst)), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void dec_dma_at(const void *lane_ptr, const void *dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(dec_lds(dst)), "v"(lane_ptr) : "memory", "m0");
 }
 // a tile of N * 1024 bytes, each request with its own lane offsets
 __device__ __forceinline__ void dec_dma_tile(const void *base, const uint32_t (&off)[4], const void *dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5 nt\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024 nt\n\t"
-                 "global_load_lds_dwordx4 %3, %5 offset:2048 nt\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072 nt"
-                 ::"s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "m0");
+    const void *b;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %6\n\tglobal_load_lds_dwordx4 %2, %0 nt\n\tglobal_load_lds_dwordx4 %3, %0 offset:1024 nt\n\t"
+                 "global_load_lds_dwordx4 %4, %0 offset:2048 nt\n\tglobal_load_lds_dwordx4 %5, %0 offset:3072 nt"
+                 : "=&s"(b) : "s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void dec_dma_tile(const void *base, const uint32_t (&off)[2], const void *dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024 nt"
-                 ::"s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "m0");
+    const void *b;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %2, %0 nt\n\tglobal_load_lds_dwordx4 %3, %0 offset:1024 nt"
+                 : "=&s"(b) : "s"(dec_lds(dst)), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 template <int N>
