@@ -158,7 +158,7 @@ struct DecSoftmax {
         }
     }
 };
-// bf16: m is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
+// bf16: m, 8 or less above the largest exponent so far, is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
 // element 16 * c + lane % 16.
 typedef float dec_f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
@@ -225,8 +225,9 @@ __device__ __forceinline__ uint32_t dec_pack_bf16(float lo, float hi) {  // roun
 // S = K Q^T with the G heads repeated over the 16 columns: a lane ends up with the scores of one head and keys 4 * (lane / 16) + {0..3}
 // of both tiles, which is the row operand of P V as it stands; the second operand is read transposed.  Sums over keys, those of the denominator too,
 // are the matrix core's.  About 0.65 us a pair where a tile took 0.65 us with dot products and reductions on the vector unit.
-// The maximum is brought up to date when a score exceeds it by 8 (weights of up to 256), so it costs no exchange between lanes in
-// the rule; sums are fp32 either way.
+// Weights are relative to 2^8 times the largest one so far, and that is brought up to date when a score exceeds it: it costs no exchange
+// between lanes in the rule, and no weight is above one, so values up to the end of the range stay finite as they do in sums of
+// weights that are relative to the maximum itself; sums are fp32 either way.
 template <int D, int G, bool SMALL_PAGES>
 __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int cur, int u_end,
                                              dec_u32x4_t (&q)[D / 32], float c_exp, DecSoftmax<WGKV_BF16, D, G> &st,
@@ -363,9 +364,9 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
                     for (int i = 0; i < 4; i++) s[t][i] = t * kTile + 4 * grp + i < valid ? s[t][i] : -INFINITY;
             }
             float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) * c_exp;
-            if (__builtin_amdgcn_ballot_w64(mt > st.m + 8.f) != 0) {  // rare once the maxima settle
+            if (__builtin_amdgcn_ballot_w64(mt > st.m) != 0) {  // rare once the maxima settle
                 const LanePair x = swap16(mt, mt);
-                const float mnew = fmaxf(st.m, max_xor32(fmaxf(x.a, x.b)));
+                const float mnew = fmaxf(st.m, max_xor32(fmaxf(x.a, x.b)) + 8.f);
                 const float corr = __builtin_amdgcn_exp2f(st.m - (mnew == -INFINITY ? 0.f : mnew));
                 st.m = mnew;
                 float ch[G];
