@@ -864,6 +864,7 @@ __device__ __forceinline__ void put_states(DecStates<DT, D, G> &s, int wave, int
 }
 
 // Place x of a state's accumulators is output element ...
+constexpr float kTiny = 1.401298464e-45f;  // the smallest above zero
 template <int DT, int D>
 __device__ __forceinline__ int out_of(int x) {
     constexpr int EP = D / 16;
@@ -889,6 +890,88 @@ __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0
 #pragma unroll
         for (int e = 0; e < VPT; e++) o[e] = fmaf(s.acc[s0 + i][x0 + e], f, o[e]);
     }
+}
+
+// bf16: the weighted sums of tiles [p0, p1) of a unit once more, for a wave one of whose sums is not finite, with each key's whole weight
+// times its value.  The parts that a weight is split into do not carry an infinity of V: later ones are zero or of either sign, and zero times
+// an infinity, or the sum of two that differ in sign, is NaN.  Sums of finite values never get here, so this is short and not fast: a
+// lane works out the scores of a key (64 keys at a time), then the lanes go through the keys.  Relative to the same maximum as the
+// sums that it replaces (states s0 .. s0 + N - 1); a weight too small for its type stays above zero as a number does.
+template <int N, int D, int G>
+__device__ __forceinline__ void sum_again(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int p0, int p1,
+                                          const DecStates<WGKV_BF16, D, G> &s, int s0, int x0, int xg, DecWaveLds<WGKV_BF16, D, G> &lds, int lane,
+                                          float (&o)[DecOut<WGKV_BF16, D, G>::VPT]) {
+    constexpr int VPT = DecOut<WGKV_BF16, D, G>::VPT;
+    struct Strip {
+        float w[64][G];
+        const char *v[64];
+    };
+    static_assert(sizeof(Strip) <= sizeof(lds), "");
+    Strip &strip = *reinterpret_cast<Strip *>(&lds);  // the wave has no requests under way
+    const char *qu = a.q + (size_t)u * G * D * 2;
+    const int n_gt = ceil_tiles(gl), last_page = max(((gl_all + pv.P - 1) >> pv.logP) - 1, 0);
+    const int32_t *sel = a.sel_pages ? a.sel_pages + (size_t)u * a.sel_stride : nullptr;
+#pragma unroll
+    for (int e = 0; e < VPT; e++) o[e] = 0.f;
+#pragma unroll 1
+    for (int t0 = p0; t0 < p1; t0 += 4) {
+        const int t = t0 + (lane >> 4);
+        const bool is_glob = t < n_gt;
+        const int tok = (is_glob ? t : t - n_gt) * kTile + (lane & 15);
+        const bool is = t < p1 && tok < (is_glob ? gl : nloc);
+        if (is) {
+            const int vp = tok >> pv.logP;
+            const int page = is_glob ? pv.global_pt[(size_t)um * pv.maxgp + (sel ? min(max(sel[vp], 0), last_page) : vp)]
+                                     : pv.local_pt[(size_t)um * pv.nlp + vp];
+            const char *row = page_ptr(pv, page) + (size_t)(tok & (pv.P - 1)) * (D * 2);
+            float sc[G];
+#pragma unroll
+            for (int g = 0; g < G; g++) sc[g] = 0.f;
+#pragma unroll 1
+            for (int x = 0; x < D / 8; x++) {
+                const uint4 kx = *reinterpret_cast<const uint4 *>(row + x * 16);
+                const uint32_t kw[4] = {kx.x, kx.y, kx.z, kx.w};
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    const uint4 qx = *reinterpret_cast<const uint4 *>(qu + g * (D * 2) + x * 16);
+                    const uint32_t qw[4] = {qx.x, qx.y, qx.z, qx.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        sc[g] = fmaf(__uint_as_float(kw[e] << 16), __uint_as_float(qw[e] << 16), sc[g]);
+                        sc[g] = fmaf(__uint_as_float(kw[e] & 0xffff0000u), __uint_as_float(qw[e] & 0xffff0000u), sc[g]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                float m = s.m[s0][g];
+#pragma unroll
+                for (int i = 1; i < N; i++) m = fmaxf(m, s.m[s0 + i][g]);
+                const float x = sc[g] * a.scale_log2e, w = __builtin_amdgcn_exp2f(x - (m == -INFINITY ? 0.f : m));
+                strip.w[lane][g] = x > -INFINITY ? fmaxf(w, kTiny) : w;
+            }
+            strip.v[lane] = row + pv.v_off;
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(is); left != 0; left &= left - 1) {
+            const int j = __builtin_ctzll(left);
+            const float w = strip.w[j][xg];
+            const char *row = strip.v[j];
+#pragma unroll
+            for (int e = 0; e < VPT; e++)
+                o[e] = fmaf(w, __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(row + out_of<WGKV_BF16, D>(x0 + e) % D * 2) << 16), o[e]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Whether a thread of the wave has a sum that is not finite.
+template <int VPT>
+__device__ __forceinline__ bool any_not_finite(const float (&o)[VPT]) {
+    float t = fabsf(o[0]) + fabsf(o[1]);
+    if constexpr (VPT == 4) t += fabsf(o[2]) + fabsf(o[3]);
+    return __builtin_expect(__builtin_amdgcn_ballot_w64(!(t < INFINITY)) != 0, 0);
 }
 
 // The maximum of a partial is kept so that what a buffer load returns past the buffer's end, zero, stands for "nothing seen".
@@ -950,14 +1033,14 @@ __device__ __forceinline__ void fold_partials(__amdgpu_buffer_rsrc_t r_ml, __amd
 #pragma unroll
             for (int i = 0; i < MB; i++) mb = fmaxf(mb, partial_m(ml[k][i].x));  // a repeated last one changes nothing
             const float ms = mb == -INFINITY ? 0.f : mb;
-            const float c = __builtin_amdgcn_exp2f(M[k] - ms);
+            const float c = fmaxf(__builtin_amdgcn_exp2f(M[k] - ms), kTiny);
             L[k] *= c;
 #pragma unroll
             for (int e = 0; e < VPT; e++) o[k][e] *= c;
 #pragma unroll
             for (int i = 0; i < MB; i++)
                 if (q0 + i < np) {
-                    const float f = __builtin_amdgcn_exp2f(partial_m(ml[k][i].x) - ms);
+                    const float f = fmaxf(__builtin_amdgcn_exp2f(partial_m(ml[k][i].x) - ms), kTiny);  // (an infinity times zero is none)
                     L[k] = fmaf(__uint_as_float(ml[k][i].y), f, L[k]);
 #pragma unroll
                     for (int e = 0; e < VPT; e++) o[k][e] = fmaf(__uint_as_float(av[k][i][e]), f, o[k][e]);
@@ -993,13 +1076,13 @@ __device__ __forceinline__ void fold_partials_block(const AttendArgs &a, int slo
         float mb = M;
 #pragma unroll
         for (int i = 0; i < MB; i++) mb = fmaxf(mb, partial_m(ml[i].x));
-        const float ms = mb == -INFINITY ? 0.f : mb, c = __builtin_amdgcn_exp2f(M - ms);
+        const float ms = mb == -INFINITY ? 0.f : mb, c = fmaxf(__builtin_amdgcn_exp2f(M - ms), kTiny);
         l *= c;
 #pragma unroll
         for (int e = 0; e < 4; e++) v[e] *= c;
 #pragma unroll
         for (int i = 0; i < MB; i++) {
-            const float f = __builtin_amdgcn_exp2f(partial_m(ml[i].x) - ms);
+            const float f = fmaxf(__builtin_amdgcn_exp2f(partial_m(ml[i].x) - ms), kTiny);  // (an infinity times zero is none)
             l = fmaf(__uint_as_float(ml[i].y), f, l);
 #pragma unroll
             for (int e = 0; e < 4; e++) v[e] = fmaf(__uint_as_float(av[i][e]), f, v[e]);
@@ -1270,6 +1353,8 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
         __syncthreads();
         float M, L, o[VPT];
         fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
+        if constexpr (DT == WGKV_BF16)
+            if (any_not_finite(o)) sum_again<OUT::NST, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], threadIdx.x & 63, o);
         float *out = a.out + (size_t)u * G * D;
         if (np > 1) {  // block-uniform
             // The stores carry the policy of a device-scope access (written through) and vmcnt counts them until they are
@@ -1484,6 +1569,11 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
             float M, L, o[VPT];
             if (by_wave) fold_states<OUT::NSW>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
             else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
+            if constexpr (DT == WGKV_BF16)
+                if (any_not_finite(o)) {
+                    if (by_wave) sum_again<OUT::NSW, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
+                    else sum_again<OUT::NST, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], lane, o);
+                }
             if (x >= NT) continue;
             if (np > 1) {
                 put_partial<D, G>(r_ml, r_acc, slot, x0, xg, M, L, o);

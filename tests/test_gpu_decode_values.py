@@ -32,3 +32,74 @@ def test_large_values_under_a_rising_score(d, G, B, Hk):
     assert np.isfinite(ref).all() and np.abs(ref).max() > 4e37
     # 2^-16 of the largest value for the weights, and a few parts in a million for the exponentials
     assert np.isfinite(out).all() and np.abs(out - ref).max() <= 2 * (2.0 ** -16 + 1e-5) * 1e38, np.abs(out - ref).max()
+
+
+def _compare(pair, seqs, q, v_finite_max):
+    out, ref = pair.attend(0, seqs, q, pair.cfg.head_dim ** -0.5)
+    np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
+    np.testing.assert_array_equal(np.isinf(out) * np.sign(out), np.isinf(ref) * np.sign(ref))
+    ok = np.isfinite(ref)
+    # 2^-16 of the largest value for the weights; a score is off by some 1e-6 of it
+    assert np.abs(out[ok] - ref[ok]).max() <= 2 * (2.0 ** -16 + 1e-5) * v_finite_max
+    return ~ok
+
+
+# (lengths, kv heads): units of one piece and of several; more units than 64; ways of cutting where there are more units than blocks:
+# whole units a wave, shares a wave, shares a block
+CALLS = {"pieces": ([1, 17, 33, 250, 2500], 2), "shares": ([1, 17, 33, 250, 2500] * 5, 8), "solo": ([90] * 40, 8),
+         "waves": ([40, 1100, 40, 200, 90, 40, 30, 60] * 5, 8), "blocks": ([1500] * 100 + [1, 17, 33, 250], 3)}
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+@pytest.mark.parametrize("d,G", SHAPES)
+@pytest.mark.parametrize("P", [16, 4])
+def test_what_is_not_finite_in_v_comes_out(call, d, G, P):
+    """+inf, -inf, both and NaN in rows that are read: exactly the elements that they reach are not finite, as in a sum of weights
+    times values."""
+    if call in ("shares", "blocks") and (d, G) not in ((128, 4), (64, 1)) or P == 4 and call not in ("pieces", "solo"):
+        pytest.skip("one shape of each path")
+    lens, Hk = CALLS[call]
+    rng = np.random.default_rng(d + G + len(lens))
+    W, B = 16, len(lens)
+    pages = sum(Hk * (n // P + 2 + -(-W // P)) for n in lens)
+    pair = Pair(1, G * Hk, Hk, d, wg.BF16, P, W, B, max(lens) // P + 2, pages, max_call_seqs=B, max_call_tokens=sum(lens))
+    k, v, _ = rand_tokens(rng, sum(lens), Hk, d, torch.bfloat16)
+    top = float(v.float().abs().max())
+    base = np.cumsum([0] + lens)
+    inf = float("inf")
+    for b, n in enumerate(lens):
+        for h in range(Hk):
+            if (b + h) % 7 == 6:
+                continue  # a unit of finite values among them
+            for col, vals in ((3, (inf,)), (17, (-inf,)), (40, (inf, -inf)), (41, (inf, inf, inf)), (63, (float("nan"),))):
+                for x in vals[:n]:
+                    row = int(rng.choice([0, n - 1, rng.integers(0, n)]))  # the oldest, the youngest (in the ring), any
+                    v[base[b] + row, h, (col + 5 * b) % d] = x
+    pair.prefill(0, list(range(B)), lens, k, v, torch.ones((sum(lens), Hk)), 0.5)
+    bad = _compare(pair, list(range(B)), (0.3 * torch.from_numpy(rng.standard_normal((B, G * Hk, d)).astype(np.float32))).to(torch.bfloat16), top)
+    assert bad.any() and not bad.all()
+
+
+@pytest.mark.parametrize("d,G", [(128, 4), (64, 1), (64, 8)])
+def test_infinities_far_below_the_largest_score(d, G):
+    """Infinities under weights that are too small for fp32, in a tile, a wave, a block and a partial of their own: an infinity all the
+    same, as in a sum of exact weights."""
+    rng = np.random.default_rng(d * G)
+    n, W, P, Hk = 3000, 16, 16, 2
+    for gap in (80.0, 130.0, 300.0):  # powers of two under the largest weight
+        for at in (0, 20, 100, 1500, 2990):
+            pair = Pair(1, G * Hk, Hk, d, wg.BF16, P, W, 1, n // P + 2, 2 * Hk * (n // P + 3), max_call_seqs=1, max_call_tokens=n)
+            k = torch.zeros((n, Hk, d), dtype=torch.bfloat16)
+            k[:, :, 0] = gap * 0.6931
+            k[at, :, 0] = 0
+            _, v, _ = rand_tokens(rng, n, Hk, d, torch.bfloat16)
+            v[at, :, 5], v[at, :, 6] = float("inf"), float("-inf")
+            pair.prefill(0, [0], [n], k, v, torch.ones((n, Hk)), 0.5)
+            q = torch.zeros((1, G * Hk, d), dtype=torch.bfloat16)
+            q[:, :, 0] = 1
+            out, ref = pair.attend(0, [0], q, 1.0)
+            assert (ref[..., 5] == np.inf).all() and (ref[..., 6] == -np.inf).all() and np.isinf(ref).sum() == 2 * G * Hk
+            np.testing.assert_array_equal(np.isfinite(out), np.isfinite(ref))
+            np.testing.assert_array_equal(out[~np.isfinite(ref)], ref[~np.isfinite(ref)])
+            ok = np.isfinite(ref)
+            assert np.abs(out[ok] - ref[ok]).max() <= 1e-3
