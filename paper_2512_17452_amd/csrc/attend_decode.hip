@@ -23,7 +23,8 @@
 // even shares to single waves; its three ways stand above it.
 //
 // Data path of bf16 pools: rows go straight into LDS, 32 KiB ahead of their use in every wave, and both products run on
-// the matrix cores (stream_pairs).  Of fp32 pools: registers and the vector unit (stream_tiles).  Either way few waves per SIMD
+// the matrix cores (stream_pairs).  Of fp32 pools, of bf16 pages smaller than a tile and of many units of one or two narrow heads
+// (launch_one): registers and the vector unit (stream_tiles).  Either way few waves per SIMD
 // cover the HBM latency and no wave depends on the issue priority of another.
 // What bounds a call: a long one the memory's rate; a short one chains of round trips and of instructions.  A wave issues one
 // instruction in four clocks at best, and the first time through, out of a cold instruction cache, 64 bytes of code take
@@ -89,9 +90,26 @@ __device__ __forceinline__ int global_tokens(const View &pv, const AttendArgs &a
 
 __device__ __forceinline__ int ceil_tiles(int n) { return (n + kTile - 1) / kTile; }
 
+// How rows are worked with: fp32, bf16 on the matrix cores, or (a third value beside the two types) bf16 on the vector unit.
+constexpr int kBf16Vec = 2;
+static_assert(kBf16Vec != WGKV_F32 && kBf16Vec != WGKV_BF16, "");
 template <int DT> struct Elem;
 template <> struct Elem<WGKV_F32> { static constexpr int es = 4; };
 template <> struct Elem<WGKV_BF16> { static constexpr int es = 2; };
+template <> struct Elem<kBf16Vec> { static constexpr int es = 2; };
+
+typedef __attribute__((ext_vector_type(2))) __bf16 dec_bf16x2_t;
+__device__ __forceinline__ float dec_dot2(uint32_t a, uint32_t b, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dec_bf16x2_t, a), __builtin_bit_cast(dec_bf16x2_t, b), c, false);
+}
+// A row's dot product with the query, 16 bytes of each.
+template <int DT>
+__device__ __forceinline__ float dec_dot(const uint32_t (&k)[4], const uint32_t (&q)[4]) {
+    float d = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; e++) d = DT == WGKV_F32 ? fmaf(__uint_as_float(k[e]), __uint_as_float(q[e]), d) : dec_dot2(k[e], q[e], d);
+    return d;
+}
 
 // Partials cross compute units (and their L2 slices) inside one launch: they are
 // written and read with device-coherent accesses, so no cache-wide flush is needed.
@@ -114,37 +132,50 @@ struct DecShape {
     static constexpr int TPW = 64 / LPT;     // token rows per wave load
     static constexpr int RPT = kTile / TPW;  // wave loads per tile (K and V each)
     static constexpr int ROWB = D * ES;      // bytes of a K or V row
-    static constexpr bool BF = DT == WGKV_BF16;
+    static constexpr bool MX = DT == WGKV_BF16;  // on the matrix cores
     static_assert(LPT == 8 || LPT == 16 || LPT == 32, "row must be 128, 256 or 512 bytes");
-    // fp32: groups of four or eight query heads: four heads' scores of a tile are as many as a row group has lanes
+    // Vector unit, groups of four or eight query heads: four heads' scores of a tile are as many as a row group has lanes
     // (16 / TPW rows x 4 = LPT), so they are spread one per lane, and max, exp and sum run once instead of LPT
     // times.  m[hh] and l[hh] then belong to head 4 * hh + sub % 4; the other entries are unused.
-    static constexpr bool SPREAD = !BF && G % 4 == 0;
+    static constexpr bool SPREAD = !MX && G % 4 == 0;
     static constexpr int HH = SPREAD ? G / 4 : 1;
-    // bf16: weights enter their product in parts of 8 bits: two for the shape of the paper's two models (error against 64 bits 2.3e-6; rounded
+    // Matrix cores: weights enter their product in parts of 8 bits: two for the shape of the paper's two models (error against 64 bits 2.3e-6; rounded
     // to one part 1.5e-3, and 9.4e-4 where each of 16 streams a wave has its largest weight exact), three for the others
     static constexpr int PARTS = D == 128 && G == 4 ? 2 : 3;
-    // fp32: register sets = tiles in flight per wave.  With one wave per SIMD the loads of a wave's own next tiles are all
+    // Vector unit: register sets = tiles in flight per wave.  With one wave per SIMD the loads of a wave's own next tiles are all
     // there is to cover the latency; 512-byte rows take 64 registers a tile, and with eight heads to a group four sets
     // leave too few registers.
     static constexpr int S = RPT <= 4 && G <= 4 ? 4 : 2;
-    // bf16: pairs of tiles that a wave has in LDS, 32 KiB
+    // Matrix cores: pairs of tiles that a wave has in LDS, 32 KiB
     static constexpr int NP = 512 / ROWB;
     static constexpr int EP = D / 16;        // output elements per lane, head and pair
-    static constexpr int NSW = BF ? 1 : TPW; // softmax states of a wave: one, or one per row group
+    static constexpr int NSW = MX ? 1 : TPW; // softmax states of a wave: one, or one per row group
 };
 
-// What a wave works with in LDS.  fp32: strips through which the weights of a tile go back to the row layout; bf16: its tiles.
+// Weights and rows of 64 keys (see sum_again).
+template <int G>
+struct DecStrip {
+    float w[64][G];
+    const char *v[64];
+};
+// What a wave works with in LDS.  Vector unit: strips through which the weights of a tile go back to the row layout; matrix cores: its tiles.
 template <int DT, int D, int G>
 struct DecWaveLds {
     float p[2][64];         // fp32 weights of a tile, four heads in each half
+};
+template <int D, int G>
+struct DecWaveLds<kBf16Vec, D, G> {
+    union {
+        float p[2][64];
+        DecStrip<G> again;
+    };
 };
 template <int D, int G>
 struct DecWaveLds<WGKV_BF16, D, G> {
     __attribute__((aligned(1024))) char t[DecShape<WGKV_BF16, D, G>::NP][2][2][kTile * D * 2];  // [pair][K, V][tile of the pair]
 };
 
-// A wave's running softmax.  fp32: per row group.
+// A wave's running softmax.  Vector unit: per row group.
 template <int DT, int D, int G>
 struct DecSoftmax {
     float m[G], l[G], acc[G][DecShape<DT, D, G>::EPL];
@@ -158,7 +189,7 @@ struct DecSoftmax {
         }
     }
 };
-// bf16: m, 8 or less above the largest exponent so far, is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
+// Matrix cores: m, 8 or less above the largest exponent so far, is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
 // element 16 * c + lane % 16.
 typedef float dec_f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
@@ -193,9 +224,6 @@ __device__ __forceinline__ void dec_dma(const void *base, uint32_t off, const vo
     const void *b;
     asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 nt" : "=&s"(b) : "s"(dec_lds(dst)), "v"(off), "s"(base) : "memory", "m0");
 }
-__device__ __forceinline__ void dec_dma_at(const void *lane_ptr, const void *dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(dec_lds(dst)), "v"(lane_ptr) : "memory", "m0");
-}
 // a tile of N * 1024 bytes, each request with its own lane offsets
 __device__ __forceinline__ void dec_dma_tile(const void *base, const uint32_t (&off)[4], const void *dst) {
     const void *b;
@@ -228,7 +256,7 @@ __device__ __forceinline__ uint32_t dec_pack_bf16(float lo, float hi) {  // roun
 // Weights are relative to 2^8 times the largest one so far, and that is brought up to date when a score exceeds it: it costs no exchange
 // between lanes in the rule, and no weight is above one, so values up to the end of the range stay finite as they do in sums of
 // weights that are relative to the maximum itself; sums are fp32 either way.
-template <int D, int G, bool SMALL_PAGES>
+template <int D, int G>
 __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int cur, int u_end,
                                              dec_u32x4_t (&q)[D / 32], float c_exp, DecSoftmax<WGKV_BF16, D, G> &st,
                                              DecWaveLds<WGKV_BF16, D, G> &lds, int lane) {
@@ -251,11 +279,9 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
         const int32_t *sel = (is_glob && a.sel_pages) ? a.sel_pages + (size_t)u * a.sel_stride : nullptr;
         const int last_page = max(((gl_all + pv.P - 1) >> pv.logP) - 1, 0);
         auto page_at = [&](int vp) __attribute__((always_inline)) { return pt[sel ? min(max(sel[vp], 0), last_page) : vp]; };
-        // A tile inside one page (P >= 16) has one address for the whole wave: lane i keeps that of tile k0 + i.  Smaller
-        // pages are looked up per row, each behind a wait for all requests before it.
+        // A tile lies inside one page (P >= 16) and has one address for the whole wave: lane i keeps that of tile k0 + i.
         const int k_lane = (k0 + min(lane, n - 1)) * kTile;
-        int page = 0;
-        if (!SMALL_PAGES) page = page_at(k_lane >> pv.logP);
+        int page = page_at(k_lane >> pv.logP);
         // (what follows from the lane alone is worked out while the page ids come: not hoisted in front of the request for them)
         int ln = lane;
         asm volatile("" : "+v"(ln));
@@ -300,7 +326,7 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
                 const uint64_t at = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(at_hi, j) << 32) | (uint32_t)__builtin_amdgcn_readlane(at_lo, j);
                 return (const char *)(at + (v_half ? pv.v_off : 0u));
             };
-            if (!SMALL_PAGES && valid_of(p) >= 2 * kTile) {
+            if (valid_of(p) >= 2 * kTile) {
                 if (v_half) {
                     dec_dma_tile(base_of(2 * p), off_v, dst);
                     dec_dma_tile(base_of(2 * p + 1), off_v, dst + TILEB);
@@ -319,12 +345,7 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
                 for (int i = 0; i < NI; i++) {
                     const int r = i * (64 / LPT) + r0, row = min(r, last_row);
                     const uint32_t x = (v_half ? off_v[i] : off_k[i]) - (uint32_t)(r0 * ROWB);
-                    if (SMALL_PAGES) {
-                        const int tok = k * kTile + row;
-                        dec_dma_at(page_ptr(pv, page_at(tok >> pv.logP)) + (size_t)(tok & (pv.P - 1)) * ROWB + (v_half ? pv.v_off : 0u) + x, dst + t * TILEB + i * 1024);
-                    } else {
-                        dec_dma(base_of(j), (uint32_t)(row * ROWB) + x, dst + t * TILEB + i * 1024);
-                    }
+                    dec_dma(base_of(j), (uint32_t)(row * ROWB) + x, dst + t * TILEB + i * 1024);
                 }
             }
         };
@@ -447,15 +468,15 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
     }
 }
 
-// fp32: the same on the vector unit.  Each lane loads 16 bytes of a K row and of a V row straight into registers, 1 KiB per
+// The same on the vector unit (fp32, and bf16 where the rule of launch_one says so).  Each lane loads 16 bytes of a K row and of a V row straight into registers, 1 KiB per
 // instruction; a wave keeps S tiles in flight in register sets that are refilled in place as soon as they have been consumed.
 // A group of lanes (LPT of them) owns one token per row, so a wave holds several independent softmax streams.
-template <int D, int G>
+template <int DT, int D, int G>
 __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl,
                                              int nloc, int cur, int u_end,
-                                             const uint32_t (&qreg)[G][4], float scale_log2e, DecSoftmax<WGKV_F32, D, G> &st,
-                                             DecWaveLds<WGKV_F32, D, G> &strips, int lane) {
-    using SH = DecShape<WGKV_F32, D, G>;
+                                             const uint32_t (&qreg)[G][4], float scale_log2e, DecSoftmax<DT, D, G> &st,
+                                             DecWaveLds<DT, D, G> &strips, int lane) {
+    using SH = DecShape<DT, D, G>;
     auto &m = st.m;
     auto &l = st.l;
     auto &acc = st.acc;
@@ -514,6 +535,15 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
             }
         };
 
+        // a head's weight times word e of a V row
+        auto weigh = [](float w, uint32_t v, float (&acc)[EPL], int e) __attribute__((always_inline)) {
+            if constexpr (DT == WGKV_F32) {
+                acc[e] = fmaf(w, __uint_as_float(v), acc[e]);
+            } else {
+                acc[2 * e] = fmaf(w, __uint_as_float(v << 16), acc[2 * e]);
+                acc[2 * e + 1] = fmaf(w, __uint_as_float(v & 0xffff0000u), acc[2 * e + 1]);
+            }
+        };
         uint4 kb[S][RPT], vb[S][RPT];
 
         // One tile out of register set ST; the set is refilled with tile j+S.
@@ -533,12 +563,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
                     for (int r = 0; r < RPT; r++) {
                         const uint32_t kw[4] = {kb[ST][r].x, kb[ST][r].y, kb[ST][r].z, kb[ST][r].w};
 #pragma unroll
-                        for (int g = 0; g < 4; g++) {
-                            float d = 0.f;
-#pragma unroll
-                            for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[4 * hh + g][e]), d);
-                            x[r * 4 + g] = d;
-                        }
+                        for (int g = 0; g < 4; g++) x[r * 4 + g] = dec_dot<DT>(kw, qreg[4 * hh + g]);
                         __builtin_amdgcn_sched_barrier(0);
                         if constexpr (REFILL)
                             if (hh == HH - 1) kb[ST][r] = load_once16(rowp[r]);
@@ -634,7 +659,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 #pragma unroll
                     for (int e = 0; e < 4; e++) {
 #pragma unroll
-                        for (int g = 0; g < G; g++) acc[g][e] = fmaf(pg[g], __uint_as_float(vw[e]), acc[g][e]);
+                        for (int g = 0; g < G; g++) weigh(pg[g], vw[e], acc[g], e);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (REFILL) vb[ST][r] = load_once16(rowp[r] + pv.v_off);
@@ -650,10 +675,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
                     const int tok = k * kTile + r * TPW + grp;
 #pragma unroll
                     for (int g = 0; g < G; g++) {
-                        float d = 0.f;
-#pragma unroll
-                        for (int e = 0; e < 4; e++) d = fmaf(__uint_as_float(kw[e]), __uint_as_float(qreg[g][e]), d);
-                        d = group_sum<LPT>(d);
+                        const float d = group_sum<LPT>(dec_dot<DT>(kw, qreg[g]));
                         s[r][g] = tok < count ? d * scale_log2e : -INFINITY;
                     }
                 }
@@ -690,7 +712,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 #pragma unroll
                     for (int e = 0; e < 4; e++)
 #pragma unroll
-                        for (int g = 0; g < G; g++) acc[g][e] = fmaf(p[r][g], __uint_as_float(vw[e]), acc[g][e]);
+                        for (int g = 0; g < G; g++) weigh(p[r][g], vw[e], acc[g], e);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the V registers are free from here on
                 if constexpr (REFILL) {
@@ -769,7 +791,7 @@ __device__ __forceinline__ void stream_tiles(const View &pv, const AttendArgs &a
 }
 
 // A wave's part of a unit: its query, and tiles [w0, w1) into a fresh softmax.
-template <int DT, int D, int G, bool SMALL>
+template <int DT, int D, int G>
 __device__ __forceinline__ void run_part(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int w0, int w1,
                                          DecSoftmax<DT, D, G> &st, DecWaveLds<DT, D, G> &lds, int lane) {
     using SH = DecShape<DT, D, G>;
@@ -790,7 +812,7 @@ __device__ __forceinline__ void run_part(const View &pv, const AttendArgs &a, in
         for (int ks = 0; ks < D / 32; ks++)
             q[ks] = *reinterpret_cast<const dec_u32x4_t *>(qu + ((lane & 15) % G) * (D * 2) + (4 * ks + (lane >> 4)) * 16);
         // (a scale of zero stays a hair above it: -inf times it stays -inf)
-        stream_pairs<D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, q, fmaxf(fabsf(a.scale_log2e), 1e-37f), st, lds, lane);
+        stream_pairs<D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, q, fmaxf(fabsf(a.scale_log2e), 1e-37f), st, lds, lane);
     } else {
         uint32_t qreg[G][4];
 #pragma unroll
@@ -798,7 +820,7 @@ __device__ __forceinline__ void run_part(const View &pv, const AttendArgs &a, in
             const uint4 t4 = *reinterpret_cast<const uint4 *>(qu + lane % SH::LPT * 16 + (size_t)g * D * SH::ES);
             qreg[g][0] = t4.x; qreg[g][1] = t4.y; qreg[g][2] = t4.z; qreg[g][3] = t4.w;
         }
-        stream_tiles<D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, a.scale_log2e, st, lds, lane);
+        stream_tiles<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, qreg, a.scale_log2e, st, lds, lane);
     }
 }
 
@@ -894,20 +916,16 @@ __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0
 
 // bf16: the weighted sums of tiles [p0, p1) of a unit once more, for a wave one of whose sums is not finite, with each key's whole weight
 // times its value.  The parts that a weight is split into do not carry an infinity of V: later ones are zero or of either sign, and zero times
-// an infinity, or the sum of two that differ in sign, is NaN.  Sums of finite values never get here, so this is short and not fast: a
+// an infinity, or the sum of two that differ in sign, is NaN; and so is an infinity times a factor too small for its type.  Sums of finite values never get here, so this is short and not fast: a
 // lane works out the scores of a key (64 keys at a time), then the lanes go through the keys.  Relative to the same maximum as the
 // sums that it replaces (states s0 .. s0 + N - 1); a weight too small for its type stays above zero as a number does.
-template <int N, int D, int G>
+template <int N, int DT, int D, int G>
 __device__ __forceinline__ void sum_again(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int p0, int p1,
-                                          const DecStates<WGKV_BF16, D, G> &s, int s0, int x0, int xg, DecWaveLds<WGKV_BF16, D, G> &lds, int lane,
-                                          float (&o)[DecOut<WGKV_BF16, D, G>::VPT]) {
-    constexpr int VPT = DecOut<WGKV_BF16, D, G>::VPT;
-    struct Strip {
-        float w[64][G];
-        const char *v[64];
-    };
-    static_assert(sizeof(Strip) <= sizeof(lds), "");
-    Strip &strip = *reinterpret_cast<Strip *>(&lds);  // the wave has no requests under way
+                                          const DecStates<DT, D, G> &s, int s0, int x0, int xg, DecWaveLds<DT, D, G> &lds, int lane,
+                                          float (&o)[DecOut<DT, D, G>::VPT]) {
+    constexpr int VPT = DecOut<DT, D, G>::VPT;
+    static_assert(sizeof(DecStrip<G>) <= sizeof(lds), "");
+    DecStrip<G> &strip = *reinterpret_cast<DecStrip<G> *>(&lds);  // the wave has no requests under way
     const char *qu = a.q + (size_t)u * G * D * 2;
     const int n_gt = ceil_tiles(gl), last_page = max(((gl_all + pv.P - 1) >> pv.logP) - 1, 0);
     const int32_t *sel = a.sel_pages ? a.sel_pages + (size_t)u * a.sel_stride : nullptr;
@@ -960,7 +978,7 @@ __device__ __forceinline__ void sum_again(const View &pv, const AttendArgs &a, i
             const char *row = strip.v[j];
 #pragma unroll
             for (int e = 0; e < VPT; e++)
-                o[e] = fmaf(w, __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(row + out_of<WGKV_BF16, D>(x0 + e) % D * 2) << 16), o[e]);
+                o[e] = fmaf(w, __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(row + out_of<DT, D>(x0 + e) % D * 2) << 16), o[e]);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -1125,7 +1143,7 @@ struct DecBlocksLds {
     int tmp[3 * kAttnWaves];
     int arrived;
 };
-template <int DT, int D, int G, bool SMALL, bool FEW>  // FEW: at most 64 units
+template <int DT, int D, int G, bool FEW>  // FEW: at most 64 units
 __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &a) {
     using OUT = DecOut<DT, D, G>;
     constexpr int VPT = OUT::VPT, NT = OUT::NT;
@@ -1343,7 +1361,7 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
         const int w0 = p0 + (p1 - p0) * wave / kAttnWaves, w1 = p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
         if (again) __syncthreads();  // the states in LDS are rewritten
         DecSoftmax<DT, D, G> st;
-        run_part<DT, D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
+        run_part<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
         // the waves of the block meet in LDS
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));  // (what follows from it is worked out here and not in front of the first row)
@@ -1353,8 +1371,8 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
         __syncthreads();
         float M, L, o[VPT];
         fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
-        if constexpr (DT == WGKV_BF16)
-            if (any_not_finite(o)) sum_again<OUT::NST, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], threadIdx.x & 63, o);
+        if constexpr (DT != WGKV_F32)
+            if (any_not_finite(o)) sum_again<OUT::NST>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], threadIdx.x & 63, o);
         float *out = a.out + (size_t)u * G * D;
         if (np > 1) {  // block-uniform
             // The stores carry the policy of a device-scope access (written through) and vmcnt counts them until they are
@@ -1414,7 +1432,7 @@ struct DecManyLds {
     int totals[3][kAttnWaves];  // a wave's tiles, units with any, and tiles of its longest unit
     int arrived;
 };
-template <int DT, int D, int G, bool SMALL>
+template <int DT, int D, int G>
 __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a) {
     using SH = DecShape<DT, D, G>;
     using OUT = DecOut<DT, D, G>;
@@ -1556,7 +1574,7 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
         const int w0 = by_wave ? p0 : p0 + (p1 - p0) * wave / kAttnWaves, w1 = by_wave ? p1 : p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
         if (again && !by_wave) __syncthreads();  // the states in LDS are rewritten
         DecSoftmax<DT, D, G> st;
-        run_part<DT, D, G, SMALL>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
+        run_part<DT, D, G>(pv, a, u, um, gl_all, gl, nloc, w0, w1, st, s_wave_lds[wave], lane);
         // the row groups of the block meet in LDS, or those of the wave (whose LDS accesses stay in order)
         __builtin_amdgcn_wave_barrier();
         put_states<DT, D, G>(s_st, wave, lane, st);
@@ -1569,10 +1587,10 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
             float M, L, o[VPT];
             if (by_wave) fold_states<OUT::NSW>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
             else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
-            if constexpr (DT == WGKV_BF16)
+            if constexpr (DT != WGKV_F32)
                 if (any_not_finite(o)) {
-                    if (by_wave) sum_again<OUT::NSW, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
-                    else sum_again<OUT::NST, D, G>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], lane, o);
+                    if (by_wave) sum_again<OUT::NSW>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
+                    else sum_again<OUT::NST>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], lane, o);
                 }
             if (x >= NT) continue;
             if (np > 1) {
@@ -1622,18 +1640,18 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
 // The kernels.  bf16 keeps to 256 registers (bounds of two waves per SIMD, though its LDS leaves room for one: that is why it is
 // allocated at the launch), where the compiler puts a product's accumulators into vector registers and not into the other half of
 // the file, from which it copies them all back in every turn; fp32 needs more.
-template <int D, int G, bool SMALL, bool FEW>
-__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_kernel(View pv, AttendArgs a) {
-    decode_blocks<WGKV_BF16, D, G, SMALL, FEW>(pv, a);
-}
-template <int D, int G, bool SMALL>
-__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_many_kernel(View pv, AttendArgs a) {
-    decode_many<WGKV_BF16, D, G, SMALL>(pv, a);
-}
 template <int D, int G, bool FEW>
-__global__ __launch_bounds__(kAttnThreads) void attend_decode_f32_kernel(View pv, AttendArgs a) { decode_blocks<WGKV_F32, D, G, false, FEW>(pv, a); }
+__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_kernel(View pv, AttendArgs a) { decode_blocks<WGKV_BF16, D, G, FEW>(pv, a); }
 template <int D, int G>
-__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_f32_kernel(View pv, AttendArgs a) { decode_many<WGKV_F32, D, G, false>(pv, a); }
+__global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_many_kernel(View pv, AttendArgs a) { decode_many<WGKV_BF16, D, G>(pv, a); }
+template <int D, int G, bool FEW>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_vec_kernel(View pv, AttendArgs a) { decode_blocks<kBf16Vec, D, G, FEW>(pv, a); }
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_vec_kernel(View pv, AttendArgs a) { decode_many<kBf16Vec, D, G>(pv, a); }
+template <int D, int G, bool FEW>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_f32_kernel(View pv, AttendArgs a) { decode_blocks<WGKV_F32, D, G, FEW>(pv, a); }
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) void attend_decode_many_f32_kernel(View pv, AttendArgs a) { decode_many<WGKV_F32, D, G>(pv, a); }
 
 // One block per compute unit: an even split is one round of blocks, and more waves on a compute unit stream slower.
 template <int DT, int D, int G>
@@ -1641,14 +1659,30 @@ static void launch_one(const View &pv, const AttendArgs &a, int grid, hipStream_
     const int n_units = a.n_seqs * pv.Hkv;
     const bool many = n_units > min(grid, kMaxUnits), few = n_units <= 64;
     void (*kernel)(View, AttendArgs);
+    unsigned lds;
+    auto take = [&](auto dt, void (*k_many)(View, AttendArgs), void (*k_few)(View, AttendArgs), void (*k)(View, AttendArgs)) {
+        using Many = DecManyLds<decltype(dt)::value, D, G>;
+        using Blocks = DecBlocksLds<decltype(dt)::value, D, G>;
+        static_assert(sizeof(Many) <= 160 * 1024 && sizeof(Blocks) <= 160 * 1024, "");
+        kernel = many ? k_many : few ? k_few : k;
+        lds = many ? sizeof(Many) : sizeof(Blocks);
+    };
+    // bf16 rows go to the vector unit
+    //  - in calls of many units where a key's products with its group fill little of a matrix instruction (of its 16 columns one head's, or two
+    //    heads' of 64): us there / on the matrix cores, 33 sequences of 600 tokens with 8 heads of 64 9.7 / 12.5, 64 of 300 with 8 heads of 128
+    //    12.7 / 13.9, 40 of 2000 with groups of two of 64 14.6 / 16.8; the next larger, groups of four of 64 or of two of 128, lose 3 to 8 %.
+    //    Few units wait for their chains, which are shorter on the matrix cores: 8 of 4096 tokens 9.4 / 8.9 (one of 64) and 9.4 / 8.8 (two),
+    //    32 of 20000 18.1 / 18.7 and 19.2 / 18.2;
+    //  - where pages are smaller than a tile: their rows are looked up one by one, and a lookup waits for every request of
+    //    the wave before it (batch 4 at 20K in pages of 8: 42 / 97).
     if constexpr (DT == WGKV_F32)
-        kernel = many ? attend_decode_many_f32_kernel<D, G> : few ? attend_decode_f32_kernel<D, G, true> : attend_decode_f32_kernel<D, G, false>;
-    else if (pv.logP < 4)  // a page lookup per row
-        kernel = many ? attend_decode_many_kernel<D, G, true> : few ? attend_decode_kernel<D, G, true, true> : attend_decode_kernel<D, G, true, false>;
+        take(std::integral_constant<int, WGKV_F32>{}, attend_decode_many_f32_kernel<D, G>, attend_decode_f32_kernel<D, G, true>, attend_decode_f32_kernel<D, G, false>);
+    else if (pv.logP < 4 || (G * D <= 128 && n_units > 16 * G))
+        take(std::integral_constant<int, kBf16Vec>{}, attend_decode_many_vec_kernel<D, G>, attend_decode_vec_kernel<D, G, true>, attend_decode_vec_kernel<D, G, false>);
+    else if constexpr (G * D <= 128)
+        take(std::integral_constant<int, WGKV_BF16>{}, nullptr, attend_decode_kernel<D, G, true>, nullptr);
     else
-        kernel = many ? attend_decode_many_kernel<D, G, false> : few ? attend_decode_kernel<D, G, false, true> : attend_decode_kernel<D, G, false, false>;
-    const unsigned lds = many ? sizeof(DecManyLds<DT, D, G>) : sizeof(DecBlocksLds<DT, D, G>);
-    static_assert(sizeof(DecManyLds<DT, D, G>) <= 160 * 1024 && sizeof(DecBlocksLds<DT, D, G>) <= 160 * 1024, "");
+        take(std::integral_constant<int, WGKV_BF16>{}, attend_decode_many_kernel<D, G>, attend_decode_kernel<D, G, true>, attend_decode_kernel<D, G, false>);
     if (ev0 && ev1)  // the events take the begin and end time stamps of this dispatch itself
         hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), lds, st, ev0, ev1, 0, pv, a);
     else
