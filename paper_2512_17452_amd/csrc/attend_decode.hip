@@ -1428,7 +1428,8 @@ struct DecManyLds {
     DecStates<DT, D, G> states;
     int ts[kMaxCallUnits + 1];  // tiles before unit u, those charged to the begin of a unit included
     int gl[kMaxCallUnits];      // entries in the unit's global cache
-    int nl[kMaxCallUnits];      // tokens in its ring
+    int um[kMaxCallUnits];      // its index into the per-unit metadata
+    int nl[kMaxCallSeqs];       // tokens in the rings of sequence b
     int totals[3][kAttnWaves];  // a wave's tiles, units with any, and tiles of its longest unit
     int arrived;
 };
@@ -1443,6 +1444,7 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
     auto &s_st = lds.states;
     auto &s_ts = lds.ts;
     auto &s_gl = lds.gl;
+    auto &s_um = lds.um;
     auto &s_nl = lds.nl;
     auto &s_wave = lds.totals;
     auto &s_arrived = lds.arrived;
@@ -1451,6 +1453,8 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int NU = kMaxCallUnits / kAttnThreads;  // consecutive units a thread looks after
     int tl[NU], um[NU], len[NU], gl_all[NU], sum = 0, some = 0, longest = 0;
+    const float per_seq = __builtin_amdgcn_rcpf((float)pv.Hkv);
+    auto seq_of = [&](int u) __attribute__((always_inline)) { return (int)(((float)u + 0.5f) * per_seq); };  // exact: u < 1024
     // What stands in front of the first row is paid by every call: all of a thread's lengths are asked for together, the last unit's
     // again past the end (a branch around each would wait for every one in turn), three sums share one barrier, and what is cut by a
     // few comparisons is not divided.  33 x 100 tokens 11.1 -> 10.2 us, 33 x 1000 22.8 -> 21.5, 64 x 1000 24.2 -> 22.7.
@@ -1474,7 +1478,8 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
         tl[i] = 0;
         if (u < n_units) {
             s_gl[u] = gl_all[i];
-            s_nl[u] = nl;
+            s_um[u] = um[i];
+            s_nl[seq_of(u)] = nl;
             tl[i] = ceil_tiles(global_tokens(pv, a, u, gl_all[i])) + ceil_tiles(nl);
         }
         sum += tl[i];
@@ -1568,7 +1573,7 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
             cur = min(s_ts[u + 1], end);
             p1 = cur - first;
         }
-        const int b = u / pv.Hkv, um = unit_meta(pv, a.sid[b], a.layer, u - b * pv.Hkv), gl_all = s_gl[u], nloc = s_nl[u];
+        const int um = s_um[u], gl_all = s_gl[u], nloc = s_nl[seq_of(u)];
         const int gl = global_tokens(pv, a, u, gl_all);
         if (solo) p1 = ceil_tiles(gl) + ceil_tiles(nloc);
         const int w0 = by_wave ? p0 : p0 + (p1 - p0) * wave / kAttnWaves, w1 = by_wave ? p1 : p0 + (p1 - p0) * (wave + 1) / kAttnWaves;
