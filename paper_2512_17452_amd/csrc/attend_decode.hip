@@ -45,8 +45,8 @@ constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = 4;
 // A block that begins a unit in the middle of its share drains its loads, folds and publishes a partial
 // and waits for the new unit's lengths, query rows and page ids.  The split charges that to the unit, as
-// tiles in front of the first real one that nobody reads: 12 / 24 / 48 / 96 tiles of a block give 86.7 /
-// 84.9 / 86.0 / 86.0 us on batch 8 at 64K-128K and 156.4 / 156.3 / 158.7 / 163.5 on 256 ragged heads.
+// tiles in front of the first real one that nobody reads: 12 / 24 / 48 tiles of a block give 75.7 / 75.9 / 76.5 us on batch 8 at
+// 100K, 25.9 / 25.5 / 25.3 on 64 ragged heads of 32K, 40.8 / 41.0 / 42.7 on batch 16 at 16K.
 constexpr int kUnitStartTiles = 24;
 // Blocks go to the XCDs round-robin, and in every launch measured the odd XCD of a pair streams
 // slower than the even one, by 4-5 % on some machines and by about twice that on others: with even
@@ -1415,12 +1415,14 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
 //           worth for a unit that begins); a unit's partials, one per wave, are put together by the wave that arrives last:
 //           for short units of very different lengths, and for rows of 128 bytes;
 //   blocks  the same over blocks, as in the kernel above: for long ones.
-// Every block estimates the three in us from the lengths and takes the cheapest.  The model is a fit to every way of 234
-// calls (33 to 128 sequences of 100 to 8000 tokens, even and ragged heads, all head shapes); its choice is 0.7 % behind the best
-// way in the mean and 8 % at most for the main head shape.  The fit was taken with 256 blocks, before the front of the kernel lost 1 us
-// and the fold of a wave's partials some more.  Against the kernel above (us; main head shape, a third of the tokens admitted): 33 x 100
-// tokens 15.2 -> 10.3, 64 x 300 24.3 -> 13.7, 128 x 300 40.7 -> 18.1, 128 x 1000 55 -> 33.7, 33 x 4000 35.7 -> 35.2; heads from 1 to 90 %:
-// 64 x 1000 27.2 -> 22.9, 128 x 1000 44.3 -> 34.4, 33 x 4000 27.8 -> 28.7.
+// Every block estimates the three in us from the lengths and takes the cheapest.  The model was fitted to the kernel that had all types on the
+// vector unit; what it picks was timed against every way of the kernels as they are (558 calls: 33 to 128 sequences of 100 to 8000
+// tokens, even and ragged heads, ten head shapes).  Behind the best way, in the mean / at most: main head shape 1.0 / 15 %, the other
+// shapes on the matrix cores 0.5 to 1.0 / 15 % (with the factor that eight heads take on the vector unit, 3.1 and 4.6 / 36 %; a fit of all
+// constants to these calls 0.5 / 14 %), on the vector unit fp32 0.8 and 1.0 / 26 %, bf16 0.3 to 1.7 / 22 %.  us of blocks / waves / solo, main
+// head shape, a third of the tokens admitted: 33 x 100 tokens 15.8 / 17.5 / 10.2, 64 x 300 23.3 / 18.8 / 12.5, 128 x 1000 49.1 / 38.3 /
+// 32.7, 33 x 4000 34.4 / 37.0 / 40.5; heads from 1 to 90 %: 64 x 1000 25.1 / 22.7 / 30.8, 128 x 1000 38.6 / 31.3 / 52.4, 33 x 4000
+// 26.0 / 29.7 / 95.2 (where it picks waves).
 constexpr int kMinWaveTiles = 16, kWaveStartTiles = 12;
 template <int DT, int D, int G>
 struct DecManyLds {
@@ -1506,10 +1508,11 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
     }
     const int share_b = max(kMinBlockTiles, (total + used * kUnitStartTiles + n_blocks - 1) / n_blocks);
     const int share_w = max(kMinWaveTiles, (total + used * kWaveStartTiles + n_waves - 1) / n_waves);
-    constexpr float kC = (float)SH::ROWB / 256.f * (G == 8 ? 1.6f : 1.f);  // a tile: its bytes, or the products of eight heads
+    constexpr bool kMany8 = G == 8 && !SH::MX;  // the products of eight heads, on the vector unit
+    constexpr float kC = (float)SH::ROWB / 256.f * (kMany8 ? 1.6f : 1.f);  // a tile: its bytes, or those products
     const float t_blocks = 8.2f + kC * 0.25f * (float)share_b, t_waves = 3.5f + (SH::ROWB >= 256 ? 1.35f : 1.18f) * kC * (float)share_w;
     // alone a wave streams faster than its share of the memory's rate, until all of them do
-    const float full = (float)n_units / (float)n_waves, alone = (G == 8 ? 1.f : 0.68f) * kC * (float)longest;
+    const float full = (float)n_units / (float)n_waves, alone = (kMany8 ? 1.f : 0.68f) * kC * (float)longest;
     const float t_solo = 4.6f + fmaxf(alone * fmaxf(1.f, full), 1.1f + 0.85f * kC * (float)total / (float)n_waves) + 0.3f * alone * full * full;
     const bool solo = t_solo <= fminf(t_blocks, t_waves), by_wave = solo || t_waves <= t_blocks;
     const int begin = solo ? 0 : by_wave ? kWaveStartTiles : kUnitStartTiles, share = by_wave ? share_w : share_b;
