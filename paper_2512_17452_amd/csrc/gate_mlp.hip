@@ -81,8 +81,8 @@ __device__ __forceinline__ float gm_squares_by_pairs(const uint4 (&raw)[D / 16])
 }
 
 // The normalised features of one token as matrix operands: the 8 features [16 ks + 8 half, +8) of every slice of 16.
-template <int D>
-__device__ __forceinline__ void gm_features(const char *k, const char *kr, size_t row, int half, float eps, bool by_pairs,
+template <int D, bool BY_PAIRS>
+__device__ __forceinline__ void gm_features(const char *k, const char *kr, size_t row, int half, float eps,
                                             gm_bf16x8_t (&xv)[2 * D / 16]) {
     constexpr int KS = 2 * D / 16;
 #pragma unroll
@@ -104,7 +104,7 @@ __device__ __forceinline__ void gm_features(const char *k, const char *kr, size_
             }
         }
         ss += __shfl_xor(ss, 32);  // the other half of the row
-        if (by_pairs) ss = gm_squares_by_pairs<D>(raw);  // wave-uniform
+        if constexpr (BY_PAIRS) ss = gm_squares_by_pairs<D>(raw);
         const float r = 1.0f / sqrtf(ss / (float)D + eps);
 #pragma unroll
         for (int j = 0; j < KS / 2; j++) {
@@ -121,7 +121,8 @@ __device__ __forceinline__ void gm_features(const char *k, const char *kr, size_
 }
 
 // CB: columns of 32 tokens per wave.  US: unit groups of the block, 4 waves each; group us takes chunks us, us + US, ...
-template <int D, int CB, int US>
+// RAGGED: the width is no multiple of 32.
+template <int D, int CB, int US, bool RAGGED>
 __global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *k, const char *kr, const char *W1,
                                                             const float *b1, const char *W2, const float *b2,
                                                             float eps, float *g_out, long long T, int Hkv,
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) {
         const long long tok = tok0 + cb * kGmTokens;  // rows past the end repeat the last token, unwritten
-        gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, width % kGmUnits != 0, xv[cb]);
+        gm_features<D, RAGGED>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv[cb]);
     }
 
     // ---- chunks of 32 hidden units: W1 rows, b1 and W2 through LDS, two buffers ----
@@ -157,9 +158,10 @@ __global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *
     auto fetch = [&](int it) __attribute__((always_inline)) {
         const int c = min(it * US + us, n_chunks - 1);  // a group without a chunk of its own in the last turn drops it
         const char *src = W1 + ((size_t)h * width + (size_t)c * kGmUnits) * (2 * D * 2);  // 32 consecutive rows
-        const int rows = min(width - c * kGmUnits, kGmUnits);  // fewer in the last chunk of a width that is no multiple of 32: units of zeros
+        const int rows = RAGGED ? min(width - c * kGmUnits, kGmUnits) : kGmUnits;  // fewer in the last chunk: units of zeros
         auto piece = [&](int p) __attribute__((always_inline)) {
             const int i = p * 256 + tid;
+            if (!RAGGED) return *reinterpret_cast<const uint4 *>(src + (size_t)i * 16);
             const uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)min(i, rows * kRowPieces - 1) * 16);
             return i < rows * kRowPieces ? v : make_uint4(0u, 0u, 0u, 0u);
         };
@@ -170,10 +172,10 @@ __global__ __launch_bounds__(256 * US, 2) void gate_mlp_mfma_kernel(const char *
             w3 = piece(3);
         }
         if (tid < kGmUnits) {
-            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + min(tid, rows - 1);
+            const size_t u = (size_t)h * width + (size_t)c * kGmUnits + (RAGGED ? min(tid, rows - 1) : tid);
             const float b = b1[u], w = gm_bf16_to_f32(*reinterpret_cast<const uint16_t *>(W2 + u * 2));
-            b1v = tid < rows ? b : 0.f;
-            w2v = tid < rows ? w : 0.f;
+            b1v = !RAGGED || tid < rows ? b : 0.f;
+            w2v = !RAGGED || tid < rows ? w : 0.f;
         }
     };
     auto put = [&](int buf, int p, const uint4 v) __attribute__((always_inline)) {
@@ -255,7 +257,7 @@ constexpr int kGmSplit = 4;  // waves of the block
 // Few tokens: what a wave has to do one after the other is the time, so a block takes 32 tokens and its four waves
 // a quarter of the hidden units each (eight waves: 15 instead of 13 us, every wave makes the features for itself).  The chunks of W1 go straight into the matrix operand (a lane reads 16 bytes of its
 // unit's row per slice, a line of 128 bytes in four consecutive requests); nothing is shared but the sum at the end.
-template <int D>
+template <int D, bool RAGGED>
 __global__ __launch_bounds__(kGmSplit * 64) void gate_mlp_split_kernel(const char *k, const char *kr, const char *W1,
                                                              const float *b1, const char *W2, const float *b2,
                                                              float eps, float *g_out, long long T, int Hkv, int width) {
@@ -269,35 +271,50 @@ __global__ __launch_bounds__(kGmSplit * 64) void gate_mlp_split_kernel(const cha
     gm_bf16x8_t wa[KS], xv[KS];
     float4 bb[4];
     uint2 ww[4];
+    // (the last chunk of a ragged width ends in units of zeros: only the wave that has it looks at the width)
     auto fetch = [&](int c) __attribute__((always_inline)) {
-        const int u = min(c, n_chunks - 1) * kGmUnits + n;  // past the last unit: a row of zeros
-        const char *src = W1 + ((size_t)h * width + min(u, width - 1)) * (2 * D * 2) + half * 16;
+        const int u = min(c, n_chunks - 1) * kGmUnits + n;
+        const char *src = W1 + ((size_t)h * width + (RAGGED ? min(u, width - 1) : u)) * (2 * D * 2) + half * 16;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            const uint4 w = *reinterpret_cast<const uint4 *>(src + ks * 32);
-            wa[ks] = __builtin_bit_cast(gm_bf16x8_t, u < width ? w : make_uint4(0u, 0u, 0u, 0u));
+        for (int ks = 0; ks < KS; ks++) wa[ks] = *reinterpret_cast<const gm_bf16x8_t *>(src + ks * 32);
+        if (RAGGED && c == n_chunks - 1) {  // wave-uniform
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++)
+                wa[ks] = __builtin_bit_cast(gm_bf16x8_t, u < width ? __builtin_bit_cast(uint4, wa[ks]) : make_uint4(0u, 0u, 0u, 0u));
         }
     };
     auto fetch_b = [&](int c) __attribute__((always_inline)) {
-        const size_t u0 = (size_t)h * width;
+        const size_t u0 = (size_t)h * width + (size_t)c * kGmUnits;
+        const uint16_t *w2 = reinterpret_cast<const uint16_t *>(W2) + u0;
+        if (RAGGED && c == n_chunks - 1) {  // wave-uniform
+            const int rows = width - c * kGmUnits;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                float b[4];
+                uint32_t w[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int u = 8 * j + 4 * half + i;
+                    const float bv = b1[u0 + min(u, rows - 1)];
+                    const uint32_t wv = w2[min(u, rows - 1)];
+                    b[i] = u < rows ? bv : 0.f;
+                    w[i] = u < rows ? wv : 0u;
+                }
+                bb[j] = make_float4(b[0], b[1], b[2], b[3]);
+                ww[j] = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            float b[4];
-            uint32_t w[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int u = min(c, n_chunks - 1) * kGmUnits + 8 * j + 4 * half + i;
-                const float bv = b1[u0 + min(u, width - 1)];
-                const uint32_t wv = reinterpret_cast<const uint16_t *>(W2)[u0 + min(u, width - 1)];
-                b[i] = u < width ? bv : 0.f;
-                w[i] = u < width ? wv : 0u;
-            }
+            const float *b = b1 + u0 + 8 * j + 4 * half;
+            const uint16_t *w = w2 + 8 * j + 4 * half;
             bb[j] = make_float4(b[0], b[1], b[2], b[3]);
-            ww[j] = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+            ww[j] = make_uint2((uint32_t)w[0] | ((uint32_t)w[1] << 16), (uint32_t)w[2] | ((uint32_t)w[3] << 16));
         }
     };
     fetch(wave);
-    gm_features<D>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, width % kGmUnits != 0, xv);
+    gm_features<D, RAGGED>(k, kr, (size_t)(tok < T ? tok : T - 1) * Hkv + h, half, eps, xv);
     float acc = 0.f;  // twice the logit
     for (int c = wave; c < n_chunks; c += kGmSplit) {  // wave-uniform
         fetch_b(c);
@@ -488,21 +505,22 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         // their own size 8.5 / 9.6 / 20.5.
         const int64_t pairs = n_tokens * n_kv_heads;
         const int64_t cols = width <= kGmUnits ? 98304 : width <= 2 * kGmUnits ? std::max<int64_t>(pairs, 98304) : pairs;
-#define WGKV_GM(D_, CB_, US_)                                                                                            \
-    hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_>),                                                            \
+#define WGKV_GM(D_, CB_, US_, R_)                                                                                       \
+    hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_, R_>),                                                        \
                        dim3((unsigned)((n_tokens + 4 * kGmTokens * CB_ - 1) / (4 * kGmTokens * CB_)), n_kv_heads),       \
                        dim3(256 * US_), 0, st, kp, krp, w1p, b1, w2p, b2, eps, g_out, (long long)n_tokens, n_kv_heads, width)
-#define WGKV_GM_D(D_)                                                                                                   \
+#define WGKV_GM_D(D_, R_)                                                                                               \
     if (cols <= 8192)                                                                                              \
-        hipLaunchKernelGGL((gate_mlp_split_kernel<D_>), dim3((unsigned)((n_tokens + kGmTokens - 1) / kGmTokens * n_kv_heads)), \
+        hipLaunchKernelGGL((gate_mlp_split_kernel<D_, R_>), dim3((unsigned)((n_tokens + kGmTokens - 1) / kGmTokens * n_kv_heads)), \
                            dim3(kGmSplit * 64), 0, st, kp, krp, w1p, b1, w2p, b2, eps, g_out, (long long)n_tokens, n_kv_heads, width); \
-    else if (cols <= 32768) WGKV_GM(D_, 1, 2);                                                                         \
-    else if (cols <= 98304) WGKV_GM(D_, 1, 1);                                                                        \
-    else WGKV_GM(D_, 2, 1)
+    else if (cols <= 32768) WGKV_GM(D_, 1, 2, R_);                                                                     \
+    else if (cols <= 98304) WGKV_GM(D_, 1, 1, R_);                                                                    \
+    else WGKV_GM(D_, 2, 1, R_)
+        const bool ragged = width % kGmUnits != 0;
         if (head_dim == 128) {
-            WGKV_GM_D(128);
+            if (ragged) { WGKV_GM_D(128, true); } else { WGKV_GM_D(128, false); }
         } else {
-            WGKV_GM_D(64);
+            if (ragged) { WGKV_GM_D(64, true); } else { WGKV_GM_D(64, false); }
         }
 #undef WGKV_GM_D
 #undef WGKV_GM
