@@ -488,7 +488,13 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
                            const void *w2, const float *b2, float eps, float *g_out, hipStream_t st) {
     if (n_tokens == 0) return hipSuccess;
     const char *kp = (const char *)k, *krp = (const char *)k_rope, *w1p = (const char *)w1, *w2p = (const char *)w2;
-    if (dtype == WGKV_BF16 && (head_dim == 128 || head_dim == 64)) {
+    const int64_t pairs = n_tokens * n_kv_heads;
+    // A few tokens at a ragged width of some hundred units are the plain kernel's: one turn of its threads over the units, where a chunk that
+    // ends in zeros, the two halves of a row's sum and the matrix operands cost a microsecond (us there / in chunks: 64 pairs, width 130
+    // 6.7 / 7.5 and 8.6 / 9.5, width 500 9.2 / 10.0 and 13.1 / 14.7, 64- and 128-wide; 400 pairs of width 500 16.8 / 10.4 and 26.9 / 15.6; 8
+    // pairs of width 33 6.3 / 5.9 and 8.1 / 7.1, of 2000 25.9 / 22.7 and 39.4 / 37.2).
+    const bool few_ragged = pairs <= 256 && width % kGmUnits != 0 && width > 96 && width < 1024;
+    if (dtype == WGKV_BF16 && (head_dim == 128 || head_dim == 64) && !few_ragged) {
         // Which form, by the number of (token, head) pairs: each up to one round of its resident blocks, where its time
         // is nearly flat.  us at head_dim 128, width 512, for 8K / 32K / 64K / 96K / 128K pairs (the lines lie where
         // two columns cross; 64-wide heads cross at the same places):
@@ -503,7 +509,6 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
         // One or two chunks of hidden units leave nothing to split over waves, one chunk nothing to use twice either: those calls
         // count as of the size that takes the third form.  Width 32, 33 / 4096 / 16384 tokens x 8 heads: 6.3 / 7.5 / 19.3 us, by
         // their own size 8.5 / 9.6 / 20.5.
-        const int64_t pairs = n_tokens * n_kv_heads;
         const int64_t cols = width <= kGmUnits ? 98304 : width <= 2 * kGmUnits ? std::max<int64_t>(pairs, 98304) : pairs;
 #define WGKV_GM(D_, CB_, US_, R_)                                                                                       \
     hipLaunchKernelGGL((gate_mlp_mfma_kernel<D_, CB_, US_, R_>),                                                        \
