@@ -531,10 +531,15 @@ hipError_t launch_gate_mlp(int dtype, int64_t n_tokens, int n_kv_heads, int head
 #undef WGKV_GM
         return hipGetLastError();
     }
-    // A block of 16 tokens stages W1 slice by slice (rows of whole 16-byte pieces), a chain that fewer than about 768 (token, head)
-    // pairs do not pay for (400 pairs 32 us alone, 48 in blocks; 3000 pairs 95 and 28).
+    // A block of 16 tokens stages W1 slice by slice (rows of whole 16-byte pieces), 64 units by 128 features, and its time is that chain up to
+    // some 300 blocks; the plain kernel's grows with the pairs from 200 on.  They cross at the fewer pairs the more of a slice is used
+    // and the more turns the plain kernel takes.  Timed over 1 to 16000 pairs, widths of 1 to 2000, head dimensions of 16 to 256; us there /
+    // here for 128-wide heads: width 512, 400 pairs 32.7 / 49.8, 800 60.6 / 49.6; width 100, 800 16.5 / 18.3, 1200 19.6 / 17.9; width 33, 1200 10.5 /
+    // 12.6, 2400 18.1 / 12.6; width 1, 1600 8.9 / 12.2, 4000 14.6 / 12.7; 16-wide heads, width 512, 1200 13.8 / 17.7, 2400 22.9 / 17.9.
+    const int64_t line = std::max<int64_t>(width >= 256 ? 640 : width >= 64 ? 1088 : width >= 32 ? 1600 : 2304,
+                                           head_dim <= 16 ? 1600 : head_dim > 32 ? 0 : width >= 256 ? 1024 : 1408);
     const size_t smem_f32 = (size_t)kGfTokens * (2 * head_dim + 4) * sizeof(float);
-    if (dtype == WGKV_F32 && n_tokens * n_kv_heads > 768 && head_dim % 2 == 0 && n_tokens < ((int64_t)1 << 34) && smem_f32 <= 40 * 1024) {
+    if (dtype == WGKV_F32 && pairs > line && head_dim % 2 == 0 && n_tokens < ((int64_t)1 << 34) && smem_f32 <= 40 * 1024) {
         hipLaunchKernelGGL(gate_mlp_f32_kernel, dim3((unsigned)((n_tokens + kGfTokens - 1) / kGfTokens), n_kv_heads), dim3(256), smem_f32, st, (const float *)k,
                            (const float *)k_rope, (const float *)w1, b1, (const float *)w2, b2, eps, g_out, (long long)n_tokens, n_kv_heads, head_dim, width);
         return hipGetLastError();

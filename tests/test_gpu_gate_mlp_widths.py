@@ -45,3 +45,11 @@ def test_few_tokens_at_ragged_widths(T, Hk, d, width):
     err = _check(torch.bfloat16, T, Hk, d, width)
     step = 4 * 2 * 0.67 * max(1.0, (32 / width) ** 0.5) / (2 * d) ** 0.5 * 2.0 ** -6 / 4
     assert np.isfinite(err).all() and err.max() <= step and (err > 2e-5).mean() <= 1e-2, (err.max(), step)
+
+
+@pytest.mark.parametrize("pairs,d,width", [(640, 128, 260), (1088, 64, 70), (1600, 64, 40), (2304, 64, 9), (1600, 16, 300), (1024, 32, 256)])
+def test_fp32_lines(pairs, d, width):
+    """As many (token, head) pairs as stay with the plain kernel, and one token more in blocks of 16."""
+    for T in (pairs, pairs + 1):
+        err = _check(torch.float32, T, 1, d, width)
+        assert np.isfinite(err).all() and err.max() <= 2e-5, (T, err.max())
