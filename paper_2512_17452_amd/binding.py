@@ -138,21 +138,37 @@ def _ids(xs):
     return _int_array(tuple(map(int, xs)))
 
 
+_current_stream = None  # gives the handle of the current device's current stream; found with the first call of a process
+
+
 def _stream():
-    t = _torch()
-    return t._C._cuda_getCurrentRawStream(t._C._cuda_getDevice())
+    return _current_stream() if _current_stream is not None else _find_stream()()
 
 
-def _torch():
-    global _torch_module
-    if _torch_module is None:
-        import torch
-        torch.cuda.init()
-        _torch_module = torch
-    return _torch_module
+def _find_stream():
+    global _current_stream
+    import torch
+    torch.cuda.init()
+
+    def public():
+        return torch.cuda.current_stream().cuda_stream
+
+    # torch has the handle without an object around it under names of its own: taken where they are there and agree
+    device, handle = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    found = public
+    if device is not None and handle is not None and handle(device()) == public():
+        def found():
+            return handle(device())
+    _current_stream = found
+    return found
 
 
-_torch_module = None
+def _forget_stream():
+    global _current_stream
+    _current_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)  # a forked child has no GPU: torch says so where it is asked to initialise
 
 
 def _check(rc, what):
