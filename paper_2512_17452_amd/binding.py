@@ -129,15 +129,18 @@ def _ptr(t):
 
 
 @functools.lru_cache(maxsize=512)
-def _int_array(xs):
+def _kept_array(xs):
     return (C.c_int32 * len(xs))(*xs)
 
 
 def _ids(xs):
-    """The int32 array that a call reads its sequence slots or token counts from.  Calls only read it, so equal lists share one."""
-    return _int_array(tuple(map(int, xs)))
+    """The int32 array that a call reads its sequence slots or token counts from.  Calls only read it, so equal lists share one; lists
+    longer than a pool's calls have (training batches of any size) are not kept."""
+    xs = tuple(map(int, xs))
+    return _kept_array(xs) if len(xs) <= _MAX_CALL_SEQS else (C.c_int32 * len(xs))(*xs)
 
 
+_MAX_CALL_SEQS = 128
 _current_stream = None  # gives the handle of the current device's current stream; found with the first call of a process
 
 

@@ -1,4 +1,4 @@
-"""What the binding keeps between calls."""
+"""What the binding keeps between calls: the way to the current stream's handle, and small int32 arrays."""
 import os
 import sys
 import types
@@ -43,3 +43,11 @@ def test_a_forked_child_asks_torch_again(monkeypatch):
         os._exit(0 if binding._current_stream is None else 1)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
     assert binding._current_stream is not None
+
+
+def test_long_lists_are_not_kept():
+    kept = binding._kept_array.cache_info().currsize
+    for n in range(300, 320):
+        assert list(binding._ids(range(n))) == list(range(n))
+    assert binding._kept_array.cache_info().currsize == kept
+    assert binding._ids([5, 7]) is binding._ids((5, 7))
