@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kSelThreads) void quest_select_kernel(View pv, Call
     uint32_t kreg[kSelOwn];
 #pragma unroll
     for (int i0 = 0; i0 < kSelOwn; i0 += 4)
-        if (i0 < own)  // block-uniform
+        if (i0 < own && a.score_stride > 0)  // block-uniform; a row of no scores (every head empty) has no last one to clamp to
 #pragma unroll
             for (int i = i0; i < i0 + 4; i++)  // clamped, not skipped: no branch around each load, they are in flight together
                 kreg[i] = __float_as_uint(sc[min((long long)(own0 + i), a.score_stride - 1)]);

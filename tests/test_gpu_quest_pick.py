@@ -34,3 +34,19 @@ def test_picks_of_a_stable_sort(lens, budget, distinct):
         assert cnt[u] == len(want)
         np.testing.assert_array_equal(sel[u, :len(want)], want)
         assert (sel[u, len(want):] == -1).all()
+
+
+def test_empty_caches_with_rows_of_no_scores():
+    """Every head's cache is empty and a score row has no elements: nothing is read from it, nothing picked."""
+    B, d = 3, 64
+    pool = wg.Pool(wg.Config(1, 2, 2, d, wg.BF16, 16, 32, B, 4, 60), B, 60)
+    k = torch.randn((B, 2, d), device="cuda").to(torch.bfloat16)
+    pool.prefill_admit(0, list(range(B)), [1] * B, k, k, torch.ones((B, 2), device="cuda"), tau=0.5)
+    lm = pool.quest_landmarks()
+    pool.quest_update(0, list(range(B)), lm, reset=True)
+    room = torch.full((8,), float("nan"), device="cuda")  # the row would begin at its end
+    sel = torch.full((2 * B, 5), 7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((2 * B,), 7, dtype=torch.int32, device="cuda")
+    rc = pool.L.wgkv_quest_select(pool.h, 0, B, wg.binding._ids(range(B)), k.data_ptr(), lm.data_ptr(), lm.numel(), 5, room.data_ptr() + 32, 0,
+                                  sel.data_ptr(), cnt.data_ptr(), wg.binding._stream())
+    assert rc == 0 and (sel == -1).all() and (cnt == 0).all() and torch.isnan(room).all()
