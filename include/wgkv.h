@@ -203,8 +203,11 @@ int wgkv_sparsity_loss(const float *g_dev, int64_t n, int64_t n_total, float *lo
  *   b1_dev float [n_kv_heads][width], b2_dev float [n_kv_heads]
  *   g_out_dev float [n_tokens][n_kv_heads]
  * All buffers are device memory owned by the caller; the call only enqueues work on
- * `stream`.  bf16 with head_dim 64 or 128 and width a multiple of 32 runs on the matrix
- * cores, every other shape on a plain kernel.  Errors: INVALID_ARG, HIP. */
+ * `stream`.  bf16 with head_dim 64 or 128 runs on the matrix cores at any width, but for up to
+ * 256 (token, head) pairs at widths between 96 and 1024 that are no multiple of 32; fp32 with an
+ * even head_dim of up to 318 runs in blocks of 16 tokens from some 640 to 2300 pairs on,
+ * by width and head_dim; everything else runs on a plain kernel.  w1_dev must be 16-byte aligned
+ * too.  Errors: INVALID_ARG, HIP. */
 int wgkv_gate_mlp_scores(int32_t dtype, int64_t n_tokens, int32_t n_kv_heads, int32_t head_dim,
                          int32_t width, const void *k_dev, const void *k_rope_dev,
                          const void *w1_dev, const float *b1_dev, const void *w2_dev,
@@ -306,6 +309,9 @@ int wgkv_decode_promote(wgkv_pool *pool, int32_t n_seqs, const int32_t *seq_ids_
  * The prefill-chunk form runs on the matrix cores for every shape the pool accepts, with fp32
  * accumulation.  The softmax weights are rounded to bf16 for bf16 pools of head_dim 128 with 4 query
  * heads per kv head (the paper's models) and keep fp32 precision for every other shape.
+ * The decode form keeps fp32 weights, or 16 bits of them for that shape with pages of 16 tokens and
+ * more.  Values of V may go up to the end of their type's range, as long as their sum stays in that of fp32;
+ * an infinity or NaN in a row that is read comes out in the elements that it reaches.
  * k_chunk_dev and v_chunk_dev must be 16-byte aligned.
  *   q_dev   : [sum n_q][n_q_heads][head_dim] of cfg.dtype
  *   out_dev : float [sum n_q][n_q_heads][head_dim]

@@ -31,7 +31,7 @@
 // about 70 ns, so what runs once is kept small.  Measured, us per launch, registers and dot products on the vector unit
 // throughout / now (rows of memory in both): batch 1 at 32K 15.8 / 13.9; at 8K 12.9 / 10.4; at 2K 12.1 / 10.1; batch 8 at 1K 12.1 /
 // 10.9; batch 2 at 60K 25.1 / 23.3; batch 8 at 100K (442 MB) 77 / 76.5; 32 x 4000 tokens 31.5 / 30.2; 64-wide heads, 2 x 30K 15.7 / 13.5;
-// groups of eight 21.6 / 18.9; of one, batch 1 at 32K 14.4 / 12.8; fp32 128-wide, 2 x 30K 18.0 / 16.5; fp32 2 heads of 20K 13.1 / 10.8.
+// groups of eight 21.6 / 18.9; of one, batch 1 at 32K 14.4 / 12.9; fp32 128-wide, 2 x 30K 18.0 / 16.5; fp32 2 heads of 20K 13.1 / 10.8.
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -1645,9 +1645,9 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
     }
 }
 
-// The kernels.  bf16 keeps to 256 registers (bounds of two waves per SIMD, though its LDS leaves room for one: that is why it is
+// The kernels.  On the matrix cores they keep to 256 registers (bounds of two waves per SIMD, though its LDS leaves room for one: that is why it is
 // allocated at the launch), where the compiler puts a product's accumulators into vector registers and not into the other half of
-// the file, from which it copies them all back in every turn; fp32 needs more.
+// the file, from which it copies them all back in every turn; on the vector unit they need more.
 template <int D, int G, bool FEW>
 __global__ __launch_bounds__(kAttnThreads, 2) void attend_decode_kernel(View pv, AttendArgs a) { decode_blocks<WGKV_BF16, D, G, FEW>(pv, a); }
 template <int D, int G>

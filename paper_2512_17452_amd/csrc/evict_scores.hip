@@ -461,7 +461,8 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
     const dim3 g_stats((n_rows + kEsTile - 1) / kEsTile, n_units);
     const dim3 g_keys((unsigned)((max_len + kEsTile - 1) / kEsTile), n_units);
     const dim3 g_pool((unsigned)((max_len + 255) / 256), n_units);
-    // (the matrix-core kernels read the queries 16 bytes at a time, part of them straight into LDS; the general ones one by one)
+    // (the matrix-core kernels read the queries 16 bytes at a time, part of them straight into LDS; the general ones four elements at a time, or one
+    // by one where they are not aligned)
     const bool q_aligned = ((uintptr_t)q_obs & 15) == 0;
     if (pv.dtype == WGKV_BF16 && pv.d == kEmD && pv.G == 4 && n_obs % 8 == 0 && q_aligned) {
         const dim3 g_stats_m((n_rows + kEmStatRows - 1) / kEmStatRows, n_units);
