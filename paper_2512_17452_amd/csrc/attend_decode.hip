@@ -920,10 +920,16 @@ __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0
 // lane works out the scores of a key (64 keys at a time), then the lanes go through the keys.  Relative to the same maximum as the
 // sums that it replaces (states s0 .. s0 + N - 1); a weight too small for its type stays above zero as a number does.
 template <int N, int DT, int D, int G>
-__device__ __forceinline__ void sum_again(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int p0, int p1,
+__device__ __forceinline__ void sum_again(int u, int um, int gl_all, int gl, int nloc, int p0, int p1,
                                           const DecStates<DT, D, G> &s, int s0, int x0, int xg, DecWaveLds<DT, D, G> &lds, int lane,
                                           float (&o)[DecOut<DT, D, G>::VPT]) {
     constexpr int VPT = DecOut<DT, D, G>::VPT;
+    // the kernel's arguments, read again: kept in registers past the loops for this they cost every call some spilled ones (batch 1 at 32K
+    // 13.97 us; 13.92 with this and the branch to here marked as rare; 13.90 without the check)
+    auto karg = (const char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(karg));
+    const View &pv = *(const View *)karg;
+    const AttendArgs &a = *(const AttendArgs *)(karg + (sizeof(View) + alignof(AttendArgs) - 1) / alignof(AttendArgs) * alignof(AttendArgs));
     static_assert(sizeof(DecStrip<G>) <= sizeof(lds), "");
     DecStrip<G> &strip = *reinterpret_cast<DecStrip<G> *>(&lds);  // the wave has no requests under way
     const char *qu = a.q + (size_t)u * G * D * 2;
@@ -989,7 +995,7 @@ template <int VPT>
 __device__ __forceinline__ bool any_not_finite(const float (&o)[VPT]) {
     float t = fabsf(o[0]) + fabsf(o[1]);
     if constexpr (VPT == 4) t += fabsf(o[2]) + fabsf(o[3]);
-    return __builtin_expect(__builtin_amdgcn_ballot_w64(!(t < INFINITY)) != 0, 0);
+    return __builtin_amdgcn_ballot_w64(!(t < INFINITY)) != 0;
 }
 
 // The maximum of a partial is kept so that what a buffer load returns past the buffer's end, zero, stands for "nothing seen".
@@ -1372,7 +1378,9 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
         float M, L, o[VPT];
         fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
         if constexpr (DT != WGKV_F32)
-            if (any_not_finite(o)) sum_again<OUT::NST>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], threadIdx.x & 63, o);
+            if (__builtin_expect(any_not_finite(o), 0))
+                sum_again<OUT::NST>(u, of_unit(s_um, u), of_unit(s_gl, u), of_unit(s_gt, u), of_unit(s_nl, u), p0, p1, s_st, 0, x0, xg, s_wave_lds[wave],
+                                    threadIdx.x & 63, o);
         float *out = a.out + (size_t)u * G * D;
         if (np > 1) {  // block-uniform
             // The stores carry the policy of a device-scope access (written through) and vmcnt counts them until they are
@@ -1596,9 +1604,9 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
             if (by_wave) fold_states<OUT::NSW>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
             else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
             if constexpr (DT != WGKV_F32)
-                if (any_not_finite(o)) {
-                    if (by_wave) sum_again<OUT::NSW>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
-                    else sum_again<OUT::NST>(pv, a, u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], lane, o);
+                if (__builtin_expect(any_not_finite(o), 0)) {
+                    if (by_wave) sum_again<OUT::NSW>(u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
+                    else sum_again<OUT::NST>(u, um, gl_all, gl, nloc, p0, p1, s_st, 0, x0, xg, s_wave_lds[wave], lane, o);
                 }
             if (x >= NT) continue;
             if (np > 1) {
