@@ -311,7 +311,8 @@ int wgkv_decode_promote(wgkv_pool *pool, int32_t n_seqs, const int32_t *seq_ids_
  * heads per kv head (the paper's models) and keep fp32 precision for every other shape.
  * The decode form keeps fp32 weights, or 16 bits of them for that shape with pages of 16 tokens and
  * more.  Values of V may go up to the end of their type's range, as long as their sum stays in that of fp32;
- * an infinity or NaN in a row that is read comes out in the elements that it reaches.
+ * an infinity or NaN in a row that is read comes out in the elements that it reaches (in fp32 pools an
+ * infinity may come out as NaN where its weight is too small for fp32).
  * k_chunk_dev and v_chunk_dev must be 16-byte aligned.
  *   q_dev   : [sum n_q][n_q_heads][head_dim] of cfg.dtype
  *   out_dev : float [sum n_q][n_q_heads][head_dim]

@@ -1693,7 +1693,7 @@ static void launch_one(const View &pv, const AttendArgs &a, int grid, hipStream_
     //    the wave before it (batch 4 at 20K in pages of 8: 42 / 97).
     if constexpr (DT == WGKV_F32)
         take(std::integral_constant<int, WGKV_F32>{}, attend_decode_many_f32_kernel<D, G>, attend_decode_f32_kernel<D, G, true>, attend_decode_f32_kernel<D, G, false>);
-    else if (pv.logP < 4 || (G * D <= 128 && n_units > 16 * G))
+    else if (pv.logP < 4 || (G * D <= 128 && (many || n_units > 16 * G)))
         take(std::integral_constant<int, kBf16Vec>{}, attend_decode_many_vec_kernel<D, G>, attend_decode_vec_kernel<D, G, true>, attend_decode_vec_kernel<D, G, false>);
     else if constexpr (G * D <= 128)
         take(std::integral_constant<int, WGKV_BF16>{}, nullptr, attend_decode_kernel<D, G, true>, nullptr);

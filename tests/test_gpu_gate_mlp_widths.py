@@ -47,7 +47,8 @@ def test_few_tokens_at_ragged_widths(T, Hk, d, width):
     assert np.isfinite(err).all() and err.max() <= step and (err > 2e-5).mean() <= 1e-2, (err.max(), step)
 
 
-@pytest.mark.parametrize("pairs,d,width", [(640, 128, 260), (1088, 64, 70), (1600, 64, 40), (2304, 64, 9), (1600, 16, 300), (1024, 32, 256)])
+@pytest.mark.parametrize("pairs,d,width", [(640, 128, 260), (1088, 64, 70), (1600, 64, 40), (2304, 64, 9), (1600, 16, 300), (1024, 32, 256), (1408, 20, 65),
+                                           (1088, 40, 65), (1088, 128, 100), (2304, 160, 30)])
 def test_fp32_lines(pairs, d, width):
     """As many (token, head) pairs as stay with the plain kernel, and one token more in blocks of 16."""
     for T in (pairs, pairs + 1):
