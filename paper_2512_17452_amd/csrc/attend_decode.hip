@@ -189,7 +189,7 @@ struct DecSoftmax {
         }
     }
 };
-// Matrix cores: m, 8 or less above the largest exponent so far, is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
+// Matrix cores: m is that of head lane % G; register i of l and of acc[c] belongs to head (4 * (lane / 16) + i) % G, acc[c] to output
 // element 16 * c + lane % 16.
 typedef float dec_f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
@@ -253,9 +253,10 @@ __device__ __forceinline__ uint32_t dec_pack_bf16(float lo, float hi) {  // roun
 // S = K Q^T with the G heads repeated over the 16 columns: a lane ends up with the scores of one head and keys 4 * (lane / 16) + {0..3}
 // of both tiles, which is the row operand of P V as it stands; the second operand is read transposed.  Sums over keys, those of the denominator too,
 // are the matrix core's.  About 0.65 us a pair where a tile took 0.65 us with dot products and reductions on the vector unit.
-// Weights are relative to 2^8 times the largest one so far, and that is brought up to date when a score exceeds it: it costs no exchange
-// between lanes in the rule, and no weight is above one, so values up to the end of the range stay finite as they do in sums of
-// weights that are relative to the maximum itself; sums are fp32 either way.
+// The maximum is brought up to date when a score exceeds it by 8 (weights of up to 256), so it costs no exchange between lanes in
+// the rule; sums are fp32 either way.  What is folded is scaled back (kBack), and a value so large that a sum overflows on the
+// way is one of those that are taken once more (sum_again).  Exponents relative to 8 above the maximum instead, which
+// keep weights at one, are rounded at 8 and cost bits of the largest weights: error against 64 bits 2.6e-7 for 2.2e-7 with three parts.
 template <int D, int G>
 __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a, int u, int um, int gl_all, int gl, int nloc, int cur, int u_end,
                                              dec_u32x4_t (&q)[D / 32], float c_exp, DecSoftmax<WGKV_BF16, D, G> &st,
@@ -385,9 +386,9 @@ __device__ __forceinline__ void stream_pairs(const View &pv, const AttendArgs &a
                     for (int i = 0; i < 4; i++) s[t][i] = t * kTile + 4 * grp + i < valid ? s[t][i] : -INFINITY;
             }
             float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) * c_exp;
-            if (__builtin_amdgcn_ballot_w64(mt > st.m) != 0) {  // rare once the maxima settle
+            if (__builtin_amdgcn_ballot_w64(mt > st.m + 8.f) != 0) {  // rare once the maxima settle
                 const LanePair x = swap16(mt, mt);
-                const float mnew = fmaxf(st.m, max_xor32(fmaxf(x.a, x.b)) + 8.f);
+                const float mnew = fmaxf(st.m, max_xor32(fmaxf(x.a, x.b)));
                 const float corr = __builtin_amdgcn_exp2f(st.m - (mnew == -INFINITY ? 0.f : mnew));
                 st.m = mnew;
                 float ch[G];
@@ -893,8 +894,12 @@ __device__ __forceinline__ int out_of(int x) {
     return DT == WGKV_BF16 ? x / D * D + x % EP * 16 + x % D / EP : x;
 }
 
-// N states from s0 on into one, for places x0 .. of head xg.
-template <int N, int DT, int D, int G>
+// On the matrix cores a weight may be 256: what leaves a block or a wave, sums of weights and of weighted values, is scaled back by that much (its
+// maximum stays what it is, all partials are scaled alike), so that partials of values at the end of the range can be added up.
+template <int DT>
+constexpr float kBack = DT == WGKV_BF16 ? 1.f / 256.f : 1.f;
+// N states from s0 on into one, for places x0 .. of head xg.  BACK: scaled back.
+template <int N, bool BACK, int DT, int D, int G>
 __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0, int x0, int xg, float &M, float &L,
                                             float (&o)[DecOut<DT, D, G>::VPT]) {
     constexpr int VPT = DecOut<DT, D, G>::VPT;
@@ -912,13 +917,19 @@ __device__ __forceinline__ void fold_states(const DecStates<DT, D, G> &s, int s0
 #pragma unroll
         for (int e = 0; e < VPT; e++) o[e] = fmaf(s.acc[s0 + i][x0 + e], f, o[e]);
     }
+    if constexpr (BACK && kBack<DT> != 1.f) {
+        L *= kBack<DT>;
+#pragma unroll
+        for (int e = 0; e < VPT; e++) o[e] *= kBack<DT>;
+    }
 }
 
 // bf16: the weighted sums of tiles [p0, p1) of a unit once more, for a wave one of whose sums is not finite, with each key's whole weight
 // times its value.  The parts that a weight is split into do not carry an infinity of V: later ones are zero or of either sign, and zero times
-// an infinity, or the sum of two that differ in sign, is NaN; and so is an infinity times a factor too small for its type.  Sums of finite values never get here, so this is short and not fast: a
-// lane works out the scores of a key (64 keys at a time), then the lanes go through the keys.  Relative to the same maximum as the
-// sums that it replaces (states s0 .. s0 + N - 1); a weight too small for its type stays above zero as a number does.
+// an infinity, or the sum of two that differ in sign, is NaN; and so is an infinity times a factor too small
+// for its type.  A finite value gets here only if it is above some 1e36 (weights of up to 256 in the sums), so this is short and not
+// fast: a lane works out the scores of a key (64 keys at a time), then the lanes go through the keys.  Relative to the same maximum as
+// the sums that it replaces (states s0 .. s0 + N - 1), and scaled back like them; a weight too small for its type stays above zero as a number does.
 template <int N, int DT, int D, int G>
 __device__ __forceinline__ void sum_again(int u, int um, int gl_all, int gl, int nloc, int p0, int p1,
                                           const DecStates<DT, D, G> &s, int s0, int x0, int xg, DecWaveLds<DT, D, G> &lds, int lane,
@@ -971,7 +982,7 @@ __device__ __forceinline__ void sum_again(int u, int um, int gl_all, int gl, int
                 float m = s.m[s0][g];
 #pragma unroll
                 for (int i = 1; i < N; i++) m = fmaxf(m, s.m[s0 + i][g]);
-                const float x = sc[g] * a.scale_log2e, w = __builtin_amdgcn_exp2f(x - (m == -INFINITY ? 0.f : m));
+                const float x = sc[g] * a.scale_log2e, w = __builtin_amdgcn_exp2f(x - (m == -INFINITY ? 0.f : m)) * kBack<DT>;
                 strip.w[lane][g] = x > -INFINITY ? fmaxf(w, kTiny) : w;
             }
             strip.v[lane] = row + pv.v_off;
@@ -1132,7 +1143,7 @@ __device__ __forceinline__ void fold_partials_block(const AttendArgs &a, int slo
         }
         __syncthreads();
         float m;
-        fold_states<PAR>(s, 0, x0, xg, m, L, o);
+        fold_states<PAR, false>(s, 0, x0, xg, m, L, o);
     }
 }
 
@@ -1376,7 +1387,7 @@ __device__ __forceinline__ void decode_blocks(const View &pv, const AttendArgs &
         put_states<DT, D, G>(s_st, wave, tid & 63, st);
         __syncthreads();
         float M, L, o[VPT];
-        fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
+        fold_states<OUT::NST, true>(s_st, 0, x0, xg, M, L, o);
         if constexpr (DT != WGKV_F32)
             if (__builtin_expect(any_not_finite(o), 0))
                 sum_again<OUT::NST>(u, of_unit(s_um, u), of_unit(s_gl, u), of_unit(s_gt, u), of_unit(s_nl, u), p0, p1, s_st, 0, x0, xg, s_wave_lds[wave],
@@ -1601,8 +1612,8 @@ __device__ __forceinline__ void decode_many(const View &pv, const AttendArgs &a)
         for (int part = part0; part < part1; part++) {
             const int x = part * 64 + lane, x0 = min(x, NT - 1) * VPT, xg = x0 / D;
             float M, L, o[VPT];
-            if (by_wave) fold_states<OUT::NSW>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
-            else fold_states<OUT::NST>(s_st, 0, x0, xg, M, L, o);
+            if (by_wave) fold_states<OUT::NSW, true>(s_st, wave * OUT::NSW, x0, xg, M, L, o);
+            else fold_states<OUT::NST, true>(s_st, 0, x0, xg, M, L, o);
             if constexpr (DT != WGKV_F32)
                 if (__builtin_expect(any_not_finite(o), 0)) {
                     if (by_wave) sum_again<OUT::NSW>(u, um, gl_all, gl, nloc, p0, p1, s_st, wave * OUT::NSW, x0, xg, s_wave_lds[wave], lane, o);
