@@ -798,14 +798,17 @@ __device__ __forceinline__ void run_part(const View &pv, const AttendArgs &a, in
     using SH = DecShape<DT, D, G>;
     st.init();
     if (w0 >= w1) return;
-    // wave-uniform, which the compiler does not always see: the requests' bases are scalar operands
-    u = __builtin_amdgcn_readfirstlane(u);
-    um = __builtin_amdgcn_readfirstlane(um);
-    gl_all = __builtin_amdgcn_readfirstlane(gl_all);
-    gl = __builtin_amdgcn_readfirstlane(gl);
-    nloc = __builtin_amdgcn_readfirstlane(nloc);
-    w0 = __builtin_amdgcn_readfirstlane(w0);
-    w1 = __builtin_amdgcn_readfirstlane(w1);
+    // wave-uniform, which the compiler does not always see: the requests' bases are scalar operands (the vector unit's loads have no use
+    // for it: 166 calls of many units there 1.4 % slower with it)
+    if constexpr (DT == WGKV_BF16) {
+        u = __builtin_amdgcn_readfirstlane(u);
+        um = __builtin_amdgcn_readfirstlane(um);
+        gl_all = __builtin_amdgcn_readfirstlane(gl_all);
+        gl = __builtin_amdgcn_readfirstlane(gl);
+        nloc = __builtin_amdgcn_readfirstlane(nloc);
+        w0 = __builtin_amdgcn_readfirstlane(w0);
+        w1 = __builtin_amdgcn_readfirstlane(w1);
+    }
     const char *qu = a.q + (size_t)u * G * D * SH::ES;
     if constexpr (DT == WGKV_BF16) {
         dec_u32x4_t q[D / 32];
