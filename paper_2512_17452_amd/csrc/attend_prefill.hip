@@ -15,25 +15,18 @@
 // query of the block sees, instead of running over the whole chunk with a mask (4096-token chunks at an
 // admission rate of a half, 0-12K tokens before them: 1095 -> 803 us per chunk of two prompts, lists included).
 //
-// attend_prefill_kernel (every shape but the one of the paper's models): one block owns 256 / G chunk
-// positions of one (sequence, kv head) with a group of G query heads;
-// its eight waves are (query head of the group) x (row block of 32 positions), so a K/V tile staged
-// in LDS feeds all of them and two waves share each SIMD.  A tile is 8 KiB of K and of V (16 bytes of
-// each per thread): 32 keys of 128 elements, 64 keys of 64.
-// K and V tiles are staged row-major; the V^T operand is read from the V tile with the
-// transposing LDS load.  Everything is computed transposed, S^T = K Q^T and O^T = V^T P^T with
+// Everything is computed transposed, S^T = K Q^T and O^T = V^T P^T with
 // v_mfma_f32_32x32x16_bf16: a lane then owns one query column, so the running max,
 // the denominator and the rescale factor are plain per-lane scalars, and the
-// probabilities leave the first product already in the operand layout of the second.
+// probabilities leave the first product already in the operand layout of the second.  Key tiles are 64 rows of K and of V that come
+// from memory straight into LDS a tile ahead; the V^T operand is read from the V tile with the transposing LDS load.  Waves are
+// (query head of the group) x (row block of 32 positions) and share a tile.
 //
 // Two forms of the weights P.  For the shape of the paper's models (128 wide, four heads a group;
 // attend_prefill_tiles_kernel) they are rounded to bf16 once, and the denominator sums the rounded ones.  For
-// every other shape they keep 24 bits: p = hi + mid + lo, each part the upper half of an fp32 word and hi, mid
-// exact remainders, three products with the same V^T operand; V is bf16, so the products are exact and
-// the sums are fp32 as they are in plain fp32 arithmetic.  The matrix cores have the room: at 64 elements
-// the vector work per score is twice the four extra products.  Measured: a 6001-token prompt of 32 / 8 heads
-// of 64 in chunks of 2048, gate and admission included, 17.3 ms -> 0.40 ms against one wave of plain fp32
-// arithmetic per (query, head), the error against 64 bits 9.3e-7 -> 6.4e-7.
+// every other shape (attend_prefill_parts_kernel) they keep 24 bits: p = hi + mid + lo, each a bf16 and hi, mid
+// with exact remainders, three products with the same V^T operand; V is bf16, so the products are exact and
+// the sums are fp32 as they are in plain fp32 arithmetic.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -47,26 +40,12 @@ typedef __attribute__((ext_vector_type(8))) __bf16 pf_bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 pf_bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
 
-// The shape of one instantiation: head_dim D, group size G.
-template <int D_, int G_>
-struct PfShape {
-    static constexpr int D = D_, G = G_;
-    static constexpr int Q = 256 / G;       // chunk positions per block (8 / G row blocks of 32)
-    static constexpr int CPR = D / 8;       // 16-byte chunks per row
-    static constexpr int KT = 512 / CPR;    // keys per tile: a chunk of K and of V per thread
-    static constexpr int NS = KT / 32;      // score tiles of 32 keys
-    static constexpr int KS = D / 16;       // contraction slices of the first product
-    static constexpr int DB = D / 32;       // output blocks of 32 elements
-    static constexpr int KPW = 64 / CPR;    // keys a wave stages
-    static constexpr int KStride = D * 2 + 16;  // bytes per key row of the K tile in LDS: rows are read whole
-    static constexpr int VStride = D * 2 + 64;  // bytes per key row of the V tile: columns are read, four rows and
-                                                // 64 bytes of each at a time per half wave, which this stride
-                                                // (320 or 192 bytes) spreads over all banks
-};
-
 struct PrefillAttnArgs {
     int nx;                 // blocks per (sequence, kv head) of the launch
     int rank0;              // place in the order of the launch's first unit
+    int n_units;
+    int by_row;             // the same positions of all units one after the other
+    int n_cu;               // compute units, if every block of the call has its place from the start (two to a unit), else 0
     int ordered;            // else the units in their own order, and `order` is only somewhere to read from
     const int32_t *order;   // [n_units] (sequence, kv head) units, the one with the longest global cache first
     const int32_t *pick;    // admitted chunk positions of every unit, ascending (pick_of), or NULL
@@ -79,41 +58,28 @@ struct PrefillAttnArgs {
     float *out;
 };
 
-// A operand of O^T += V^T P^T from the row-major V tile: the output row of this lane is
-// d = db*32 + qn, its 8 contraction slots are keys r0 + 4*half + {0..3} and r0 + 8 + 4*half + {0..3}
-// of the tile.  ds_read_b64_tr_b16 transposes inside groups of 16 lanes: lane i of a group receives
-// element i%4 of the 8 bytes addressed by lanes i/4, 4 + i/4, 8 + i/4 and 12 + i/4, so lane s of a
-// group addresses (key s/4 of the four, columns 4*(s%4)..+3 of the group's 16).
-typedef short pf_s16x4_t __attribute__((ext_vector_type(4)));
-template <int STRIDE>
-__device__ __forceinline__ pf_bf16x8_t pf_get_cols(const char *tile, int lane, int db, int r0) {
-    const int half = lane >> 5;
-    const char *p = tile + (r0 + 4 * half + ((lane & 15) >> 2)) * STRIDE +
-                    (db * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-    typedef pf_s16x4_t __attribute__((address_space(3))) *lds_ptr_t;
-    const pf_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)p);
-    const pf_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * STRIDE));
-    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-    const uint4 u4 = make_uint4(l2.x, l2.y, h2.x, h2.y);
-    return __builtin_bit_cast(pf_bf16x8_t, u4);
-}
-
 __device__ __forceinline__ uint32_t pf_pack(float lo, float hi) {
     pf_bf16x2_t t = {(__bf16)lo, (__bf16)hi};
     return __builtin_bit_cast(uint32_t, t);
 }
 
-// The upper halves of two fp32 words as one pair of bf16 (the low word first).
-__device__ __forceinline__ uint32_t pf_top(float lo, float hi) {
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+// A pair of fp32 as three pairs of bf16 whose sums they are: the nearest, the nearest to the rest, the rest of that.  (A rest is
+// exact: a two-element dot product with (-1, 0) or (0, -1) takes the element from the pair, where unpacking and subtracting are two
+// instructions.  The two come in registers: as a constant (-1, 0) is taken for the inline -1.0, which is (0, -1) to this instruction.)
+struct PfMinus {
+    uint32_t first = 0xbf80u, second = 0xbf800000u;
+    __device__ __forceinline__ PfMinus() { asm volatile("" : "+s"(first), "+s"(second)); }
+    __device__ __forceinline__ float rest(uint32_t pair, bool upper, float x) const {
+        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pair), __builtin_bit_cast(pf_bf16x2_t, upper ? second : first), x, false);
+    }
+};
+__device__ __forceinline__ void pf_split(const PfMinus &minus, float p0, float p1, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    hi = pf_pack(p0, p1);
+    const float r0 = minus.rest(hi, false, p0), r1 = minus.rest(hi, true, p1);
+    mid = pf_pack(r0, r1);
+    lo = pf_pack(minus.rest(mid, false, r0), minus.rest(mid, true, r1));
 }
-__device__ __forceinline__ float pf_rest(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 
-// Eight bf16 hold an inf or a NaN: an exponent of ones carries into the bit above it.
-__device__ __forceinline__ bool pf_nonfinite(const uint4 &x) {
-    constexpr uint32_t kExp = 0x7f807f80u, kOne = 0x00800080u;
-    return ((((x.x & kExp) + kOne) | ((x.y & kExp) + kOne) | ((x.z & kExp) + kOne) | ((x.w & kExp) + kOne)) & 0x80008000u) != 0u;
-}
 // Takes the infinities and NaNs out of an operand of V^T and gives them to the columns of o that see their keys (seen:
 // bf16 ones and zeros in the operand layout of P^T): one product of codes counts +inf, -inf and NaN (at most 16 of
 // each: 1, 32 and 1024 apiece), then o gets what the sum would have had.
@@ -161,260 +127,321 @@ __device__ __forceinline__ bool pf_no_mask(int t, int KT, int n_g, int n_plain, 
     return i0 + KT - 1 <= q_first && q_last - i0 < W;
 }
 
-template <int D_, int G_>
-__global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
-    using S = PfShape<D_, G_>;
-    constexpr int D = S::D, G = S::G, KT = S::KT, NS = S::NS, KS = S::KS, DB = S::DB;
-    __shared__ __attribute__((aligned(16))) char s_k[2][KT * S::KStride];
-    __shared__ __attribute__((aligned(16))) char s_v[2][KT * S::VStride];
-    __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
-    __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
-    __shared__ int s_bad[2];  // the tile in that buffer if it holds a V that is not finite
+// The query at position qpos sees a key that is visible to n positions from lo on: all positions, those from the key's own on,
+// its window's, or none.
+constexpr uint32_t kPfAll = 0xffffffffu, kPfOn = 0x80000000u;
+__device__ __forceinline__ bool pf_sees(int qpos, int lo, uint32_t n) { return (uint32_t)qpos - (uint32_t)lo < n; }
 
-    // Blocks are handed out in the order of their index and go to the 8 XCDs round-robin: all
-    // blocks of the unit with the longest global cache come first, its latest positions (which see
-    // the most chunk keys) at the front, then the next unit.  Admission is head-specific, so units
-    // differ several-fold in work: with the long ones at the front the launch does not end on a
-    // late-started long one, and every unit is spread evenly over the XCDs (giving each XCD whole
-    // heads, for the sake of its L2, leaves the XCDs as unbalanced as the heads are).
-    const int rank = a.rank0 + (int)(blockIdx.x / a.nx), unit = a.ordered ? a.order[rank] : rank;
+// ---------------------------------------------------------------------------------------------
+// Every shape but the one of the paper's models: weights of 24 bits
+//
+// A block is four waves, two to a compute unit.  Groups of four and eight: four heads of 32 positions, a wave each.  Groups
+// of one and two: 64 and 32 positions, two waves to 32 queries, which take half of every tile's keys each and are folded at the end
+// (the block then has half as many positions, and a call of a few heads twice the blocks).  Two waves to all queries is slower for
+// the larger groups: 4000 tokens of 64 / 8 heads of 128, whole call, 324 -> 373 us.
+//
+// Bound by the instructions of a wave, a few of which run beside each other on a SIMD: a tile is some 300 of the vector unit, 8 and 24
+// (16 and 48 at 128 elements) products, and what it takes to request the next one.  So: tiles without a mask whose successor lies in pages that
+// hold all rows of a wave have a loop of their own with one page id and one address each; scores are not scaled, the
+// exponent's multiply-add does that; a weight is split by dot products (pf_split); the weights of 16 keys are formed beside the
+// products of the 16 before; nothing in the loop waits for a load but its end; values that are not finite are looked for once, in the
+// sums.  Whole calls, gate, admission and freeing included, against 256 / G positions a block with tiles through registers, us before / now:
+// a 6001-token prompt of 32 / 8 heads of 64 in chunks of 2048 408 / 362, 5000 tokens in one of 4096 and one of 904 213 / 162; 4000
+// tokens of 64 / 8 heads of 128 299 / 275, of 16 / 8 209 / 136, of 8 / 8 220 / 130; 3000 of 8 / 8 heads of 64 152 / 93.  Slower:
+// 4000 tokens of 64 / 8 heads of 128 in chunks of 1000 that admit 7 %, 312 / 318 (tiles of 64 keys, not 32, are filled up with more).
+// ---------------------------------------------------------------------------------------------
+// The block's unit and its place among the nx of that unit, the longest rows (latest positions) first.
+// Blocks are handed out in the order of their index and go to the 8 XCDs round-robin: all
+// blocks of the unit with the longest global cache come first, its latest positions (which see
+// the most chunk keys) at the front, then the next unit.  Admission is head-specific, so units
+// differ several-fold in work: with the long ones at the front the launch does not end on a
+// late-started long one, and every unit is spread evenly over the XCDs (giving each XCD whole
+// heads, for the sake of its L2, leaves the XCDs as unbalanced as the heads are).
+// Short calls go row by row instead (launch_units).
+// Where all blocks run at once, two to a compute unit, there is no late start but the pairs: the first of every pair go by descending length
+// from position to position over all units, the second ones by ascending length, so that a long one shares with a short one (a 6001-token
+// prompt of 32 / 8 heads of 64 in chunks of 2048, whole call: 400 -> 357 us).
+__device__ __forceinline__ void pf_item(const PrefillAttnArgs &a, int &unit, int &x) {
+    int i = (int)blockIdx.x;
+    if (a.n_cu > 0) {
+        const int total = a.nx * a.n_units;
+        if (i >= a.n_cu) i = total - 1 - (i - a.n_cu);
+        x = i / a.n_units;
+        // one unit's blocks go to all XCDs; the step in the middle keeps the two of a pair in different units if these are even in number
+        unit = (i + x + (a.nx % 2 == 0 && x >= a.nx / 2 ? 1 : 0)) % a.n_units;
+        return;
+    }
+    const int per = (int)gridDim.x / a.nx;
+    x = a.by_row ? i / per : i % a.nx;
+    const int rank = a.rank0 + (a.by_row ? (i + x) % per : i / a.nx);
+    unit = a.ordered ? a.order[rank] : rank;
+}
+
+template <int D_, int G_>
+struct PfShape {
+    static constexpr int D = D_, G = G_;
+    static constexpr int KSP = G < 4 ? 2 : 1;                    // waves that share 32 queries
+    static constexpr int HB = G < 4 ? G : 4;                     // query heads of a block
+    static constexpr int HG = G / HB;                            // blocks per group and position range
+    static constexpr int RB = HB == 1 ? 2 : 1;                   // row blocks of 32 positions
+    static constexpr int NW = HB * RB * KSP;                     // waves
+    static constexpr int Q = 32 * RB;                            // chunk positions per block
+    static constexpr int KT = 64, NS = KT / 32 / KSP;            // keys per tile, score tiles of 32 keys per wave
+    static constexpr int KS = D / 16;                            // contraction slices of the first product
+    static constexpr int DB = D / 32;                            // output blocks of 32 elements
+    static constexpr int RowB = D * 2;
+    static constexpr int TileB = KT * RowB;
+    static constexpr int FoldB = KSP == 1 ? 0 : NW / 2 * (DB * 16 + 2) * 256;
+    static constexpr int Smem = FoldB > 4 * TileB ? FoldB : 4 * TileB;
+};
+
+template <int D_, int G_>
+__global__ __launch_bounds__((PfShape<D_, G_>::NW * 64), 2)
+void attend_prefill_parts_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
+    using S = PfShape<D_, G_>;
+    constexpr int D = S::D, G = S::G, KT = S::KT, NS = S::NS, KS = S::KS, DB = S::DB, NW = S::NW, Q = S::Q, RowB = S::RowB;
+    constexpr int kRows = KT / NW;       // rows of a tile that a wave brings
+    constexpr int kPer = 1024 / RowB;    // rows per request
+    __shared__ __attribute__((aligned(1024))) char s_t[S::Smem];  // two tiles of K and of V, at the end the fold
+    __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
+    __shared__ __attribute__((aligned(16))) uint32_t s_n[2][KT];
+
+    int unit, x;
+    pf_item(a, unit, x);
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
-    const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
+    const int qt = (a.nx - 1 - x) / S::HG;
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
-    if (qt * S::Q >= T) return;  // block-uniform
-    const int sid = cs.sid[b];
-    const int um = unit_meta(pv, sid, a.layer, h);
-    // eight waves: wave -> (query head of the group, row block of 32 positions); two waves
-    // share a SIMD, so one can run its softmax while the other keeps the matrix core busy
+    if (qt * Q >= T) return;  // block-uniform
+    const int um = unit_meta(pv, cs.sid[b], a.layer, h);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int head = wave % G, rb = wave / G;
+    const int head = wave % S::HB + (S::HG > 1 ? x % S::HG * S::HB : 0);
+    const int rb = wave / S::HB % S::RB, ksp = wave / (S::HB * S::RB);
     const int qn = lane & 31, half = lane >> 5;
     const int gl = pv.global_len[um];
     const int w_eff = min(pv.W, t0);              // ring entries that exist
-    const int i_end = min(T, qt * S::Q + S::Q);   // chunk keys this block can see: [0, i_end)
+    const int i_end = min(T, qt * Q + Q);         // chunk keys this block can see: [0, i_end)
     // tiles: global cache, ring, picked chunk keys below `near`, all chunk keys from there on
-    const int near = a.pick ? max(0, qt * S::Q - pv.W + 1) / KT * KT : 0;  // no window of the block reaches below
+    const int near = a.pick ? max(0, qt * Q - pv.W + 1) / KT * KT : 0;  // no window of the block reaches below
     const int32_t *pick = a.pick ? a.pick + pick_of(pv.Hkv, b, h, base, T) : a.order;
     const int n_far = near > 0 ? a.picked[picked_of(pv.Hkv, b, h, base, T) + near / 32] : 0;
     const int n_g = (gl + KT - 1) / KT, n_r = (w_eff + KT - 1) / KT;
     const int t_far = n_g + n_r, t_near = t_far + (n_far + KT - 1) / KT;  // first tile of each kind
     const int n_tiles = t_near + (i_end - near + KT - 1) / KT;
 
-    // ---- Q^T operand: this lane's query, all d-slices of 16 ----
+    // the maximum is taken of the products themselves: a negative scale turns the query's sign instead (and one of zero
+    // stays a hair above it: -inf times it is -inf, not a NaN)
+    const float c2 = fmaxf(fabsf(a.scale_log2e), 1e-45f);
+    const uint32_t sign = a.scale_log2e < 0.f ? 0x80008000u : 0u;
     pf_bf16x8_t qv[KS];
-    const int q_first = qt * S::Q + rb * 32;      // first position of this wave's rows
+    const int q_first = qt * Q + rb * 32;         // first position of this wave's rows
     const int qi = min(q_first + qn, T - 1);
     const int qpos = t0 + qi;
     {
-        const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * D * 2;
+        const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * RowB;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++)
-            qv[ks] = *reinterpret_cast<const pf_bf16x8_t *>(qp + (ks * 16 + half * 8) * 2);
+        for (int ks = 0; ks < KS; ks++) {
+            uint4 w = *reinterpret_cast<const uint4 *>(qp + (ks * 16 + half * 8) * 2);
+            w.x ^= sign; w.y ^= sign; w.z ^= sign; w.w ^= sign;
+            qv[ks] = __builtin_bit_cast(pf_bf16x8_t, w);
+        }
     }
-    pf_f32x16_t o[DB];
-    float m = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; db++)
-#pragma unroll
-        for (int c = 0; c < 16; c++) o[db][c] = 0.f;
 
-    // ---- staging of a key tile: thread -> (key of the tile, 16-byte d chunk), K and V row-major ----
-    const int ld_key = threadIdx.x / S::CPR, ld_dc = threadIdx.x % S::CPR;
-    // two sets of staging registers: a tile is requested two iterations before it is multiplied
-    // (plain variables passed one by one: a struct of them ends up in scratch memory)
-    uint4 k0r, v0r, k1r, v1r;
-    int lo0r, hi0r, lo1r, hi1r;
-    // Page ids live in registers, one per lane, so that the address of a key row never
-    // waits for a page-table load: 64 consecutive entries of the global table (reloaded
-    // every 64 pages) and the whole local table when it has at most 64 entries.
+    // Page ids live in registers, one per lane, so that the address of a key row never waits for a page-table load: 64
+    // consecutive entries of the global table (reloaded every 64 pages) and the whole local table of at most 64 entries.
     int pt_base = 0;
     int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
     const bool lp_in_reg = pv.nlp <= 64;
-    const int lpreg = (lp_in_reg && lane < pv.nlp) ? pv.local_pt[(size_t)um * pv.nlp + lane] : 0;
+    int lpreg = (lp_in_reg && lane < pv.nlp) ? pv.local_pt[(size_t)um * pv.nlp + lane] : 0;
+    auto ring_page = [&](int slot) __attribute__((always_inline)) {
+        if (lp_in_reg) return __shfl(lpreg, slot >> pv.logP);
+        int pg = pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
+        asm volatile("" : "+v"(pg));  // waited for here: where the two ways meet, every request would be waited for
+        return pg;
+    };
     const int slot0 = t0 > pv.W ? t0 % pv.W : 0;  // ring slot of the oldest position
-    const int64_t v_delta_chunk = a.v - a.k;
-    // position of this thread's key of a picked tile (anything for another tile): asked for an iteration before its
-    // row is
-    auto ask_far = [&](int t) __attribute__((always_inline)) {
-        return pick[max(0, min((t - t_far) * KT + ld_key, n_far - 1))];
+    auto ring_slot = [&](int idx) __attribute__((always_inline)) {
+        const int s = slot0 + min(idx, w_eff - 1);
+        return s >= pv.W ? s - pv.W : s;
     };
-    auto fetch = [&](int t, int far, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
-        const char *kp;
-        int64_t v_delta;
-        int lo = INT_MAX, hi = INT_MAX;  // invisible unless shown otherwise
-        if (t < n_g) {  // global cache: visible to every query
-            if (((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
-                pt_base = (t * KT) >> pv.logP;
-                ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
-            }
-            const int idx = t * KT + ld_key, idc = min(idx, gl - 1);
-            const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
-            kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
-            if (idx < gl) lo = INT_MIN;
-            v_delta = pv.v_off;
-        } else if (t < t_far) {  // ring, oldest position first
-            const int idx = (t - n_g) * KT + ld_key, idc = min(idx, w_eff - 1);
-            int slot = slot0 + idc;
-            slot = slot >= pv.W ? slot - pv.W : slot;
-            const int pos = t0 - w_eff + idc;
-            const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
-                                     : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
-            kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
-            if (idx < w_eff) {
-                lo = pos;
-                hi = (pv.ring_g[(size_t)um * pv.W + slot] >= a.tau) ? INT_MAX : pos + pv.W - 1;
-            }
-            v_delta = pv.v_off;
-        } else if (t < t_near) {  // picked keys of this chunk: visible to every query
-            kp = a.k + ((size_t)(base + far) * pv.Hkv + h) * (D * 2);
-            if ((t - t_far) * KT + ld_key < n_far) lo = INT_MIN;
-            v_delta = v_delta_chunk;
-        } else {  // this chunk
-            const int idx = near + (t - t_near) * KT + ld_key, idc = min(idx, T - 1);
-            const size_t row = (size_t)(base + idc) * pv.Hkv + h;
-            kp = a.k + row * (D * 2);
-            if (idx < T) {
-                lo = t0 + idx;
-                hi = (a.g[row] >= a.tau) ? INT_MAX : t0 + idx + pv.W - 1;
-            }
-            v_delta = v_delta_chunk;
-        }
-        r_k = *reinterpret_cast<const uint4 *>(kp + ld_dc * 16);
-        r_v = *reinterpret_cast<const uint4 *>(kp + v_delta + ld_dc * 16);
-        r_lo = lo;
-        r_hi = hi;
+    // this lane's pieces of the rows that its wave brings: row kPer * i + sub of those, 16 bytes in the order of the LDS tile
+    constexpr int kReq = kRows / kPer;
+    const int sub = lane / (RowB / 16);
+    static_assert(kRows == 16, "the order of the pieces repeats every 16 rows");
+    const uint32_t off0 = (uint32_t)(sub * RowB + (lane % (RowB / 16) ^ sa_sw_f<D>(sub)) * 16);
+    auto off_of = [&](uint32_t o0, int i) __attribute__((always_inline)) { return (o0 ^ (i * kPer / 4 * 16)) + i * 1024; };
+    auto fresh = [&]() __attribute__((always_inline)) {
+        uint32_t o0 = off0;
+        asm volatile("" : "+v"(o0));  // (formed per tile: 128 elements leave no registers to keep them)
+        return o0;
     };
-    // Full tiles of the global cache, pages of at least as many tokens as a wave stages: its keys
-    // share a page, so the page base is scalar and a lane only adds a fixed offset.
-    const bool lean_ok = pv.P >= S::KPW;
-    const uint32_t lean_k_off = (uint32_t)(ld_key & (pv.P - 1)) * (D * 2) + ld_dc * 16;
-    auto fetch_lean = [&](int t, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
+    // chunk positions of those rows of a picked tile (anything for another tile): asked for a tile before the rows are
+    auto ask_far = [&](int t, int (&far)[kReq]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kReq; i++) far[i] = pick[max(0, min((t - t_far) * KT + wave * kRows + kPer * i + sub, n_far - 1))];
+    };
+    const int n_plain = gl / KT;                     // full tiles of the global cache
+    const int n_lean = pv.P >= kRows ? n_plain : 0;  // those whose pages hold all rows that a wave brings
+    // page ids of tile t's global rows into ptreg
+    auto see_pages = [&](int t) __attribute__((always_inline)) {
         if (((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
             pt_base = (t * KT) >> pv.logP;
             ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
+            asm volatile("" : "+v"(ptreg));  // waited for here: behind the branch every tile would wait for all that is in flight
         }
-        const int pg = __builtin_amdgcn_readlane(ptreg, ((t * KT + S::KPW * wave) >> pv.logP) - pt_base);
-        // inside its page the tile begins at row (KT t) mod P (0 unless a page holds several tiles)
-        const char *sb = page_ptr(pv, pg) + (size_t)((t * KT) & (pv.P - 1)) * (D * 2);
-        r_k = *reinterpret_cast<const uint4 *>(sb + lean_k_off);
-        r_v = *reinterpret_cast<const uint4 *>(sb + lean_k_off + pv.v_off);
-        r_lo = INT_MIN;
-        r_hi = INT_MAX;
     };
-    auto stage = [&](int buf, const uint4 &r_k, const uint4 &r_v, int r_lo, int r_hi) __attribute__((always_inline)) {
-        *reinterpret_cast<uint4 *>(&s_k[buf][ld_key * S::KStride + ld_dc * 16]) = r_k;
-        *reinterpret_cast<uint4 *>(&s_v[buf][ld_key * S::VStride + ld_dc * 16]) = r_v;
-        if (ld_dc == 0) { s_lo[buf][ld_key] = r_lo; s_hi[buf][ld_key] = r_hi; }
+    auto lds_k = [&](int t) __attribute__((always_inline)) { return s_t + (t & 1) * (2 * S::TileB) + wave * kRows * RowB; };
+    // a full tile of the global cache whose pages hold all rows that a wave brings
+    auto fetch_lean = [&](int t) __attribute__((always_inline)) {
+        char *lk = lds_k(t);
+        see_pages(t);
+        const int idx = t * KT + kRows * wave;
+        const int pg = __builtin_amdgcn_readlane(ptreg, (idx >> pv.logP) - pt_base);
+        const char *sb = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * RowB;
+        const uint32_t o0 = fresh();
+#pragma unroll
+        for (int i = 0; i < kReq; i++) {
+            sa_dma16(sb, off_of(o0, i), lk + i * 1024);
+            sa_dma16(sb + pv.v_off, off_of(o0, i), lk + S::TileB + i * 1024);
+        }
     };
-    const int n_plain = gl / KT;  // full tiles of the global cache
+    const uint32_t c_stride = (uint32_t)(pv.Hkv * RowB);  // bytes from a chunk position to the next
+    const size_t c_base = ((size_t)base * pv.Hkv + h) * RowB;
+    const bool c_near = (uint64_t)T * c_stride < (1ull << 31);  // their requests take an offset of 32 bits
+    auto fetch = [&](int t, const int (&far)[kReq]) __attribute__((always_inline)) {
+        char *lk = lds_k(t), *lv = lk + S::TileB;
+        if (t < n_g) see_pages(t);
+        const uint32_t o0 = fresh();
+        if (t >= t_far && c_near) {  // this chunk
+#pragma unroll
+            for (int i = 0; i < kReq; i++) {
+                const int idc = t < t_near ? far[i] : min(near + (t - t_near) * KT + wave * kRows + kPer * i + sub, T - 1);
+                const uint32_t o = (uint32_t)idc * c_stride + (off_of(o0, i) & (RowB - 1));
+                sa_dma16(a.k + c_base, o, lk + i * 1024);
+                sa_dma16(a.v + c_base, o, lv + i * 1024);
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < kReq; i++) {  // a row past the end of its region repeats the region's last one
+            const int r = wave * kRows + kPer * i + sub;
+            const char *kp;
+            int64_t v_delta = pv.v_off;
+            if (t < n_g) {  // global cache
+                const int idc = min(t * KT + r, gl - 1);
+                const int pg = __shfl(ptreg, (idc >> pv.logP) - pt_base);
+                kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * RowB;
+            } else if (t < t_far) {  // ring, oldest position first
+                const int slot = ring_slot((t - n_g) * KT + r);
+                kp = page_ptr(pv, ring_page(slot)) + (size_t)(slot & (pv.P - 1)) * RowB;
+            } else {  // this chunk
+                const int idc = t < t_near ? far[i] : min(near + (t - t_near) * KT + r, T - 1);
+                kp = a.k + ((size_t)(base + idc) * pv.Hkv + h) * RowB;
+                v_delta = a.v - a.k;
+            }
+            kp += off_of(o0, i) & (RowB - 1);
+            sa_dma16_at(kp, lk + i * 1024);
+            sa_dma16_at(kp + v_delta, lv + i * 1024);
+        }
+    };
     auto no_mask = [&](int t) __attribute__((always_inline)) {
-        return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, qt * S::Q, qt * S::Q + S::Q - 1);
+        return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, qt * Q, qt * Q + Q - 1);
     };
-    // A weight of zero does not keep an inf or NaN of V out of a product, and the middle and low parts of a weight are often zero,
-    // of a visible key too: every tile is looked through (t: the one that goes to the buffer).
-    auto look = [&](int buf, const uint4 &r_v, int t) __attribute__((always_inline)) {
-        if (pf_nonfinite(r_v)) s_bad[buf] = t;  // all writers of a tile write the same
+    // Who sees key `lane` of a tile with a mask: n positions from lo on.  A wave of the block in turn asks for its score and,
+    // at the end of the turn, writes the two bounds.
+    auto ask_score = [&](int t) __attribute__((always_inline)) {
+        const int idx = t < t_far ? (t - n_g) * KT + lane : near + (t - t_near) * KT + lane;
+        const float *gp = pv.ring_g;  // anything for a tile of the global cache or of picked keys
+        if (t >= n_g && t < t_far) gp += (size_t)um * pv.W + ring_slot(idx);
+        if (t >= t_near) gp = a.g + (size_t)(base + min(idx, T - 1)) * pv.Hkv + h;
+        return *gp;
     };
-    if (threadIdx.x < 2) s_bad[threadIdx.x] = -1;
-
-    auto fetch_any = [&](int t, int far, uint4 &r_k, uint4 &r_v, int &r_lo, int &r_hi) __attribute__((always_inline)) {
-        if (lean_ok && t < n_plain) fetch_lean(t, r_k, r_v, r_lo, r_hi);
-        else fetch(t, far, r_k, r_v, r_lo, r_hi);
-    };
-    const int far0 = ask_far(0), far1 = ask_far(1);
-    int far_next = ask_far(2);
-    fetch_any(0, far0, k0r, v0r, lo0r, hi0r);
-    stage(0, k0r, v0r, lo0r, hi0r);
-    __syncthreads();  // s_bad is set
-    look(0, v0r, 0);
-    if (n_tiles > 1) fetch_any(1, far1, k1r, v1r, lo1r, hi1r);
-    __syncthreads();
-
-    // one iteration: tile t is multiplied, tile t+2 is requested into rf, tile t+1 goes from rs to LDS
-    auto body = [&](int t, uint4 &f_k, uint4 &f_v, int &f_lo, int &f_hi, const uint4 &s_kk, const uint4 &s_vv,
-                    const int &s_lo_, const int &s_hi_) __attribute__((always_inline)) {
-        const int buf = t & 1;
-        // A block of more than 64 positions has waves whose rows end before a chunk tile begins, and a short
-        // sequence leaves waves without rows: they only stage.  (At 64 positions it is one tile in a block.)
-        const bool act = S::Q <= 64 || (q_first < T && near + (t - t_near) * KT <= q_first + 31);  // wave-uniform
-        // LDS latency is the scarce thing here: the K fragments are requested at once,
-        // the address arithmetic and global loads of the next tile run while they arrive,
-        // and the V fragments are requested before the softmax that hides their latency.
-        pf_bf16x8_t ka[NS][KS];
-        if (act) {
-#pragma unroll
-            for (int n = 0; n < NS; n++)
-#pragma unroll
-                for (int ks = 0; ks < KS; ks++)
-                    ka[n][ks] = *reinterpret_cast<const pf_bf16x8_t *>(
-                        &s_k[buf][(32 * n + qn) * S::KStride + (ks * 16 + half * 8) * 2]);
+    auto put_bounds = [&](int t, float g) __attribute__((always_inline)) {
+        int lo = 0;
+        uint32_t n = 0;  // invisible unless shown otherwise
+        if (t < n_g) {
+            if (t * KT + lane < gl) n = kPfAll;
+        } else if (t < t_far) {
+            const int idx = (t - n_g) * KT + lane;
+            if (idx < w_eff) {
+                lo = t0 - w_eff + idx;
+                n = g >= a.tau ? kPfOn : (uint32_t)pv.W;
+            }
+        } else if (t < t_near) {
+            if ((t - t_far) * KT + lane < n_far) n = kPfAll;
+        } else {
+            const int idx = near + (t - t_near) * KT + lane;
+            if (idx < T) {
+                lo = t0 + idx;
+                n = g >= a.tau ? kPfOn : (uint32_t)pv.W;
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        const int far = far_next;
-        far_next = ask_far(t + 3);
-        if (t + 2 < n_tiles) fetch_any(t + 2, far, f_k, f_v, f_lo, f_hi);  // in flight while this tile and the next are multiplied
-        __builtin_amdgcn_sched_barrier(0);
-        if (act) {
+        s_lo[t & 1][lane] = lo;
+        s_n[t & 1][lane] = n;
+    };
+
+    asm volatile("" : "+v"(ptreg), "+v"(lpreg));  // waited for here, not behind the requests; so is the query
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(qv[ks]));
+
+    const PfMinus minus;
+    const int o_row = sa_sw_row<D>(qn, half), o_col = sa_sw_col<D>(lane);
+    pf_f32x16_t o[DB];
+    float m, l;
+    // Tile t is multiplied, tile t + 1 is requested.  kLean: tile t has no mask, tile t + 1 is a lean one.  kLook: a value of V is not
+    // finite.
+    auto body = [&](int t, int (&far_next)[kReq], bool &plain_next, auto lean_t, auto look_t) __attribute__((always_inline)) {
+        constexpr bool kLean = decltype(lean_t)::value, kLook = decltype(look_t)::value;
+        const int buf = t & 1;
+        const char *tk = s_t + buf * (2 * S::TileB) + ksp * NS * 32 * RowB, *tv = tk + S::TileB;
+        bool plain = true, mine = false;
+        float g_next = 0.f;
+        if (kLean) {
+            fetch_lean(t + 1);
+        } else {
+            plain = plain_next;
+            plain_next = !kLook && no_mask(t + 1);
+            mine = t + 1 < n_tiles && wave == (t + 1) % NW && !plain_next;
+            if (t + 1 < n_lean) fetch_lean(t + 1);
+            else if (t + 1 < n_tiles) fetch(t + 1, far_next);
+            ask_far(t + 2, far_next);  // behind the requests, which would wait for it
+            if (mine) g_next = ask_score(t + 1);
+        }
+        // A block of more than 32 positions has waves whose rows end before a chunk tile begins, and a short
+        // sequence leaves waves without rows: they only bring their share.
+        if (S::RB == 1 || (q_first < T && near + (t - t_near) * KT <= q_first + 31)) {  // wave-uniform
             // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
             pf_f32x16_t s[NS];
 #pragma unroll
-            for (int n = 0; n < NS; n++) {
+            for (int n = 0; n < NS; n++)
 #pragma unroll
                 for (int c = 0; c < 16; c++) s[n][c] = 0.f;
 #pragma unroll
-                for (int ks = 0; ks < KS; ks++)
-                    s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[n][ks], qv[ks], s[n], 0, 0, 0);
-            }
-            // V^T fragments read column-wise from the row-major V tile
-            // (there are no registers for all of them during the softmax: read at their products)
-            pf_bf16x8_t va[DB];
-            auto read_v = [&](int t2) __attribute__((always_inline)) {
+            for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-                for (int db = 0; db < DB; db++) va[db] = pf_get_cols<S::VStride>(s_v[buf], lane, db, 16 * t2);
-            };
-            __builtin_amdgcn_sched_barrier(0);
-            // register c = 4j+i of a lane holds key 8j + 4*half + i of a score tile
-            const bool plain = no_mask(t);
-            float sc[16 * NS];
-            float mt = -INFINITY;
-            if (plain) {
-#pragma unroll
-                for (int c = 0; c < 16 * NS; c++) {
-                    sc[c] = s[c / 16][c % 16] * a.scale_log2e;
-                    mt = fmaxf(mt, sc[c]);
-                }
-            } else {
+                for (int n = 0; n < NS; n++)
+                    s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + n * 32 * RowB, o_row, ks), qv[ks], s[n], 0, 0, 0);
+            // register c = 4j+i of a lane holds key 8j + 4*half + i of the wave's keys
+            if (!kLean && !plain) {
 #pragma unroll
                 for (int j = 0; j < 4 * NS; j++) {
-                    const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
-                    const int4 hi4 = *reinterpret_cast<const int4 *>(&s_hi[buf][8 * j + 4 * half]);
-                    const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi_[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
+                    const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][32 * NS * ksp + 8 * j + 4 * half]);
+                    const uint4 n4 = *reinterpret_cast<const uint4 *>(&s_n[buf][32 * NS * ksp + 8 * j + 4 * half]);
+                    const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
+                    const uint32_t n_[4] = {n4.x, n4.y, n4.z, n4.w};
 #pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const bool vis = (qpos >= lo_[i]) && (qpos <= hi_[i]);
-                        const float x = vis ? s[j / 4][4 * (j % 4) + i] * a.scale_log2e : -INFINITY;
-                        sc[4 * j + i] = x;
-                        mt = fmaxf(mt, x);
-                    }
+                    for (int i = 0; i < 4; i++)
+                        s[j / 4][4 * (j % 4) + i] = pf_sees(qpos, lo_[i], n_[i]) ? s[j / 4][4 * (j % 4) + i] : -INFINITY;
                 }
             }
-            mt = fmaxf(mt, __shfl_xor(mt, 32));  // the other half of the keys of this query
-            const float mnew = fmaxf(m, mt);
-            const float msafe = mnew == -INFINITY ? 0.f : mnew;
-            const float corr = __builtin_amdgcn_exp2f(m - msafe);
-            uint32_t pb[3][8 * NS];
-            float ps = 0.f;
+            float mt = -INFINITY;
 #pragma unroll
-            for (int c = 0; c < 8 * NS; c++) {
-                const float p0 = __builtin_amdgcn_exp2f(sc[2 * c] - msafe), p1 = __builtin_amdgcn_exp2f(sc[2 * c + 1] - msafe);
-                ps += p0 + p1;
-                const float r0 = pf_rest(p0), r1 = pf_rest(p1);
-                pb[0][c] = pf_top(p0, p1);
-                pb[1][c] = pf_top(r0, r1);
-                pb[2][c] = pf_top(pf_rest(r0), pf_rest(r1));
-            }
-            l = l * corr + ps;
+            for (int c = 0; c < 16 * NS; c++) mt = fmaxf(mt, s[c / 16][c % 16]);
+            mt = max_xor32(mt);  // the other half of the keys of this query
+            const float mnew = fmaxf(m, mt * c2);
+            const float msafe = mnew == -INFINITY ? 0.f : mnew;
             if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
+                const float corr = __builtin_amdgcn_exp2f(m - msafe);
+                l *= corr;
 #pragma unroll
                 for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -422,63 +449,154 @@ __global__ __launch_bounds__(512) void attend_prefill_kernel(View pv, CallSeqs c
             }
             m = mnew;
             // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys, small parts first ----
-            __builtin_amdgcn_sched_barrier(0);
+            uint32_t pb[2][3][4];
+            float ps = 0.f;  // the sum of a tile first: one after the other, 7 % more of the error against 64 bits
+            auto weights = [&](int t2) __attribute__((always_inline)) {  // of 16 keys, eight a lane
 #pragma unroll
-            for (int t2 = 0; t2 < 2 * NS; t2++) {
-                read_v(t2);
-                if (s_bad[buf] == t) {  // block-uniform
-                    // the finite values go on to the product; the queries that see the others get them here
+                for (int c = 0; c < 4; c++) {
+                    const int e = 8 * t2 + 2 * c;
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16], c2, -msafe));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16 + 1], c2, -msafe));
+                    ps += p0 + p1;
+                    pf_split(minus, p0, p1, pb[t2 & 1][0][c], pb[t2 & 1][1][c], pb[t2 & 1][2][c]);
+                }
+            };
+            auto part = [&](int t2, int i) __attribute__((always_inline)) {
+                const uint32_t *w = pb[t2 & 1][i];
+                return __builtin_bit_cast(pf_bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+            };
+            if (!kLook) {
+                weights(0);
+#pragma unroll
+                for (int t2 = 0; t2 < 2 * NS; t2++) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    pf_bf16x8_t va[DB];
+#pragma unroll
+                    for (int db = 0; db < DB; db++) va[db] = sa_sw_get_cols<D>(tv, o_col, db, t2);
+                    if (t2 + 1 < 2 * NS) weights(t2 + 1);
+#pragma unroll
+                    for (int i = 2; i >= 0; i--)
+#pragma unroll
+                        for (int db = 0; db < DB; db++) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], part(t2, i), o[db], 0, 0, 0);
+                    // a product, then some of the next weights' instructions beside it
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2 * DB, 0);
+                    if (t2 + 1 < 2 * NS)
+#pragma unroll
+                        for (int i = 0; i < 3 * DB; i++) {
+                            __builtin_amdgcn_sched_group_barrier(0x402, 20 / DB, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        }
+                }
+            } else {
+#pragma unroll
+                for (int t2 = 0; t2 < 2 * NS; t2++) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    weights(t2);
+                    // A weight of zero does not keep an inf or NaN of V out of a product, and the middle and low parts of a
+                    // weight are often zero, of a visible key too: the finite values go on to the product, the queries
+                    // that see the others get them here.
                     uint32_t seen[4];
 #pragma unroll
                     for (int c = 0; c < 4; c++) {  // pair c of the eight keys of this lane's half
-                        const int key = 16 * t2 + 8 * (c / 2) + 4 * half + 2 * (c % 2);
-                        seen[c] = (qpos >= s_lo[buf][key] && qpos <= s_hi[buf][key] ? 0x3f80u : 0u) |
-                                  (qpos >= s_lo[buf][key + 1] && qpos <= s_hi[buf][key + 1] ? 0x3f800000u : 0u);
+                        const int key = 32 * NS * ksp + 16 * t2 + 8 * (c / 2) + 4 * half + 2 * (c % 2);
+                        seen[c] = (pf_sees(qpos, s_lo[buf][key], s_n[buf][key]) ? 0x3f80u : 0u) |
+                                  (pf_sees(qpos, s_lo[buf][key + 1], s_n[buf][key + 1]) ? 0x3f800000u : 0u);
                     }
 #pragma unroll
-                    for (int db = 0; db < DB; db++) pf_take_nonfinite(va[db], seen, o[db]);
-                }
+                    for (int db = 0; db < DB; db++) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        pf_bf16x8_t va = sa_sw_get_cols<D>(tv, o_col, db, t2);
+                        pf_take_nonfinite(va, seen, o[db]);
 #pragma unroll
-                for (int part = 2; part >= 0; part--) {
-                    const uint4 p4 = make_uint4(pb[part][4 * t2], pb[part][4 * t2 + 1], pb[part][4 * t2 + 2], pb[part][4 * t2 + 3]);
-                    const pf_bf16x8_t pbv = __builtin_bit_cast(pf_bf16x8_t, p4);
-#pragma unroll
-                    for (int db = 0; db < DB; db++)
-                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], pbv, o[db], 0, 0, 0);
+                        for (int i = 2; i >= 0; i--) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, part(t2, i), o[db], 0, 0, 0);
+                    }
                 }
             }
+            l += ps;
         }
-        if (t + 1 < n_tiles) {
-            stage(buf ^ 1, s_kk, s_vv, s_lo_, s_hi_);
-            look(buf ^ 1, s_vv, t + 1);
-        }
-        __syncthreads();
+        if (mine) put_bounds(t + 1, g_next);
+        sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
+        if (!kLean)  // they are here too, as the compiler learns: it would wait for them behind the next requests
+#pragma unroll
+            for (int i = 0; i < kReq; i++) asm volatile("" : "+v"(far_next[i]));
     };
-    {
+    // all tiles, once
+    auto sweep = [&](auto look_t) __attribute__((always_inline)) {
+        constexpr bool kLook = decltype(look_t)::value;
+        m = -INFINITY;
+        l = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+#pragma unroll
+            for (int c = 0; c < 16; c++) o[db][c] = 0.f;
+        int far_next[kReq];
+        ask_far(0, far_next);
+        fetch(0, far_next);
+        if (wave == 0) put_bounds(0, ask_score(0));
         int t = 0;
-        for (; t + 1 < n_tiles; t += 2) {
-            body(t, k0r, v0r, lo0r, hi0r, k1r, v1r, lo1r, hi1r);
-            body(t + 1, k1r, v1r, lo1r, hi1r, k0r, v0r, lo0r, hi0r);
+        if (!kLook && n_lean > 1) {
+            sa_dma_wait_barrier<0>();
+            bool none = true;
+            for (; t + 1 < n_lean; t++) body(t, far_next, none, std::true_type(), std::false_type());
+            ask_far(t + 1, far_next);
+#pragma unroll
+            for (int i = 0; i < kReq; i++) asm volatile("" : "+v"(far_next[i]));
+        } else {
+            ask_far(1, far_next);
+            sa_dma_wait_barrier<0>();
+#pragma unroll
+            for (int i = 0; i < kReq; i++) asm volatile("" : "+v"(far_next[i]));
         }
-        if (t < n_tiles) body(t, k0r, v0r, lo0r, hi0r, k1r, v1r, lo1r, hi1r);
-    }
+        bool plain_next = !kLook && no_mask(t);
+        for (; t < n_tiles; t++) body(t, far_next, plain_next, std::false_type(), look_t);
+    };
+    sweep(std::false_type());
+    // A value of V that is not finite leaves none of the block's sums of its column finite: then everything once more, with a look
+    // at every value (a sum that overflows comes here too, and comes out the same).
+    bool finite = true;
+#pragma unroll
+    for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int c = 0; c < 16; c++) finite = finite && fabsf(o[db][c]) < INFINITY;
+    if (__syncthreads_or(!finite)) sweep(std::true_type());
 
-    // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
-    {
-        const int i = q_first + qn;
-        const float lt = l + __shfl_xor(l, 32);
-        if (i < T) {
-            const float inv = 1.0f / lt;
-            float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * D;
+    // ---- the waves that share queries add up ----
+    l = sum_xor32(l);
+    if constexpr (S::KSP > 1) {
+        constexpr int kGive = NW / 2;
+        float *red = reinterpret_cast<float *>(s_t) + (size_t)(wave % kGive) * ((DB * 16 + 2) * 64) + lane;
+        if (ksp > 0) {
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const float4 w4 = make_float4(o[db][4 * j] * inv, o[db][4 * j + 1] * inv,
-                                                  o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv);
-                    *reinterpret_cast<float4 *>(op + 32 * db + 8 * j + 4 * half) = w4;
-                }
+                for (int c = 0; c < 16; c++) red[(db * 16 + c) * 64] = o[db][c];
+            red[DB * 16 * 64] = m;
+            red[(DB * 16 + 1) * 64] = l;
         }
+        __syncthreads();
+        if (ksp > 0) return;
+        const float m2 = red[DB * 16 * 64], l2 = red[(DB * 16 + 1) * 64], M = fmaxf(m, m2);  // finite: a query sees itself
+        const float f = __builtin_amdgcn_exp2f(m - M), f2 = __builtin_amdgcn_exp2f(m2 - M);
+        l = l * f + l2 * f2;
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+#pragma unroll
+            for (int c = 0; c < 16; c++) o[db][c] = fmaf(red[(db * 16 + c) * 64], f2, o[db][c] * f);
+    }
+
+    // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
+    const int i = q_first + qn;
+    if (i < T) {
+        const float inv = 1.0f / l;
+        float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * D;
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const float4 w4 = make_float4(o[db][4 * j] * inv, o[db][4 * j + 1] * inv,
+                                              o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv);
+                *reinterpret_cast<float4 *>(op + 32 * db + 8 * j + 4 * half) = w4;
+            }
     }
 }
 
@@ -501,12 +619,12 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     constexpr int NW = 4, Q = kPfTilesQ, KT = 64, kRows = KT / NW, G = 4, D = kSaD;
     __shared__ __attribute__((aligned(1024))) char s_t[2][2][KT * D * 2];  // K and V
     __shared__ __attribute__((aligned(16))) int s_lo[2][KT];
-    __shared__ __attribute__((aligned(16))) int s_hi[2][KT];
+    __shared__ __attribute__((aligned(16))) uint32_t s_n[2][KT];
 
-    // order of the blocks: as in attend_prefill_kernel
-    const int rank = a.rank0 + (int)(blockIdx.x / a.nx), unit = a.ordered ? a.order[rank] : rank;
+    int unit, x;
+    pf_item(a, unit, x);
     const int b = unit / pv.Hkv, h = unit % pv.Hkv;
-    const int qt = a.nx - 1 - (int)(blockIdx.x % a.nx);
+    const int qt = a.nx - 1 - x;
     const int T = cs.ntok[b], t0 = cs.t0[b], base = cs.base[b];
     if (qt * Q >= T) return;  // block-uniform
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
@@ -546,6 +664,12 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
     const bool lp_in_reg = pv.nlp <= 64;
     int lpreg = (lp_in_reg && lane < pv.nlp) ? pv.local_pt[(size_t)um * pv.nlp + lane] : 0;
+    auto ring_page = [&](int slot) __attribute__((always_inline)) {
+        if (lp_in_reg) return __shfl(lpreg, slot >> pv.logP);
+        int pg = pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
+        asm volatile("" : "+v"(pg));  // waited for here: where the two ways meet, every request would be waited for
+        return pg;
+    };
     const int slot0 = t0 > pv.W ? t0 % pv.W : 0;  // ring slot of the oldest position
     auto ring_slot = [&](int idx) __attribute__((always_inline)) {
         const int s = slot0 + min(idx, w_eff - 1);
@@ -566,6 +690,7 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
         if (t < n_g && ((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
             pt_base = (t * KT) >> pv.logP;
             ptreg = (pt_base + ln < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + ln] : 0;
+            asm volatile("" : "+v"(ptreg));  // waited for here: behind the branch every tile would wait for all that is in flight
         }
         if (lean_ok && t < n_plain) {
             const int idx = t * KT + kRows * wave;
@@ -595,8 +720,7 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
                     kp = page_ptr(pv, pg) + (size_t)(idc & (pv.P - 1)) * (D * 2);
                 } else if (t < t_far) {  // ring, oldest position first
                     const int slot = ring_slot((t - n_g) * KT + r);
-                    const int pg = lp_in_reg ? __shfl(lpreg, slot >> pv.logP)
-                                             : pv.local_pt[(size_t)um * pv.nlp + (slot >> pv.logP)];
+                    const int pg = ring_page(slot);
                     kp = page_ptr(pv, pg) + (size_t)(slot & (pv.P - 1)) * (D * 2);
                 } else {  // this chunk
                     const int idc = t < t_near ? __shfl(far, 4 * i + sub) : min(near + (t - t_near) * KT + r, T - 1);
@@ -615,35 +739,37 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     auto no_mask = [&](int t) __attribute__((always_inline)) {
         return pf_no_mask(t, KT, n_g, n_plain, t_far, t_near, n_far, near, w_eff, pv.W, q_first, q_first + Q - 1);
     };
-    // Who sees key `lane` of a tile with a mask: positions lo to hi.  A wave of the block in turn asks for its score and,
+    // Who sees key `lane` of a tile with a mask: n positions from lo on.  A wave of the block in turn asks for its score and,
     // at the end of the turn, writes the two bounds.
     auto ask_score = [&](int t) __attribute__((always_inline)) {
         const int idx = t < t_far ? (t - n_g) * KT + lane : near + (t - t_near) * KT + lane;
-        if (t >= n_g && t < t_far) return pv.ring_g[(size_t)um * pv.W + ring_slot(idx)];
-        if (t >= t_near) return a.g[(size_t)(base + min(idx, T - 1)) * pv.Hkv + h];
-        return 0.f;
+        const float *gp = pv.ring_g;  // anything for a tile of the global cache or of picked keys
+        if (t >= n_g && t < t_far) gp += (size_t)um * pv.W + ring_slot(idx);
+        if (t >= t_near) gp = a.g + (size_t)(base + min(idx, T - 1)) * pv.Hkv + h;
+        return *gp;
     };
     auto put_bounds = [&](int t, float g) __attribute__((always_inline)) {
-        int lo = INT_MAX, hi = INT_MAX;  // invisible unless shown otherwise
+        int lo = 0;
+        uint32_t n = 0;  // invisible unless shown otherwise
         if (t < n_g) {
-            if (t * KT + lane < gl) lo = INT_MIN;
+            if (t * KT + lane < gl) n = kPfAll;
         } else if (t < t_far) {
             const int idx = (t - n_g) * KT + lane;
             if (idx < w_eff) {
                 lo = t0 - w_eff + idx;
-                hi = g >= a.tau ? INT_MAX : lo + pv.W - 1;
+                n = g >= a.tau ? kPfOn : (uint32_t)pv.W;
             }
         } else if (t < t_near) {
-            if ((t - t_far) * KT + lane < n_far) lo = INT_MIN;
+            if ((t - t_far) * KT + lane < n_far) n = kPfAll;
         } else {
             const int idx = near + (t - t_near) * KT + lane;
             if (idx < T) {
                 lo = t0 + idx;
-                hi = g >= a.tau ? INT_MAX : lo + pv.W - 1;
+                n = g >= a.tau ? kPfOn : (uint32_t)pv.W;
             }
         }
         s_lo[t & 1][lane] = lo;
-        s_hi[t & 1][lane] = hi;
+        s_n[t & 1][lane] = n;
     };
 
     asm volatile("" : "+v"(ptreg), "+v"(lpreg));  // waited for here, not behind the requests; so is the query
@@ -654,18 +780,18 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     fetch(0, ask_far(0));
     if (wave == 0) put_bounds(0, ask_score(0));
     sa_dma_wait_barrier<0>();
+    asm volatile("" : "+v"(far_next));
     bool plain_next = no_mask(0);
     for (int t = 0; t < n_tiles; t++) {
         const int buf = t & 1;
         const char *tk = s_t[buf][0], *tv = s_t[buf][1];
-        const int far = far_next;
-        far_next = ask_far(t + 2);
         const bool plain = plain_next;
         plain_next = no_mask(t + 1);
         const bool mine = t + 1 < n_tiles && wave == (t + 1) % NW && !plain_next;
         float g_next = 0.f;
+        if (t + 1 < n_tiles) fetch(t + 1, far_next);
+        far_next = ask_far(t + 2);  // behind the requests, which would wait for it
         if (mine) g_next = ask_score(t + 1);
-        if (t + 1 < n_tiles) fetch(t + 1, far);
         // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
         pf_f32x16_t s[2];
 #pragma unroll
@@ -688,18 +814,19 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
-                const int4 hi4 = *reinterpret_cast<const int4 *>(&s_hi[buf][8 * j + 4 * half]);
-                const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi_[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
+                const uint4 n4 = *reinterpret_cast<const uint4 *>(&s_n[buf][8 * j + 4 * half]);
+                const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
+                const uint32_t n_[4] = {n4.x, n4.y, n4.z, n4.w};
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const bool vis = (qpos >= lo_[i]) && (qpos <= hi_[i]);
+                    const bool vis = pf_sees(qpos, lo_[i], n_[i]);
                     const float x = vis ? s[j / 4][4 * (j % 4) + i] * a.scale_log2e : -INFINITY;
                     s[j / 4][4 * (j % 4) + i] = x;
                     mt = fmaxf(mt, x);
                 }
             }
         }
-        mt = fmaxf(mt, __shfl_xor(mt, 32));  // the other half of the keys of this query
+        mt = max_xor32(mt);  // the other half of the keys of this query
         const float mnew = fmaxf(m, mt);
         const float msafe = mnew == -INFINITY ? 0.f : mnew;
         const float corr = __builtin_amdgcn_exp2f(m - msafe);
@@ -730,6 +857,7 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
         }
         if (mine) put_bounds(t + 1, g_next);
         sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
+        asm volatile("" : "+v"(far_next));  // here too, as the compiler learns: it would wait for it behind the next requests
     }
 
     // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
@@ -801,14 +929,24 @@ size_t attend_prefill_ws_bytes(const View &pv, int n_seqs, int64_t total_q) {
     return kPfOrderBytes + sizeof(int32_t) * (size_t)pv.Hkv * (size_t)(total_q + total_q / 32 + n_seqs);
 }
 
-// Blocks of q positions for every unit of the call.  A launch holds fewer than 2^32 threads: where one long chunk beside many
+// hg blocks of every q positions for every unit of the call.  A launch holds fewer than 2^32 threads: where one long chunk beside many
 // short ones would be over that (every unit has the blocks of the longest), the units go to several launches.
 template <class Kernel>
-static hipError_t launch_units(Kernel kernel, int q, int threads, const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t,
-                               hipStream_t st) {
-    a.nx = (max_t + q - 1) / q;
+static hipError_t launch_units(Kernel kernel, int q, int hg, int threads, const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t,
+                               int n_cu, hipStream_t st) {
+    a.nx = (max_t + q - 1) / q * hg;
     const int n_units = cs.n * pv.Hkv;
+    int max_end = 0;
+    for (int b = 0; b < cs.n; b++) max_end = std::max(max_end, cs.t0[b] + cs.ntok[b]);
+    // Row by row the launch ends on short blocks, unit by unit the blocks that run at once share the keys in an L2.  The line is where a head's
+    // keys and values may come to more than half of it; whole calls, us unit by unit / row by row: eight prompts of 131-1501
+    // tokens 328 / 318, 4000 tokens of 64 / 8 heads of 128 307 / 281, 5000 of 32 / 8 heads of 64 140 / 132; 6000 tokens of 128-wide heads in
+    // chunks of 2048 347 / 354, 12000 in chunks of 4096 603 / 657.
+    a.by_row = (int64_t)max_end * pv.row_bytes * 2 <= 9 << 18;
+    a.n_units = n_units;
+    a.n_cu = a.ordered ? 0 : n_cu;
     const int per = (int)std::min<int64_t>(n_units, (((int64_t)1 << 32) - 1) / ((int64_t)a.nx * threads));
+    if (per < 1) return hipErrorInvalidValue;
     for (a.rank0 = 0; a.rank0 < n_units; a.rank0 += per) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)a.nx * std::min(per, n_units - a.rank0)), dim3(threads), 0, st, pv, cs, a);
         const hipError_t e = hipGetLastError();
@@ -817,8 +955,9 @@ static hipError_t launch_units(Kernel kernel, int q, int threads, const View &pv
     return hipSuccess;
 }
 template <int D, int G>
-static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t, hipStream_t st) {
-    return launch_units(attend_prefill_kernel<D, G>, PfShape<D, G>::Q, 512, pv, cs, a, max_t, st);
+static hipError_t launch_shape(const View &pv, const CallSeqs &cs, PrefillAttnArgs &a, int max_t, int n_cu, hipStream_t st) {
+    using S = PfShape<D, G>;
+    return launch_units(attend_prefill_parts_kernel<D, G>, S::Q, S::HG, S::NW * 64, pv, cs, a, max_t, n_cu, st);
 }
 
 // Lists of picked chunk keys pay as soon as some block of the call has keys behind all its windows, and need room; without them
@@ -862,27 +1001,26 @@ hipError_t launch_attend_prefill(const View &pv, const CallSeqs &cs, int layer, 
     for (int b = 0; b < cs.n; b++) max_t = max(max_t, cs.ntok[b]);
     if (max_t == 0) return hipSuccess;
     if (max_t >= 1 << 28) return hipErrorInvalidValue;  // the blocks of one unit have to fit a launch
-    // The order is for launches of more than one round of blocks (a block per compute unit, two of the tiles kernel): below, its
+    // The order is for launches of more than one round of blocks (two to a compute unit): below, its
     // own launch is all it adds.  us with / without: 33 tokens of 16 / 8 heads of 128 12.5 / 9.8, 16 x 100 of 32 / 8 24.2 / 19.4.
-    const bool tiles = pv.d == 128 && pv.G == 4;
-    const int per_block = tiles ? kPfTilesQ : 256 / pv.G;
-    a.ordered = (int64_t)((max_t + per_block - 1) / per_block) * pv.Hkv * cs.n > (int64_t)n_cu * (tiles ? 2 : 1);
+    const int per_block = pv.G > 1 ? 32 : 64, per_group = pv.G == 8 ? 2 : 1;
+    a.ordered = (int64_t)((max_t + per_block - 1) / per_block) * per_group * pv.Hkv * cs.n > (int64_t)n_cu * 2;
     hipError_t e = launch_prefill_look(pv, cs, layer, tau, g, ws, ws_bytes, a.ordered, &a.order, &a.pick, &a.picked, st);
     if (e != hipSuccess) return e;
     if (pv.d == 128) {
         switch (pv.G) {
-            case 1: return launch_shape<128, 1>(pv, cs, a, max_t, st);
-            case 2: return launch_shape<128, 2>(pv, cs, a, max_t, st);
-            case 4: return launch_units(attend_prefill_tiles_kernel, kPfTilesQ, 256, pv, cs, a, max_t, st);
-            case 8: return launch_shape<128, 8>(pv, cs, a, max_t, st);
+            case 1: return launch_shape<128, 1>(pv, cs, a, max_t, n_cu, st);
+            case 2: return launch_shape<128, 2>(pv, cs, a, max_t, n_cu, st);
+            case 4: return launch_units(attend_prefill_tiles_kernel, kPfTilesQ, 1, 256, pv, cs, a, max_t, n_cu, st);
+            case 8: return launch_shape<128, 8>(pv, cs, a, max_t, n_cu, st);
             default: break;
         }
     } else if (pv.d == 64) {
         switch (pv.G) {
-            case 1: return launch_shape<64, 1>(pv, cs, a, max_t, st);
-            case 2: return launch_shape<64, 2>(pv, cs, a, max_t, st);
-            case 4: return launch_shape<64, 4>(pv, cs, a, max_t, st);
-            case 8: return launch_shape<64, 8>(pv, cs, a, max_t, st);
+            case 1: return launch_shape<64, 1>(pv, cs, a, max_t, n_cu, st);
+            case 2: return launch_shape<64, 2>(pv, cs, a, max_t, n_cu, st);
+            case 4: return launch_shape<64, 4>(pv, cs, a, max_t, n_cu, st);
+            case 8: return launch_shape<64, 8>(pv, cs, a, max_t, n_cu, st);
             default: break;
         }
     }

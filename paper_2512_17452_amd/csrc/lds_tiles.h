@@ -15,13 +15,19 @@ constexpr int kSaTileB = kSaT * kSaD * 2;
 
 typedef short sa_s16x4_t __attribute__((ext_vector_type(4)));
 
-// ---- tiles of 32 rows of 256 bytes that come straight from memory into LDS (no registers, no staging stores) ----
+// ---- tiles of 32 rows of 256 (128) bytes that come straight from memory into LDS (no registers, no staging stores) ----
 // The rows lie unpadded; 16-byte chunk c of row r sits at chunk c ^ f(r), which the request's lane picks on the memory
-// side.  f takes the row's low two bits to the chunk's high ones and the next two to its low ones: sixteen consecutive
-// rows put one column on sixteen different chunks (reads of whole rows), and four consecutive rows put a 64-byte piece
-// on four different quarters of the banks (reads of columns), so both kinds of read are free of bank conflicts.
-__device__ __forceinline__ int sa_sw_f(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-__device__ __forceinline__ int sa_sw_row(int qn, int half) { return qn * (kSaD * 2) + (half ^ sa_sw_f(qn)) * 16; }
+// side.  For rows of 256 bytes f takes the row's low two bits to the chunk's high ones and the next two to its low ones: sixteen
+// consecutive rows put one column on sixteen different chunks (reads of whole rows), and four consecutive rows put a 64-byte piece
+// on four different quarters of the banks (reads of columns), so both kinds of read are free of bank conflicts.  Rows of 128 bytes lie
+// in pairs, whose lowest bit the row's place has already: the same with the bit above it alone.
+template <int D = kSaD>
+__device__ __forceinline__ int sa_sw_f(int row) {
+    static_assert(D == 128 || D == 64, "");
+    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : ((row & 2) << 1) | ((row >> 2) & 3);
+}
+template <int D = kSaD>
+__device__ __forceinline__ int sa_sw_row(int qn, int half) { return qn * (D * 2) + (half ^ sa_sw_f<D>(qn)) * 16; }
 // row operand of a product over d: row qn of a tile, d slice ks
 __device__ __forceinline__ sa_bf16x8_t sa_sw_get_row(const char *tile, int o_row, int ks) {
     return *reinterpret_cast<const sa_bf16x8_t *>(tile + (o_row ^ (ks * 32)));
@@ -32,16 +38,18 @@ __device__ __forceinline__ sa_bf16x8_t sa_sw_get_row(const char *tile, int o_row
 // ds_read_b64_tr_b16 transposes inside groups of 16 lanes: lane i of a group receives element i%4 of the 8 bytes
 // addressed by lanes i/4, 4 + i/4, 8 + i/4 and 12 + i/4.  So lane s of a group addresses (row s/4 of the four, columns
 // 4*(s%4)..+3 of the group's 16) and ends up with the four rows at its own column.
+template <int D = kSaD>
 __device__ __forceinline__ int sa_sw_col(int lane) {
     const int half = lane >> 5, a = (lane & 15) >> 2;
     const int c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    return (4 * half + a) * (kSaD * 2) + ((c ^ half) | (a << 2)) * 16 + 8 * (lane & 1);
+    return (4 * half + a) * (D * 2) + (c ^ sa_sw_f<D>(4 * half + a)) * 16 + 8 * (lane & 1);
 }
+template <int D = kSaD>
 __device__ __forceinline__ sa_bf16x8_t sa_sw_get_cols(const char *tile, int o_col, int db, int t2) {
     typedef __attribute__((address_space(3))) sa_s16x4_t *lds_ptr_t;
-    const char *p = tile + t2 * 16 * (kSaD * 2);
+    const char *p = tile + t2 * 16 * (D * 2);
     const sa_s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + (o_col ^ (db * 64))));
-    const sa_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * (kSaD * 2) + (o_col ^ (db * 64) ^ 32)));
+    const sa_s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * (D * 2) + (o_col ^ (db * 64) ^ 32)));
     const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
     return __builtin_bit_cast(sa_bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
 }

@@ -1,0 +1,69 @@
+"""Chunk attention of the shapes whose weights keep 24 bits: scales that are negative or
+zero, values of V at the ends of the range, and launches in which every block runs at once (two to a compute unit) or the
+positions of all units come one after the other."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_17452_amd as wg
+from oracle import attend_definition
+from test_gpu_prefill_shapes import _tol
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(64, 1), (64, 4), (64, 8), (128, 1), (128, 2), (128, 8)]
+IDS = [f"d{d}-G{G}" for d, G in SHAPES]
+
+
+def _inputs(d, G, Hk, T, seed):
+    gen = torch.Generator().manual_seed(seed)
+    q, k, v = (torch.randn((T, h, d), generator=gen).bfloat16() for h in (G * Hk, Hk, Hk))
+    return q, k, v, torch.rand((T, Hk), generator=gen)
+
+
+def _attend(d, G, Hk, lens, q, k, v, g, W, tau, scale):
+    pool = wg.Pool(wg.Config(1, G * Hk, Hk, d, wg.BF16, 16, W, len(lens), max(lens) // 16 + 2, 64), len(lens), sum(lens))
+    out = torch.full((sum(lens), G * Hk, d), float("nan"), device="cuda:0")
+    pool.attend(0, list(range(len(lens))), q, out, scale, n_q=lens, k_chunk=k, v_chunk=v, g_chunk=g, tau=tau)
+    return out
+
+
+@pytest.mark.parametrize("d,G", SHAPES, ids=IDS)
+@pytest.mark.parametrize("scale", [-0.1, 0.0])
+def test_scales_that_are_not_positive(d, G, scale):
+    T, W, tau = 140, 40, 0.6
+    q, k, v, g = _inputs(d, G, 2, T, d + G)
+    out = _attend(d, G, 2, [T], *(x.to("cuda:0") for x in (q, k, v, g)), W, tau, scale).cpu().numpy()
+    ref = attend_definition(k.float().numpy(), v.float().numpy(), g.numpy(), q.float().numpy(), np.arange(T), W, tau, scale)
+    assert np.abs(out - ref).max() <= _tol(wg.BF16, d, G)
+
+
+@pytest.mark.parametrize("d,G", SHAPES, ids=IDS)
+@pytest.mark.parametrize("size", [2.0 ** 126, 2.0 ** -100])
+def test_values_at_the_ends_of_the_range(d, G, size):
+    """2^126 times a normal value is finite in bf16 below 4, and so is every weighted mean; the sums in front of the division are not
+    where many keys weigh alike, so the queries see a few keys each."""
+    T, W, tau = 96, 2, 2.0
+    q, k, v, g = _inputs(d, G, 2, T, d + G)
+    v = v.clamp(-1.5, 1.5)
+    out = _attend(d, G, 2, [T], *(x.to("cuda:0") for x in (q, k, (v.float() * size).bfloat16(), g)), W, tau, 1 / math.sqrt(d)).cpu().numpy()
+    ref = attend_definition(k.float().numpy(), v.float().numpy(), g.numpy(), q.float().numpy(), np.arange(T), W, tau, 1 / math.sqrt(d))
+    assert np.abs(out.astype(np.float64) / size - ref).max() <= _tol(wg.BF16, d, G)
+
+
+@pytest.mark.parametrize("d,G,lens", [(64, 4, [480, 3, 450]), (128, 4, [2048]), (128, 2, [1500, 700]), (64, 8, [900]), (64, 4, [1000, 3, 997, 640]), (128, 1, [2100, 64])])
+def test_every_block_has_its_place(d, G, lens):
+    """Between one and two blocks for every compute unit (more than two in one case): each (unit, position range) exactly once."""
+    W, tau, Hk = 100, 0.7, 8
+    q, k, v, g = _inputs(d, G, Hk, sum(lens), d + G)
+    out = _attend(d, G, Hk, lens, *(x.to("cuda:0") for x in (q, k, v, g)), W, tau, 1 / math.sqrt(d)).cpu().numpy()
+    assert np.isfinite(out).all()
+    base = 0
+    for n in lens:
+        rows = np.arange(n - 1, -1, -31)
+        kk, vv, gg, qq = (x[base:base + n].float().numpy() for x in (k, v, g, q))
+        ref = attend_definition(kk, vv, gg, qq[rows], rows, W, tau, 1 / math.sqrt(d))
+        assert np.abs(out[base:base + n][rows] - ref).max() <= _tol(wg.BF16, d, G)
+        base += n
