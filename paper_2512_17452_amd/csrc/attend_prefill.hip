@@ -608,8 +608,10 @@ void attend_prefill_parts_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
 // copy each).  Against blocks of 64 positions with tiles of 32 keys staged through registers, which this shape had:
 // two 16K prompts in 4096-token chunks 797 -> 708 us per launch, eight of 131-1501 tokens 81 -> 71, four 128K prompts,
 // all 32 chunks, 350 -> 312 ms (808 -> 906 TFLOP/s).  Two row blocks of 32 that share a tile: 732 us, 81 us, 316 ms.
-// Bound by the matrix cores and the softmax beside them: the last chunks run at 950 TFLOP/s, where a library product of
-// 8192 cubed reaches 1260 on the same card.
+// Bound by power and by the instructions beside the products, as attend_prefill_parts_kernel is and with the same remedies (a loop for
+// tiles without a mask, no scaling of scores, weights beside products, requests that wait for nothing, addresses of 32 bits in the chunk).  Whole
+// calls, us before / now: two prompts of 14-16K tokens with the linear gate 2870 / 2640, one of 16384 tokens 804 / 735, of 3000 140 / 125, eight
+// of 131-1501 tokens and eight decode steps 340 / 313.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPfTilesQ = 32;
 // What stands in V past the last row of a region: a weight of zero does not keep an infinity out of a product, so these
@@ -642,6 +644,9 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     const int t_far = n_g + n_r, t_near = t_far + (n_far + KT - 1) / KT;  // first tile of each kind
     const int n_tiles = t_near + (i_end - near + KT - 1) / KT;
 
+    // the maximum is taken of the products themselves: as in attend_prefill_parts_kernel
+    const float c2 = fmaxf(fabsf(a.scale_log2e), 1e-45f);
+    const uint32_t sign = a.scale_log2e < 0.f ? 0x80008000u : 0u;
     sa_bf16x8_t qv[8];
     const int q_first = qt * Q;
     const int qi = min(q_first + qn, T - 1);
@@ -649,7 +654,11 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     {
         const char *qp = a.q + ((size_t)(base + qi) * pv.Hq + (size_t)h * G + head) * D * 2;
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) qv[ks] = *reinterpret_cast<const sa_bf16x8_t *>(qp + (ks * 16 + half * 8) * 2);
+        for (int ks = 0; ks < 8; ks++) {
+            uint4 w = *reinterpret_cast<const uint4 *>(qp + (ks * 16 + half * 8) * 2);
+            w.x ^= sign; w.y ^= sign; w.z ^= sign; w.w ^= sign;
+            qv[ks] = __builtin_bit_cast(sa_bf16x8_t, w);
+        }
     }
     pf_f32x16_t o[4];
     float m = -INFINITY, l = 0.f;
@@ -680,33 +689,53 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     auto ask_far = [&](int t) __attribute__((always_inline)) {
         return pick[max(0, min((t - t_far) * KT + wave * kRows + (lane & (kRows - 1)), n_far - 1))];
     };
-    const bool lean_ok = pv.P >= kRows;  // the wave's rows of a full tile of the global cache share a page
-    const int n_plain = gl / KT;         // full tiles of the global cache
+    const int n_plain = gl / KT;                     // full tiles of the global cache
+    const int n_lean = pv.P >= kRows ? n_plain : 0;  // those whose pages hold all rows that a wave brings
+    auto see_pages = [&](int t) __attribute__((always_inline)) {  // page ids of tile t's global rows into ptreg
+        if (((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
+            pt_base = (t * KT) >> pv.logP;
+            ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
+            asm volatile("" : "+v"(ptreg));  // waited for here: behind the branch every tile would wait for all that is in flight
+        }
+    };
+    uint32_t off[kRows / 4];  // this lane's pieces of the wave's rows
+#pragma unroll
+    for (int i = 0; i < kRows / 4; i++)
+        off[i] = (uint32_t)((4 * i + (lane >> 4)) * (D * 2) + ((lane & 15) ^ sa_sw_f(wave * kRows + 4 * i + (lane >> 4))) * 16);
+    auto fetch_lean = [&](int t) __attribute__((always_inline)) {
+        char *lk = &s_t[t & 1][0][wave * kRows * (D * 2)], *lv = &s_t[t & 1][1][wave * kRows * (D * 2)];
+        see_pages(t);
+        const int idx = t * KT + kRows * wave;
+        const int pg = __builtin_amdgcn_readlane(ptreg, (idx >> pv.logP) - pt_base);
+        const char *sb = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (D * 2);
+#pragma unroll
+        for (int i = 0; i < kRows / 4; i++) {
+            sa_dma16(sb, off[i], lk + i * 1024);
+            sa_dma16(sb + pv.v_off, off[i], lv + i * 1024);
+        }
+    };
+    const uint32_t c_stride = (uint32_t)(pv.Hkv * (D * 2));  // bytes from a chunk position to the next
+    const size_t c_base = ((size_t)base * pv.Hkv + h) * (D * 2);
+    const bool c_near = (uint64_t)T * c_stride < (1ull << 31);  // requests for its rows take an offset of 32 bits
     auto fetch = [&](int t, int far) __attribute__((always_inline)) {
         char *lk = &s_t[t & 1][0][wave * kRows * (D * 2)], *lv = &s_t[t & 1][1][wave * kRows * (D * 2)];
         int ln = lane;
         asm volatile("" : "+v"(ln));  // the lane's offsets are formed per tile: no registers to keep them
         const int sub = ln >> 4;
-        if (t < n_g && ((t * KT + KT - 1) >> pv.logP) >= pt_base + 64) {
-            pt_base = (t * KT) >> pv.logP;
-            ptreg = (pt_base + ln < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + ln] : 0;
-            asm volatile("" : "+v"(ptreg));  // waited for here: behind the branch every tile would wait for all that is in flight
-        }
-        if (lean_ok && t < n_plain) {
-            const int idx = t * KT + kRows * wave;
-            const int pg = __builtin_amdgcn_readlane(ptreg, (idx >> pv.logP) - pt_base);
-            const char *sb = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (D * 2);
-#pragma unroll
-            for (int i = 0; i < kRows / 4; i++) {
-                const uint32_t off = (uint32_t)((4 * i + sub) * (D * 2) + ((ln & 15) ^ sa_sw_f(wave * kRows + 4 * i + sub)) * 16);
-                sa_dma16(sb, off, lk + i * 1024);
-                sa_dma16(sb + pv.v_off, off, lv + i * 1024);
-            }
-            return;
-        }
+        if (t < n_g) see_pages(t);
         // rows of the region from this tile on: the tile's others are past its end
         const int rows = t < n_g ? gl - t * KT : t < t_far ? w_eff - (t - n_g) * KT : t < t_near ? n_far - (t - t_far) * KT
                                                                                               : T - near - (t - t_near) * KT;
+        if (t >= t_far && rows >= KT && c_near) {  // this chunk, all rows of the tile
+#pragma unroll
+            for (int i = 0; i < kRows / 4; i++) {
+                const int idc = t < t_near ? __shfl(far, 4 * i + sub) : near + (t - t_near) * KT + wave * kRows + 4 * i + sub;
+                const uint32_t o = (uint32_t)idc * c_stride + (off[i] & (D * 2 - 1));
+                sa_dma16(a.k + c_base, o, lk + i * 1024);
+                sa_dma16(a.v + c_base, o, lv + i * 1024);
+            }
+            return;
+        }
         auto pieces = [&](auto last_t) __attribute__((always_inline)) {
             constexpr bool kLast = decltype(last_t)::value;
 #pragma unroll
@@ -781,36 +810,38 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
     if (wave == 0) put_bounds(0, ask_score(0));
     sa_dma_wait_barrier<0>();
     asm volatile("" : "+v"(far_next));
+    // Tile t is multiplied, tile t + 1 is requested.  kLean: tile t has no mask, tile t + 1 is a lean one.
     bool plain_next = no_mask(0);
-    for (int t = 0; t < n_tiles; t++) {
+    auto body = [&](int t, auto lean_t) __attribute__((always_inline)) {
+        constexpr bool kLean = decltype(lean_t)::value;
         const int buf = t & 1;
         const char *tk = s_t[buf][0], *tv = s_t[buf][1];
-        const bool plain = plain_next;
-        plain_next = no_mask(t + 1);
-        const bool mine = t + 1 < n_tiles && wave == (t + 1) % NW && !plain_next;
+        bool plain = true, mine = false;
         float g_next = 0.f;
-        if (t + 1 < n_tiles) fetch(t + 1, far_next);
-        far_next = ask_far(t + 2);  // behind the requests, which would wait for it
-        if (mine) g_next = ask_score(t + 1);
+        if (kLean) {
+            fetch_lean(t + 1);
+        } else {
+            plain = plain_next;
+            plain_next = no_mask(t + 1);
+            mine = t + 1 < n_tiles && wave == (t + 1) % NW && !plain_next;
+            if (t + 1 < n_lean) fetch_lean(t + 1);
+            else if (t + 1 < n_tiles) fetch(t + 1, far_next);
+            far_next = ask_far(t + 2);  // behind the requests, which would wait for it
+            if (mine) g_next = ask_score(t + 1);
+        }
         // ---- S^T = K Q^T : rows = keys of the tile, columns = this wave's queries ----
         pf_f32x16_t s[2];
 #pragma unroll
-        for (int n = 0; n < 2; n++) {
+        for (int n = 0; n < 2; n++)
 #pragma unroll
             for (int c = 0; c < 16; c++) s[n][c] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++)
-                s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + n * kSaTileB, o_row, ks), qv[ks], s[n], 0, 0, 0);
-        }
-        // register c = 4j+i of s[n] holds key 32*n + 8j + 4*half + i
-        float mt = -INFINITY;
-        if (plain) {
+        for (int ks = 0; ks < 8; ks++)
 #pragma unroll
-            for (int c = 0; c < 32; c++) {
-                s[c / 16][c % 16] *= a.scale_log2e;
-                mt = fmaxf(mt, s[c / 16][c % 16]);
-            }
-        } else {
+            for (int n = 0; n < 2; n++)
+                s[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + n * kSaTileB, o_row, ks), qv[ks], s[n], 0, 0, 0);
+        // register c = 4j+i of s[n] holds key 32*n + 8j + 4*half + i
+        if (!kLean && !plain) {
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 const int4 lo4 = *reinterpret_cast<const int4 *>(&s_lo[buf][8 * j + 4 * half]);
@@ -818,51 +849,77 @@ __global__ __launch_bounds__(256, 2) void attend_prefill_tiles_kernel(View pv, C
                 const int lo_[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
                 const uint32_t n_[4] = {n4.x, n4.y, n4.z, n4.w};
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const bool vis = pf_sees(qpos, lo_[i], n_[i]);
-                    const float x = vis ? s[j / 4][4 * (j % 4) + i] * a.scale_log2e : -INFINITY;
-                    s[j / 4][4 * (j % 4) + i] = x;
-                    mt = fmaxf(mt, x);
-                }
+                for (int i = 0; i < 4; i++)
+                    s[j / 4][4 * (j % 4) + i] = pf_sees(qpos, lo_[i], n_[i]) ? s[j / 4][4 * (j % 4) + i] : -INFINITY;
             }
         }
-        mt = max_xor32(mt);  // the other half of the keys of this query
-        const float mnew = fmaxf(m, mt);
-        const float msafe = mnew == -INFINITY ? 0.f : mnew;
-        const float corr = __builtin_amdgcn_exp2f(m - msafe);
-        uint32_t pb[16];
-        float ps = 0.f;
-        const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+        float mt = -INFINITY;
 #pragma unroll
-        for (int c = 0; c < 16; c++) {
-            pb[c] = pf_pack(__builtin_amdgcn_exp2f(s[c / 8][2 * c % 16] - msafe), __builtin_amdgcn_exp2f(s[c / 8][2 * c % 16 + 1] - msafe));
-            // the denominator sums the rounded weights, the ones the second product uses
-            ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[c]), ones, ps, false);
-        }
-        l = l * corr + ps;
+        for (int c = 0; c < 32; c++) mt = fmaxf(mt, s[c / 16][c % 16]);
+        mt = max_xor32(mt);  // the other half of the keys of this query
+        const float mnew = fmaxf(m, mt * c2);
+        const float msafe = mnew == -INFINITY ? 0.f : mnew;
         if (__builtin_amdgcn_ballot_w64(mnew > m) != 0) {
+            const float corr = __builtin_amdgcn_exp2f(m - msafe);
+            l *= corr;
 #pragma unroll
             for (int db = 0; db < 4; db++)
 #pragma unroll
                 for (int c = 0; c < 16; c++) o[db][c] *= corr;
         }
         m = mnew;
-        // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys ----
+        // ---- O^T += V^T P^T : rows = d, columns = queries, contraction over the keys, the weights of the next 16 keys beside the
+        // products of 16 ----
+        const pf_bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+        uint32_t pb[2][4];
+        float ps = 0.f;
+        auto weights = [&](int t2) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const int e = 8 * t2 + 2 * c;
+                pb[t2 & 1][c] = pf_pack(__builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16], c2, -msafe)),
+                                        __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16 + 1], c2, -msafe)));
+                // the denominator sums the rounded weights, the ones the second product uses
+                ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pf_bf16x2_t, pb[t2 & 1][c]), ones, ps, false);
+            }
+        };
+        weights(0);
 #pragma unroll
         for (int t2 = 0; t2 < 4; t2++) {
-            const uint4 p4 = make_uint4(pb[4 * t2], pb[4 * t2 + 1], pb[4 * t2 + 2], pb[4 * t2 + 3]);
+            __builtin_amdgcn_sched_barrier(0);
+            sa_bf16x8_t va[4];
+#pragma unroll
+            for (int db = 0; db < 4; db++) va[db] = sa_sw_get_cols(tv, o_col, db, t2);
+            if (t2 + 1 < 4) weights(t2 + 1);
+            const uint32_t *w = pb[t2 & 1];
 #pragma unroll
             for (int db = 0; db < 4; db++)
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_cols(tv, o_col, db, t2), __builtin_bit_cast(sa_bf16x8_t, p4), o[db], 0, 0, 0);
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], __builtin_bit_cast(sa_bf16x8_t, make_uint4(w[0], w[1], w[2], w[3])), o[db], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+            if (t2 + 1 < 4)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                }
         }
+        l += ps;
         if (mine) put_bounds(t + 1, g_next);
         sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
-        asm volatile("" : "+v"(far_next));  // here too, as the compiler learns: it would wait for it behind the next requests
+        if (!kLean) asm volatile("" : "+v"(far_next));  // here too, as the compiler learns: it would wait for it behind the next requests
+    };
+    int t = 0;
+    if (n_lean > 1) {
+        for (; t + 1 < n_lean; t++) body(t, std::true_type());
+        plain_next = no_mask(t);
+        far_next = ask_far(t + 1);
+        asm volatile("" : "+v"(far_next));
     }
+    for (; t < n_tiles; t++) body(t, std::false_type());
 
     // ---- normalise and write: register c = 4j+i of o[db] is d = 32*db + 8j + 4*half + i ----
     const int i = q_first + qn;
-    const float lt = l + __shfl_xor(l, 32);
+    const float lt = sum_xor32(l);
     if (i < T) {
         const float inv = 1.0f / lt;
         float *op = a.out + ((size_t)(base + i) * pv.Hq + (size_t)h * G + head) * D;
