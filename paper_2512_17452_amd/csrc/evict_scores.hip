@@ -215,7 +215,7 @@ __device__ __forceinline__ size_t em_q_off(const View &pv, const EvictScoreArgs 
 // maximum and denominator are per-lane scalars.  Four waves of a block hold 128 query rows, four more hold the
 // same ones and take the other 64 keys of a tile of 128: four waves to a SIMD with two blocks on a compute unit.
 // 64 heads of 4.5K entries, 1024 rows: 132 -> 105 us against 256 rows a block, tiles of 32 keys through registers
-// and a scaled score per product; 8 heads of 2.2K 57 -> 28.
+// and a scaled score per product; 8 heads of 2.2K 57 -> 28.  Where a page holds a wave's rows one page id and one address do for them: 106 -> 97.
 constexpr int kEmStatRows = 128, kEmStatKeys = 128;
 __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
     __shared__ __attribute__((aligned(1024))) char s_k[2][kEmStatKeys * kEmD * 2];
@@ -243,6 +243,7 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
     }
     int pt_base = 0;  // 64 page ids from here on, one per lane
     int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
+    const uint32_t off0 = (uint32_t)((lane >> 4) * (kEmD * 2) + ((lane & 15) ^ sa_sw_f(lane >> 4)) * 16);  // this lane's piece of the first four rows
     auto fetch = [&](int t) __attribute__((always_inline)) {
         // a wave brings 16 rows, four per request; rows past the last key of the cache repeat it or are left as they are
         const int r0 = t * kEmStatKeys + wave * 16;
@@ -250,6 +251,14 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
         if (((r0 + 15) >> pv.logP) >= pt_base + 64) {
             pt_base = r0 >> pv.logP;
             ptreg = (pt_base + lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + pt_base + lane] : 0;
+            asm volatile("" : "+v"(ptreg));  // waited for here, not behind the branch
+        }
+        if (pv.P >= 16 && r0 + 16 <= N) {  // a page holds the wave's rows: one id and one address for all of them
+            const int pg = __builtin_amdgcn_readlane(ptreg, (r0 >> pv.logP) - pt_base);
+            const char *sb = page_ptr(pv, pg) + (size_t)(r0 & (pv.P - 1)) * (kEmD * 2);
+#pragma unroll
+            for (int i = 0; i < 4; i++) sa_dma16(sb, (off0 ^ (i * 16)) + i * 1024, &s_k[t & 1][(wave * 16 + 4 * i) * (kEmD * 2)]);
+            return;
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -273,13 +282,12 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
         if (k0 < N) {  // wave-uniform
             es_f32x16_t s[2];
 #pragma unroll
-            for (int j = 0; j < 2; j++) {
+            for (int i = 0; i < 16; i++) { s[0][i] = 0.f; s[1][i] = 0.f; }
 #pragma unroll
-                for (int i = 0; i < 16; i++) s[j][i] = 0.f;
+            for (int ks = 0; ks < 8; ks++)
 #pragma unroll
-                for (int ks = 0; ks < 8; ks++)
+                for (int j = 0; j < 2; j++)
                     s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + j * kSaTileB, o_row, ks), qv[ks], s[j], 0, 0, 0);
-            }
             // register i of s[j] holds key 32*j + 8*(i/4) + 4*half + i%4 of the tile
             if (k0 + 64 > N) {  // only the last tile can reach past the end of the cache
 #pragma unroll
