@@ -10,6 +10,8 @@
 //   weight pass : block = (unit, 64 keys), all query rows   -> S_raw of its keys
 //   pool pass   : S from S_raw
 // Every sum runs in a fixed order, so the scores (and what gets evicted) repeat run to run.
+#include <type_traits>
+
 #include "lds_tiles.h"
 #include "wgkv_dev.h"
 
@@ -196,19 +198,33 @@ __global__ __launch_bounds__(256) void evict_weights_kernel(View pv, CallSeqs cs
 
 
 // ---------------------------------------------------------------------------------------------
-// Matrix-core versions of the two sweeps for the shape of the paper's models (bf16, head_dim 128,
-// group of 4, n_obs a multiple of 8), v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  A wave keeps its columns as
+// Matrix-core versions of the two sweeps for bf16 pools and windows of a multiple of 32 query rows (n_obs * G),
+// v_mfma_f32_32x32x16_bf16 with fp32 accumulation; others go to the plain fp32 tiles above.  A wave keeps its columns as
 // operands in registers and all waves of a block read the streamed rows from LDS tiles that are requested a tile ahead.
 // Both are bound by the vector unit (in the statistics a maximum, a multiply-add, a quarter-rate exponential and a sum per score take
 // 26 of its clocks where the products take 16), which wants other waves' products and reads beside it.  The weights take one
 // exponential for a group: the largest of its four weights is the exponential of the largest exponent (64 heads of 4.5K entries, this
-// sweep 89 -> 78 us).
+// sweep 89 -> 78 us).  The other shapes, whole calls with admission, removal and attention, us in plain fp32 tiles / here: 2 sequences of 2K entries
+// a head, 256 observations, 32 / 8 heads of 64 420 / 108, 64 / 8 of 128 916 / 153; 1 of 1.5K, 16 / 8 of 128 448 / 92; 4 of 1K, 32 observations, 8 / 8 of
+// 128 286 / 105; 8 of 500, 64 observations, 32 / 8 of 64 183 / 104.  Errors against 64 bits 5.5-7.8e-8 -> 4.5-7.3e-8.
 typedef __attribute__((ext_vector_type(16))) float es_f32x16_t;
-constexpr int kEmD = 128;
 
-// byte offset of query row `col` (observation row col / 4, head col % 4 of the group) of a unit
-__device__ __forceinline__ size_t em_q_off(const View &pv, const EvictScoreArgs &a, int b, int h, int col) {
-    return (((size_t)b * a.n_obs + (col >> 2)) * pv.Hq + (size_t)h * 4 + (col & 3)) * (kEmD * 2);
+// Whether a group's largest weight is taken as the exponential of its largest exponent: the exponent then holds the denominator's
+// logarithm, whose rounding (2^-21 of a weight at some thousand keys) is an error of 2.1-2.5e-7 of the scores.  The shape of the paper's models has it
+// so; the others keep reference and denominator apart, as in the plain fp32 sweeps (7e-8), and take an exponential a weight.
+template <int D, int G>
+constexpr bool kOne = D == 128 && G == 4;
+// to sixteenths: what is taken off an exponent is exact
+__device__ __forceinline__ float em_coarse(float x) { return rintf(x * 16.0f) * 0.0625f; }
+
+// byte offset of a unit's first query row, and of its row `col` (observation row col / G, head col % G of the group) from there
+template <int D, int G>
+__device__ __forceinline__ size_t em_q_unit(const View &pv, const EvictScoreArgs &a, int b, int h) {
+    return ((size_t)b * a.n_obs * pv.Hq + (size_t)h * G) * (D * 2);
+}
+template <int D, int G>
+__device__ __forceinline__ uint32_t em_q_off(const View &pv, int col) {
+    return (uint32_t)((col / G) * pv.Hq + col % G) * (D * 2);
 }
 
 // Statistics, S^T = K Q^T: rows = 32 keys, columns = 32 query rows of a wave, so a lane owns one query row and its
@@ -217,25 +233,27 @@ __device__ __forceinline__ size_t em_q_off(const View &pv, const EvictScoreArgs 
 // 64 heads of 4.5K entries, 1024 rows: 132 -> 105 us against 256 rows a block, tiles of 32 keys through registers
 // and a scaled score per product; 8 heads of 2.2K 57 -> 28.  Where a page holds a wave's rows one page id and one address do for them: 106 -> 97.
 constexpr int kEmStatRows = 128, kEmStatKeys = 128;
+template <int D, int G>
 __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    __shared__ __attribute__((aligned(1024))) char s_k[2][kEmStatKeys * kEmD * 2];
+    constexpr int kRowB = D * 2, kPer = 1024 / kRowB;  // bytes of a row, rows of a request
+    __shared__ __attribute__((aligned(1024))) char s_k[2][kEmStatKeys * kRowB];
     __shared__ float s_ml[4][2][64];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
-    const int N = pv.global_len[um], n_cols = a.n_obs * 4;
+    const int N = pv.global_len[um], n_cols = a.n_obs * G;
     if (N == 0) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5, part = wave >> 2;
     const int col = blockIdx.x * kEmStatRows + (wave & 3) * 32 + n;
-    sa_bf16x8_t qv[8];
+    sa_bf16x8_t qv[D / 16];
     // the maximum is taken of the products themselves: a negative scale turns the query's sign instead
     // (and one of zero stays a hair above it: the initial maximum of -inf times it is -inf, not a NaN)
     const float c = fmaxf(fabsf(a.scale_log2e), 1e-37f);
     const uint32_t sign = a.scale_log2e < 0.f ? 0x80008000u : 0u;
     {
-        const char *qp = a.q + em_q_off(pv, a, b, h, min(col, n_cols - 1));
+        const char *qp = a.q + em_q_unit<D, G>(pv, a, b, h) + em_q_off<D, G>(pv, min(col, n_cols - 1));
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) {
+        for (int ks = 0; ks < D / 16; ks++) {
             uint4 w = *reinterpret_cast<const uint4 *>(qp + (ks * 16 + half * 8) * 2);
             w.x ^= sign; w.y ^= sign; w.z ^= sign; w.w ^= sign;
             qv[ks] = __builtin_bit_cast(sa_bf16x8_t, w);
@@ -243,7 +261,8 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
     }
     int pt_base = 0;  // 64 page ids from here on, one per lane
     int ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
-    const uint32_t off0 = (uint32_t)((lane >> 4) * (kEmD * 2) + ((lane & 15) ^ sa_sw_f(lane >> 4)) * 16);  // this lane's piece of the first four rows
+    const int sub = lane / (kRowB / 16);
+    const uint32_t off0 = (uint32_t)(sub * kRowB + (lane % (kRowB / 16) ^ sa_sw_f<D>(sub)) * 16);  // this lane's piece of the first rows
     auto fetch = [&](int t) __attribute__((always_inline)) {
         // a wave brings 16 rows, four per request; rows past the last key of the cache repeat it or are left as they are
         const int r0 = t * kEmStatKeys + wave * 16;
@@ -255,39 +274,39 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
         }
         if (pv.P >= 16 && r0 + 16 <= N) {  // a page holds the wave's rows: one id and one address for all of them
             const int pg = __builtin_amdgcn_readlane(ptreg, (r0 >> pv.logP) - pt_base);
-            const char *sb = page_ptr(pv, pg) + (size_t)(r0 & (pv.P - 1)) * (kEmD * 2);
+            const char *sb = page_ptr(pv, pg) + (size_t)(r0 & (pv.P - 1)) * kRowB;
 #pragma unroll
-            for (int i = 0; i < 4; i++) sa_dma16(sb, (off0 ^ (i * 16)) + i * 1024, &s_k[t & 1][(wave * 16 + 4 * i) * (kEmD * 2)]);
+            for (int i = 0; i < 16 / kPer; i++) sa_dma16(sb, (off0 ^ (i * kPer / 4 * 16)) + i * 1024, &s_k[t & 1][(wave * 16 + kPer * i) * kRowB]);
             return;
         }
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int r = 4 * i + (lane >> 4), idx = min(r0 + r, N - 1);
+        for (int i = 0; i < 16 / kPer; i++) {
+            const int r = kPer * i + sub, idx = min(r0 + r, N - 1);
             const int pg = __shfl(ptreg, (idx >> pv.logP) - pt_base);
-            const char *kp = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * (kEmD * 2) + ((lane & 15) ^ sa_sw_f(r)) * 16;
-            sa_dma16_at(kp, &s_k[t & 1][(wave * 16 + 4 * i) * (kEmD * 2)]);
+            const char *kp = page_ptr(pv, pg) + (size_t)(idx & (pv.P - 1)) * kRowB + (lane % (kRowB / 16) ^ sa_sw_f<D>(r)) * 16;
+            sa_dma16_at(kp, &s_k[t & 1][(wave * 16 + kPer * i) * kRowB]);
         }
     };
     const int n_tiles = (N + kEmStatKeys - 1) / kEmStatKeys;
-    const int o_row = sa_sw_row(n, half);
+    const int o_row = sa_sw_row<D>(n, half);
 #pragma unroll
-    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qv[ks]));  // waited for here, not in the loop
+    for (int ks = 0; ks < D / 16; ks++) asm volatile("" : "+v"(qv[ks]));  // waited for here, not in the loop
     fetch(0);
     sa_dma_wait_barrier<0>();
-    float m = -INFINITY, l = 0.f;  // m in units of the products
+    float m = -INFINITY, l = 0.f, m_ref = 0.f;  // m in units of the products, m_ref what l is relative to
     for (int t = 0; t < n_tiles; t++) {
         if (t + 1 < n_tiles) fetch(t + 1);
-        const char *tk = s_k[t & 1] + part * (64 * kEmD * 2);
+        const char *tk = s_k[t & 1] + part * (64 * kRowB);
         const int k0 = t * kEmStatKeys + part * 64;
         if (k0 < N) {  // wave-uniform
             es_f32x16_t s[2];
 #pragma unroll
             for (int i = 0; i < 16; i++) { s[0][i] = 0.f; s[1][i] = 0.f; }
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++)
+            for (int ks = 0; ks < D / 16; ks++)
 #pragma unroll
                 for (int j = 0; j < 2; j++)
-                    s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + j * kSaTileB, o_row, ks), qv[ks], s[j], 0, 0, 0);
+                    s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa_sw_get_row(tk + j * 32 * kRowB, o_row, ks), qv[ks], s[j], 0, 0, 0);
             // register i of s[j] holds key 32*j + 8*(i/4) + 4*half + i%4 of the tile
             if (k0 + 64 > N) {  // only the last tile can reach past the end of the cache
 #pragma unroll
@@ -297,16 +316,21 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
             float mt = m;
 #pragma unroll
             for (int i = 0; i < 32; i++) mt = fmaxf(mt, s[i >> 4][i & 15]);
-            const float ms = mt == -INFINITY ? 0.f : mt;  // this half may hold no valid key of the last tile
+            const float ms = mt == -INFINITY ? 0.f : kOne<D, G> ? mt * c : em_coarse(mt * c);  // this half may hold no valid key of the last tile
             // the hardware exponential: one instruction, a relative error of about an ulp, 0 for -inf
-            const float off = -ms * c;
+            const float off = -ms;
             float p0 = 0.f, p1 = 0.f;
 #pragma unroll
             for (int i = 0; i < 16; i++) {
                 p0 += __builtin_amdgcn_exp2f(fmaf(s[0][i], c, off));
                 p1 += __builtin_amdgcn_exp2f(fmaf(s[1][i], c, off));
             }
-            l = l * __builtin_amdgcn_exp2f(fmaf(m, c, off)) + (p0 + p1);
+            if (kOne<D, G>) {
+                l = l * __builtin_amdgcn_exp2f(fmaf(m, c, off)) + (p0 + p1);
+            } else {
+                l = l * __builtin_amdgcn_exp2f(m_ref + off) + (p0 + p1);
+                m_ref = ms;
+            }
             m = mt;
         }
         sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
@@ -317,11 +341,30 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
         l = l * exp2f(fmaf(m, c, off)) + l2 * exp2f(fmaf(m2, c, off));
         m = M;
     };
-    join(__shfl_xor(m, 32), __shfl_xor(l, 32));
-    if (part == 1) { s_ml[wave & 3][0][lane] = m; s_ml[wave & 3][1][lane] = l; }
-    __syncthreads();
-    if (part == 1) return;
-    join(s_ml[wave][0][lane], s_ml[wave][1][lane]);  // m is finite: N > 0
+    if constexpr (kOne<D, G>) {
+        join(__shfl_xor(m, 32), __shfl_xor(l, 32));
+        if (part == 1) { s_ml[wave & 3][0][lane] = m; s_ml[wave & 3][1][lane] = l; }
+        __syncthreads();
+        if (part == 1) return;
+        join(s_ml[wave][0][lane], s_ml[wave][1][lane]);  // m is finite: N > 0
+    } else {
+        // what the sums are relative to is coarse, so that the differences are exact; a part without keys has a sum of zero
+        auto join_ref = [&](float r2, float l2) __attribute__((always_inline)) {
+            const float R = l > 0.f && l2 > 0.f ? fmaxf(m_ref, r2) : l2 > 0.f ? r2 : m_ref;
+            l = (l > 0.f ? l * exp2f(m_ref - R) : l) + (l2 > 0.f ? l2 * exp2f(r2 - R) : l2);
+            m_ref = R;
+        };
+        join_ref(__shfl_xor(m_ref, 32), __shfl_xor(l, 32));
+        if (part == 1) { s_ml[wave & 3][0][lane] = m_ref; s_ml[wave & 3][1][lane] = l; }
+        __syncthreads();
+        if (part == 1) return;
+        join_ref(s_ml[wave][0][lane], s_ml[wave][1][lane]);
+        if (half == 0 && col < n_cols) {
+            a.stats[(size_t)u * n_cols * 2 + col] = m_ref;
+            a.stats[(size_t)u * n_cols * 2 + n_cols + col] = 1.0f / l;
+        }
+        return;
+    }
     // per unit: first n_cols values M + log2(L), what the weight sweep subtracts in the exponent
     // (exp2(x - M) / L = exp2(x - (M + log2 L))), then the n_cols denominators
     if (half == 0 && col < n_cols) {
@@ -336,54 +379,60 @@ __global__ __launch_bounds__(512, 4) void evict_stats_mfma_kernel(View pv, CallS
 // the window a sum inside the lane, then over the two halves of the wave, then over the TS waves that share keys,
 // in a fixed order.  64 heads of 4.5K entries, 1024 rows: 125 -> 93 us against 128 keys a wave with its query rows
 // loaded by every wave for itself.  A wave holds 64 keys, a block 256 / TS; n_cols is a multiple of 32 (n_obs of 8).
-template <int TS>
+template <int D, int G, int TS>
 __global__ __launch_bounds__(256, TS == 4 ? 2 : 4) void evict_weights_mfma_kernel(View pv, CallSeqs cs, EvictScoreArgs a) {
-    constexpr int kEmKeys = 256 / TS, kEmTurn = TS == 4 ? 128 : 64, kRows = kEmTurn / 4;
-    __shared__ __attribute__((aligned(1024))) char s_q[2][kEmTurn * kEmD * 2];
-    __shared__ __attribute__((aligned(16))) float s_off[2][kEmTurn];
+    constexpr int kEmKeys = 256 / TS, kEmTurn = TS == 4 ? 128 : 64, kRows = kEmTurn / 4, kRowB = D * 2, kPer = 1024 / kRowB;
+    __shared__ __attribute__((aligned(1024))) char s_q[2][kEmTurn * kRowB];
+    __shared__ __attribute__((aligned(16))) float s_off[2][kEmTurn], s_inv[2][kOne<D, G> ? 4 : kEmTurn];
     __shared__ float s_acc[4][64];
     const int u = blockIdx.y, b = u / pv.Hkv, h = u % pv.Hkv;
     const int um = unit_meta(pv, cs.sid[b], a.layer, h);
-    const int N = pv.global_len[um], n_cols = a.n_obs * 4;
+    const int N = pv.global_len[um], n_cols = a.n_obs * G;
     const int key0 = blockIdx.x * kEmKeys;
     if (key0 >= N) return;  // block-uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
     const float *off_u = a.stats + (size_t)u * n_cols * 2;
-    // a wave brings a quarter of a tile's query rows, four (the heads of an observation row: 1 KiB) per request; rows past the
-    // last one are never multiplied
+    // a wave brings a quarter of a tile's query rows, 1 KiB of them per request; rows past the last one are never multiplied
+    const char *q_unit = a.q + em_q_unit<D, G>(pv, a, b, h);
     auto fetch = [&](int t) __attribute__((always_inline)) {
         int ln = lane;
         asm volatile("" : "+v"(ln));  // the lane's offsets are formed per tile: no registers to keep them
 #pragma unroll
-        for (int i = 0; i < kRows / 4; i++) {
-            const int r = wave * kRows + 4 * i, rl = r + (ln >> 4);
-            sa_dma16(a.q + em_q_off(pv, a, b, h, min(t * kEmTurn + r, n_cols - 4)),
-                     (uint32_t)((ln >> 4) * (kEmD * 2) + ((ln & 15) ^ sa_sw_f(rl)) * 16), &s_q[t & 1][r * (kEmD * 2)]);
+        for (int i = 0; i < kRows / kPer; i++) {
+            const int r = wave * kRows + kPer * i, rl = r + ln / (kRowB / 16);
+            const uint32_t piece = (uint32_t)((ln % (kRowB / 16)) ^ sa_sw_f<D>(rl)) * 16;
+            if constexpr (G % kPer == 0)  // neighbouring heads of an observation row
+                sa_dma16(q_unit + em_q_off<D, G>(pv, min(t * kEmTurn + r, n_cols - kPer)), (uint32_t)(ln / (kRowB / 16)) * kRowB + piece, &s_q[t & 1][r * kRowB]);
+            else
+                sa_dma16(q_unit, em_q_off<D, G>(pv, min(t * kEmTurn + rl, n_cols - 1)) + piece, &s_q[t & 1][r * kRowB]);
         }
         if (wave == (t & 3))
 #pragma unroll
             for (int i = 0; i < kEmTurn; i += 64)
+            {
                 sa_dma4(off_u, (uint32_t)min(t * kEmTurn + i + ln, n_cols - 1) * 4u, &s_off[t & 1][i]);
+                if (!kOne<D, G>) sa_dma4(off_u + n_cols, (uint32_t)min(t * kEmTurn + i + ln, n_cols - 1) * 4u, &s_inv[t & 1][i]);
+            }
     };
     const int key_w = key0 + wave / TS * 64;
-    sa_bf16x8_t kreg[2][8];
+    sa_bf16x8_t kreg[2][D / 16];
     {
         int pg[2];
 #pragma unroll
         for (int kt = 0; kt < 2; kt++) pg[kt] = pv.global_pt[(size_t)um * pv.maxgp + (min(key_w + kt * 32 + n, N - 1) >> pv.logP)];
 #pragma unroll
         for (int kt = 0; kt < 2; kt++) {
-            const char *kp = page_ptr(pv, pg[kt]) + (size_t)(min(key_w + kt * 32 + n, N - 1) & (pv.P - 1)) * (kEmD * 2);
+            const char *kp = page_ptr(pv, pg[kt]) + (size_t)(min(key_w + kt * 32 + n, N - 1) & (pv.P - 1)) * kRowB;
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++) kreg[kt][ks] = *reinterpret_cast<const sa_bf16x8_t *>(kp + (ks * 16 + half * 8) * 2);
+            for (int ks = 0; ks < D / 16; ks++) kreg[kt][ks] = *reinterpret_cast<const sa_bf16x8_t *>(kp + (ks * 16 + half * 8) * 2);
         }
     }
 #pragma unroll
     for (int kt = 0; kt < 2; kt++)
 #pragma unroll
-        for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(kreg[kt][ks]));  // waited for here, not in the loop
-    const int o_row = sa_sw_row(n, half);
+        for (int ks = 0; ks < D / 16; ks++) asm volatile("" : "+v"(kreg[kt][ks]));  // waited for here, not in the loop
+    const int o_row = sa_sw_row<D>(n, half);
     const int n_turns = (n_cols + kEmTurn - 1) / kEmTurn;
     float acc[2] = {0.f, 0.f};
     fetch(0);
@@ -394,34 +443,49 @@ __global__ __launch_bounds__(256, TS == 4 ? 2 : 4) void evict_weights_mfma_kerne
         for (int i = 0; i < kEmTurn / 32 / TS; i++) {
             const int sub = i * TS + wave % TS;
             if (t * kEmTurn + 32 * sub >= n_cols) break;  // uniform
-            const char *tq = s_q[t & 1] + sub * kSaTileB;
+            const char *tq = s_q[t & 1] + sub * 32 * kRowB;
             es_f32x16_t s[2];
 #pragma unroll
             for (int c = 0; c < 16; c++) { s[0][c] = 0.f; s[1][c] = 0.f; }
 #pragma unroll
-            for (int ks = 0; ks < 8; ks++) {
+            for (int ks = 0; ks < D / 16; ks++) {
                 const sa_bf16x8_t f = sa_sw_get_row(tq, o_row, ks);
                 s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kreg[0][ks], s[0], 0, 0, 0);
                 s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kreg[1][ks], s[1], 0, 0, 0);
             }
-            // register 4j+i of a product: query row 8j + 4*half + i of the rows = observation row 2j + half, head i
+            float part[2] = {0.f, 0.f};  // of these rows: a sum of sums is the more exact
+            // register 4j+i of a product: query row 8j + 4*half + i of the rows (groups of four: observation row 2j + half, head i)
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 const float4 off = *reinterpret_cast<const float4 *>(&s_off[t & 1][32 * sub + 8 * j + 4 * half]);
 #pragma unroll
                 for (int kt = 0; kt < 2; kt++) {
-                    // the largest of the group's four weights is the exponential of the largest exponent
                     const float x0 = fmaf(s[kt][4 * j], a.scale_log2e, -off.x), x1 = fmaf(s[kt][4 * j + 1], a.scale_log2e, -off.y);
                     const float x2 = fmaf(s[kt][4 * j + 2], a.scale_log2e, -off.z), x3 = fmaf(s[kt][4 * j + 3], a.scale_log2e, -off.w);
-                    acc[kt] += __builtin_amdgcn_exp2f(fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)));
+                    if constexpr (kOne<D, G>) {
+                        acc[kt] += __builtin_amdgcn_exp2f(fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)));
+                    } else {
+                        const float4 inv = *reinterpret_cast<const float4 *>(&s_inv[t & 1][32 * sub + 8 * j + 4 * half]);
+                        const float p0 = __builtin_amdgcn_exp2f(x0) * inv.x, p1 = __builtin_amdgcn_exp2f(x1) * inv.y;
+                        const float p2 = __builtin_amdgcn_exp2f(x2) * inv.z, p3 = __builtin_amdgcn_exp2f(x3) * inv.w;
+                        if (G == 1) part[kt] += (p0 + p1) + (p2 + p3);
+                        else if (G == 2) part[kt] += fmaxf(p0, p1) + fmaxf(p2, p3);
+                        else if (G == 4) part[kt] += fmaxf(fmaxf(p0, p1), fmaxf(p2, p3));
+                        else part[kt] += max_xor32(fmaxf(fmaxf(p0, p1), fmaxf(p2, p3)));  // the other half has the group's other four heads, and the same sum
+                    }
                 }
+            }
+            if (!kOne<D, G>) {
+                acc[0] += part[0];
+                acc[1] += part[1];
             }
         }
         sa_dma_wait_barrier<0>();  // tile t + 1 is there, and nobody reads tile t any more
     }
-    // the two halves of a wave hold different observation rows of the same key
+    // the two halves of a wave hold different observation rows of the same key (groups of eight: the same ones)
+    if (G < 8)
 #pragma unroll
-    for (int kt = 0; kt < 2; kt++) acc[kt] += __shfl_xor(acc[kt], 32);
+        for (int kt = 0; kt < 2; kt++) acc[kt] += __shfl_xor(acc[kt], 32);
     float v = half ? acc[1] : acc[0];  // of key key_w + lane
     if constexpr (TS > 1) {
         s_acc[wave][lane] = v;
@@ -449,6 +513,39 @@ size_t evict_scores_ws_bytes(const View &pv, int n_units, int n_obs) {
     return (((size_t)n_units * n_obs * pv.G * 2 * sizeof(float)) + 255) / 256 * 256;
 }
 
+template <int D, int G>
+static void launch_evict_mfma_shape(const View &pv, const CallSeqs &cs, const EvictScoreArgs &a, int n_rows, int n_units, int64_t max_len,
+                                    hipStream_t st) {
+    hipLaunchKernelGGL((evict_stats_mfma_kernel<D, G>), dim3((n_rows + kEmStatRows - 1) / kEmStatRows, n_units), dim3(512), 0, st, pv, cs, a);
+    // A wave that walks the whole window alone takes 25 us for 256 observation rows, however few keys there are: waves
+    // share keys as long as compute units are idle.  TS = 1 / 2 / 4, in us, 8 kv heads, 256 rows: 1 sequence of 2250
+    // entries a head 26 / - / 17, 2 of 2250 27 / 24 / 28, 2 of 4500 39 / - / 43, 4 of 3000 40 / - / 56.
+    // The lines are those of 256 rows and 256 compute units.  Calls of 1 to 1024 rows were timed against one key a lane and 128
+    // keys a block throughout, the form before: slower only for some 50 entries in each of many heads (40 sequences, 64 rows
+    // 24 -> 32 us).  Sharing keys there (TS = 4 up to 64 entries, 2 up to 128) gives 29 with 64 rows, 35 instead of 40 with 16
+    // sequences and 256 rows, and costs up to a fifth with 8 rows (100 sequences 23 -> 28): left.
+    const int64_t n_blocks = (int64_t)((max_len + 255) / 256) * n_units;  // of TS = 1
+    if (n_blocks <= 96)
+        hipLaunchKernelGGL((evict_weights_mfma_kernel<D, G, 4>), dim3((unsigned)((max_len + 63) / 64), n_units), dim3(256), 0, st, pv, cs, a);
+    else if (n_blocks <= 256)
+        hipLaunchKernelGGL((evict_weights_mfma_kernel<D, G, 2>), dim3((unsigned)((max_len + 127) / 128), n_units), dim3(256), 0, st, pv, cs, a);
+    else
+        hipLaunchKernelGGL((evict_weights_mfma_kernel<D, G, 1>), dim3((unsigned)((max_len + 255) / 256), n_units), dim3(256), 0, st, pv, cs, a);
+}
+static bool launch_evict_mfma(const View &pv, const CallSeqs &cs, const EvictScoreArgs &a, int n_rows, int n_units, int64_t max_len, hipStream_t st) {
+    auto shape = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        switch (pv.G) {
+            case 1: launch_evict_mfma_shape<D, 1>(pv, cs, a, n_rows, n_units, max_len, st); return true;
+            case 2: launch_evict_mfma_shape<D, 2>(pv, cs, a, n_rows, n_units, max_len, st); return true;
+            case 4: launch_evict_mfma_shape<D, 4>(pv, cs, a, n_rows, n_units, max_len, st); return true;
+            case 8: launch_evict_mfma_shape<D, 8>(pv, cs, a, n_rows, n_units, max_len, st); return true;
+            default: return false;
+        }
+    };
+    return pv.d == 128 ? shape(std::integral_constant<int, 128>()) : pv.d == 64 && shape(std::integral_constant<int, 64>());
+}
+
 // max_len: upper bound of the units' lengths (sizes the grids; blocks past a unit's end return at once)
 hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, const void *q_obs, int n_obs,
                                float scale, int pool_w, float *raw, float *out, int64_t stride, int64_t max_len,
@@ -472,23 +569,8 @@ hipError_t launch_evict_scores(const View &pv, const CallSeqs &cs, int layer, co
     // (the matrix-core kernels read the queries 16 bytes at a time, part of them straight into LDS; the general ones four elements at a time, or one
     // by one where they are not aligned)
     const bool q_aligned = ((uintptr_t)q_obs & 15) == 0;
-    if (pv.dtype == WGKV_BF16 && pv.d == kEmD && pv.G == 4 && n_obs % 8 == 0 && q_aligned) {
-        const dim3 g_stats_m((n_rows + kEmStatRows - 1) / kEmStatRows, n_units);
-        hipLaunchKernelGGL(evict_stats_mfma_kernel, g_stats_m, dim3(512), 0, st, pv, cs, a);
-        // A wave that walks the whole window alone takes 25 us for 256 observation rows, however few keys there are: waves
-        // share keys as long as compute units are idle.  TS = 1 / 2 / 4, in us, 8 kv heads, 256 rows: 1 sequence of 2250
-        // entries a head 26 / - / 17, 2 of 2250 27 / 24 / 28, 2 of 4500 39 / - / 43, 4 of 3000 40 / - / 56.
-        // The lines are those of 256 rows and 256 compute units.  Calls of 1 to 1024 rows were timed against one key a lane and 128
-        // keys a block throughout, the form before: slower only for some 50 entries in each of many heads (40 sequences, 64 rows
-        // 24 -> 32 us).  Sharing keys there (TS = 4 up to 64 entries, 2 up to 128) gives 29 with 64 rows, 35 instead of 40 with 16
-        // sequences and 256 rows, and costs up to a fifth with 8 rows (100 sequences 23 -> 28): left.
-        const int64_t n_blocks = (int64_t)((max_len + 255) / 256) * n_units;  // of TS = 1
-        if (n_blocks <= 96)
-            hipLaunchKernelGGL(evict_weights_mfma_kernel<4>, dim3((unsigned)((max_len + 63) / 64), n_units), dim3(256), 0, st, pv, cs, a);
-        else if (n_blocks <= 256)
-            hipLaunchKernelGGL(evict_weights_mfma_kernel<2>, dim3((unsigned)((max_len + 127) / 128), n_units), dim3(256), 0, st, pv, cs, a);
-        else
-            hipLaunchKernelGGL(evict_weights_mfma_kernel<1>, dim3((unsigned)((max_len + 255) / 256), n_units), dim3(256), 0, st, pv, cs, a);
+    if (pv.dtype == WGKV_BF16 && n_rows % 32 == 0 && q_aligned && (int64_t)n_obs * pv.Hq * pv.row_bytes < ((int64_t)1 << 32) &&
+        launch_evict_mfma(pv, cs, a, n_rows, n_units, max_len, st)) {
     } else if (pv.dtype == WGKV_F32) {
         hipLaunchKernelGGL(evict_stats_kernel<WGKV_F32>, g_stats, dim3(256), 0, st, pv, cs, a);
         hipLaunchKernelGGL(evict_weights_kernel<WGKV_F32>, g_keys, dim3(256), 0, st, pv, cs, a);
