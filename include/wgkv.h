@@ -428,8 +428,8 @@ int wgkv_attend_selected(wgkv_pool *pool, int32_t layer, int32_t n_seqs, const i
  *               cover the host's upper bound of every head's length (see wgkv_status)
  * fp32 arithmetic; sums run in a fixed order, so the result repeats run to run (the order over the
  * observation rows follows the call's size: the number of heads and the host's bound of their lengths).
- * q_obs_dev may have any alignment; from 16 bytes on bf16 / head_dim 128 / group 4 with n_obs a multiple
- * of 8 runs on the matrix cores.  The
+ * q_obs_dev may have any alignment; from 16 bytes on bf16 pools with n_obs * group a multiple
+ * of 32 run on the matrix cores.  The
  * workspace from wgkv_query_sizes covers n_obs <= 256 (n_units * n_obs * group * 8 bytes
  * are needed); n_obs <= 4096, pool_w <= 255, the group size must divide 64.
  * Errors: INVALID_ARG, WORKSPACE, HIP. */
