@@ -523,6 +523,11 @@ void attend_prefill_parts_kernel(View pv, CallSeqs cs, PrefillAttnArgs a) {
     // all tiles, once
     auto sweep = [&](auto look_t) __attribute__((always_inline)) {
         constexpr bool kLook = decltype(look_t)::value;
+        if (kLook && pt_base != 0) {  // back to the first pages
+            pt_base = 0;
+            ptreg = (lane < pv.maxgp) ? pv.global_pt[(size_t)um * pv.maxgp + lane] : 0;
+            asm volatile("" : "+v"(ptreg));
+        }
         m = -INFINITY;
         l = 0.f;
 #pragma unroll

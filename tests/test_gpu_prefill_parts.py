@@ -1,5 +1,5 @@
 """Chunk attention of the shapes whose weights keep 24 bits: scales that are negative or
-zero, values of V at the ends of the range, and launches in which every block runs at once (two to a compute unit) or the
+zero, values of V at the ends of the range or not finite, and launches in which every block runs at once (two to a compute unit) or the
 positions of all units come one after the other."""
 import math
 
@@ -9,7 +9,7 @@ import torch
 
 import paper_2512_17452_amd as wg
 from oracle import attend_definition
-from test_gpu_prefill_shapes import _tol
+from test_gpu_prefill_shapes import _feed, _tol, _with_nonfinite
 
 pytestmark = pytest.mark.gpu
 
@@ -51,6 +51,25 @@ def test_values_at_the_ends_of_the_range(d, G, size):
     out = _attend(d, G, 2, [T], *(x.to("cuda:0") for x in (q, k, (v.float() * size).bfloat16(), g)), W, tau, 1 / math.sqrt(d)).cpu().numpy()
     ref = attend_definition(k.float().numpy(), v.float().numpy(), g.numpy(), q.float().numpy(), np.arange(T), W, tau, 1 / math.sqrt(d))
     assert np.abs(out.astype(np.float64) / size - ref).max() <= _tol(wg.BF16, d, G)
+
+
+@pytest.mark.parametrize("d,G", SHAPES, ids=IDS)
+def test_values_that_are_not_finite_behind_more_than_64_pages(d, G):
+    """A block that finds one goes through its tiles again, from the first page on."""
+    W, P, tau = 32, 8, 0.0  # everything admitted: 171 pages a head
+
+    def spoil(call, v):
+        v[len(v) // 3, 0, 5] = float("inf")
+        v[len(v) - 2, 1, d - 1] = -float("inf")
+
+    for s, t0, K, V, g, q, out in _feed(wg.BF16, d, G, 2, [[1400], [70]], W, P, tau, seed=d + G, spoil=spoil):
+        if t0 == 0:
+            continue  # the second call reads the pages
+        ref = _with_nonfinite(K, V, g, q, t0, W, tau, 1 / math.sqrt(d), G)
+        fin = np.isfinite(ref)
+        np.testing.assert_array_equal(np.isnan(out), np.isnan(ref))
+        np.testing.assert_array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.abs(out[fin] - ref[fin]).max() <= _tol(wg.BF16, d, G)
 
 
 @pytest.mark.parametrize("d,G,lens", [(64, 4, [480, 3, 450]), (128, 4, [2048]), (128, 2, [1500, 700]), (64, 8, [900]), (64, 4, [1000, 3, 997, 640]), (128, 1, [2100, 64])])
